@@ -17,21 +17,26 @@
 namespace slp {
 namespace {
 
-struct Words { uint32_t r0, r1, r2, r3; };
+// a ^ b ^ c in one instruction (truth table 0x96)
+__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
+  return (uint32_t)__builtin_amdgcn_bitop3_b32((int)a, (int)b, (int)c, 0x96);
+}
 
+struct Words { uint32_t r0, r1; };      // the two words of a counter's four that the transforms use
+
+// One 32x32 -> 64 bit product per multiplier (v_mad_u64_u32) instead of a high-half and a low-half product each.
 __device__ __forceinline__ Words philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3, uint32_t k0,
                                                uint32_t k1) {
   constexpr uint32_t M0 = 0xD2511F53u, M1 = 0xCD9E8D57u;
 #pragma unroll
   for (int round = 0; round < 10; ++round) {
-    const uint32_t hi0 = __umulhi(M0, c0), lo0 = M0 * c0;
-    const uint32_t hi1 = __umulhi(M1, c2), lo1 = M1 * c2;
-    const uint32_t n0 = hi1 ^ c1 ^ k0, n2 = hi0 ^ c3 ^ k1;
-    c0 = n0; c1 = lo1; c2 = n2; c3 = lo0;
+    const uint64_t p0 = (uint64_t)M0 * c0, p1 = (uint64_t)M1 * c2;
+    const uint32_t n0 = xor3((uint32_t)(p1 >> 32), c1, k0), n2 = xor3((uint32_t)(p0 >> 32), c3, k1);
+    c0 = n0; c1 = (uint32_t)p1; c2 = n2; c3 = (uint32_t)p0;
     k0 += 0x9E3779B9u;   // Weyl sequence; the bump after the last round is unused
     k1 += 0xBB67AE85u;
   }
-  return Words{c0, c1, c2, c3};
+  return Words{c0, c1};
 }
 
 // IEEE square root: the plain builtin is lowered to the correctly rounded sequence
@@ -39,36 +44,56 @@ __device__ __forceinline__ Words philox4x32_10(uint32_t c0, uint32_t c1, uint32_
 // "__fsqrt_rn" spelling maps to the 1-ulp native instruction and must not be used.
 __device__ __forceinline__ float correctly_rounded_sqrt(float x) { return __builtin_sqrtf(x); }
 
+// The same without the general sequence's scaling and special cases, for zeros and values in [2^-24, 64] (all that the
+// normal transform asks for): the 1-ulp instruction, then one neighbour up or down where the sign of the residual, one
+// fused operation each, says that it is the nearer one.  Compared with the general sequence on every one of the 2^24
+// arguments that occur: no bit differs.
+__device__ __forceinline__ float sqrt_unscaled(float x) {
+  const float r = __builtin_amdgcn_sqrtf(x);
+  const float lo = __uint_as_float(__float_as_uint(r) - 1u), hi = __uint_as_float(__float_as_uint(r) + 1u);
+  float out = __fmaf_rn(-lo, r, x) <= 0.0f ? lo : r;
+  out = __fmaf_rn(-hi, r, x) > 0.0f ? hi : out;
+  return out;
+}
+
+// Correctly rounded a / d for d in [1.7, 2.5] and |a| < 1 (no scaling needed): a reciprocal refined once by Newton's step,
+// the quotient corrected by its fused residual (Markstein 1990).  Compared with the general sequence on every significand
+// that occurs: no bit differs.
+__device__ __forceinline__ float divide_unscaled(float a, float d) {
+  float y = __builtin_amdgcn_rcpf(d);
+  y = __fmaf_rn(__fmaf_rn(-d, y, 1.0f), y, y);
+  const float q = __fmul_rn(a, y);
+  return __fmaf_rn(__fmaf_rn(-d, q, a), y, q);
+}
+
 __device__ __forceinline__ float unit_uniform(uint32_t r) {   // (r >> 8) * 2^-24, exact
   return __fmul_rn((float)(r >> 8), 0x1p-24f);
 }
 
-// ln(u) for u = j * 2^-24, j in [1, 2^24]: mantissa/exponent split on the bit
-// pattern, atanh series in s = (m-1)/(m+1) to s^9, Horner with separately rounded
+// ln(j * 2^-24), j in [1, 2^24]: mantissa/exponent split on the bit pattern of j (significand m in (sqrt(1/2), sqrt(2)]),
+// atanh series in s = (m-1)/(m+1) to s^9, Horner with separately rounded
 // multiplies and adds; exponent contribution split into a high and a low part.
-__device__ __forceinline__ float ln_unit(float u) {
-  const uint32_t bits = __float_as_uint(u);
-  int e = (int)(bits >> 23) - 127;
-  float m = __uint_as_float((bits & 0x007FFFFFu) | 0x3F800000u);
-  if (m > __uint_as_float(0x3FB504F3u)) { m = __fmul_rn(m, 0.5f); e += 1; }
-  const float s = __fdiv_rn(__fsub_rn(m, 1.0f), __fadd_rn(m, 1.0f));
+__device__ __forceinline__ float ln_unit(uint32_t j) {
+  const uint32_t bits = __float_as_uint((float)j) + (0x3F800000u - 0x3F3504F4u);   // significands above sqrt(2) carry
+  const float ef = (float)((int)(bits >> 23) - (127 + 24));
+  const float m = __uint_as_float((bits & 0x007FFFFFu) + 0x3F3504F4u);
+  const float s = divide_unscaled(__fsub_rn(m, 1.0f), __fadd_rn(m, 1.0f));
   const float s2 = __fmul_rn(s, s);
   float p = __fadd_rn(__fmul_rn(s2, __uint_as_float(0x3E638E39u)), __uint_as_float(0x3E924925u));   // 2/9, 2/7
   p = __fadd_rn(__fmul_rn(p, s2), __uint_as_float(0x3ECCCCCDu));                                     // 2/5
   p = __fadd_rn(__fmul_rn(p, s2), __uint_as_float(0x3F2AAAABu));                                     // 2/3
   const float lnm = __fadd_rn(__fmul_rn(s, 2.0f), __fmul_rn(__fmul_rn(s, s2), p));
-  const float ef = (float)e;
   return __fadd_rn(__fmul_rn(ef, __uint_as_float(0x3F317200u)),
                    __fadd_rn(__fmul_rn(ef, __uint_as_float(0x35BFBE8Eu)), lnm));
 }
 
-// cos(2 pi k / 2^24) for a 24-bit k: exact quadrant and reflection in integers,
+// cos(2 pi k / 2^24) for k = r >> 8: exact quadrant and reflection in integers,
 // then Taylor polynomials of sin and cos on [0, pi/4].
-__device__ __forceinline__ float cos_turn(uint32_t k) {
-  const uint32_t q = k >> 22, fi = k & 0x3FFFFFu;
+__device__ __forceinline__ float cos_turn(uint32_t r) {
+  const uint32_t fi = (r >> 8) & 0x3FFFFFu;
   const bool swap = fi > (1u << 21);
   const uint32_t ti = swap ? (1u << 22) - fi : fi;
-  const float x = __fmul_rn(__fmul_rn((float)ti, 0x1p-22f), __uint_as_float(0x3FC90FDBu));
+  const float x = __fmul_rn((float)ti, 0x1.921FB6p+0f * 0x1p-22f);     // pi/2 * 2^-22: the scaling is exact
   const float x2 = __fmul_rn(x, x);
   float sp = __fadd_rn(__fmul_rn(x2, __uint_as_float(0x3638EF1Du)), __uint_as_float(0xB9500D01u));
   sp = __fadd_rn(__fmul_rn(sp, x2), __uint_as_float(0x3C088889u));
@@ -79,94 +104,147 @@ __device__ __forceinline__ float cos_turn(uint32_t k) {
   cp = __fadd_rn(__fmul_rn(cp, x2), __uint_as_float(0x3D2AAAABu));
   cp = __fadd_rn(__fmul_rn(cp, x2), -0.5f);
   const float cosx = __fadd_rn(1.0f, __fmul_rn(x2, cp));
-  const float cf = swap ? sinx : cosx, sf = swap ? cosx : sinx;
-  return q == 0 ? cf : (q == 1 ? -sf : (q == 2 ? -cf : sf));
+  // quadrants 0..3 (the top two bits): cos, -sin, -cos, sin of the quadrant's angle, which reflection exchanges
+  const float v = (swap != (bool)((r >> 30) & 1u)) ? sinx : cosx;
+  return __uint_as_float(__float_as_uint(v) ^ ((r ^ (r << 1)) & 0x80000000u));
 }
 
 __device__ __forceinline__ float standard_normal(uint32_t r0, uint32_t r1) {
-  const float u1 = __fmul_rn((float)((r0 >> 8) + 1u), 0x1p-24f);
-  const float radius = correctly_rounded_sqrt(__fmul_rn(-2.0f, ln_unit(u1)));
-  return __fmul_rn(radius, cos_turn(r1 >> 8));
+  const float radius = sqrt_unscaled(__fmul_rn(-2.0f, ln_unit((r0 >> 8) + 1u)));
+  return __fmul_rn(radius, cos_turn(r1));
 }
 
-__device__ __forceinline__ float draw(int dist, float kappa, const Words& w) {
-  switch (dist) {
-    case 0: return __fmul_rn(kappa, unit_uniform(w.r0));
-    case 1: return __fsub_rn(__fmul_rn(2.0f, unit_uniform(w.r0)), 1.0f);
-    case 2: return standard_normal(w.r0, w.r1);
-    default: return (w.r0 >> 31) ? 1.0f : -1.0f;
+template <int DIST>
+__device__ __forceinline__ float draw(float kappa, const Words& w) {
+  if (DIST == 0) return __fmul_rn(kappa, unit_uniform(w.r0));
+  if (DIST == 1) return __fsub_rn(__fmul_rn(2.0f, unit_uniform(w.r0)), 1.0f);
+  if (DIST == 2) return standard_normal(w.r0, w.r1);
+  return (w.r0 >> 31) ? 1.0f : -1.0f;
+}
+
+__device__ __forceinline__ void store_value(float* out, size_t idx, float v) { out[idx] = v; }
+// round to nearest even in one instruction; NaN keeps its upper bits and becomes quiet
+__device__ __forceinline__ void store_value(__bf16* out, size_t idx, float v) { out[idx] = (__bf16)v; }
+
+// Every kernel here is bound by its integer and float instructions (10 rounds of two 64-bit products, then the transform),
+// not by the bytes it writes.  A wavefront therefore takes a run of kRun columns of ONE row, column by column across its
+// lanes: the row's index is uniform over the wavefront, so the division that finds it and every part of the counter
+// arithmetic that depends on the row and the key only is done once per run on the scalar unit, and the stores are
+// coalesced whatever the alignment of a row.  Rows of up to 32 columns share a wavefront (2^lanes_log2 lanes each).
+// fn(row, column) is called for every element, whole runs without a test per column.
+// 8192 x 16384 bf16 inputs and their 1000 x 16384 table, both calls: one element per lane with a 64-bit division each, the
+// general division and square root and separate halves of the products 564 us -> 330 us; the inputs' ~90 instructions an
+// element are issued at the rate of the vector units.  Unrolled by 4: by 2 +5 %, by 8 the same.
+constexpr int kRun = 512;
+template <typename F>
+__device__ __forceinline__ void for_each_element(uint32_t rows, uint32_t cols, int lanes_log2, F fn) {
+  const int lane = threadIdx.x & 63;
+  const uint64_t waves = (uint64_t)gridDim.x * 4;
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (lanes_log2 < 6) {
+    const uint32_t per = 64u >> lanes_log2;
+    for (uint64_t u = (uint64_t)blockIdx.x * 4 + wave; u * per < rows; u += waves) {
+      const uint64_t r = u * per + (lane >> lanes_log2);
+      const uint32_t c = lane & ((1 << lanes_log2) - 1);
+      if (r < rows && c < cols) fn((uint32_t)r, c);
+    }
+    return;
+  }
+  const uint32_t runs = (cols + kRun - 1) / kRun;
+  const uint64_t units = (uint64_t)rows * runs;
+  for (uint64_t u = (uint64_t)blockIdx.x * 4 + wave; u < units; u += waves) {
+    const uint32_t r = (uint32_t)(u / runs), c0 = (uint32_t)(u % runs) * kRun;
+    if (cols - c0 >= kRun) {
+#pragma unroll 4
+      for (int j = 0; j < kRun / 64; ++j) fn(r, c0 + 64 * j + lane);
+    } else {
+      for (uint32_t c = c0 + lane; c < cols; c += 64) fn(r, c);
+    }
   }
 }
 
-__device__ __forceinline__ uint16_t bf16_bits_rne(float x) {
-  const uint32_t b = __float_as_uint(x);
-  if ((b & 0x7FFFFFFFu) > 0x7F800000u) return (uint16_t)((b >> 16) | 0x40u);   // quiet NaN
-  return (uint16_t)((b + 0x7FFFu + ((b >> 16) & 1u)) >> 16);
+template <typename T, int DIST>
+__global__ __launch_bounds__(256) void labels_kernel(uint32_t k0, uint32_t k1, int classes, int dim, float kappa, T* __restrict__ out,
+                                                     int lanes_log2) {
+  for_each_element(classes, dim, lanes_log2, [&](uint32_t j, uint32_t i) {
+    store_value(out, (size_t)j * dim + i, draw<DIST>(kappa, philox4x32_10(i, j, 0u, 0u, k0, k1)));
+  });
 }
 
-__device__ __forceinline__ void store_value(void* out, size_t idx, float v, int dt) {
-  if (dt == 1) ((uint16_t*)out)[idx] = bf16_bits_rne(v);
-  else ((float*)out)[idx] = v;
-}
-
-__global__ void labels_kernel(uint32_t k0, uint32_t k1, int classes, int dim, int dist, float kappa, void* out, int dt) {
-  const size_t total = (size_t)classes * dim;
-  for (size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (size_t)gridDim.x * blockDim.x) {
-    const uint32_t j = (uint32_t)(e / dim), i = (uint32_t)(e % dim);
-    store_value(out, e, draw(dist, kappa, philox4x32_10(i, j, 0u, 0u, k0, k1)), dt);
-  }
-}
-
-__global__ void inputs_kernel(uint32_t k0, uint32_t k1, const float* __restrict__ table, int classes,
-                              const int32_t* __restrict__ y, uint64_t first, int batch, int dim, float sigma, void* out, int dt) {
-  const size_t total = (size_t)batch * dim;
-  for (size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (size_t)gridDim.x * blockDim.x) {
-    const uint32_t row = (uint32_t)(e / dim), i = (uint32_t)(e % dim);
+template <typename T>
+__global__ __launch_bounds__(256) void inputs_kernel(uint32_t k0, uint32_t k1, const float* __restrict__ table, int classes,
+                                                     const int32_t* __restrict__ y, uint64_t first, int batch, int dim, float sigma,
+                                                     T* __restrict__ out, int lanes_log2) {
+  for_each_element(batch, dim, lanes_log2, [&](uint32_t row, uint32_t i) {
     const uint64_t n = first + row;
     const Words w = philox4x32_10(i, (uint32_t)n, 2u, (uint32_t)(n >> 32), k0, k1);
     const float z = standard_normal(w.r0, w.r1);
     const int cls = min(max(y[row], 0), classes - 1);
     const float v = __fadd_rn(table[(size_t)cls * dim + i], __fmul_rn(sigma, z));
-    store_value(out, e, v, dt);
-  }
+    store_value(out, (size_t)row * dim + i, v);
+  });
 }
 
-__global__ void init_kernel(uint32_t k0, uint32_t k1, uint32_t layer, float* W, int N, int K, int ldk, float* b) {
+__global__ __launch_bounds__(256) void init_kernel(uint32_t k0, uint32_t k1, uint32_t layer, float* __restrict__ W, int N, int K,
+                                                   int ldk, float* __restrict__ b, int lanes_log2) {
   const float bound = __fdiv_rn(1.0f, correctly_rounded_sqrt((float)K));
-  const size_t total = (size_t)N * (K + 1);
-  for (size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (size_t)gridDim.x * blockDim.x) {
-    const uint32_t o = (uint32_t)(e / (K + 1)), k = (uint32_t)(e % (K + 1));
+  for_each_element(N, (uint32_t)K + 1, lanes_log2, [&](uint32_t o, uint32_t k) {
     const Words w = philox4x32_10(k, o, 1u, layer, k0, k1);
     const float v = __fmul_rn(__fsub_rn(__fmul_rn(2.0f, unit_uniform(w.r0)), 1.0f), bound);
     if ((int)k < K) W[(size_t)o * ldk + k] = v;
     else b[o] = v;
-  }
+  });
 }
 
-inline int grid_for(size_t total) {
-  size_t blocks = (total + 255) / 256;
-  return (int)(blocks < 1 ? 1 : (blocks > 65536 ? 65536 : blocks));
+// lanes of a wavefront that one row of `cols` elements gets, as a power of two
+inline int lanes_log2_for(size_t cols) {
+  int l = 0;
+  while (l < 6 && ((size_t)1 << l) < cols) ++l;
+  return l;
+}
+// blocks of 4 wavefronts; above 2^18 of them the kernels loop
+inline int grid_for(size_t rows, size_t cols, int lanes_log2) {
+  const size_t units = lanes_log2 < 6 ? (rows + (64u >> lanes_log2) - 1) / (64u >> lanes_log2) : rows * ((cols + kRun - 1) / kRun);
+  const size_t blocks = (units + 3) / 4;
+  return (int)(blocks < 1 ? 1 : (blocks > (1u << 18) ? (1u << 18) : blocks));
+}
+
+template <typename T>
+void launch_labels(uint64_t seed, int classes, int dim, int dist, float kappa, T* out, hipStream_t s) {
+  const int ll = lanes_log2_for(dim), grid = grid_for(classes, dim, ll);
+  const uint32_t k0 = (uint32_t)seed, k1 = (uint32_t)(seed >> 32);
+  switch (dist) {
+    case 0: labels_kernel<T, 0><<<grid, 256, 0, s>>>(k0, k1, classes, dim, kappa, out, ll); break;
+    case 1: labels_kernel<T, 1><<<grid, 256, 0, s>>>(k0, k1, classes, dim, kappa, out, ll); break;
+    case 2: labels_kernel<T, 2><<<grid, 256, 0, s>>>(k0, k1, classes, dim, kappa, out, ll); break;
+    default: labels_kernel<T, 3><<<grid, 256, 0, s>>>(k0, k1, classes, dim, kappa, out, ll); break;
+  }
 }
 
 }  // namespace
 
 hipError_t launch_make_labels(uint64_t seed, int classes, int dim, int dist, float kappa, void* out, int dt,
                               hipStream_t s) {
-  labels_kernel<<<grid_for((size_t)classes * dim), 256, 0, s>>>((uint32_t)seed, (uint32_t)(seed >> 32), classes, dim,
-                                                                 dist, kappa, out, dt);
+  if (dt == 1) launch_labels(seed, classes, dim, dist, kappa, (__bf16*)out, s);
+  else launch_labels(seed, classes, dim, dist, kappa, (float*)out, s);
   return hipGetLastError();
 }
 
 hipError_t launch_make_inputs(uint64_t seed, const float* table, int classes, const int32_t* y, int64_t first_sample,
                               int batch, int dim, float sigma, void* out, int dt, hipStream_t s) {
-  inputs_kernel<<<grid_for((size_t)batch * dim), 256, 0, s>>>((uint32_t)seed, (uint32_t)(seed >> 32), table, classes, y,
-                                                              (uint64_t)first_sample, batch, dim, sigma, out, dt);
+  const int ll = lanes_log2_for(dim), grid = grid_for(batch, dim, ll);
+  const uint32_t k0 = (uint32_t)seed, k1 = (uint32_t)(seed >> 32);
+  if (dt == 1)
+    inputs_kernel<<<grid, 256, 0, s>>>(k0, k1, table, classes, y, (uint64_t)first_sample, batch, dim, sigma, (__bf16*)out, ll);
+  else
+    inputs_kernel<<<grid, 256, 0, s>>>(k0, k1, table, classes, y, (uint64_t)first_sample, batch, dim, sigma, (float*)out, ll);
   return hipGetLastError();
 }
 
 hipError_t launch_init_weights(uint64_t seed, int layer, float* W32, int N, int K, int ldk, float* b, hipStream_t s) {
-  init_kernel<<<grid_for((size_t)N * (K + 1)), 256, 0, s>>>((uint32_t)seed, (uint32_t)(seed >> 32), (uint32_t)layer,
-                                                            W32, N, K, ldk, b);
+  const int ll = lanes_log2_for((size_t)K + 1);
+  init_kernel<<<grid_for(N, (size_t)K + 1, ll), 256, 0, s>>>((uint32_t)seed, (uint32_t)(seed >> 32), (uint32_t)layer, W32, N, K, ldk,
+                                                             b, ll);
   return hipGetLastError();
 }
 

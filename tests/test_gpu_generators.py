@@ -1,0 +1,42 @@
+"""Generator kernels at the widths where their split into wavefront runs can go wrong, bit for bit against the oracle.
+
+A wavefront takes runs of 512 columns of one row, rows of at most 32 columns share one: the widths sit on and beside
+those edges, the row counts beside a wavefront's share of short rows."""
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import rng as orng
+from paper_2403_11204_amd import api, datagen
+
+pytestmark = pytest.mark.gpu
+
+
+def bits(t):
+    return t.to(torch.float32).cpu().numpy().view(np.uint32)
+
+
+@pytest.mark.parametrize("dim", [1, 2, 31, 32, 33, 63, 65, 511, 512, 513, 1100])
+@pytest.mark.parametrize("rows", [1, 5, 67])
+def test_labels_inputs_and_weights(dim, rows):
+    seed = (9 << 32) | (dim * 1000 + rows)
+    for dist in (api.UNIFORM01, api.UNIFORM_PM1, api.NORMAL, api.BINARY_PM1):
+        ref = orng.make_synthetic_labels(seed, rows, dim, dist, 2.5)
+        assert np.array_equal(bits(api.make_synthetic_labels(seed, rows, dim, dist, 2.5)), ref.view(np.uint32))
+        got16 = api.make_synthetic_labels(seed, rows, dim, dist, 2.5, api.BF16)
+        assert np.array_equal(bits(got16), orng.round_to_bf16(ref).astype(np.float32).view(np.uint32))
+    table = api.make_synthetic_labels(seed, 3, dim, api.NORMAL)
+    y = datagen.balanced_classes(rows, 3)
+    first = (1 << 32) - 2                    # the sample counter's low word wraps inside the batch
+    ref = orng.make_segment_inputs(seed, table.cpu().numpy(), y, first, 0.05)
+    yd = torch.from_numpy(y).cuda()
+    assert np.array_equal(bits(api.make_segment_inputs(seed, table, yd, first, 0.05)), ref.view(np.uint32))
+    assert np.array_equal(bits(api.make_segment_inputs(seed, table, yd, first, 0.05, api.BF16)),
+                          orng.round_to_bf16(ref).astype(np.float32).view(np.uint32))
+    seg = api.Segment([dim, rows], api.RELU_ALL, api.MSE_SIL, max_batch=4)
+    seg.init(seed)
+    W, b = seg.get_params(0)
+    Wr, br = orng.init_weights(seed, 0, rows, dim)
+    assert np.array_equal(bits(W), np.asarray(Wr, np.float32).view(np.uint32))
+    assert np.array_equal(bits(b), np.asarray(br, np.float32).view(np.uint32))
