@@ -44,36 +44,13 @@
 //     its own 4 MB L2 sees a compact set of operand rows), then walked in column-major groups of 8 tile-rows.
 //     Big products whose tile grid divides into 16 x 16 regions are walked region by region instead, all 8 XCDs
 //     inside one region at a time (see the kernel).
-#include "slp_kernels.h"
+#include "gemm_device.h"
 
 namespace slp {
 namespace {
 
-typedef __bf16 bf16;
-typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
-typedef __attribute__((ext_vector_type(16))) float f32x16;
-typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
-typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
-typedef __attribute__((ext_vector_type(4))) float f32x4;
-
-constexpr uint32_t kOutOfRange = 0x80000000u;   // byte offset beyond any operand (sizes are checked < 2 GiB)
-constexpr int kXcds = 8;
 constexpr int kGroupM = 8;
 constexpr int kRegionWalk = -1;   // GemmArgs::group_m value: walk 16 x 16 regions of tiles (big kernel only)
-
-template <typename T> struct Chunk;
-template <> struct Chunk<bf16> { static constexpr int elems = 8; };
-template <> struct Chunk<float> { static constexpr int elems = 4; };
-
-// 32x32 block forms (one 16-byte chunk pair per call), used by the contraction-split kernel for small products
-__device__ __forceinline__ void mma_chunk(f32x16& acc, const u32x4& a, const u32x4& b, bf16*) {
-  acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), acc, 0, 0, 0);
-}
-__device__ __forceinline__ void mma_chunk(f32x16& acc, const u32x4& a, const u32x4& b, float*) {
-  const f32x4 af = __builtin_bit_cast(f32x4, a), bfv = __builtin_bit_cast(f32x4, b);
-#pragma unroll
-  for (int q = 0; q < 4; ++q) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(af[q], bfv[q], acc, 0, 0, 0);
-}
 
 // MFMA geometry per element type.  bf16: v_mfma_f32_16x16x32_bf16 (a 16x16 block over 32 k = 4 chunks per row; the
 // block's 4 accumulator registers hold rows 4*(lane/16)..+3 of column lane%16); float32: v_mfma_f32_32x32x2_f32, four
@@ -95,27 +72,6 @@ template <> struct Mma<float> {
     for (int q = 0; q < 4; ++q) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(af[q], bfv[q], acc, 0, 0, 0);
   }
 };
-
-template <typename T> struct Vec4;
-template <> struct Vec4<bf16> { typedef bf16x4 type; };
-template <> struct Vec4<float> { typedef f32x4 type; };
-
-// 4x4 transpose across the 4 lanes of a quad (lanes 4g..4g+3): on return, lane i holds in v[j] what lane j held
-// in v[i].  Two butterfly stages of quad-permute DPP moves; every lane of the quad must be active.
-__device__ __forceinline__ float quad_xor(float x, bool by_two) {
-  const int xi = __builtin_bit_cast(int, x);
-  const int r = by_two ? __builtin_amdgcn_update_dpp(0, xi, 0x4E, 0xF, 0xF, true)      // lanes [2,3,0,1]
-                       : __builtin_amdgcn_update_dpp(0, xi, 0xB1, 0xF, 0xF, true);     // lanes [1,0,3,2]
-  return __builtin_bit_cast(float, r);
-}
-__device__ __forceinline__ void quad_transpose(float (&v)[4], int lane) {
-  const bool b0 = lane & 1, b1 = lane & 2;
-  float r;
-  r = quad_xor(b0 ? v[0] : v[1], false); if (b0) v[0] = r; else v[1] = r;
-  r = quad_xor(b0 ? v[2] : v[3], false); if (b0) v[2] = r; else v[3] = r;
-  r = quad_xor(b1 ? v[0] : v[2], true);  if (b1) v[0] = r; else v[2] = r;
-  r = quad_xor(b1 ? v[1] : v[3], true);  if (b1) v[1] = r; else v[3] = r;
-}
 
 // Epilogue of one accumulator register quad: rows mb..mb+3 of output column n, v[e] = row mb+e.  The 4 lanes of
 // a quad hold 4 consecutive columns (n - lane%4 is a multiple of 4), and a lane whose column is past N takes part
@@ -707,99 +663,6 @@ __global__ __launch_bounds__(NW * 64) void gemm_nt_big_kernel(const GemmArgs g) 
 #endif
 }
 
-// Small products: a grid of 64x64 tiles that covers less than half of the compute units leaves
-// most matrix pipes idle, and one wavefront cannot drive more than its own SIMD's pipe.  This
-// variant cuts the output into 32x32 tiles (4x as many workgroups) and splits the CONTRACTION over
-// the 4 wavefronts of a workgroup instead: every k-tile of 128 bytes per row is 4 chunk pairs,
-// wavefront w multiplies pair w of every k-tile into its own 32x32 accumulator, and the four
-// partial accumulators are added through LDS in a fixed order (0,1,2,3: deterministic) before the
-// shared epilogue.  Same LDS-direct loads, row layout and swizzle as the kernel above; four
-// stages of 8 KB, loads three k-tiles ahead, one barrier per k-tile.
-template <typename T, int EPI>
-__global__ __launch_bounds__(256) void gemm_nt_ksplit_kernel(const GemmArgs g) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];   // 4 stages of 64 rows x 128 bytes
-  constexpr int ES = sizeof(T);
-  constexpr int CH = Chunk<T>::elems;
-  constexpr int BK = 128 / ES;
-  constexpr int STAGE = 64 * 128, NS = 4;
-
-  const int tilesM = (g.M + 31) / 32;
-  const int tm = blockIdx.x % tilesM, tn = blockIdx.x / tilesM;   // neighbours share the B rows
-  const int m0 = tm * 32, n0 = tn * 32;
-  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-  const int half = lane >> 5, l32 = lane & 31;
-
-  const int Kr = (g.K + CH - 1) / CH * CH;
-  const __amdgpu_buffer_rsrc_t rsrcA =
-      __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(g.A), 0, (int)((size_t)g.M * g.lda * ES), 0x00020000);
-  const __amdgpu_buffer_rsrc_t rsrcB =
-      __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(g.B), 0, (int)((size_t)g.N * g.ldb * ES), 0x00020000);
-  // one load instruction of the workgroup covers 32 rows: wavefront w rows [8w, 8w+8), lane l -> (row 8w + l/8, chunk l%8)
-  const int prow = w * 8 + (lane >> 3);
-  const int pchunk = (lane & 7) ^ ((prow >> 1) & 7);
-  const uint32_t voffA = (uint32_t)(((size_t)(m0 + prow) * g.lda + pchunk * CH) * ES);
-  const uint32_t voffB = (uint32_t)(((size_t)(n0 + prow) * g.ldb + pchunk * CH) * ES);
-  typedef __attribute__((address_space(3))) void* lds_ptr_t;
-  const uint32_t lds_wave = (uint32_t)__builtin_amdgcn_readfirstlane(w * 8 * 128);
-  auto gload = [&](int kt) {
-    const bool in_k = kt * BK + pchunk * CH < Kr;      // past the end of K every load becomes a zero fill
-    const uint32_t koff = (uint32_t)kt * 128u;
-    unsigned char* sb = smem + (kt & (NS - 1)) * STAGE + lds_wave;
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrcA, (lds_ptr_t)sb, 16, in_k ? voffA + koff : kOutOfRange, 0, 0, 0);
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrcB, (lds_ptr_t)(sb + 32 * 128), 16, in_k ? voffB + koff : kOutOfRange, 0, 0, 0);
-  };
-  // this wavefront's chunk pair of every k-tile: chunks 2w (lanes 0-31) and 2w+1 (lanes 32-63)
-  const uint32_t frag = (uint32_t)(l32 * 128 + (((w * 2 + half) ^ ((lane >> 1) & 7)) << 4));
-
-  const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem;
-  f32x16 acc;
-#pragma unroll
-  for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
-#define VMCNT(n) ((((n) & 15) | 0x0F70 | (((n) >> 4) << 14)))
-  const int nk = (Kr + BK - 1) / BK;
-  gload(0); gload(1); gload(2);
-  for (int kt = 0; kt < nk; ++kt) {
-    // tile kt has landed once at most the loads of tiles kt+1 and kt+2 (two each) are outstanding
-    // A bare barrier between compiler-level memory fences: the workgroup release fence of __syncthreads() makes
-    // the wavefront wait for ALL outstanding LDS-direct loads, which would undo the prefetch.  What the barrier
-    // has to order is covered by hand: this wavefront's loads of tile kt by the vmcnt wait, its LDS reads of tile
-    // kt-1 by the lgkmcnt wait that precedes their MFMA.
-    __builtin_amdgcn_s_waitcnt(VMCNT(4));
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_barrier();  // every wavefront's part of tile kt is in LDS; all are done with tile kt-1
-    asm volatile("" ::: "memory");
-    // fragment reads as instructions, so that their completion is waited for exactly where written
-    const uint32_t sb = lds_base + (uint32_t)((kt & (NS - 1)) * STAGE) + frag;
-    u32x4 a, b;
-    asm volatile("ds_read_b128 %0, %2\n\tds_read_b128 %1, %2 offset:4096" : "=&v"(a), "=&v"(b) : "v"(sb) : "memory");
-    gload(kt + 3);                 // into the stage tile kt-1 occupied
-    asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(a), "+v"(b) : : "memory");
-    mma_chunk(acc, a, b, (T*)nullptr);
-  }
-  __builtin_amdgcn_s_waitcnt(VMCNT(0));
-#undef VMCNT
-  __syncthreads();                 // all stage reads and all (zero-fill) loads are over: the stages become the reduction buffer
-  float* red = (float*)smem;       // [4 wavefronts][16 registers][64 lanes]
-#pragma unroll
-  for (int r = 0; r < 16; ++r) red[(w * 16 + r) * 64 + lane] = acc[r];
-  __syncthreads();
-  // wavefront w finishes register quad w: rows 8w + 4*half .. +3 of column l32
-  float v[4];
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    float sum = red[(0 * 16 + 4 * w + e) * 64 + lane];
-#pragma unroll
-    for (int p = 1; p < 4; ++p) sum += red[(p * 16 + 4 * w + e) * 64 + lane];
-    v[e] = sum;
-  }
-  const int n = n0 + l32;
-  float bias = 0.0f;
-  if (EPI == EPI_FWD && n < g.N) bias = g.bias[n];
-  store_quad<T, EPI>(g, n, m0 + 8 * w + 4 * half, bias, v, lane);
-#endif
-}
-
 // ---- host side -------------------------------------------------------------------------------
 struct TileCfg { int bm, bn; const char* name; };
 const TileCfg kCfgs[3] = {{256, 256, "256x256"}, {128, 128, "128x128"}, {64, 64, "64x64"}};
@@ -877,33 +740,12 @@ hipError_t launch_cfg(int cfg, const GemmArgs& g, hipStream_t s) {
       else return launch_one<T, 256, 256, EPI, 8, 2>(g, s);
     case 1: return launch_one<T, 128, 128, EPI, 8, 4>(g, s);     // 8 wavefronts of 64x32: +5-10 % over 4 of 64x64 here
     case kCfg128TwoStage: return launch_one<T, 128, 128, EPI, 4, 2>(g, s);
-    default: return launch_one<T, 64, 64, EPI, 4, 4>(g, s);
+    default: return hipErrorInvalidValue;     // (small products are launched before the switch)
   }
-}
-
-template <typename T, int EPI>
-hipError_t launch_ksplit(const GemmArgs& g, hipStream_t s) {
-  const int tiles = ((g.M + 31) / 32) * ((g.N + 31) / 32);
-  hipLaunchKernelGGL((gemm_nt_ksplit_kernel<T, EPI>), dim3(tiles), dim3(256), 4 * 64 * 128, s, g);
-  return hipGetLastError();
-}
-
-// 64x64 tiles on fewer than this many workgroups: the contraction-split 32x32 variant fills the chip better
-constexpr long kKsplitBelowTiles = 128;
-bool use_ksplit(int M, int N) {
-  return (long)((M + 63) / 64) * ((N + 63) / 64) < kKsplitBelowTiles;
 }
 
 template <typename T>
 hipError_t launch_epi(int epi, int cfg, const GemmArgs& g, hipStream_t s) {
-  if (cfg == 2 && use_ksplit(g.M, g.N)) {   // (pick_cfg returns 2 for everything small)
-    switch (epi) {
-      case EPI_FWD: return launch_ksplit<T, EPI_FWD>(g, s);
-      case EPI_DGRAD: return launch_ksplit<T, EPI_DGRAD>(g, s);
-      case EPI_WGRAD_UPDATE: return launch_ksplit<T, EPI_WGRAD_UPDATE>(g, s);
-      default: return launch_ksplit<T, EPI_WGRAD>(g, s);
-    }
-  }
   switch (epi) {
     case EPI_FWD: return launch_cfg<T, EPI_FWD>(cfg, g, s);
     case EPI_DGRAD: return launch_cfg<T, EPI_DGRAD>(cfg, g, s);
@@ -919,7 +761,6 @@ hipError_t configure_epi() {
   else e = configure_one<T, 256, 256, EPI, 8, 2>();
   if (e == hipSuccess) e = configure_one<T, 128, 128, EPI, 8, 4>();
   if (e == hipSuccess) e = configure_one<T, 128, 128, EPI, 4, 2>();
-  if (e == hipSuccess) e = configure_one<T, 64, 64, EPI, 4, 4>();
   return e;
 }
 
@@ -936,13 +777,14 @@ hipError_t gemm_configure_all() {
   if (e == hipSuccess) e = configure_epi<float, EPI_DGRAD>();
   if (e == hipSuccess) e = configure_epi<float, EPI_WGRAD>();
   if (e == hipSuccess) e = configure_epi<float, EPI_WGRAD_UPDATE>();
+  if (e == hipSuccess) e = small_configure_all();
   return e;
 }
 
 const char* gemm_config_name(int dtype, int M, int N, int K) {
-  (void)dtype; (void)K;
-  const int c = pick_cfg(M, N);
-  if (c == 2 && use_ksplit(M, N)) return "32x32 k-split";
+  (void)K;
+  const int c = pick_cfg(M, N), t = small_tile(dtype, M, N);
+  if (c == 2 && t < 64) return t == 16 ? "16x16 k-split" : "32x32 k-split";
   return c == kCfg128TwoStage ? "128x128 (2 stages)" : kCfgs[c].name;
 }
 
@@ -965,6 +807,7 @@ hipError_t launch_gemm(int dtype, int epi, const GemmArgs& g, hipStream_t s) {
     return hipErrorInvalidValue;
   if (epi == EPI_WGRAD && (g.ldc % 4 || ((uintptr_t)g.Cf & 15))) return hipErrorInvalidValue;
   const int cfg = pick_cfg(g.M, g.N);
+  if (cfg == 2) return launch_small_product(dtype, epi, g, s);
   GemmArgs h = g;
   // Height of the tile groups each XCD walks (the 32 tiles an XCD runs together are group_m tile rows x 32/group_m
   // tile columns).  8 is best everywhere except the weight gradient of a tall output (64 or more tile rows), whose

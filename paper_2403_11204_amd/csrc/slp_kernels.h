@@ -66,6 +66,11 @@ struct GemmArgs {
 
 // dtype: 0 = float32 operands, 1 = bf16 operands (float32 accumulation in both).
 hipError_t launch_gemm(int dtype, int epi, const GemmArgs& g, hipStream_t s);
+// The products launch_gemm gives to the kernel for small layers (arguments as checked by launch_gemm): 64x64 tiles, or 32x32
+// or 16x16 ones with the contraction split over the wavefronts of a workgroup.
+int small_tile(int dtype, int M, int N);
+hipError_t launch_small_product(int dtype, int epi, const GemmArgs& g, hipStream_t s);
+hipError_t small_configure_all();
 // Name of the tile configuration launch_gemm would pick (for logs and profiles).
 const char* gemm_config_name(int dtype, int M, int N, int K);
 
