@@ -220,6 +220,8 @@ int slp_segment_set_graph(slp_segment* seg, int on);
  * 0.14 ms per step of both partitions).  It pays where a layer's products are short; for very wide layers the separate
  * update, which streams beside the next products, is faster.  on = 0: off (default); 1: every layer; 2: the layers
  * where it measured faster, those with at most 4,194,304 weights; on > 2: the layers with at most `on` weights.
+ * Layers with fewer than 224 tiles of 128x128 weights take the update inside the product in any case, off or on; off, the
+ * gradient is stored beside it.
  * Results equal the separate update's to float32 rounding (the same expressions on the same values).  For a layer
  * that is fused, slp_segment_get_grads returns the bias gradient only (a request for dW fails with SLP_ERR_STATE).
  * Drops captured graphs.  Errors: SLP_ERR_ARG (null handle, on < 0). */

@@ -149,6 +149,24 @@ int run_gemm(slp_segment* s, int epi, const GemmArgs& g, hipStream_t st) {
   return SLP_OK;
 }
 
+// The same for a launch of small layers; the time of what rides along in it counts as the products'.
+int run_group(slp_segment* s, const SmallGroup& gr, hipStream_t st) {
+  ProfRec rec{nullptr, nullptr, 0.0};
+  for (int p = 0; p < gr.n; ++p) rec.flops += 2.0 * gr.g[p].M * (double)gr.g[p].N * gr.g[p].K;
+  if (s->prof) {
+    rec.a = get_event(s);
+    rec.b = get_event(s);
+    if (!rec.a || !rec.b) return fail(SLP_ERR_DEVICE, "hipEventCreate failed");
+    HIP_TRY(hipEventRecord(rec.a, st));
+  }
+  HIP_TRY(launch_small_group(s->dtype, gr, st));
+  if (s->prof) {
+    HIP_TRY(hipEventRecord(rec.b, st));
+    s->prof_log.push_back(rec);
+  }
+  return SLP_OK;
+}
+
 int check_seg(const slp_segment* s, bool need_bound, bool need_params) {
   if (!s) return fail(SLP_ERR_ARG, "segment handle is NULL");
   if (need_bound && !s->bound) return fail(SLP_ERR_STATE, "segment has no device buffers: call slp_segment_bind first");
@@ -164,47 +182,96 @@ int ingest(slp_segment* s, const void* X, int batch, bool with_transpose, hipStr
   return SLP_OK;
 }
 
-// x_direct / out_direct (forward-only passes): the caller's dense input is the first layer's operand and the caller's
-// dense output buffer the last layer's result, when their rows are 16-byte aligned; the workspace copies are skipped.
-int forward_layers(slp_segment* s, int batch, bool training, hipStream_t st, const void* x_direct = nullptr,
-                   void* out_direct = nullptr) {
+// Whether the first layer's product can read the caller's dense input itself: a small layer whose input rows start on 16-byte
+// boundaries.  The copies the rest of the step needs are then made in the same launch.
+bool reads_input(const slp_segment* s, const void* X, int batch) {
+  return product_is_small(batch, s->widths[1]) && (size_t)s->widths[0] * esize(s) % 16 == 0 && ((uintptr_t)X & 15) == 0;
+}
+
+struct Forward {
+  bool training;
+  const void* X;            // the caller's input, dense
+  const void* x_direct;     // large layers of a forward-only pass: X itself is the first layer's operand ...
+  void* out_direct;         // ... and the caller's dense output buffer the last layer's result (their rows are aligned)
+  void* out;                // forward-only: the caller's output buffer
+  const OutJob* last;       // training: the gradient of the output rides along with a small last layer
+};
+
+// Ingest and all layers.  *out_done: the last layer wrote f.out itself; *last_done: it formed the output's gradient.
+int forward_layers(slp_segment* s, int batch, const Forward& f, hipStream_t st, bool* out_done, bool* last_done) {
+  const bool direct = !f.x_direct && reads_input(s, f.X, batch);
+  if (!f.x_direct && !direct) {
+    int rc = ingest(s, f.X, batch, f.training, st);
+    if (rc) return rc;
+  }
   for (int l = 1; l <= s->L; ++l) {
     const Layer& ly = s->layers[l - 1];
     GemmArgs g{};
     g.A = s->A[l - 1]; g.lda = s->ldw[l - 1];
-    if (l == 1 && x_direct) { g.A = x_direct; g.lda = s->widths[0]; }
+    if (l == 1 && (f.x_direct || direct)) { g.A = f.X; g.lda = s->widths[0]; }
     g.B = ly.Wop;      g.ldb = ly.ldk;
     g.M = batch; g.N = ly.N; g.K = ly.K;
     g.C = s->A[l]; g.ldc = s->ldw[l];
-    if (l == s->L && out_direct) { g.C = out_direct; g.ldc = s->widths[l]; }
-    g.CT = (training && l < s->L) ? s->AT[l] : nullptr; g.ldct = s->ldb;
-    g.bits_out = (training && l < s->L) ? s->bits[l] : nullptr; g.ldbits = s->ldbits;
+    if (l == s->L && f.out_direct) { g.C = f.out_direct; g.ldc = s->widths[l]; }
+    g.CT = (f.training && l < s->L) ? s->AT[l] : nullptr; g.ldct = s->ldb;
+    g.bits_out = (f.training && l < s->L) ? s->bits[l] : nullptr; g.ldbits = s->ldbits;
     g.bias = ly.b; g.relu = relu_on(s, l) ? 1 : 0;
-    int rc = run_gemm(s, EPI_FWD, g, st);
+    int rc;
+    if (product_is_small(g.M, g.N)) {
+      SmallGroup gr{};
+      gr.n = 1; gr.epi[0] = EPI_FWD;
+      if (l == 1 && direct) {
+        const int rows_t = (batch + 7) & ~7;
+        gr.has_copy = true;
+        gr.copy = CopyJob{f.X, s->widths[0], batch, s->widths[0], s->A[0], s->ldw[0], f.training ? s->AT[0] : nullptr, s->ldb, rows_t};
+      }
+      if (l == s->L && f.out && f.out != g.C) { g.C2 = f.out; g.ldc2 = s->widths[l]; *out_done = true; }
+      if (l == s->L && f.last) { gr.epi[0] = EPI_FWD_OUT; gr.out = *f.last; *last_done = true; }
+      gr.g[0] = g;
+      rc = run_group(s, gr, st);
+    } else {
+      rc = run_gemm(s, EPI_FWD, g, st);
+    }
     if (rc) return rc;
   }
   return SLP_OK;
 }
 
-// loss and dZ_L (row-major for the data gradient, transposed for the weight gradient)
-int loss_and_output_grad(slp_segment* seg, const int32_t* targets, int batch, float* loss_out, hipStream_t st) {
+// Forward pass of a training step with the loss and dZ_L (row-major for the data gradient, transposed -- with_transpose --
+// for the weight gradient).  *sum: the loss's partial sums, still to be added up.
+int forward_and_loss(slp_segment* seg, const void* X, const int32_t* targets, int batch, bool with_transpose, float* loss_out,
+                     SumJob* sum, hipStream_t st) {
   const int L = seg->L, D = seg->widths[L];
-  if (seg->loss == SLP_MSE_SIL) {
-    HIP_TRY(launch_mse_loss_grad(seg->dtype, seg->A[L], seg->ldw[L], targets, seg->table, seg->classes, batch, D,
-                                 relu_on(seg, L) ? 1 : 0, seg->dZ[L], seg->dZT[L], seg->ldb, seg->partials, seg->bad_ids, st));
-    HIP_TRY(launch_reduce_loss(seg->partials, mse_partial_count(batch, D), 1.0 / ((double)batch * D), seg->loss_dev, loss_out, st));
+  bool out_done = false, last_done = false;
+  OutJob oj{};
+  const bool mse = seg->loss == SLP_MSE_SIL;
+  oj.y = targets; oj.table = seg->table; oj.classes = seg->classes;
+  oj.scale = (float)(2.0 / ((double)batch * (double)D));
+  oj.partials = seg->partials; oj.bad_ids = seg->bad_ids;
+  oj.dZ = seg->dZ[L]; oj.lddz = seg->ldw[L]; oj.dZT = seg->dZT[L]; oj.lddzt = seg->ldb;
+  int rc = forward_layers(seg, batch, Forward{true, X, nullptr, nullptr, nullptr, mse ? &oj : nullptr}, st, &out_done, &last_done);
+  if (rc) return rc;
+  *sum = SumJob{seg->partials, 0, 0.0, seg->loss_dev, loss_out};
+  if (mse) {
+    sum->scale = 1.0 / ((double)batch * D);
+    sum->n = last_done ? small_tile_count(seg->dtype, batch, D) : mse_partial_count(batch, D);
+    if (!last_done)
+      HIP_TRY(launch_mse_loss_grad(seg->dtype, seg->A[L], seg->ldw[L], targets, seg->table, seg->classes, batch, D,
+                                   relu_on(seg, L) ? 1 : 0, seg->dZ[L], seg->dZT[L], seg->ldb, seg->partials, seg->bad_ids, st));
   } else {
+    sum->scale = 1.0 / (double)batch;
+    sum->n = batch;
     HIP_TRY(launch_xent_loss_grad(seg->dtype, seg->A[L], seg->ldw[L], targets, batch, D, relu_on(seg, L) ? 1 : 0,
                                   seg->dZ[L], seg->partials, seg->bad_ids, st));
-    HIP_TRY(launch_copy_transpose(seg->dtype, seg->dZ[L], seg->ldw[L], batch, D, nullptr, 0, seg->dZT[L], seg->ldb, 1,
-                                  nullptr, 0, st));
-    HIP_TRY(launch_reduce_loss(seg->partials, batch, 1.0 / (double)batch, seg->loss_dev, loss_out, st));
+    if (with_transpose)
+      HIP_TRY(launch_copy_transpose(seg->dtype, seg->dZ[L], seg->ldw[L], batch, D, nullptr, 0, seg->dZT[L], seg->ldb, 1,
+                                    nullptr, 0, st));
   }
   return SLP_OK;
 }
 
 // dZ_{l-1} = (dZ_l W_l) * [A_{l-1} > 0]; for l = 1 the result is the gradient w.r.t. the segment input (no mask)
-int data_gradient(slp_segment* seg, int l, int batch, hipStream_t st) {
+GemmArgs data_gradient(slp_segment* seg, int l, int batch) {
   Layer& ly = seg->layers[l - 1];
   GemmArgs g{};
   g.A = seg->dZ[l]; g.lda = seg->ldw[l];
@@ -214,7 +281,7 @@ int data_gradient(slp_segment* seg, int l, int batch, hipStream_t st) {
   g.CT = l > 1 ? seg->dZT[l - 1] : nullptr; g.ldct = seg->ldb;
   g.maskT = l > 1 ? seg->AT[l - 1] : nullptr; g.ldmask = seg->ldb;
   g.bits = l > 1 ? seg->bits[l - 1] : nullptr; g.ldbits = seg->ldbits;
-  return run_gemm(seg, EPI_DGRAD, g, st);
+  return g;
 }
 
 // backward + update, last layer first; the data gradient of layer l reads W_l before it is updated
@@ -242,7 +309,12 @@ constexpr int kSideUpdateWorkgroups = 256;
 // or 4 M weights is 1-2 % faster than fusing none, fusing the 8 M and 16 M layers as well 2 % and 9 % slower (their
 // epilogues wait on weight and momentum loads that the separate, massively parallel update kernel streams).
 constexpr long kFusedAutoMaxWeights = 1L << 22;
-int backward_and_update(slp_segment* seg, int batch, hipStream_t st) {
+//
+// Small layers: the weight gradient's product always applies the update in its epilogue (and stores the gradient as well, unless
+// the fused update is on), and it waits for company: the product of layer l + 1 goes into one launch with the data gradient of
+// layer l, which does not read what it writes, or with the weight gradient of layer l at the end; the bias gradients ride
+// along, and `sum` with the first such launch.  A step of 784-128-64 is 4 launches instead of 10 that way.
+int backward_and_update(slp_segment* seg, int batch, const SumJob* sum, hipStream_t st) {
   // a join cannot be left to a later call while the launches are being captured into a graph
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   if (seg->defer_join && st) HIP_TRY(hipStreamIsCapturing(st, &cap));
@@ -254,10 +326,31 @@ int backward_and_update(slp_segment* seg, int batch, hipStream_t st) {
   // measured: comparison configuration (8192 rows) best at 10-16 units, deep configuration run serially (4096) at 8-14,
   // wide configuration (1024) 18 % slower with any pause.
   const int pause = defer ? std::min(14, std::max(0, (batch - 2048) / 256)) : 0;
+  SmallGroup pending{};                  // weight-gradient products waiting for company
+  auto ride_along = [&](SmallGroup& gr) {
+    if (!sum) return;
+    gr.has_sum = true;
+    gr.sum = *sum;
+    sum = nullptr;
+  };
+  if (sum && !product_is_small(seg->L > 1 ? batch : seg->widths[1], seg->L > 1 ? seg->layers[seg->L - 1].K : seg->widths[0])) {
+    HIP_TRY(launch_reduce_loss(sum->partials, sum->n, sum->scale, sum->out0, sum->out1, st));
+    sum = nullptr;
+  }
   for (int l = seg->L; l >= 1; --l) {
     Layer& ly = seg->layers[l - 1];
     if (l > 1) {
-      int rc = data_gradient(seg, l, batch, st);
+      const GemmArgs d = data_gradient(seg, l, batch);
+      const bool small = product_is_small(d.M, d.N);
+      if (small) {
+        pending.g[pending.n] = d;
+        pending.epi[pending.n++] = EPI_DGRAD;
+        ride_along(pending);
+      }
+      int rc = SLP_OK;
+      if (pending.n) rc = run_group(seg, pending, st);
+      pending = SmallGroup{};
+      if (!rc && !small) rc = run_gemm(seg, EPI_DGRAD, d, st);
       if (rc) return rc;
     }
     GemmArgs g{};
@@ -266,6 +359,28 @@ int backward_and_update(slp_segment* seg, int batch, hipStream_t st) {
     g.M = ly.N; g.N = ly.K; g.K = batch;
     g.Cf = ly.dW; g.ldc = ly.ldk;
     const bool fused = seg->fused_update && (long)ly.N * ly.K <= seg->fused_max_params;
+    if (product_is_small(g.M, g.N)) {
+      if (fused) g.Cf = nullptr;
+      g.uW = ly.W32; g.uV = ly.vW; g.uW16 = ly.W16; g.uWT = ly.WT; g.ldwt = ly.ldn;
+      g.lr = seg->lr; g.mu = seg->mu;
+      pending.g[pending.n] = g;
+      pending.epi[pending.n++] = EPI_WGRAD_UPDATE;
+      pending.bias[pending.n_bias++] = BiasJob{seg->dZT[l], seg->ldb, ly.N, batch, ly.db, ly.b, ly.vb, seg->lr, seg->mu};
+      if (l > 1) continue;
+      ride_along(pending);               // (a segment of one layer)
+    }
+    if (l == 1 && pending.n) {           // the last products: with a deferred join they run beside the caller's next work
+      hipStream_t us = defer ? seg->side : st;
+      if (us != st) {
+        HIP_TRY(hipEventRecord(seg->ev_fork[0], st));
+        HIP_TRY(hipStreamWaitEvent(us, seg->ev_fork[0], 0));
+        forked = true;
+      }
+      int rc = run_group(seg, pending, us);
+      pending = SmallGroup{};
+      if (rc) return rc;
+      if (product_is_small(g.M, g.N)) continue;
+    }
     if (fused) {     // weights, momentum and the derived copies are rewritten by the product's epilogue
       g.uW = ly.W32; g.uV = ly.vW; g.uW16 = ly.W16; g.uWT = ly.WT; g.ldwt = ly.ldn;
       g.lr = seg->lr; g.mu = seg->mu;
@@ -445,7 +560,8 @@ int slp_segment_create(const int* widths, int n_widths, int act, int loss, const
       s->odZT[l] = take((size_t)s->widths[l] * s->ldb * es);
     }
   }
-  s->n_partials = loss == SLP_MSE_SIL ? mse_partial_count(s->max_batch, s->widths[s->L]) : s->max_batch;
+  // one per 64x64 tile of the output; small layers take smaller tiles, but never more than 1024 of them
+  s->n_partials = loss == SLP_MSE_SIL ? std::max(mse_partial_count(s->max_batch, s->widths[s->L]), 1024) : s->max_batch;
   s->oPartials = take((size_t)s->n_partials * 4);
   s->oLoss = take(4);
   s->oBadIds = take(4);
@@ -616,13 +732,11 @@ int slp_segment_forward(slp_segment* seg, const void* X, int batch, void* out, s
   const int w0 = seg->widths[0], w = seg->widths[seg->L];
   const bool x_direct = w0 % kLdRows == 0 && ((uintptr_t)X & 127) == 0;      // rows on cache-line boundaries, else the copy pays
   const bool out_direct = w % kLdAlign == 0 && ((uintptr_t)out & 15) == 0;
-  if (!x_direct) {
-    rc = ingest(seg, X, batch, false, st);
-    if (rc) return rc;
-  }
-  rc = forward_layers(seg, batch, false, st, x_direct ? X : nullptr, out_direct ? out : nullptr);
+  bool out_done = false, last_done = false;
+  rc = forward_layers(seg, batch, Forward{false, X, x_direct ? X : nullptr, out_direct ? out : nullptr, out, nullptr}, st, &out_done,
+                      &last_done);
   if (rc) return rc;
-  if (!out_direct)
+  if (!out_direct && !out_done)
     HIP_TRY(launch_copy_transpose(seg->dtype, seg->A[seg->L], seg->ldw[seg->L], batch, w, out, w, nullptr, 0, 0, nullptr, 0, st));
   seg->last_batch = batch;
   return SLP_OK;
@@ -640,10 +754,9 @@ int slp_segment_step(slp_segment* seg, const void* X, const int32_t* targets, in
   if (rc) return rc;
 
   auto launch_all = [&]() -> int {
-    int r = ingest(seg, X, batch, true, st);
-    if (!r) r = forward_layers(seg, batch, true, st);
-    if (!r) r = loss_and_output_grad(seg, targets, batch, loss_out, st);
-    if (!r) r = backward_and_update(seg, batch, st);
+    SumJob sum{};
+    int r = forward_and_loss(seg, X, targets, batch, true, loss_out, &sum, st);
+    if (!r) r = backward_and_update(seg, batch, &sum, st);
     return r;
   };
   // Eager launches when graphs are off, when launches are being timed one by one, on the null stream (it
@@ -759,18 +872,27 @@ int slp_segment_input_grad(slp_segment* seg, const void* X, const int32_t* targe
   hipStream_t st = (hipStream_t)stream;
   rc = settle(seg, st);
   if (rc) return rc;
-  rc = ingest(seg, X, batch, true, st);
+  SumJob sum{};
+  rc = forward_and_loss(seg, X, targets, batch, false, loss_out, &sum, st);
   if (rc) return rc;
-  rc = forward_layers(seg, batch, true, st);
-  if (rc) return rc;
-  rc = loss_and_output_grad(seg, targets, batch, loss_out, st);
-  if (rc) return rc;
+  const int w0 = seg->widths[0];
+  bool summed = false, dx_done = false;
   for (int l = seg->L; l >= 1; --l) {       // data gradients only, down to the input; parameters untouched
-    rc = data_gradient(seg, l, batch, st);
+    GemmArgs d = data_gradient(seg, l, batch);
+    if (product_is_small(d.M, d.N)) {
+      SmallGroup gr{};
+      if (l == 1) { d.C2 = dX; d.ldc2 = w0; dx_done = true; }
+      gr.g[0] = d; gr.epi[0] = EPI_DGRAD; gr.n = 1;
+      if (!summed) { gr.has_sum = summed = true; gr.sum = sum; }
+      rc = run_group(seg, gr, st);
+    } else {
+      rc = run_gemm(seg, EPI_DGRAD, d, st);
+    }
     if (rc) return rc;
   }
-  const int w0 = seg->widths[0];
-  HIP_TRY(launch_copy_transpose(seg->dtype, seg->dZ[0], seg->ldw[0], batch, w0, dX, w0, nullptr, 0, 0, nullptr, 0, st));
+  if (!summed) HIP_TRY(launch_reduce_loss(sum.partials, sum.n, sum.scale, sum.out0, sum.out1, st));
+  if (!dx_done)
+    HIP_TRY(launch_copy_transpose(seg->dtype, seg->dZ[0], seg->ldw[0], batch, w0, dX, w0, nullptr, 0, 0, nullptr, 0, st));
   seg->last_batch = batch;
   return SLP_OK;
 }
@@ -784,14 +906,17 @@ int slp_segment_step_external(slp_segment* seg, const void* X, const void* dA_ou
   rc = settle(seg, st);
   if (rc) return rc;
   const int L = seg->L, D = seg->widths[L];
-  rc = ingest(seg, X, batch, true, st);
-  if (rc) return rc;
-  rc = forward_layers(seg, batch, true, st);
-  if (rc) return rc;
   // dZ_L = dA_out * [A_L > 0] (ReLU on the last layer) or dA_out, in both layouts
-  HIP_TRY(launch_copy_transpose(seg->dtype, dA_out, D, batch, D, seg->dZ[L], seg->ldw[L], seg->dZT[L], seg->ldb, 1,
-                                relu_on(seg, L) ? seg->A[L] : nullptr, seg->ldw[L], st));
-  rc = backward_and_update(seg, batch, st);
+  OutJob oj{};
+  oj.ext = dA_out;
+  oj.dZ = seg->dZ[L]; oj.lddz = seg->ldw[L]; oj.dZT = seg->dZT[L]; oj.lddzt = seg->ldb;
+  bool out_done = false, last_done = false;
+  rc = forward_layers(seg, batch, Forward{true, X, nullptr, nullptr, nullptr, &oj}, st, &out_done, &last_done);
+  if (rc) return rc;
+  if (!last_done)
+    HIP_TRY(launch_copy_transpose(seg->dtype, dA_out, D, batch, D, seg->dZ[L], seg->ldw[L], seg->dZT[L], seg->ldb, 1,
+                                  relu_on(seg, L) ? seg->A[L] : nullptr, seg->ldw[L], st));
+  rc = backward_and_update(seg, batch, nullptr, st);
   if (rc) return rc;
   seg->last_batch = batch;
   return SLP_OK;

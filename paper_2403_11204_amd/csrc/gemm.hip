@@ -781,6 +781,8 @@ hipError_t gemm_configure_all() {
   return e;
 }
 
+bool product_is_small(int M, int N) { return pick_cfg(M, N) == 2; }
+
 const char* gemm_config_name(int dtype, int M, int N, int K) {
   (void)K;
   const int c = pick_cfg(M, N), t = small_tile(dtype, M, N);
@@ -807,7 +809,11 @@ hipError_t launch_gemm(int dtype, int epi, const GemmArgs& g, hipStream_t s) {
     return hipErrorInvalidValue;
   if (epi == EPI_WGRAD && (g.ldc % 4 || ((uintptr_t)g.Cf & 15))) return hipErrorInvalidValue;
   const int cfg = pick_cfg(g.M, g.N);
-  if (cfg == 2) return launch_small_product(dtype, epi, g, s);
+  if (cfg == 2) {
+    SmallGroup one{};
+    one.g[0] = g; one.epi[0] = epi; one.n = 1;
+    return launch_small_group(dtype, one, s);
+  }
   GemmArgs h = g;
   // Height of the tile groups each XCD walks (the 32 tiles an XCD runs together are group_m tile rows x 32/group_m
   // tile columns).  8 is best everywhere except the weight gradient of a tall output (64 or more tile rows), whose

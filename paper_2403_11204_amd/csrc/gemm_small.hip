@@ -16,6 +16,9 @@
 //   * Each XCD takes a contiguous range of tiles (float32 256x1024x1024: 12 instead of 33 MB into the eight L2s).
 //   * Operand rows are staged as in gemm.hip (128 bytes per row and k-tile, LDS-direct 16-byte loads, XOR swizzle on the
 //     global side, out-of-range rows and k-tail chunks read as zero through the buffer resource's range check).
+#include <stddef.h>
+
+#include "elementwise_device.h"
 #include "gemm_device.h"
 
 namespace slp {
@@ -25,38 +28,67 @@ namespace {
 template <typename T> struct QuadOperands {
   f32x4 w, v;                          // EPI_WGRAD_UPDATE: master weights and momenta of the 4 columns of this lane's row
   typename Vec4<T>::type mask;         // EPI_DGRAD: stored activations of the 4 rows of this lane's column
+  int id;                              // EPI_FWD_OUT: class id of this lane's row ...
+  f32x4 t;                             // ... and its label's, or the given gradient's, 4 columns
 };
 
 // A quad is 4 rows mb..mb+3 of column n in a lane, and, after the 4x4 transpose inside the quad of lanes, 4 columns
 // nb..nb+3 of one row.
 template <typename T, int EPI>
-__device__ __forceinline__ void request_quad(const GemmArgs& g, int n, int mb, int lane, QuadOperands<T>& o) {
+__device__ __forceinline__ void request_quad(const GemmArgs& g, const OutJob& out, int n, int mb, int lane, QuadOperands<T>& o) {
   const int row = mb + (lane & 3), nb = n - (lane & 3);
   if (EPI == EPI_WGRAD_UPDATE) {
-    if (row < g.M && nb < g.N) {
+    if (g.uW && row < g.M && nb < g.N) {
       const size_t idx = (size_t)row * g.ldc + nb;
       o.w = *(const f32x4*)(g.uW + idx);
       if (g.mu != 0.0f) o.v = *(const f32x4*)(g.uV + idx);
     }
   } else if (EPI == EPI_DGRAD && g.maskT && n < g.N && mb < ((g.M + 7) & ~7)) {
     o.mask = *(const typename Vec4<T>::type*)((const T*)g.maskT + (size_t)n * g.ldmask + mb);
+  } else if (EPI == EPI_FWD_OUT && out.table && row < g.M) {
+    o.id = out.y[row];
+  }
+}
+
+// EPI_FWD_OUT, second part, issued behind the first operand loads: the label's columns wait for the class id
+template <typename T>
+__device__ __forceinline__ void request_target(const GemmArgs& g, const OutJob& out, int n, int mb, int lane, QuadOperands<T>& o) {
+  const int row = mb + (lane & 3), nb = n - (lane & 3);
+  o.t = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  if (row >= g.M || nb >= g.N) return;
+  const bool whole = (g.N & 3) == 0;     // rows of the caller's dense matrices divide into whole quads
+  if (out.table) {
+    const float* trow = out.table + (size_t)min(max(o.id, 0), out.classes - 1) * g.N + nb;   // ids are the caller's; never index outside the table
+    if (whole) o.t = *(const f32x4*)trow;
+    else
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (nb + e < g.N) o.t[e] = trow[e];
+  } else {
+    const T* erow = (const T*)out.ext + (size_t)row * g.N + nb;
+    if (whole && ((uintptr_t)out.ext & (4 * sizeof(T) - 1)) == 0) {
+      const typename Vec4<T>::type v = *(const typename Vec4<T>::type*)erow;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o.t[e] = (float)v[e];
+    } else
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (nb + e < g.N) o.t[e] = (float)erow[e];
   }
 }
 
 template <typename T, int EPI>
-__device__ __forceinline__ void finish_quad(const GemmArgs& g, int n, int mb, float bias, float (&v)[4], int lane,
-                                            const QuadOperands<T>& o) {
+__device__ __forceinline__ void finish_quad(const GemmArgs& g, const OutJob& out, int n, int mb, float bias, float (&v)[4], int lane,
+                                            const QuadOperands<T>& o, float& loss) {
   typedef typename Vec4<T>::type vec4;
   const bool col_ok = n < g.N;
   const int row = mb + (lane & 3), nb = n - (lane & 3);
-  if (EPI == EPI_WGRAD || EPI == EPI_WGRAD_UPDATE) {
+  const bool in = row < g.M && nb < g.N;
+  if (EPI == EPI_WGRAD_UPDATE) {
     quad_transpose(v, lane);
-    const bool in = row < g.M && nb < g.N;
     const size_t idx = (size_t)row * g.ldc + nb;
-    if (EPI == EPI_WGRAD) {
-      if (in) *(f32x4*)(g.Cf + idx) = f32x4{v[0], v[1], v[2], v[3]};
-      return;
-    }
+    if (g.Cf && in) *(f32x4*)(g.Cf + idx) = f32x4{v[0], v[1], v[2], v[3]};
+    if (!g.uW) return;
     // v = mu v + g; w -= lr v on 4 consecutive weights of one output row (pad columns hold zeros and stay zero), then back
     // through the transpose: one vector store of 4 output rows of one input column into the transposed copy
     float w[4] = {0.0f, 0.0f, 0.0f, 0.0f};
@@ -79,7 +111,7 @@ __device__ __forceinline__ void finish_quad(const GemmArgs& g, int n, int mb, fl
     return;
   }
   if (mb >= ((g.M + 7) & ~7)) return;       // the same for the whole quad
-  if (EPI == EPI_FWD) {
+  if (EPI == EPI_FWD || EPI == EPI_FWD_OUT) {
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       v[e] += bias;
@@ -94,13 +126,45 @@ __device__ __forceinline__ void finish_quad(const GemmArgs& g, int n, int mb, fl
   for (int e = 0; e < 4; ++e)
     if (mb + e >= g.M || !col_ok) v[e] = 0.0f;
   if (g.CT && col_ok) *(vec4*)((T*)g.CT + (size_t)n * g.ldct + mb) = vec4{(T)v[0], (T)v[1], (T)v[2], (T)v[3]};
-  if (g.C) {
-    quad_transpose(v, lane);
-    if (row < g.M && nb < g.N) *(vec4*)((T*)g.C + (size_t)row * g.ldc + nb) = vec4{(T)v[0], (T)v[1], (T)v[2], (T)v[3]};
+  if (EPI != EPI_FWD_OUT && !g.C && !g.C2) return;
+  quad_transpose(v, lane);
+  const vec4 r = vec4{(T)v[0], (T)v[1], (T)v[2], (T)v[3]};
+  if (g.C && in) *(vec4*)((T*)g.C + (size_t)row * g.ldc + nb) = r;
+  if (g.C2 && in) {
+    T* c2 = (T*)g.C2 + (size_t)row * g.ldc2 + nb;
+    if (((g.ldc2 | g.N) & 3) == 0 && ((uintptr_t)g.C2 & (4 * sizeof(T) - 1)) == 0) *(vec4*)c2 = r;
+    else
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (nb + e < g.N) c2[e] = r[e];
+  }
+  if (EPI == EPI_FWD_OUT) {
+    float d[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    if (row < g.M) {
+      if (out.table && nb == 0 && (o.id < 0 || o.id >= out.classes)) atomicAdd(out.bad_ids, 1u);   // once per row; rare, and the count is an integer
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (nb + e < g.N) {
+          const float a = (float)r[e];
+          if (out.table) {
+            const float diff = a - o.t[e];
+            loss += diff * diff;
+            d[e] = out.scale * diff;
+          } else d[e] = o.t[e];
+          if (g.relu && !(a > 0.0f)) d[e] = 0.0f;
+        }
+    }
+    if (in) *(vec4*)((T*)out.dZ + (size_t)row * out.lddz + nb) = vec4{(T)d[0], (T)d[1], (T)d[2], (T)d[3]};
+    quad_transpose(d, lane);
+    if (col_ok) *(vec4*)((T*)out.dZT + (size_t)n * out.lddzt + mb) = vec4{(T)d[0], (T)d[1], (T)d[2], (T)d[3]};
   }
 }
 
 typedef __attribute__((address_space(3))) void* lds_ptr_t;
+
+// LDS: four stages of 16 KB at TILE 64, of 8 KB at TILE 16 and 32 (several workgroups per compute unit), and 64 bytes behind
+// the 32 or 64 KB for the partial sums of the loss
+constexpr int kStages = 4, kTailBytes = 64, kLds32 = kStages * 64 * 128 + kTailBytes, kLds64 = kStages * 128 * 128 + kTailBytes;
 
 // 16x16 block; lane -> row lane % 16, k-group lane / 16; the accumulator holds rows 4 * (lane / 16) .. + 3 of column lane % 16.
 // bf16: 4 chunks (64 bytes) per row, one per group.  float32: a chunk pair per row, the even chunk in groups 0 and 2, the odd
@@ -124,7 +188,7 @@ __device__ __forceinline__ void mma16(f32x4& acc, const u32x4& a, const u32x4& b
     asm volatile("" ::: "memory");                     \
   } while (0)
 template <typename T, int TILE, int STAGES, int EPI>
-__device__ __forceinline__ void product_tile(const GemmArgs& g, int tm, int tn, unsigned char* smem) {
+__device__ __forceinline__ void product_tile(const GemmArgs& g, const OutJob& out, int tm, int tn, int tile_index, unsigned char* smem) {
 #if defined(__HIP_DEVICE_COMPILE__)
   constexpr int ES = sizeof(T), CH = Chunk<T>::elems, BK = 128 / ES;
   constexpr int NQ = TILE == 64 ? 4 : 1;       // accumulator quads a lane finishes
@@ -136,11 +200,11 @@ __device__ __forceinline__ void product_tile(const GemmArgs& g, int tm, int tn, 
   const int mq = TILE == 16 ? m0 + 4 * g16 : (TILE == 32 ? m0 + 8 * w + 4 * half : m0 + (w & 1) * 32 + 4 * half);
   const int n = TILE == 16 ? n0 + l16 : (TILE == 32 ? n0 + l32 : n0 + (w >> 1) * 32 + l32);
   QuadOperands<T> ops[NQ];
-  float bias = 0.0f;
+  float bias = 0.0f, loss = 0.0f;
   if (TILE != 16 || w == 0) {
 #pragma unroll
-    for (int q = 0; q < NQ; ++q) request_quad<T, EPI>(g, n, mq + 8 * q, lane, ops[q]);
-    if (EPI == EPI_FWD && n < g.N) bias = g.bias[n];
+    for (int q = 0; q < NQ; ++q) request_quad<T, EPI>(g, out, n, mq + 8 * q, lane, ops[q]);
+    if ((EPI == EPI_FWD || EPI == EPI_FWD_OUT) && n < g.N) bias = g.bias[n];
   }
 
   const int Kr = (g.K + CH - 1) / CH * CH, nk = (Kr + BK - 1) / BK;
@@ -191,6 +255,7 @@ __device__ __forceinline__ void product_tile(const GemmArgs& g, int tm, int tn, 
     const int nit = (nk + KT - 1) / KT;        // k-tiles past the end are zeros: their products change nothing
 #pragma unroll
     for (int s = 0; s < STAGES - 1; ++s) load(s, s);
+    if (EPI == EPI_FWD_OUT && (TILE != 16 || w == 0)) request_target<T>(g, out, n, mq, lane, ops[0]);
     for (int it = 0; it < nit; ++it) {
       SLP_WAIT_BARRIER((STAGES - 2) * KT * LPT);       // stage `it` has landed; nobody reads the one before any more
       const unsigned char* d = smem + (it & (STAGES - 1)) * STAGE + fo;
@@ -224,7 +289,7 @@ __device__ __forceinline__ void product_tile(const GemmArgs& g, int tm, int tn, 
       for (int p = 1; p < 4; ++p) sum += red[(p * NR + q0 + e) * 64 + lane];
       v[e] = sum;
     }
-    finish_quad<T, EPI>(g, n, mq, bias, v, lane, ops[0]);
+    finish_quad<T, EPI>(g, out, n, mq, bias, v, lane, ops[0], loss);
   } else {
     // shared stages: [STAGES][A 64 rows, B 64 rows][128 bytes]; wavefront w loads rows 8 w + lr and 32 + 8 w + lr of both
     constexpr int STAGE = 128 * 128;
@@ -249,6 +314,10 @@ __device__ __forceinline__ void product_tile(const GemmArgs& g, int tm, int tn, 
     const uint32_t fa = (uint32_t)((w & 1) * 4096), fb = (uint32_t)(8192 + (w >> 1) * 4096);
 #pragma unroll
     for (int s = 0; s < STAGES - 1; ++s) load(s, s);
+    if (EPI == EPI_FWD_OUT) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) request_target<T>(g, out, n, mq + 8 * q, lane, ops[q]);
+    }
     for (int kt = 0; kt < nk; ++kt) {
       SLP_WAIT_BARRIER((STAGES - 2) * 4);        // tile kt has landed; nobody reads the stage of tile kt - 1 any more
       const unsigned char* d = smem + (kt & (STAGES - 1)) * STAGE;
@@ -269,57 +338,92 @@ __device__ __forceinline__ void product_tile(const GemmArgs& g, int tm, int tn, 
       float v[4];
 #pragma unroll
       for (int e = 0; e < 4; ++e) v[e] = acc[4 * q + e];
-      finish_quad<T, EPI>(g, n, mq + 8 * q, bias, v, lane, ops[q]);
+      finish_quad<T, EPI>(g, out, n, mq + 8 * q, bias, v, lane, ops[q], loss);
+    }
+  }
+  if (EPI == EPI_FWD_OUT && out.table) {     // one partial sum per tile, the wavefronts' added in a fixed order
+    loss = wave_sum(loss);
+    if (TILE == 16) {
+      if (lane == 0) out.partials[tile_index] = loss;
+    } else {
+      float* part = (float*)(smem + (TILE == 64 ? kLds64 : kLds32) - kTailBytes);
+      if (lane == 0) part[w] = loss;
+      __syncthreads();
+      if (t == 0) out.partials[tile_index] = (part[0] + part[1]) + (part[2] + part[3]);
     }
   }
 #endif
 }
 
-template <typename T, int TILE, int STAGES>
-__global__ __launch_bounds__(256) void small_product_kernel(const GemmArgs g, const int epi) {
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+struct GroupLaunch {
+  SmallGroup s;                   // (g[0], g[1] first)
+  int tile[2], tiles[2];          // per product: tile edge, number of tiles
+  int first[2];                   // first workgroup of each product, a multiple of 8
+  int bias_first[2], sum_first, copy_first;
+};
+
+template <typename T, int TILE>
+__device__ __forceinline__ void product_block(const GemmArgs& g, int epi, const OutJob& out, int local, int total, unsigned char* smem) {
+  if (local >= total) return;     // (padding up to the next product's first workgroup)
   // consecutive workgroups go round-robin over the 8 XCDs: each XCD gets a contiguous range of tiles, walked along the shorter
   // side of the output, so that its L2 fetches that side's operand once and an eighth of the other
-  const int tilesM = (g.M + TILE - 1) / TILE, tilesN = (g.N + TILE - 1) / TILE, total = tilesM * tilesN;
-  const int xcd = blockIdx.x % kXcds, base = total / kXcds, rem = total % kXcds;
-  const int tid = xcd * base + (xcd < rem ? xcd : rem) + blockIdx.x / kXcds;
+  const int tilesM = (g.M + TILE - 1) / TILE, tilesN = (g.N + TILE - 1) / TILE;
+  const int xcd = local % kXcds, base = total / kXcds, rem = total % kXcds;
+  const int tid = xcd * base + (xcd < rem ? xcd : rem) + local / kXcds;
   const bool down = tilesM <= tilesN;
   const int tm = down ? tid % tilesM : tid / tilesN, tn = down ? tid / tilesM : tid % tilesN;
-  switch (epi) {       // (uniform over the launch)
-    case EPI_FWD: product_tile<T, TILE, STAGES, EPI_FWD>(g, tm, tn, smem); break;
-    case EPI_DGRAD: product_tile<T, TILE, STAGES, EPI_DGRAD>(g, tm, tn, smem); break;
-    case EPI_WGRAD: product_tile<T, TILE, STAGES, EPI_WGRAD>(g, tm, tn, smem); break;
-    default: product_tile<T, TILE, STAGES, EPI_WGRAD_UPDATE>(g, tm, tn, smem); break;
+  switch (epi) {
+    case EPI_FWD: product_tile<T, TILE, kStages, EPI_FWD>(g, out, tm, tn, tid, smem); break;
+    case EPI_DGRAD: product_tile<T, TILE, kStages, EPI_DGRAD>(g, out, tm, tn, tid, smem); break;
+    case EPI_WGRAD:               // (the same without uW)
+    case EPI_WGRAD_UPDATE: product_tile<T, TILE, kStages, EPI_WGRAD_UPDATE>(g, out, tm, tn, tid, smem); break;
+    default: product_tile<T, TILE, kStages, EPI_FWD_OUT>(g, out, tm, tn, tid, smem); break;
   }
 }
 
-constexpr int lds_bytes(int tile, int stages) { return stages * (tile == 64 ? 128 : 64) * 128; }
+static_assert(offsetof(GroupLaunch, s) == 0 && offsetof(SmallGroup, g) == 0, "the kernel reads its products from the start of its arguments");
 
-template <typename T, int TILE, int STAGES>
+// One launch: the tiles of up to two products, then the bias gradients, the sum of the loss and the input's copies, a range of
+// workgroups each.  Everything that selects a path is uniform over a workgroup.
+template <typename T>
+__global__ __launch_bounds__(256) void small_group_kernel(const GroupLaunch a) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  const int b = blockIdx.x;
+  if (b < a.bias_first[0]) {
+    const bool second = a.s.n > 1 && b >= a.first[1];
+    // read at an offset into the argument segment, not as a choice between two of its parts (which goes through memory)
+#if defined(__HIP_DEVICE_COMPILE__)
+    const GemmArgs& g = ((const GemmArgs*)(const void*)__builtin_amdgcn_kernarg_segment_ptr())[second ? 1 : 0];
+#else
+    const GemmArgs& g = a.s.g[0];
+#endif
+    const int epi = second ? a.s.epi[1] : a.s.epi[0], tile = second ? a.tile[1] : a.tile[0];
+    const int total = second ? a.tiles[1] : a.tiles[0], local = second ? b - a.first[1] : b;
+    if (tile == 16) product_block<T, 16>(g, epi, a.s.out, local, total, smem);
+    else if (tile == 32) product_block<T, 32>(g, epi, a.s.out, local, total, smem);
+    else product_block<T, 64>(g, epi, a.s.out, local, total, smem);
+  } else if (b < a.sum_first) {
+    const bool second = b >= a.bias_first[1];
+    const BiasJob& j = second ? a.s.bias[1] : a.s.bias[0];
+    bias_grad_update_block<T>(second ? b - a.bias_first[1] : b - a.bias_first[0], (const T*)j.dZT, j.ldt, j.N, j.B, j.db, j.b, j.vb, j.lr, j.mu);
+  } else if (b < a.copy_first) {
+    reduce_loss_block((double*)smem, a.s.sum.partials, a.s.sum.n, a.s.sum.scale, a.s.sum.out0, a.s.sum.out1);
+  } else {
+    const CopyJob& c = a.s.copy;
+    const int local = b - a.copy_first, across = (c.C + 63) / 64;
+    copy_transpose_block<T, 64>(local % across, local / across, (typename Vec16<T>::type*)smem, (const T*)c.in, c.ldin, c.R, c.C,
+                                (T*)c.out, c.ldo, (T*)c.outT, c.ldt, c.rows_t, nullptr, 0);
+  }
+}
+
+template <typename T>
 hipError_t configure() {
   static std::once_flag once;
   static hipError_t result = hipSuccess;
   std::call_once(once, [] {
-    result = hipFuncSetAttribute((const void*)small_product_kernel<T, TILE, STAGES>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                 lds_bytes(TILE, STAGES));
+    result = hipFuncSetAttribute((const void*)small_group_kernel<T>, hipFuncAttributeMaxDynamicSharedMemorySize, kLds64);
   });
   return result;
-}
-
-template <typename T, int TILE, int STAGES>
-hipError_t launch(const GemmArgs& g, int epi, hipStream_t s) {
-  hipError_t e = configure<T, TILE, STAGES>();
-  if (e != hipSuccess) return e;
-  const int tiles = ((g.M + TILE - 1) / TILE) * ((g.N + TILE - 1) / TILE);
-  small_product_kernel<T, TILE, STAGES><<<tiles, 256, lds_bytes(TILE, STAGES), s>>>(g, epi);
-  return hipGetLastError();
-}
-
-template <typename T>
-hipError_t launch_t(const GemmArgs& g, int epi, int tile, hipStream_t s) {
-  if (tile == 64) return launch<T, 64, 4>(g, epi, s);
-  if (tile == 32) return launch<T, 32, 4>(g, epi, s);
-  return launch<T, 16, 4>(g, epi, s);
 }
 
 }  // namespace
@@ -338,19 +442,67 @@ int small_tile(int dtype, int M, int N) {
   return tiles(64) < 128 ? 32 : 64;
 }
 
-hipError_t small_configure_all() {
-  hipError_t e = configure<bf16, 16, 4>();
-  if (e == hipSuccess) e = configure<bf16, 32, 4>();
-  if (e == hipSuccess) e = configure<bf16, 64, 4>();
-  if (e == hipSuccess) e = configure<float, 16, 4>();
-  if (e == hipSuccess) e = configure<float, 32, 4>();
-  if (e == hipSuccess) e = configure<float, 64, 4>();
-  return e;
+int small_tile_count(int dtype, int M, int N) {
+  const int t = small_tile(dtype, M, N);
+  return ((M + t - 1) / t) * ((N + t - 1) / t);
 }
 
-hipError_t launch_small_product(int dtype, int epi, const GemmArgs& g, hipStream_t s) {
-  const int tile = small_tile(dtype, g.M, g.N);
-  return dtype == 1 ? launch_t<bf16>(g, epi, tile, s) : launch_t<float>(g, epi, tile, s);
+hipError_t small_configure_all() {
+  hipError_t e = configure<bf16>();
+  return e == hipSuccess ? configure<float>() : e;
+}
+
+hipError_t launch_small_group(int dtype, const SmallGroup& group, hipStream_t s) {
+  const int es = dtype == 1 ? 2 : 4, ch = 16 / es;
+  auto off = [](const void* p) { return ((uintptr_t)p & 15) != 0; };
+  if (group.n < 1 || group.n > 2 || group.n_bias < 0 || group.n_bias > 2) return hipErrorInvalidValue;
+  GroupLaunch a{};
+  a.s = group;
+  int next = 0, lds = kLds32;
+  for (int p = 0; p < group.n; ++p) {
+    const GemmArgs& g = group.g[p];
+    const int epi = group.epi[p];
+    if (g.M <= 0 || g.N <= 0 || g.K <= 0 || !g.A || !g.B || off(g.A) || off(g.B) || g.lda % ch || g.ldb % ch) return hipErrorInvalidValue;
+    // operands are addressed with 32-bit byte offsets and a 2 GiB sentinel
+    if ((size_t)g.M * g.lda * es >= 0x80000000ull || (size_t)g.N * g.ldb * es >= 0x80000000ull) return hipErrorInvalidValue;
+    if (epi == EPI_WGRAD || epi == EPI_WGRAD_UPDATE) {
+      if (g.ldc % 4 || off(g.Cf) || (epi == EPI_WGRAD && !g.Cf)) return hipErrorInvalidValue;
+      if (epi == EPI_WGRAD_UPDATE && (!g.uW || !g.uV || off(g.uW) || off(g.uV) || off(g.uW16) || off(g.uWT) || (g.uWT && g.ldwt % kLdAlign)))
+        return hipErrorInvalidValue;
+    } else {
+      if ((epi != EPI_DGRAD && !g.bias) || (!g.C && !g.CT && !g.C2)) return hipErrorInvalidValue;
+      if ((g.C && (g.ldc % kLdAlign || off(g.C))) || (g.CT && (g.ldct % kLdAlign || off(g.CT)))) return hipErrorInvalidValue;
+      if (epi == EPI_DGRAD && g.maskT && (g.ldmask % kLdAlign || off(g.maskT))) return hipErrorInvalidValue;
+    }
+    if (epi == EPI_FWD_OUT) {
+      const OutJob& o = group.out;
+      if (p != 0 || !g.C || !o.dZ || !o.dZT || off(o.dZ) || off(o.dZT) || o.lddz % kLdAlign || o.lddzt % kLdAlign) return hipErrorInvalidValue;
+      if (o.table ? (!o.y || !o.partials || !o.bad_ids || o.classes <= 0) : !o.ext) return hipErrorInvalidValue;
+    }
+    a.tile[p] = small_tile(dtype, g.M, g.N);
+    a.tiles[p] = small_tile_count(dtype, g.M, g.N);
+    a.first[p] = round_up(next, kXcds);
+    next = a.first[p] + a.tiles[p];
+    if (a.tile[p] == 64) lds = kLds64;
+  }
+  for (int p = 0; p < 2; ++p) {
+    a.bias_first[p] = next;
+    if (p < group.n_bias) next += (group.bias[p].N + 3) / 4;
+  }
+  a.sum_first = next;
+  if (group.has_sum) next += 1;
+  a.copy_first = next;
+  if (group.has_copy) {
+    const CopyJob& c = group.copy;
+    if (off(c.in) || off(c.out) || off(c.outT) || c.ldin % ch || (c.out && c.ldo % ch) || (c.outT && (c.ldt % ch || c.rows_t % ch)))
+      return hipErrorInvalidValue;
+    next += ((c.C + 63) / 64) * ((c.R + 63) / 64);
+  }
+  hipError_t e = dtype == 1 ? configure<bf16>() : configure<float>();
+  if (e != hipSuccess) return e;
+  if (dtype == 1) small_group_kernel<bf16><<<next, 256, lds, s>>>(a);
+  else small_group_kernel<float><<<next, 256, lds, s>>>(a);
+  return hipGetLastError();
 }
 
 }  // namespace slp

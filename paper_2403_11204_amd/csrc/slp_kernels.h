@@ -27,7 +27,7 @@ inline int internal_ld(int width, int esize) {
   return ld;
 }
 
-enum Epilogue { EPI_FWD = 0, EPI_DGRAD = 1, EPI_WGRAD = 2, EPI_WGRAD_UPDATE = 3 };
+enum Epilogue { EPI_FWD = 0, EPI_DGRAD = 1, EPI_WGRAD = 2, EPI_WGRAD_UPDATE = 3, EPI_FWD_OUT = 4 /* small layers only, see OutJob */ };
 
 // C[m][n] = sum_k A[m][k] * B[n][k]  ("NT": both operands contraction-contiguous).
 struct GemmArgs {
@@ -62,14 +62,50 @@ struct GemmArgs {
   float* uW; float* uV; void* uW16; void* uWT;
   int ldwt;
   float lr, mu;
+  // Small layers only: a second copy of C for EPI_FWD and EPI_DGRAD, e.g. the caller's dense matrix ([M][ldc2], any
+  // alignment; columns >= N are not written), and, for EPI_WGRAD_UPDATE, Cf may be given to store the gradient as well.
+  void* C2;
+  int ldc2;
 };
 
 // dtype: 0 = float32 operands, 1 = bf16 operands (float32 accumulation in both).
 hipError_t launch_gemm(int dtype, int epi, const GemmArgs& g, hipStream_t s);
-// The products launch_gemm gives to the kernel for small layers (arguments as checked by launch_gemm): 64x64 tiles, or 32x32
-// or 16x16 ones with the contraction split over the wavefronts of a workgroup.
+// Small layers (product_is_small: fewer 128x128 tiles than compute units) run in a kernel of their own, on 64x64 tiles or 32x32
+// or 16x16 ones with the contraction split over the wavefronts of a workgroup.  One launch takes up to two products that do
+// not depend on each other and what hangs on them: a step of small layers is a chain of launches of a few microseconds
+// each, so what can share one does.
+bool product_is_small(int M, int N);
 int small_tile(int dtype, int M, int N);
-hipError_t launch_small_product(int dtype, int epi, const GemmArgs& g, hipStream_t s);
+int small_tile_count(int dtype, int M, int N);
+// EPI_FWD_OUT: the forward product of the last layer together with the gradient of the output.  A = act(acc + bias) goes to C
+// as for EPI_FWD; the pre-activation's gradient, zero where relu and A is not positive, to dZ ([M][lddz]) and dZT ([N][lddzt],
+// zero-filled pads):
+//   table given: mean squared error against table[y[m]] ([classes][N], float32): scale * (A - label); one partial sum of
+//     squares per tile to partials; ids outside the table are clamped and their rows counted into *bad_ids;
+//   else: ext[m][n], the caller's dense gradient of the output.
+struct OutJob {
+  const int32_t* y; const float* table; int classes; float scale; float* partials; unsigned* bad_ids;
+  const void* ext;
+  void* dZ; void* dZT; int lddz, lddzt;
+};
+// bias gradient and update from dZT ([N][ldt], B columns), see launch_layer_update
+struct BiasJob { const void* dZT; int ldt, N, B; float *db, *b, *vb; float lr, mu; };
+// out0 (and out1 if not null) = scale * sum(partials[0..n))
+struct SumJob { const float* partials; int n; double scale; float *out0, *out1; };
+// in[R][ldin] -> out[R][ldo] (may be null) and outT[C][ldt] (may be null) with columns up to rows_t; every row of every
+// matrix on a 16-byte boundary
+struct CopyJob { const void* in; int ldin, R, C; void* out; int ldo; void* outT; int ldt, rows_t; };
+struct SmallGroup {
+  GemmArgs g[2];
+  int epi[2];
+  int n, n_bias;             // products (1 or 2; the second is never EPI_FWD_OUT), bias jobs (0 to 2)
+  BiasJob bias[2];
+  bool has_sum, has_copy;
+  SumJob sum;
+  CopyJob copy;
+  OutJob out;
+};
+hipError_t launch_small_group(int dtype, const SmallGroup& group, hipStream_t s);
 hipError_t small_configure_all();
 // Name of the tile configuration launch_gemm would pick (for logs and profiles).
 const char* gemm_config_name(int dtype, int M, int N, int K);

@@ -66,3 +66,32 @@ def test_products_of_one_layer(B, K, N, fused, dtype):
     P2 = torch.softmax(Z2, 1)
     P2[torch.arange(B), y.long()] -= 1.0
     assert close(dX2, (P2 / B) @ W2.cpu().to(tdt).double(), TOL[dtype])
+
+
+@pytest.mark.parametrize("dtype", [api.F32, api.BF16])
+@pytest.mark.parametrize("w0", [24, 60, 61, 64])
+@pytest.mark.parametrize("wl", [8, 12, 47])
+def test_workspace_copies_of_input_and_output(w0, wl, dtype):
+    """Small layers read the caller's input and write its output themselves where the rows' alignment allows it: the copies
+    that slp_segment_get_activation returns are made all the same, but where the interface says that X and out are used in
+    place (rows of X on 128-byte boundaries with a width that divides by 64, of out on 16-byte ones with one by 8)."""
+    g = torch.Generator().manual_seed(w0 + wl)
+    tdt = torch.float32 if dtype == api.F32 else torch.bfloat16
+    B = 37
+    seg = api.Segment([w0, 33, wl], api.RELU_ALL, api.MSE_SIL, max_batch=B, dtype=dtype)
+    seg.init(3)
+    table = torch.rand(5, wl, generator=g).cuda()
+    seg.set_labels(table)
+    X = torch.rand(B, w0, generator=g).to(tdt).cuda()
+    y = torch.randint(0, 5, (B,), generator=g, dtype=torch.int32).cuda()
+    out = seg.forward(X)
+    if w0 != 64:
+        assert torch.equal(seg.get_activation(0, B), X)
+    if wl != 8:
+        assert torch.equal(seg.get_activation(2, B), out)
+    loss = seg.step(X, y)
+    assert torch.equal(seg.get_activation(0, B), X) and torch.equal(seg.get_activation(2, B), out)
+    diff = out.double() - table.double()[y.long()]
+    assert abs(float(loss) - float(diff.square().mean())) <= 1e-5 * float(diff.square().mean())
+    dz = torch.where(out > 0, diff * (2.0 / (B * wl)), torch.zeros_like(diff))
+    assert close(seg.get_activation(2, B, kind=1), dz, TOL[dtype])
