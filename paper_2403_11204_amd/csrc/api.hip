@@ -185,7 +185,7 @@ int ingest(slp_segment* s, const void* X, int batch, bool with_transpose, hipStr
 // Whether the first layer's product can read the caller's dense input itself: a small layer whose input rows start on 16-byte
 // boundaries.  The copies the rest of the step needs are then made in the same launch.
 bool reads_input(const slp_segment* s, const void* X, int batch) {
-  return product_is_small(batch, s->widths[1]) && (size_t)s->widths[0] * esize(s) % 16 == 0 && ((uintptr_t)X & 15) == 0;
+  return product_is_small(s->dtype, EPI_FWD, batch, s->widths[1]) && (size_t)s->widths[0] * esize(s) % 16 == 0 && ((uintptr_t)X & 15) == 0;
 }
 
 struct Forward {
@@ -217,7 +217,7 @@ int forward_layers(slp_segment* s, int batch, const Forward& f, hipStream_t st, 
     g.bits_out = (f.training && l < s->L) ? s->bits[l] : nullptr; g.ldbits = s->ldbits;
     g.bias = ly.b; g.relu = relu_on(s, l) ? 1 : 0;
     int rc;
-    if (product_is_small(g.M, g.N)) {
+    if (product_is_small(s->dtype, EPI_FWD, g.M, g.N)) {
       SmallGroup gr{};
       gr.n = 1; gr.epi[0] = EPI_FWD;
       if (l == 1 && direct) {
@@ -333,7 +333,8 @@ int backward_and_update(slp_segment* seg, int batch, const SumJob* sum, hipStrea
     gr.sum = *sum;
     sum = nullptr;
   };
-  if (sum && !product_is_small(seg->L > 1 ? batch : seg->widths[1], seg->L > 1 ? seg->layers[seg->L - 1].K : seg->widths[0])) {
+  if (sum && !(seg->L > 1 ? product_is_small(seg->dtype, EPI_DGRAD, batch, seg->layers[seg->L - 1].K)
+                          : product_is_small(seg->dtype, EPI_WGRAD_UPDATE, seg->widths[1], seg->widths[0]))) {
     HIP_TRY(launch_reduce_loss(sum->partials, sum->n, sum->scale, sum->out0, sum->out1, st));
     sum = nullptr;
   }
@@ -341,7 +342,7 @@ int backward_and_update(slp_segment* seg, int batch, const SumJob* sum, hipStrea
     Layer& ly = seg->layers[l - 1];
     if (l > 1) {
       const GemmArgs d = data_gradient(seg, l, batch);
-      const bool small = product_is_small(d.M, d.N);
+      const bool small = product_is_small(seg->dtype, EPI_DGRAD, d.M, d.N);
       if (small) {
         pending.g[pending.n] = d;
         pending.epi[pending.n++] = EPI_DGRAD;
@@ -359,7 +360,8 @@ int backward_and_update(slp_segment* seg, int batch, const SumJob* sum, hipStrea
     g.M = ly.N; g.N = ly.K; g.K = batch;
     g.Cf = ly.dW; g.ldc = ly.ldk;
     const bool fused = seg->fused_update && (long)ly.N * ly.K <= seg->fused_max_params;
-    if (product_is_small(g.M, g.N)) {
+    const bool small = product_is_small(seg->dtype, EPI_WGRAD_UPDATE, g.M, g.N);
+    if (small) {
       if (fused) g.Cf = nullptr;
       g.uW = ly.W32; g.uV = ly.vW; g.uW16 = ly.W16; g.uWT = ly.WT; g.ldwt = ly.ldn;
       g.lr = seg->lr; g.mu = seg->mu;
@@ -379,8 +381,9 @@ int backward_and_update(slp_segment* seg, int batch, const SumJob* sum, hipStrea
       int rc = run_group(seg, pending, us);
       pending = SmallGroup{};
       if (rc) return rc;
-      if (product_is_small(g.M, g.N)) continue;
+      if (small) continue;
     }
+      g.Cf = nullptr;
     if (fused) {     // weights, momentum and the derived copies are rewritten by the product's epilogue
       g.uW = ly.W32; g.uV = ly.vW; g.uW16 = ly.W16; g.uWT = ly.WT; g.ldwt = ly.ldn;
       g.lr = seg->lr; g.mu = seg->mu;
@@ -879,7 +882,7 @@ int slp_segment_input_grad(slp_segment* seg, const void* X, const int32_t* targe
   bool summed = false, dx_done = false;
   for (int l = seg->L; l >= 1; --l) {       // data gradients only, down to the input; parameters untouched
     GemmArgs d = data_gradient(seg, l, batch);
-    if (product_is_small(d.M, d.N)) {
+    if (product_is_small(seg->dtype, EPI_DGRAD, d.M, d.N)) {
       SmallGroup gr{};
       if (l == 1) { d.C2 = dX; d.ldc2 = w0; dx_done = true; }
       gr.g[0] = d; gr.epi[0] = EPI_DGRAD; gr.n = 1;

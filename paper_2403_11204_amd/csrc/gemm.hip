@@ -73,6 +73,53 @@ template <> struct Mma<float> {
   }
 };
 
+// The optimiser step in the epilogue of the weight gradient (EPI_WGRAD_UPDATE), one accumulator register quad: the float32
+// weights and momenta of 4 consecutive columns of the output row the lane holds after the transpose ...
+__device__ __forceinline__ void request_update(const GemmArgs& g, int n, int mb, int lane, f32x4& w, f32x4& vel) {
+  const int row = mb + (lane & 3), nb = n - (lane & 3);
+  if (row < g.M && nb < g.N) {
+    const size_t idx = (size_t)row * g.ldc + nb;
+    w = *(const f32x4*)(g.uW + idx);
+    if (g.mu != 0.0f) vel = *(const f32x4*)(g.uV + idx);
+  }
+}
+// ... and the step itself (pad columns hold zeros in every stream and stay zero); then back through the transpose, so that the
+// lane holds 4 consecutive output rows of one input column: one vector store into the transposed copy.
+template <typename T>
+__device__ __forceinline__ void update_quad(const GemmArgs& g, int n, int mb, float (&v)[4], int lane, const f32x4& wo, const f32x4& vo) {
+  quad_transpose(v, lane);
+  const int row = mb + (lane & 3), nb = n - (lane & 3);
+  float w[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+  if (row < g.M && nb < g.N) {
+    const size_t idx = (size_t)row * g.ldc + nb;
+    f32x4 vel = f32x4{v[0], v[1], v[2], v[3]};
+    if (g.Cf) *(f32x4*)(g.Cf + idx) = vel;
+    if (g.mu != 0.0f) {
+      vel = g.mu * vo + vel;
+      *(f32x4*)(g.uV + idx) = vel;
+    }
+    const f32x4 wn = wo - g.lr * vel;
+    *(f32x4*)(g.uW + idx) = wn;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) w[e] = wn[e];
+    if (g.uW16) {
+      bf16x4 h;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) h[e] = (bf16)w[e];
+      *(bf16x4*)((bf16*)g.uW16 + idx) = h;
+    }
+  }
+  if (g.uWT) {      // (uniform over the launch)
+    quad_transpose(w, lane);
+    if (n < g.N && mb < g.M) {     // rows past M inside the vector carry zeros: the pads of the copy stay zero
+      typename Vec4<T>::type o;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o[e] = (T)w[e];
+      *(typename Vec4<T>::type*)((T*)g.uWT + (size_t)n * g.ldwt + mb) = o;
+    }
+  }
+}
+
 // Epilogue of one accumulator register quad: rows mb..mb+3 of output column n, v[e] = row mb+e.  The 4 lanes of
 // a quad hold 4 consecutive columns (n - lane%4 is a multiple of 4), and a lane whose column is past N takes part
 // with zeros: nothing here may diverge inside a quad before the transpose.
@@ -93,40 +140,9 @@ __device__ __forceinline__ void store_quad(const GemmArgs& g, int n, int mb, flo
     return;
   }
   if (EPI == EPI_WGRAD_UPDATE) {
-    // The optimiser step on the 4 consecutive weights of one output row this lane holds after the transpose
-    // (pad columns hold zeros in every stream and stay zero); then back through the transpose, so that the lane
-    // holds 4 consecutive output rows of one input column: one vector store into the transposed copy.
-    quad_transpose(v, lane);
-    const bool in = row < g.M && nb < g.N;
-    float w[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-    if (in) {
-      const size_t idx = (size_t)row * g.ldc + nb;
-      const f32x4_t w4 = *(const f32x4_t*)(g.uW + idx);
-      f32x4_t vel = f32x4_t{v[0], v[1], v[2], v[3]};
-      if (g.mu != 0.0f) {
-        vel = g.mu * *(const f32x4_t*)(g.uV + idx) + vel;
-        *(f32x4_t*)(g.uV + idx) = vel;
-      }
-      const f32x4_t wn = w4 - g.lr * vel;
-      *(f32x4_t*)(g.uW + idx) = wn;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) w[e] = wn[e];
-      if (g.uW16) {
-        bf16x4 h;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) h[e] = (bf16)w[e];
-        *(bf16x4*)((bf16*)g.uW16 + idx) = h;
-      }
-    }
-    if (g.uWT) {      // (uniform over the launch)
-      quad_transpose(w, lane);
-      if (col_ok && mb < g.M) {     // rows past M inside the vector carry zeros: the pads of the copy stay zero
-        typename Vec4<T>::type o;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) o[e] = (T)w[e];
-        *(typename Vec4<T>::type*)((T*)g.uWT + (size_t)n * g.ldwt + mb) = o;
-      }
-    }
+    f32x4 w, vel;
+    request_update(g, n, mb, lane, w, vel);
+    update_quad<T>(g, n, mb, v, lane, w, vel);
     return;
   }
   if (mb >= ((g.M + 7) & ~7)) return;       // the same for the whole quad
@@ -324,6 +340,33 @@ __global__ __launch_bounds__(NW * 64) void gemm_nt_kernel(const GemmArgs g) {
   // Accumulator layout of an MB x MB block: lane holds column n = lane % MB and, in register r, row
   // (64 / MB * 4) * (r / 4) + 4 * (lane / MB) + (r % 4): four consecutive rows per register quad, which is what
   // makes the transposed store a vector store.
+  constexpr int NQ = MM::ACC / 4;
+  if constexpr (EPI == EPI_WGRAD_UPDATE) {
+    // The weights and momenta of a whole row of blocks are requested before any of them is used: quad by quad every load
+    // waited for the stores of the quad before (loads and stores share one counter).  With two workgroups on a compute unit
+    // (two-stage configuration) one's products run beside the other's traffic.
+#pragma unroll
+    for (int i = 0; i < MI; ++i) {
+      f32x4 w[NI][NQ], v[NI][NQ];
+#pragma unroll
+      for (int j = 0; j < NI; ++j)
+#pragma unroll
+        for (int q = 0; q < NQ; ++q)
+          request_update(g, n0 + wn * WTN + j * MB + lrow, m0 + wm * WTM + i * MB + (256 / MB) * q + 4 * lgrp, lane, w[j][q], v[j][q]);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int j = 0; j < NI; ++j)
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+          float x[4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) x[e] = acc[i][j][4 * q + e];
+          update_quad<T>(g, n0 + wn * WTN + j * MB + lrow, m0 + wm * WTM + i * MB + (256 / MB) * q + 4 * lgrp, x, lane, w[j][q], v[j][q]);
+        }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    return;
+  }
 #pragma unroll
   for (int j = 0; j < NI; ++j) {
     const int n = n0 + wn * WTN + j * MB + lrow;
@@ -666,23 +709,32 @@ __global__ __launch_bounds__(NW * 64) void gemm_nt_big_kernel(const GemmArgs g) 
 // ---- host side -------------------------------------------------------------------------------
 struct TileCfg { int bm, bn; const char* name; };
 const TileCfg kCfgs[3] = {{256, 256, "256x256"}, {128, 128, "128x128"}, {64, 64, "64x64"}};
-constexpr int kCfg128TwoStage = 3;
+constexpr int kCfg128TwoStage = 3, kCfg128x64 = 4;
 
 long tiles_of(int M, int N, int c) {
   return (long)((M + kCfgs[c].bm - 1) / kCfgs[c].bm) * ((N + kCfgs[c].bn - 1) / kCfgs[c].bn);
 }
 
-int pick_cfg(int M, int N) {
-  // largest tile that still gives every compute unit (256 of them) work
-  for (int c = 0; c < 3; ++c)
-    if (tiles_of(M, N, c) >= 224) {
-      // 128x128 with two 32 KB stages lets two workgroups share a compute unit; with 512 or more tiles that hides
-      // more latency than four stages of one workgroup do (measured 880 against 730 TFLOP/s on 8192x1000x16384),
-      // with fewer tiles the four stages win (681 -> 812 TFLOP/s on 1024x4096x4096)
-      if (c == 1 && tiles_of(M, N, 1) >= 512) return kCfg128TwoStage;
-      return c;
-    }
-  return 2;
+// The tile configuration of a product: the largest tile that still gives most of the 256 compute units work.
+int pick_cfg(int dtype, int epi, int M, int N) {
+  const long t128 = tiles_of(M, N, 1);
+  if (tiles_of(M, N, 0) >= 224) return 0;
+  // 128x128 with two 32 KB stages lets two workgroups share a compute unit, four stages of one workgroup are faster as long as
+  // every tile has a unit of its own.  bf16, microseconds with four / two stages: 1024x4096x4096 (256 tiles) 32 / 48,
+  // 3001x1500x1000 (288) 21.6 / 19.2, 1500x3500x1000 (336) 25.7 / 23.4, 2500x2500x1000 (400) 26.3 / 23.1, 2048x4096x1024
+  // (512) 23.4 / 19.4.  float32, bound by the matrix pipe: 2048x2048x1024 (256) 71 / 73.
+  const int cfg128 = t128 > (dtype == 1 ? 256 : 511) ? kCfg128TwoStage : 1;
+  if (dtype == 1 && (epi == EPI_FWD || epi == EPI_DGRAD)) {
+    // More than half of the units busy with 128x128 tiles beat all of them on 64x64 ones, whose operands take twice the way
+    // into LDS per product: 1280x1664x1024 (130 tiles) 13.7 against 15.4 us, 1000x3001x1500 (192) 17.1 against 20.4.  Below
+    // that 128x64 tiles, if they come to most of 256: 1000x1500x3001 (192) 19.6 against 21.6 on 64x64, 1024x2048x4096 (256)
+    // 24.0 against 29.2; 1000x777x3001 (104) 18.3 against 14.3.
+    if (t128 > 128) return cfg128;
+    const long t = (long)((M + 127) / 128) * ((N + 63) / 64);
+    return t >= 176 && t <= 256 ? kCfg128x64 : 2;
+  }
+  // weight gradients (the kernel for small layers takes the update along) and float32
+  return t128 >= 224 ? cfg128 : 2;
 }
 
 template <typename T, int BM, int BN, int EPI, int NW, int NS>
@@ -740,6 +792,9 @@ hipError_t launch_cfg(int cfg, const GemmArgs& g, hipStream_t s) {
       else return launch_one<T, 256, 256, EPI, 8, 2>(g, s);
     case 1: return launch_one<T, 128, 128, EPI, 8, 4>(g, s);     // 8 wavefronts of 64x32: +5-10 % over 4 of 64x64 here
     case kCfg128TwoStage: return launch_one<T, 128, 128, EPI, 4, 2>(g, s);
+    case kCfg128x64:
+      if constexpr (sizeof(T) == 2 && (EPI == EPI_FWD || EPI == EPI_DGRAD)) return launch_one<T, 128, 64, EPI, 8, 4>(g, s);
+      else return hipErrorInvalidValue;
     default: return hipErrorInvalidValue;     // (small products are launched before the switch)
   }
 }
@@ -761,6 +816,9 @@ hipError_t configure_epi() {
   else e = configure_one<T, 256, 256, EPI, 8, 2>();
   if (e == hipSuccess) e = configure_one<T, 128, 128, EPI, 8, 4>();
   if (e == hipSuccess) e = configure_one<T, 128, 128, EPI, 4, 2>();
+  if constexpr (sizeof(T) == 2 && (EPI == EPI_FWD || EPI == EPI_DGRAD)) {
+    if (e == hipSuccess) e = configure_one<T, 128, 64, EPI, 8, 4>();
+  }
   return e;
 }
 
@@ -781,12 +839,13 @@ hipError_t gemm_configure_all() {
   return e;
 }
 
-bool product_is_small(int M, int N) { return pick_cfg(M, N) == 2; }
+bool product_is_small(int dtype, int epi, int M, int N) { return pick_cfg(dtype, epi, M, N) == 2; }
 
 const char* gemm_config_name(int dtype, int M, int N, int K) {
   (void)K;
-  const int c = pick_cfg(M, N), t = small_tile(dtype, M, N);
+  const int c = pick_cfg(dtype, EPI_FWD, M, N), t = small_tile(dtype, M, N);
   if (c == 2 && t < 64) return t == 16 ? "16x16 k-split" : "32x32 k-split";
+  if (c == kCfg128x64) return "128x64";
   return c == kCfg128TwoStage ? "128x128 (2 stages)" : kCfgs[c].name;
 }
 
@@ -808,7 +867,7 @@ hipError_t launch_gemm(int dtype, int epi, const GemmArgs& g, hipStream_t s) {
   if (epi != EPI_WGRAD && epi != EPI_WGRAD_UPDATE && ((g.C && (g.ldc % kLdAlign || ((uintptr_t)g.C & 15))) || (g.CT && (g.ldct % kLdAlign || ((uintptr_t)g.CT & 15)))))
     return hipErrorInvalidValue;
   if (epi == EPI_WGRAD && (g.ldc % 4 || ((uintptr_t)g.Cf & 15))) return hipErrorInvalidValue;
-  const int cfg = pick_cfg(g.M, g.N);
+  const int cfg = pick_cfg(dtype, epi, g.M, g.N);
   if (cfg == 2) {
     SmallGroup one{};
     one.g[0] = g; one.epi[0] = epi; one.n = 1;

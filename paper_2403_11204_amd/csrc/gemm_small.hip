@@ -460,6 +460,7 @@ hipError_t launch_small_group(int dtype, const SmallGroup& group, hipStream_t s)
   a.s = group;
   int next = 0, lds = kLds32;
   for (int p = 0; p < group.n; ++p) {
+    if (group.epi[p] == EPI_WGRAD) a.s.g[p].uW = nullptr;      // the kernel's mark for a gradient without an update
     const GemmArgs& g = group.g[p];
     const int epi = group.epi[p];
     if (g.M <= 0 || g.N <= 0 || g.K <= 0 || !g.A || !g.B || off(g.A) || off(g.B) || g.lda % ch || g.ldb % ch) return hipErrorInvalidValue;

@@ -58,23 +58,23 @@ struct GemmArgs {
   // EPI_WGRAD_UPDATE: the gradient never goes to memory; the epilogue applies the optimiser step to the tile it holds
   // (paper Sec. 3: SGD with momentum), v = mu v + acc; w -= lr v, on the float32 master weights uW and momentum uV
   // (both [M][ldc]), and rewrites the derived copies uW16 (bf16 [M][ldc], may be null) and uWT ([N][ldwt], element
-  // type T, may be null).  Cf is not used.
+  // type T, may be null).
   float* uW; float* uV; void* uW16; void* uWT;
   int ldwt;
   float lr, mu;
-  // Small layers only: a second copy of C for EPI_FWD and EPI_DGRAD, e.g. the caller's dense matrix ([M][ldc2], any
-  // alignment; columns >= N are not written), and, for EPI_WGRAD_UPDATE, Cf may be given to store the gradient as well.
+  // EPI_WGRAD_UPDATE: Cf may be given to store the gradient as well.  Small layers only: a second copy of C for EPI_FWD and
+  // EPI_DGRAD, e.g. the caller's dense matrix ([M][ldc2], any alignment; columns >= N are not written).
   void* C2;
   int ldc2;
 };
 
 // dtype: 0 = float32 operands, 1 = bf16 operands (float32 accumulation in both).
 hipError_t launch_gemm(int dtype, int epi, const GemmArgs& g, hipStream_t s);
-// Small layers (product_is_small: fewer 128x128 tiles than compute units) run in a kernel of their own, on 64x64 tiles or 32x32
+// The products of small layers (product_is_small: too few 128-wide tiles for the chip) run in a kernel of their own, on 64x64 tiles or 32x32
 // or 16x16 ones with the contraction split over the wavefronts of a workgroup.  One launch takes up to two products that do
 // not depend on each other and what hangs on them: a step of small layers is a chain of launches of a few microseconds
 // each, so what can share one does.
-bool product_is_small(int M, int N);
+bool product_is_small(int dtype, int epi, int M, int N);
 int small_tile(int dtype, int M, int N);
 int small_tile_count(int dtype, int M, int N);
 // EPI_FWD_OUT: the forward product of the last layer together with the gradient of the output.  A = act(acc + bias) goes to C
