@@ -262,10 +262,7 @@ int forward_and_loss(slp_segment* seg, const void* X, const int32_t* targets, in
     sum->scale = 1.0 / (double)batch;
     sum->n = batch;
     HIP_TRY(launch_xent_loss_grad(seg->dtype, seg->A[L], seg->ldw[L], targets, batch, D, relu_on(seg, L) ? 1 : 0,
-                                  seg->dZ[L], seg->partials, seg->bad_ids, st));
-    if (with_transpose)
-      HIP_TRY(launch_copy_transpose(seg->dtype, seg->dZ[L], seg->ldw[L], batch, D, nullptr, 0, seg->dZT[L], seg->ldb, 1,
-                                    nullptr, 0, st));
+                                  seg->dZ[L], with_transpose ? seg->dZT[L] : nullptr, seg->ldb, seg->partials, seg->bad_ids, st));
   }
   return SLP_OK;
 }
@@ -383,10 +380,10 @@ int backward_and_update(slp_segment* seg, int batch, const SumJob* sum, hipStrea
       if (rc) return rc;
       if (small) continue;
     }
-      g.Cf = nullptr;
     if (fused) {     // weights, momentum and the derived copies are rewritten by the product's epilogue
       g.uW = ly.W32; g.uV = ly.vW; g.uW16 = ly.W16; g.uWT = ly.WT; g.ldwt = ly.ldn;
       g.lr = seg->lr; g.mu = seg->mu;
+      g.Cf = nullptr;
     }
     int rc = run_gemm(seg, fused ? EPI_WGRAD_UPDATE : EPI_WGRAD, g, st);
     if (rc) return rc;
@@ -443,6 +440,7 @@ int copy_matrix(float* dense, float* padded, int rows, int cols, int ld, bool to
   return SLP_OK;
 }
 
+constexpr long kSmallCopy = 1L << 22;      // floats
 int exchange(slp_segment* s, int layer, float* W, float* b, int which, bool set, int on_device, hipStream_t st) {
   int rc = check_seg(s, true, !set);
   if (rc) return rc;
@@ -454,11 +452,17 @@ int exchange(slp_segment* s, int layer, float* W, float* b, int which, bool set,
   float* vecs[3] = {ly.b, ly.db, ly.vb};
   if (W && which == 1 && s->fused_update && (long)ly.N * ly.K <= s->fused_max_params)
     return fail(SLP_ERR_STATE, "the weight gradient of layer %d is not stored: its update is fused into the product (slp_segment_set_fused_update)", layer);
-  if (W) {
+  // small layers between device buffers: both in one launch of a kernel; large ones are the runtime's copies' (6 TB/s)
+  const bool small = on_device && (long)ly.N * ly.K <= kSmallCopy;
+  if (small && (W || b)) {
+    if (set) HIP_TRY(launch_copy_layer(W, ly.K, W ? mats[which] : nullptr, ly.ldk, ly.N, ly.K, b, vecs[which], st));
+    else HIP_TRY(launch_copy_layer(W ? mats[which] : nullptr, ly.ldk, W, ly.K, ly.N, ly.K, b ? vecs[which] : nullptr, b, st));
+  }
+  if (W && !small) {
     rc = copy_matrix(W, mats[which], ly.N, ly.K, ly.ldk, set, on_device, st);
     if (rc) return rc;
   }
-  if (b) {
+  if (b && !small) {
     const hipMemcpyKind kind = on_device ? hipMemcpyDeviceToDevice : (set ? hipMemcpyHostToDevice : hipMemcpyDeviceToHost);
     if (set) HIP_TRY(hipMemcpyAsync(vecs[which], b, (size_t)ly.N * 4, kind, st));
     else HIP_TRY(hipMemcpyAsync(b, vecs[which], (size_t)ly.N * 4, kind, st));

@@ -125,10 +125,13 @@ hipError_t launch_mse_loss_grad(int dtype, const void* AL, int ld, const int32_t
                                 hipStream_t s);
 int mse_partial_count(int B, int D);
 
-// Softmax cross-entropy per row: dZ[m][c] = (softmax - onehot)/B (zeroed where the
-// last layer's ReLU is inactive when relu_last), per-row loss to partials[m].
+// Softmax cross-entropy per row: dZ[m][c] = (softmax - onehot)/B (zeroed where the last layer's ReLU is inactive when
+// relu_last), and transposed to dZT ([C][ldt], zero-filled pads; may be null); per-row loss to partials[m].
 hipError_t launch_xent_loss_grad(int dtype, const void* ZL, int ld, const int32_t* y, int B, int C, int relu_last,
-                                 void* dZ, float* partials, unsigned* bad_ids, hipStream_t s);
+                                 void* dZ, void* dZT, int ldt, float* partials, unsigned* bad_ids, hipStream_t s);
+
+// Wd[n][0..K) = W[n][0..K) (rows lds and ldd floats apart; W may be null) and bd[0..N) = b[0..N) (b may be null).
+hipError_t launch_copy_layer(const float* W, int lds, float* Wd, int ldd, int N, int K, const float* b, float* bd, hipStream_t s);
 
 // out0[0] (and out1[0] if not null) = scale * sum(partials[0..n)), fixed summation order.
 hipError_t launch_reduce_loss(const float* partials, int n, double scale, float* out0, float* out1, hipStream_t s);
