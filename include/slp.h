@@ -202,6 +202,8 @@ int slp_segment_step_external(slp_segment* seg, const void* X /*device*/, const 
  * sequence depends on -- and replays that graph, one launch, on every later call with the
  * same combination (up to 16 are kept, least recently used evicted).  Results are those of
  * the eager launches, bit for bit: the same kernels with the same arguments in the same order.
+ * Steps of small layers that come to at most 8 launches are launched one by one all the same: that measured faster than
+ * starting a graph (784-128-64, batch 64: 4 launches, 18.5 us a step against 25.8).
  * Eager launches are used regardless while launches are being timed (profile hooks on), on the
  * null stream, for the first step of a handle, and when `stream` is already being captured by
  * the caller (the launches then become part of the caller's graph).  slp_segment_set_lr,

@@ -62,6 +62,10 @@ struct StepGraph {
   uint64_t used;
 };
 constexpr size_t kMaxStepGraphs = 16;
+// Steps of at most this many launches are launched one by one even where graphs are on: starting a graph costs the host more
+// than that many launches, and the device as much between its kernels.  Replayed / one by one, microseconds a step:
+// 784-128-64 batch 64 (4 launches) 25.8 / 18.5, 784-80-60 batch 1410 (4) 31.7 / 26.7, 512-1024-1024-47 batch 256 (7) 65 / 60.
+constexpr int kDirectLaunches = 8;
 
 }  // namespace
 
@@ -184,12 +188,24 @@ int ingest(slp_segment* s, const void* X, int batch, bool with_transpose, hipStr
 
 // Whether the first layer's product can read the caller's dense input itself: a small layer whose input rows start on 16-byte
 // boundaries.  The copies the rest of the step needs are then made in the same launch.
+// Launches of a training step whose products are all small (one stream, no events); 0 for any other step.
+int direct_launches(const slp_segment* s, const void* X, int batch);
+
 bool reads_input(const slp_segment* s, const void* X, int batch) {
   return product_is_small(s->dtype, EPI_FWD, batch, s->widths[1]) && (size_t)s->widths[0] * esize(s) % 16 == 0 && ((uintptr_t)X & 15) == 0;
 }
 
 struct Forward {
   bool training;
+int direct_launches(const slp_segment* s, const void* X, int batch) {
+  for (int l = 1; l <= s->L; ++l)
+    if (!product_is_small(s->dtype, EPI_FWD, batch, s->widths[l]) || !product_is_small(s->dtype, EPI_WGRAD_UPDATE, s->widths[l], s->widths[l - 1]) ||
+        (l > 1 && !product_is_small(s->dtype, EPI_DGRAD, batch, s->widths[l - 1])))
+      return 0;
+  // ingest unless it rides along, forward, cross-entropy, data gradients (weight gradients ride along), the last weight gradients
+  return (reads_input(s, X, batch) ? 0 : 1) + s->L + (s->loss == SLP_MSE_SIL ? 0 : 1) + (s->L - 1) + 1;
+}
+
   const void* X;            // the caller's input, dense
   const void* x_direct;     // large layers of a forward-only pass: X itself is the first layer's operand ...
   void* out_direct;         // ... and the caller's dense output buffer the last layer's result (their rows are aligned)
@@ -776,7 +792,8 @@ int slp_segment_step(slp_segment* seg, const void* X, const int32_t* targets, in
   // pay a capture per step: after 2 x cache size misses in a row the handle goes back to eager launches until
   // slp_segment_set_graph is called again.
   const bool thrashing = seg->graph_misses > 2 * (int)kMaxStepGraphs;
-  if (!seg->use_graph || thrashing || seg->prof || !st || cap != hipStreamCaptureStatusNone || !seg->graph_warm) {
+  const int direct = seg->use_graph ? direct_launches(seg, X, batch) : 0;
+  if (!seg->use_graph || thrashing || (direct > 0 && direct <= kDirectLaunches) || seg->prof || !st || cap != hipStreamCaptureStatusNone || !seg->graph_warm) {
     seg->graph_warm = true;
     return launch_all();
   }
