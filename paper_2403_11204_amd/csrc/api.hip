@@ -80,9 +80,11 @@ struct slp_segment {
   std::vector<void*> A, AT, dZ, dZT;
   std::vector<uint32_t*> bits;   // bf16 mode: [A_l > 0] of the hidden activations, one bit per element (GemmArgs::bits)
   int ldbits;
-  size_t oPartials, oLoss, oBadIds;
+  size_t oPartials, oLoss, oBadIds, oHurry;
   int n_partials;
   float *partials, *loss_dev;
+  unsigned* hurry;                           // device flag that ends the pauses of paced updates (see settle)
+  bool paced;                                // updates pending that are paced and have not been told to hurry
   unsigned* bad_ids;                         // rows whose class id was out of range, counted by the loss kernels
   bool bound, have_params;
   bool input_grad;                           // keeps W_1^T and a dZ_0 buffer so that d loss / d input can be formed
@@ -186,17 +188,15 @@ int ingest(slp_segment* s, const void* X, int batch, bool with_transpose, hipStr
   return SLP_OK;
 }
 
-// Whether the first layer's product can read the caller's dense input itself: a small layer whose input rows start on 16-byte
-// boundaries.  The copies the rest of the step needs are then made in the same launch.
 // Launches of a training step whose products are all small (one stream, no events); 0 for any other step.
 int direct_launches(const slp_segment* s, const void* X, int batch);
 
+// Whether the first layer's product can read the caller's dense input itself: a small layer whose input rows start on 16-byte
+// boundaries.  The copies the rest of the step needs are then made in the same launch.
 bool reads_input(const slp_segment* s, const void* X, int batch) {
   return product_is_small(s->dtype, EPI_FWD, batch, s->widths[1]) && (size_t)s->widths[0] * esize(s) % 16 == 0 && ((uintptr_t)X & 15) == 0;
 }
 
-struct Forward {
-  bool training;
 int direct_launches(const slp_segment* s, const void* X, int batch) {
   for (int l = 1; l <= s->L; ++l)
     if (!product_is_small(s->dtype, EPI_FWD, batch, s->widths[l]) || !product_is_small(s->dtype, EPI_WGRAD_UPDATE, s->widths[l], s->widths[l - 1]) ||
@@ -206,6 +206,8 @@ int direct_launches(const slp_segment* s, const void* X, int batch) {
   return (reads_input(s, X, batch) ? 0 : 1) + s->L + (s->loss == SLP_MSE_SIL ? 0 : 1) + (s->L - 1) + 1;
 }
 
+struct Forward {
+  bool training;
   const void* X;            // the caller's input, dense
   const void* x_direct;     // large layers of a forward-only pass: X itself is the first layer's operand ...
   void* out_direct;         // ... and the caller's dense output buffer the last layer's result (their rows are aligned)
@@ -310,6 +312,10 @@ int settle(slp_segment* seg, hipStream_t st) {
       return fail(SLP_ERR_STATE, "updates of an overlapped step are still pending and a stream that is being captured cannot "
                                  "wait for them: call slp_segment_set_overlap(seg, 0) before the capture");
   }
+  if (seg->paced) {     // when `st` gets here nothing of it runs beside the updates any more: no reason to pace them
+    HIP_TRY(launch_hurry(seg->hurry, 1, st));
+    seg->paced = false;
+  }
   HIP_TRY(hipStreamWaitEvent(st, seg->ev_join, 0));
   return SLP_OK;
 }
@@ -339,6 +345,7 @@ int backward_and_update(slp_segment* seg, int batch, const SumJob* sum, hipStrea
   // measured: comparison configuration (8192 rows) best at 10-16 units, deep configuration run serially (4096) at 8-14,
   // wide configuration (1024) 18 % slower with any pause.
   const int pause = defer ? std::min(14, std::max(0, (batch - 2048) / 256)) : 0;
+  if (pause > 0) HIP_TRY(launch_hurry(seg->hurry, 0, st));
   SmallGroup pending{};                  // weight-gradient products waiting for company
   auto ride_along = [&](SmallGroup& gr) {
     if (!sum) return;
@@ -407,7 +414,7 @@ int backward_and_update(slp_segment* seg, int batch, const SumJob* sum, hipStrea
       // The data gradient of layer l read W_l^T before this product was queued (same stream).  What is left of the
       // layer is its bias: one small launch, on the caller's stream (nothing worth a second stream).
       HIP_TRY(launch_layer_update(seg->dtype, nullptr, nullptr, nullptr, ly.N, 0, ly.ldk, nullptr, nullptr, ly.ldn, seg->dZT[l],
-                                  seg->ldb, batch, ly.db, ly.b, ly.vb, seg->lr, seg->mu, 0, 0, 0, st));
+                                  seg->ldb, batch, ly.db, ly.b, ly.vb, seg->lr, seg->mu, 0, 0, 0, nullptr, st));
       continue;
     }
     // fork: everything layer l still needs (bias gradient, both updates) reads dZ_l^T / dW_l, which are
@@ -423,12 +430,12 @@ int backward_and_update(slp_segment* seg, int batch, const SumJob* sum, hipStrea
     // of its own first: inside one launch its long reads of dZ^T slowed the matrix products beside it (measured 1 %).
     if ((size_t)ly.N * ly.K <= ((size_t)1 << 22)) {
       HIP_TRY(launch_layer_update(seg->dtype, ly.W32, ly.vW, ly.dW, ly.N, ly.K, ly.ldk, ly.W16, ly.WT, ly.ldn, seg->dZT[l],
-                                  seg->ldb, batch, ly.db, ly.b, ly.vb, seg->lr, seg->mu, 0, 0, 0, us));
+                                  seg->ldb, batch, ly.db, ly.b, ly.vb, seg->lr, seg->mu, 0, 0, 0, nullptr, us));
     } else {
       HIP_TRY(launch_layer_update(seg->dtype, nullptr, nullptr, nullptr, ly.N, 0, ly.ldk, nullptr, nullptr, ly.ldn, seg->dZT[l],
-                                  seg->ldb, batch, ly.db, ly.b, ly.vb, seg->lr, seg->mu, 0, 0, 0, us));
+                                  seg->ldb, batch, ly.db, ly.b, ly.vb, seg->lr, seg->mu, 0, 0, 0, nullptr, us));
       HIP_TRY(launch_layer_update(seg->dtype, ly.W32, ly.vW, ly.dW, ly.N, ly.K, ly.ldk, ly.W16, ly.WT, ly.ldn, nullptr, 0, 0,
-                                  nullptr, nullptr, nullptr, seg->lr, seg->mu, 0, us != st ? kSideUpdateWorkgroups : 0, us != st ? pause : 0, us));
+                                  nullptr, nullptr, nullptr, seg->lr, seg->mu, 0, us != st ? kSideUpdateWorkgroups : 0, us != st ? pause : 0, seg->hurry, us));
     }
   }
   if (forked) {     // join: later work on the caller's stream sees every update
@@ -436,6 +443,7 @@ int backward_and_update(slp_segment* seg, int batch, const SumJob* sum, hipStrea
     if (!defer) HIP_TRY(hipStreamWaitEvent(st, seg->ev_join, 0));
   }
   seg->join_pending = defer && forked;
+  seg->paced = seg->join_pending && pause > 0;
   return SLP_OK;
 }
 
@@ -443,7 +451,7 @@ int refresh_copies(slp_segment* s, int layer, hipStream_t st) {
   Layer& ly = s->layers[layer];
   if (!ly.W16 && !ly.WT) return SLP_OK;
   HIP_TRY(launch_layer_update(s->dtype, ly.W32, ly.vW, ly.dW, ly.N, ly.K, ly.ldk, ly.W16, ly.WT, ly.ldn, nullptr, 0, 0, nullptr,
-                              nullptr, nullptr, 0.0f, 0.0f, 1, 0, 0, st));
+                              nullptr, nullptr, 0.0f, 0.0f, 1, 0, 0, nullptr, st));
   return SLP_OK;
 }
 
@@ -588,6 +596,7 @@ int slp_segment_create(const int* widths, int n_widths, int act, int loss, const
   s->oPartials = take((size_t)s->n_partials * 4);
   s->oLoss = take(4);
   s->oBadIds = take(4);
+  s->oHurry = take(4);
   s->work_bytes = off;
 
   s->side = nullptr; s->ev_join = nullptr;
@@ -595,6 +604,7 @@ int slp_segment_create(const int* widths, int n_widths, int act, int loss, const
   s->bound = false; s->have_params = false; s->table = nullptr; s->classes = 0; s->last_batch = 0; s->prof = false;
   s->use_graph = false; s->graph_warm = false; s->graph_tick = 0; s->graph_misses = 0;
   s->partials = nullptr; s->loss_dev = nullptr; s->bad_ids = nullptr;
+  s->hurry = nullptr; s->paced = false;
   *out = s;
   return SLP_OK;
 }
@@ -652,6 +662,7 @@ int slp_segment_bind(slp_segment* seg, void* params, size_t params_bytes, void* 
   seg->partials = (float*)at(seg->oPartials);
   seg->loss_dev = (float*)at(seg->oLoss);
   seg->bad_ids = (unsigned*)at(seg->oBadIds);
+  seg->hurry = (unsigned*)at(seg->oHurry);
   if (!seg->side) {     // host-side objects only; default priority
     HIP_TRY(hipStreamCreateWithFlags(&seg->side, hipStreamNonBlocking));
     HIP_TRY(hipEventCreateWithFlags(&seg->ev_join, hipEventDisableTiming));

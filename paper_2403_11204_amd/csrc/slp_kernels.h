@@ -141,10 +141,12 @@ hipError_t launch_reduce_loss(const float* partials, int n, double scale, float*
 // the bias: db[n] = sum_{m < B} dZT[n][m], then the same update on b, vb.
 // refresh_only: skip the arithmetic and only rebuild the copies from W32 (dZT must be null).
 // max_workgroups > 0 (weights-only launches): run on at most that many workgroups, for updates issued beside matrix products;
-// pause: units of ~0.5 us each of those workgroups sleeps between two tiles (paces the update's memory traffic).
+// pause: units of ~0.5 us each of those workgroups sleeps between two tiles (paces the update's memory traffic) until *hurry
+// (device) is not zero; launch_hurry sets it.
 hipError_t launch_layer_update(int dtype, float* W32, float* vW, const float* dW, int N, int K, int ldk, void* W16, void* WT,
                                int ldn, const void* dZT, int ldt, int B, float* db, float* b, float* vb, float lr, float mu,
-                               int refresh_only, int max_workgroups, int pause, hipStream_t s);
+                               int refresh_only, int max_workgroups, int pause, const unsigned* hurry, hipStream_t s);
+hipError_t launch_hurry(unsigned* hurry, unsigned value, hipStream_t s);
 
 // Counter-based generators (Philox4x32-10).
 hipError_t launch_make_labels(uint64_t seed, int classes, int dim, int dist, float kappa, void* out, int dt,
