@@ -342,28 +342,33 @@ __global__ __launch_bounds__(NW * 64) void gemm_nt_kernel(const GemmArgs g) {
   // makes the transposed store a vector store.
   constexpr int NQ = MM::ACC / 4;
   if constexpr (EPI == EPI_WGRAD_UPDATE) {
-    // The weights and momenta of a whole row of blocks are requested before any of them is used: quad by quad every load
-    // waited for the stores of the quad before (loads and stores share one counter).  With two workgroups on a compute unit
-    // (two-stage configuration) one's products run beside the other's traffic.
+    // The weights and momenta of all blocks (4 wavefronts: of one row of blocks, the registers of two workgroups per compute
+    // unit do not hold more) are requested before any of them is used: quad by quad every load waited for the stores of the
+    // quad before (loads and stores share one counter).
+    constexpr int IB = NW == 8 && MI * NI * NQ * 8 <= 128 ? MI : 1;
 #pragma unroll
-    for (int i = 0; i < MI; ++i) {
-      f32x4 w[NI][NQ], v[NI][NQ];
+    for (int i0 = 0; i0 < MI; i0 += IB) {
+      f32x4 w[IB][NI][NQ], v[IB][NI][NQ];
 #pragma unroll
-      for (int j = 0; j < NI; ++j)
+      for (int i = 0; i < IB; ++i)
 #pragma unroll
-        for (int q = 0; q < NQ; ++q)
-          request_update(g, n0 + wn * WTN + j * MB + lrow, m0 + wm * WTM + i * MB + (256 / MB) * q + 4 * lgrp, lane, w[j][q], v[j][q]);
+        for (int j = 0; j < NI; ++j)
+#pragma unroll
+          for (int q = 0; q < NQ; ++q)
+            request_update(g, n0 + wn * WTN + j * MB + lrow, m0 + wm * WTM + (i0 + i) * MB + (256 / MB) * q + 4 * lgrp, lane, w[i][j][q], v[i][j][q]);
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int j = 0; j < NI; ++j)
+      for (int i = 0; i < IB; ++i)
 #pragma unroll
-        for (int q = 0; q < NQ; ++q) {
-          float x[4];
+        for (int j = 0; j < NI; ++j)
 #pragma unroll
-          for (int e = 0; e < 4; ++e) x[e] = acc[i][j][4 * q + e];
-          update_quad<T>(g, n0 + wn * WTN + j * MB + lrow, m0 + wm * WTM + i * MB + (256 / MB) * q + 4 * lgrp, x, lane, w[j][q], v[j][q]);
-        }
-      __builtin_amdgcn_sched_barrier(0);
+          for (int q = 0; q < NQ; ++q) {
+            float x[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) x[e] = acc[i0 + i][j][4 * q + e];
+            update_quad<T>(g, n0 + wn * WTN + j * MB + lrow, m0 + wm * WTM + (i0 + i) * MB + (256 / MB) * q + 4 * lgrp, x, lane, w[i][j][q], v[i][j][q]);
+            __builtin_amdgcn_sched_barrier(0);
+          }
     }
     return;
   }
