@@ -346,6 +346,12 @@ int backward_and_update(slp_segment* seg, int batch, const SumJob* sum, hipStrea
   // wide configuration (1024) 18 % slower with any pause.
   const int pause = defer ? std::min(14, std::max(0, (batch - 2048) / 256)) : 0;
   if (pause > 0) HIP_TRY(launch_hurry(seg->hurry, 0, st));
+  // Without a deferred join an update beside the next layers' products has to pay for the fork and the join, some 35 us, and for
+  // what the two cost each other: it does where the products are long.  Microseconds a step of three equal layers, beside / in
+  // the caller's stream: bf16 4096 wide, batch 256 408 / 344, 1024 578 / 523, 1400 670 / 682, 4096 990 / 1004, 8192 1768 / 1795;
+  // 8192 wide, 1024 2163 / 1999, 2048 2418 / 2430, 8192 6624 / 6835; float32 2048 wide, 256 329 / 317, 512 378 / 369, 1024
+  // 611 / 621; 4096 wide, 256 780 / 778, 1024 2194 / 2242.
+  const bool beside = batch >= (seg->dtype == SLP_BF16 ? 1400 : 640);
   SmallGroup pending{};                  // weight-gradient products waiting for company
   auto ride_along = [&](SmallGroup& gr) {
     if (!sum) return;
@@ -353,11 +359,6 @@ int backward_and_update(slp_segment* seg, int batch, const SumJob* sum, hipStrea
     gr.sum = *sum;
     sum = nullptr;
   };
-  if (sum && !(seg->L > 1 ? product_is_small(seg->dtype, EPI_DGRAD, batch, seg->layers[seg->L - 1].K)
-                          : product_is_small(seg->dtype, EPI_WGRAD_UPDATE, seg->widths[1], seg->widths[0]))) {
-    HIP_TRY(launch_reduce_loss(sum->partials, sum->n, sum->scale, sum->out0, sum->out1, st));
-    sum = nullptr;
-  }
   for (int l = seg->L; l >= 1; --l) {
     Layer& ly = seg->layers[l - 1];
     if (l > 1) {
@@ -366,10 +367,12 @@ int backward_and_update(slp_segment* seg, int batch, const SumJob* sum, hipStrea
       if (small) {
         pending.g[pending.n] = d;
         pending.epi[pending.n++] = EPI_DGRAD;
-        ride_along(pending);
       }
       int rc = SLP_OK;
-      if (pending.n) rc = run_group(seg, pending, st);
+      if (pending.n) {
+        ride_along(pending);
+        rc = run_group(seg, pending, st);
+      }
       pending = SmallGroup{};
       if (!rc && !small) rc = run_gemm(seg, EPI_DGRAD, d, st);
       if (rc) return rc;
@@ -389,7 +392,6 @@ int backward_and_update(slp_segment* seg, int batch, const SumJob* sum, hipStrea
       pending.epi[pending.n++] = EPI_WGRAD_UPDATE;
       pending.bias[pending.n_bias++] = BiasJob{seg->dZT[l], seg->ldb, ly.N, batch, ly.db, ly.b, ly.vb, seg->lr, seg->mu};
       if (l > 1) continue;
-      ride_along(pending);               // (a segment of one layer)
     }
     if (l == 1 && pending.n) {           // the last products: with a deferred join they run beside the caller's next work
       hipStream_t us = defer ? seg->side : st;
@@ -397,6 +399,8 @@ int backward_and_update(slp_segment* seg, int batch, const SumJob* sum, hipStrea
         HIP_TRY(hipEventRecord(seg->ev_fork[0], st));
         HIP_TRY(hipStreamWaitEvent(us, seg->ev_fork[0], 0));
         forked = true;
+      } else {
+        ride_along(pending);             // (the loss belongs to `st`)
       }
       int rc = run_group(seg, pending, us);
       pending = SmallGroup{};
@@ -417,18 +421,18 @@ int backward_and_update(slp_segment* seg, int batch, const SumJob* sum, hipStrea
                                   seg->ldb, batch, ly.db, ly.b, ly.vb, seg->lr, seg->mu, 0, 0, 0, nullptr, st));
       continue;
     }
-    // fork: everything layer l still needs (bias gradient, both updates) reads dZ_l^T / dW_l, which are
-    // complete here, and writes only layer l's parameters, which nothing below reads in this step
-    // without a deferred join the first layer has nothing left in this step to overlap with
-    hipStream_t us = (l > 1 || defer) ? seg->side : st;
+    // everything layer l still needs (bias gradient, both updates) reads dZ_l^T / dW_l, which are complete here, and writes
+    // only layer l's parameters, which nothing below reads in this step; without a deferred join the first layer has nothing
+    // left in this step to overlap with
+    hipStream_t us = (defer || (l > 1 && beside)) ? seg->side : st;
     if (us != st) {
       HIP_TRY(hipEventRecord(seg->ev_fork[l - 1], st));
       HIP_TRY(hipStreamWaitEvent(us, seg->ev_fork[l - 1], 0));
       forked = true;
     }
-    // small layers are bound by launch latency: weights and bias in one launch.  Large ones run the bias part as a launch
-    // of its own first: inside one launch its long reads of dZ^T slowed the matrix products beside it (measured 1 %).
-    if ((size_t)ly.N * ly.K <= ((size_t)1 << 22)) {
+    // weights and bias in one launch, but for large layers beside products: there the bias part is a launch of its own first,
+    // inside one launch its long reads of dZ^T slowed the products (measured 1 %)
+    if ((size_t)ly.N * ly.K <= ((size_t)1 << 22) || us == st) {
       HIP_TRY(launch_layer_update(seg->dtype, ly.W32, ly.vW, ly.dW, ly.N, ly.K, ly.ldk, ly.W16, ly.WT, ly.ldn, seg->dZT[l],
                                   seg->ldb, batch, ly.db, ly.b, ly.vb, seg->lr, seg->mu, 0, 0, 0, nullptr, us));
     } else {
@@ -438,6 +442,7 @@ int backward_and_update(slp_segment* seg, int batch, const SumJob* sum, hipStrea
                                   nullptr, nullptr, nullptr, seg->lr, seg->mu, 0, us != st ? kSideUpdateWorkgroups : 0, us != st ? pause : 0, seg->hurry, us));
     }
   }
+  if (sum) HIP_TRY(launch_reduce_loss(sum->partials, sum->n, sum->scale, sum->out0, sum->out1, st));   // found no company
   if (forked) {     // join: later work on the caller's stream sees every update
     HIP_TRY(hipEventRecord(seg->ev_join, seg->side));
     if (!defer) HIP_TRY(hipStreamWaitEvent(st, seg->ev_join, 0));
@@ -464,7 +469,7 @@ int copy_matrix(float* dense, float* padded, int rows, int cols, int ld, bool to
   return SLP_OK;
 }
 
-constexpr long kSmallCopy = 1L << 22;      // floats
+constexpr long kSmallCopy = 1L << 25;      // floats
 int exchange(slp_segment* s, int layer, float* W, float* b, int which, bool set, int on_device, hipStream_t st) {
   int rc = check_seg(s, true, !set);
   if (rc) return rc;
@@ -476,7 +481,7 @@ int exchange(slp_segment* s, int layer, float* W, float* b, int which, bool set,
   float* vecs[3] = {ly.b, ly.db, ly.vb};
   if (W && which == 1 && s->fused_update && (long)ly.N * ly.K <= s->fused_max_params)
     return fail(SLP_ERR_STATE, "the weight gradient of layer %d is not stored: its update is fused into the product (slp_segment_set_fused_update)", layer);
-  // small layers between device buffers: both in one launch of a kernel; large ones are the runtime's copies' (6 TB/s)
+  // between device buffers: both in one launch of a kernel; very large layers are left to the runtime's copies (6 TB/s)
   const bool small = on_device && (long)ly.N * ly.K <= kSmallCopy;
   if (small && (W || b)) {
     if (set) HIP_TRY(launch_copy_layer(W, ly.K, W ? mats[which] : nullptr, ly.ldk, ly.N, ly.K, b, vecs[which], st));
