@@ -95,3 +95,95 @@ def test_workspace_copies_of_input_and_output(w0, wl, dtype):
     assert abs(float(loss) - float(diff.square().mean())) <= 1e-5 * float(diff.square().mean())
     dz = torch.where(out > 0, diff * (2.0 / (B * wl)), torch.zeros_like(diff))
     assert close(seg.get_activation(2, B, kind=1), dz, TOL[dtype])
+
+
+@pytest.mark.parametrize("dtype", [api.F32, api.BF16])
+@pytest.mark.parametrize("B,K,N", [(1000, 1500, 1490), (1030, 200, 2300), (1500, 200, 3500), (4090, 100, 500)])
+def test_products_on_the_tiles_between_small_and_large(B, K, N, dtype):
+    """bf16: 128x64 tiles (1000 x 1490, 4090 x 500), 128x128 on part of the chip (1030 x 2300), two workgroups per unit (1500 x
+    3500)."""
+    test_products_of_one_layer(B, K, N, 0, dtype)
+
+
+@pytest.mark.parametrize("dtype", [api.F32, api.BF16])
+@pytest.mark.parametrize("B,C", [(1, 1), (3, 2), (5, 63), (8, 64), (13, 65), (66, 256), (31, 257), (129, 1000)])
+def test_cross_entropy_gradient_and_its_transpose(B, C, dtype):
+    """Classes on and beside the sizes that stay in registers (64, 256), batches that leave a wavefront's four rows and the
+    padded columns of the transposed gradient partly filled: dZ, its column sums (read from the transpose) and the loss."""
+    g = torch.Generator().manual_seed(B * 1000 + C)
+    tdt = torch.float32 if dtype == api.F32 else torch.bfloat16
+    K = 24
+    seg = api.Segment([K, C], api.RELU_HIDDEN_IDENTITY_LAST, api.SOFTMAX_XENT, max_batch=B, dtype=dtype, lr=0.0, momentum=0.0)
+    W, b = torch.randn(C, K, generator=g), torch.randn(C, generator=g)
+    seg.set_params(0, W.cuda(), b.cuda())
+    X = torch.rand(B, K, generator=g).to(tdt)
+    y = torch.randint(0, C, (B,), generator=g, dtype=torch.int32)
+    loss = float(seg.step(X.cuda(), y.cuda()))
+    Z = seg.get_activation(1, B).cpu().double()       # the stored logits are what the loss reads
+    lse = torch.logsumexp(Z, 1)
+    ref = float((lse - Z[torch.arange(B), y.long()]).mean())
+    # float32: the log-sum and a logit of up to 10 each carry 2^-24 of themselves, absolutely
+    assert abs(loss - ref) <= 1e-5 * max(abs(ref), 1.0)
+    P = torch.exp(Z - lse[:, None])
+    P[torch.arange(B), y.long()] -= 1.0
+    P /= B
+    scale = max(float(P.abs().max()), 1e-6 / B)       # one class: the gradient is zero to rounding
+    assert float((seg.get_activation(1, B, kind=1).cpu().double() - P).abs().max()) <= TOL[dtype] * scale + 1e-6 / B
+    assert float((seg.get_bias_grad(0).cpu().double() - P.sum(0)).abs().max()) <= TOL[dtype] * scale * math.sqrt(B) + 1e-6
+    assert float((seg.get_grads(0)[0].cpu().double() - P.t() @ X.double()).abs().max()) <= TOL[dtype] * scale * math.sqrt(B) + 1e-6
+
+
+@pytest.mark.parametrize("loss", [api.MSE_SIL, api.SOFTMAX_XENT])
+@pytest.mark.parametrize("dtype", [api.F32, api.BF16])
+def test_replayed_steps_of_more_launches_than_go_one_by_one(dtype, loss):
+    """Five small layers come to 10 launches and more, which graphs are still used for: the same bits as eager steps."""
+    widths, B, classes = [40, 50, 60, 50, 40, 30], 48, 30
+    g = torch.Generator().manual_seed(5)
+    tdt = torch.float32 if dtype == api.F32 else torch.bfloat16
+    table = torch.rand(classes, widths[-1], generator=g).cuda()
+    Xs = [torch.rand(B, widths[0], generator=g).to(tdt).cuda() for _ in range(2)]
+    ys = [torch.randint(0, classes, (B,), generator=g, dtype=torch.int32).cuda() for _ in range(2)]
+    finals = []
+    stream = torch.cuda.Stream()
+    stream.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(stream):
+        for graph in (False, True):
+            seg = api.Segment(widths, api.RELU_ALL if loss == api.MSE_SIL else api.RELU_HIDDEN_IDENTITY_LAST, loss, max_batch=B, dtype=dtype,
+                              lr=0.05, momentum=0.9)
+            seg.init(9)
+            if loss == api.MSE_SIL:
+                seg.set_labels(table)
+            seg.set_graph(graph)
+            seen = []
+            for it in range(7):
+                seen.append(seg.step(Xs[it % 2], ys[it % 2]).clone())
+                if it in (3, 6):                      # reads between replays
+                    seen += [t.clone() for l in range(seg.L) for t in seg.get_params(l) + seg.get_momentum(l)]
+            stream.synchronize()
+            finals.append(seen)
+    for a, b in zip(*finals):
+        assert torch.equal(a, b)
+
+
+def test_paced_updates_leave_the_same_bits():
+    """A batch above 2048 rows paces the updates of an overlapped step; whoever waits for them ends the pauses."""
+    B, widths = 2400, [64, 2304, 2304, 64]
+    g = torch.Generator().manual_seed(6)
+    table = torch.rand(10, widths[-1], generator=g).cuda()
+    X = torch.rand(B, widths[0], generator=g).to(torch.bfloat16).cuda()
+    y = torch.randint(0, 10, (B,), generator=g, dtype=torch.int32).cuda()
+    finals = []
+    for overlap in (False, True):
+        seg = api.Segment(widths, api.RELU_ALL, api.MSE_SIL, max_batch=B, dtype=api.BF16, lr=0.05, momentum=0.9)
+        seg.init(9)
+        seg.set_labels(table)
+        seg.set_overlap(overlap)
+        seen = []
+        for it in range(4):
+            seen.append(seg.step(X, y).clone())
+            if it != 1:
+                seen += [t.clone() for l in range(seg.L) for t in seg.get_params(l)]
+        finals.append(seen)
+    torch.cuda.synchronize()
+    for a, b in zip(*finals):
+        assert torch.equal(a, b)
