@@ -20,7 +20,7 @@
  *     that returns an error has launched nothing;
  *   - calls on ONE handle must not overlap in time (they share its workspace); different
  *     handles are independent and may run concurrently on different streams (Sec. 2.1:
- *     partitions are independent jobs).  A training step also uses a second stream that
+ *     partitions are independent jobs).  A training step may also use a second stream that
  *     the handle owns (default priority) for parameter updates; it is forked from and
  *     joined back into `stream` inside the call, so `stream` alone orders everything.
  */

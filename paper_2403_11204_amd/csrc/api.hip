@@ -95,8 +95,9 @@ struct slp_segment {
   std::vector<ProfRec> prof_log;
   std::vector<hipEvent_t> ev_pool;
   // The parameter update of layer l is memory-bound and independent of the matrix products of the
-  // layers below it, so it runs on a side stream next to them (fork after the weight gradient of
-  // layer l, join at the end of the step: the caller's stream still orders everything).
+  // layers below it, so where those are long enough (see backward_and_update) it runs on a side stream next to
+  // them (fork after the weight gradient of layer l, join at the end of the step: the caller's stream still orders
+  // everything).
   hipStream_t side;
   std::vector<hipEvent_t> ev_fork;   // one per layer
   hipEvent_t ev_join;

@@ -118,8 +118,9 @@ __global__ __launch_bounds__(256) void mse_loss_grad_kernel(const T* __restrict_
 // ---------------------------------------------------------------------------------
 // A lane holds column c of four consecutive rows, so that it can store them into the transposed gradient as one vector (8 or
 // 16 bytes; neighbouring wavefronts fill the rest of the line in L2) and the four rows' reductions run side by side: what
-// bounds this kernel at the sizes in use is their latency, not its bytes.  256 x 47 float32, loss and transposed copy: 7.4 us
-// in two launches of one row per wavefront -> one of 4.3.  The order of each row's sum is that of one row per wavefront.
+// bounds this kernel at the sizes in use is their latency, not its bytes.  256 x 47 float32, loss and transposed copy: 4.0 + 2.9
+// us in two launches (one row per wavefront) and what lies between two launches, another 4 -> one of 4.5-5.  The order of each
+// row's sum is that of one row per wavefront.
 // NC > 0: C <= 64 NC, the logits are read once and stay in registers; NC = 0: any C, read three times.
 template <typename T, int NC>
 __global__ __launch_bounds__(256) void xent_loss_grad_kernel(const T* __restrict__ ZL, int ld, const int32_t* __restrict__ y,
