@@ -217,9 +217,8 @@ int slp_segment_set_graph(slp_segment* seg, int on);
 /* ---- optimiser step inside the weight-gradient product (Sec. 3: SGD with momentum) ----------------------
  * With the fused update on, the matrix product that forms dW_l applies v = mu v + dW; w = w - lr v to the tile of the
  * weight matrix it holds and rewrites the bf16 and transposed copies from there: the gradient is never written to
- * memory and never read back (20 instead of 28 bytes per parameter and step in bf16 mode), and a step of a small
- * segment ends with its last product instead of a tail of update launches (the paper's own network, Sec. 3: 0.20 ->
- * 0.14 ms per step of both partitions).  It pays where a layer's products are short; for very wide layers the separate
+ * memory and never read back (20 instead of 28 bytes per parameter and step in bf16 mode), and a step of a mid-size
+ * segment ends with its last product instead of a tail of update launches.  It pays where a layer's products are short; for very wide layers the separate
  * update, which streams beside the next products, is faster.  on = 0: off (default); 1: every layer; 2: the layers
  * where it measured faster, those with at most 4,194,304 weights; on > 2: the layers with at most `on` weights.
  * Layers with fewer than 224 tiles of 128x128 weights take the update inside the product in any case, off or on; off, the
