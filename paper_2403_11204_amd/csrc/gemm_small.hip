@@ -167,10 +167,11 @@ typedef __attribute__((address_space(3))) void* lds_ptr_t;
 constexpr int kStages = 4, kTailBytes = 64, kLds32 = kStages * 64 * 128 + kTailBytes, kLds64 = kStages * 128 * 128 + kTailBytes;
 
 // 16x16 block; lane -> row lane % 16, k-group lane / 16; the accumulator holds rows 4 * (lane / 16) .. + 3 of column lane % 16.
-// bf16: 4 chunks (64 bytes) per row, one per group.  float32: a chunk pair per row, the even chunk in groups 0 and 2, the odd
-// one in 1 and 3.  float32 products add one k after the other, the groups of a product in order, so fed like that the order is
-// the order of two 32x32x2 products on the pair (first elements of both chunks, second elements, ...): the tile size does not
-// change a bit of the result.
+// A product adds its groups in order, so what they are fed with keeps the order that the 32x32 block's products have, and the
+// choice between tiles 16 and 32 does not change a bit of the result in either type.  bf16: 4 chunks per row, one per group,
+// chunk pair w of two successive k-tiles: the order of two 32x32x16 products.  float32: a chunk pair per row, the even chunk in
+// groups 0 and 2, the odd one in 1 and 3: the order of two 32x32x2 products on the pair (first elements of both chunks, second
+// elements, ...).
 __device__ __forceinline__ void mma16(f32x4& acc, const u32x4& a, const u32x4& b, bool, bf16*) {
   acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), acc, 0, 0, 0);
 }
@@ -244,14 +245,14 @@ __device__ __forceinline__ void product_tile(const GemmArgs& g, const OutJob& ou
         }
       }
     };
-    // What this wavefront multiplies of every KT k-tiles.  TILE 32 and float32: chunk pair w, chunks 2w and 2w+1, of each
-    // (of a k-tile's 8; one chunk each for the two lane halves, at TILE 16 for groups 0, 2 and 1, 3: see mma16).  TILE 16 in
-    // bf16, where one product takes 4 chunks: half w & 1 of k-tile w / 2.
-    constexpr bool kHalves = TILE == 16 && ES == 2;
-    constexpr int NJ = kHalves ? 1 : KT;
+    // What this wavefront multiplies of every KT k-tiles: chunk pair w, chunks 2w and 2w+1, of each (of a k-tile's 8; one chunk
+    // each for the two lane halves, at TILE 16 for groups 0, 2 and 1, 3: see mma16).  TILE 16 in bf16, where one product takes 4
+    // chunks: the pairs of both k-tiles, the first in groups 0 and 1, the second in 2 and 3.
+    constexpr bool kBoth = TILE == 16 && ES == 2;
+    constexpr int NJ = kBoth ? 1 : KT;
     const int frow = TILE == 32 ? l32 : l16;
-    const int fch = TILE == 32 ? 2 * w + half : (kHalves ? 4 * (w & 1) + g16 : 2 * w + (g16 & 1));
-    const uint32_t fo = (uint32_t)((kHalves ? (w >> 1) * TSZ : 0) + frow * 128 + ((fch ^ ((frow >> 1) & 7)) << 4));
+    const int fch = TILE == 32 ? 2 * w + half : 2 * w + (g16 & 1);
+    const uint32_t fo = (uint32_t)((kBoth ? (g16 >> 1) * TSZ : 0) + frow * 128 + ((fch ^ ((frow >> 1) & 7)) << 4));
     const int nit = (nk + KT - 1) / KT;        // k-tiles past the end are zeros: their products change nothing
 #pragma unroll
     for (int s = 0; s < STAGES - 1; ++s) load(s, s);

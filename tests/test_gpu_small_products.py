@@ -69,6 +69,38 @@ def test_products_of_one_layer(B, K, N, fused, dtype):
 
 
 @pytest.mark.parametrize("dtype", [api.F32, api.BF16])
+@pytest.mark.parametrize("K", [40, 200, 784, 1023, 4096])
+def test_tiles_16_and_32_leave_the_same_bits(K, dtype):
+    """Elements of an output do not depend on each other, so the same ones as part of a small output (tile 16) and of a larger
+    one (tile 32) differ only by the order of their sums: not at all.  K leaves one, an odd and an even number of k-tiles.  The
+    weight gradient is seen in float32, the other two products as stored."""
+    g = torch.Generator().manual_seed(K)
+    tdt = torch.float32 if dtype == api.F32 else torch.bfloat16
+    n, big = 48, 640                    # 3 x 3 16x16 tiles; 40 x 40 of them are 10 x 10 64x64 ones: tile 32
+    W1, W2 = torch.randn(big, K, generator=g), torch.randn(K, big, generator=g)
+    X = torch.randn(big, K, generator=g).to(tdt).cuda()
+    XT, dAT = torch.randn(K, big, generator=g).to(tdt).cuda(), torch.randn(K, big, generator=g).to(tdt).cuda()
+    dA = torch.randn(big, K, generator=g).to(tdt).cuda()
+    outs = []
+    for m in (n, big):
+        def segment(widths, batch):
+            return api.Segment(widths, api.RELU_HIDDEN_IDENTITY_LAST, api.SOFTMAX_XENT, max_batch=batch, dtype=dtype, lr=0.0, momentum=0.5)
+
+        fwd = segment([K, m], m)
+        fwd.set_params(0, W1[:m].cuda(), torch.zeros(m).cuda())
+        wgrad = segment([m, m], K)      # contraction over a batch of K rows
+        wgrad.init(1)
+        wgrad.step_external(XT[:, :m].contiguous(), dAT[:, :m].contiguous())
+        dgrad = segment([8, m, K], m)   # hidden units all at one, so that the mask passes every element
+        dgrad.set_params(0, torch.zeros(m, 8).cuda(), torch.ones(m).cuda())
+        dgrad.set_params(1, W2[:, :m].contiguous().cuda(), torch.zeros(K).cuda())
+        dgrad.step_external(torch.zeros(m, 8, dtype=tdt, device="cuda"), dA[:m].contiguous())
+        outs.append([t[:n, :n] for t in (fwd.forward(X[:m]), wgrad.get_momentum(0)[0], dgrad.get_activation(1, m, kind=1))])
+    for a, b in zip(*outs):
+        assert torch.count_nonzero(a) > 0.9 * a.numel() and torch.equal(a, b)
+
+
+@pytest.mark.parametrize("dtype", [api.F32, api.BF16])
 @pytest.mark.parametrize("w0", [24, 60, 61, 64])
 @pytest.mark.parametrize("wl", [8, 12, 47])
 def test_workspace_copies_of_input_and_output(w0, wl, dtype):
