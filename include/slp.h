@@ -175,7 +175,7 @@ int slp_segment_target_errors(slp_segment* seg, int64_t* count_out /*host*/, slp
  * are not changed; the activation workspace is overwritten (X and out themselves are
  * used in place of its first and last entries when their rows are aligned: X with a
  * width that is a multiple of 64 on a 128-byte boundary, out with a width that is a
- * multiple of 8 on a 16-byte boundary).  Errors as for the step. */
+ * multiple of 8 on a 16-byte boundary).  out may overlap X.  Errors as for the step. */
 int slp_segment_forward(slp_segment* seg, const void* X /*device*/, int batch, void* out /*device*/, slp_stream stream);
 
 /* ---- recovery phase (Sec. 5: the left partition is trained some more while the

@@ -213,12 +213,13 @@ struct Forward {
   const void* x_direct;     // large layers of a forward-only pass: X itself is the first layer's operand ...
   void* out_direct;         // ... and the caller's dense output buffer the last layer's result (their rows are aligned)
   void* out;                // forward-only: the caller's output buffer
+  bool keeps_input;         // whether nothing is written to X before the last launch that could read it has ended
   const OutJob* last;       // training: the gradient of the output rides along with a small last layer
 };
 
 // Ingest and all layers.  *out_done: the last layer wrote f.out itself; *last_done: it formed the output's gradient.
 int forward_layers(slp_segment* s, int batch, const Forward& f, hipStream_t st, bool* out_done, bool* last_done) {
-  const bool direct = !f.x_direct && reads_input(s, f.X, batch);
+  const bool direct = !f.x_direct && f.keeps_input && reads_input(s, f.X, batch);
   if (!f.x_direct && !direct) {
     int rc = ingest(s, f.X, batch, f.training, st);
     if (rc) return rc;
@@ -268,7 +269,7 @@ int forward_and_loss(slp_segment* seg, const void* X, const int32_t* targets, in
   oj.scale = (float)(2.0 / ((double)batch * (double)D));
   oj.partials = seg->partials; oj.bad_ids = seg->bad_ids;
   oj.dZ = seg->dZ[L]; oj.lddz = seg->ldw[L]; oj.dZT = seg->dZT[L]; oj.lddzt = seg->ldb;
-  int rc = forward_layers(seg, batch, Forward{true, X, nullptr, nullptr, nullptr, mse ? &oj : nullptr}, st, &out_done, &last_done);
+  int rc = forward_layers(seg, batch, Forward{true, X, nullptr, nullptr, nullptr, true, mse ? &oj : nullptr}, st, &out_done, &last_done);
   if (rc) return rc;
   *sum = SumJob{seg->partials, 0, 0.0, seg->loss_dev, loss_out};
   if (mse) {
@@ -770,10 +771,14 @@ int slp_segment_forward(slp_segment* seg, const void* X, int batch, void* out, s
   // the stored-response pass over a whole dataset (Sec. 2) is this call in a loop: no activation is kept for a
   // backward pass, and dense caller buffers whose rows start on 16-byte boundaries are used in place
   const int w0 = seg->widths[0], w = seg->widths[seg->L];
-  const bool x_direct = w0 % kLdRows == 0 && ((uintptr_t)X & 127) == 0;      // rows on cache-line boundaries, else the copy pays
+  // One layer: its launch reads X and writes out, so where the two overlap X goes through the workspace.  (With more layers X has
+  // been read before the launch that writes out begins.)
+  const uintptr_t xa = (uintptr_t)X, oa = (uintptr_t)out;
+  const bool keeps_input = seg->L > 1 || xa + (size_t)batch * w0 * esize(seg) <= oa || oa + (size_t)batch * w * esize(seg) <= xa;
+  const bool x_direct = keeps_input && w0 % kLdRows == 0 && (xa & 127) == 0;      // rows on cache-line boundaries, else the copy pays
   const bool out_direct = w % kLdAlign == 0 && ((uintptr_t)out & 15) == 0;
   bool out_done = false, last_done = false;
-  rc = forward_layers(seg, batch, Forward{false, X, x_direct ? X : nullptr, out_direct ? out : nullptr, out, nullptr}, st, &out_done,
+  rc = forward_layers(seg, batch, Forward{false, X, x_direct ? X : nullptr, out_direct ? out : nullptr, out, keeps_input, nullptr}, st, &out_done,
                       &last_done);
   if (rc) return rc;
   if (!out_direct && !out_done)
@@ -952,7 +957,7 @@ int slp_segment_step_external(slp_segment* seg, const void* X, const void* dA_ou
   oj.ext = dA_out;
   oj.dZ = seg->dZ[L]; oj.lddz = seg->ldw[L]; oj.dZT = seg->dZT[L]; oj.lddzt = seg->ldb;
   bool out_done = false, last_done = false;
-  rc = forward_layers(seg, batch, Forward{true, X, nullptr, nullptr, nullptr, &oj}, st, &out_done, &last_done);
+  rc = forward_layers(seg, batch, Forward{true, X, nullptr, nullptr, nullptr, true, &oj}, st, &out_done, &last_done);
   if (rc) return rc;
   if (!last_done)
     HIP_TRY(launch_copy_transpose(seg->dtype, dA_out, D, batch, D, seg->dZ[L], seg->ldw[L], seg->dZT[L], seg->ldb, 1,

@@ -130,6 +130,28 @@ def test_workspace_copies_of_input_and_output(w0, wl, dtype):
 
 
 @pytest.mark.parametrize("dtype", [api.F32, api.BF16])
+@pytest.mark.parametrize("shift", [0, 1, -1])
+@pytest.mark.parametrize("B,widths", [(70, [80, 80]), (70, [61, 61]), (300, [64, 64]), (200, [1024, 1024]), (1000, [1600, 1500]), (70, [80, 40, 96])])
+def test_forward_into_its_own_input(B, widths, shift, dtype):
+    """out on X itself, or some rows before or behind: one layer's only launch reads the one and writes the other, at widths
+    that it could take from X as they are (80; 64, 1024 and 1600 with rows on cache lines) and one that it could not (61).
+    The same bits as into a buffer of its own."""
+    g = torch.Generator().manual_seed(B + widths[0])
+    tdt = torch.float32 if dtype == api.F32 else torch.bfloat16
+    seg = api.Segment(widths, api.RELU_ALL, api.MSE_SIL, max_batch=B, dtype=dtype)
+    seg.init(3)
+    X = torch.rand(B, widths[0], generator=g).to(tdt).cuda()
+    ref = seg.forward(X).clone()
+    most, far = B * max(widths), shift * (B // 3) * 64             # elements; whole cache lines
+    buf = torch.zeros(most + 2 * abs(far) + 64, dtype=tdt, device="cuda")
+    x0 = abs(far) + 64 // buf.element_size() if widths[0] == 80 else abs(far)
+    xin = buf[x0:x0 + B * widths[0]].view(B, widths[0])
+    out = buf[x0 + far:x0 + far + B * widths[-1]].view(B, widths[-1])
+    xin.copy_(X)
+    assert torch.equal(seg.forward(xin, out=out), ref)
+
+
+@pytest.mark.parametrize("dtype", [api.F32, api.BF16])
 @pytest.mark.parametrize("B,K,N", [(1000, 1500, 1490), (1030, 200, 2300), (1500, 200, 3500), (4090, 100, 500)])
 def test_products_on_the_tiles_between_small_and_large(B, K, N, dtype):
     """bf16: 128x64 tiles (1000 x 1490, 4090 x 500), 128x128 on part of the chip (1030 x 2300), two workgroups per unit (1500 x
