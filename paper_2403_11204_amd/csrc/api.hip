@@ -95,7 +95,7 @@ struct slp_segment {
   std::vector<ProfRec> prof_log;
   std::vector<hipEvent_t> ev_pool;
   // The parameter update of layer l is memory-bound and independent of the matrix products of the
-  // layers below it, so where those are long enough (see backward_and_update) it runs on a side stream next to
+  // layers below it, so where that pays (see updates_beside) it runs on a side stream next to
   // them (fork after the weight gradient of layer l, join at the end of the step: the caller's stream still orders
   // everything).
   hipStream_t side;
@@ -301,6 +301,49 @@ GemmArgs data_gradient(slp_segment* seg, int l, int batch) {
   return g;
 }
 
+// Whether the caller asked for the optimiser step of this layer inside its weight-gradient product.
+bool update_is_fused(const slp_segment* s, const Layer& ly) { return s->fused_update && (long)ly.N * ly.K <= s->fused_max_params; }
+
+// Whether the separate updates of a step without a deferred join run on the side stream, beside the products still to come.
+// There they pay for the fork and the join, some 35 us, and for what the two cost each other; in the caller's stream they follow
+// their product at full width.  Microseconds a step, beside / in the caller's stream:
+//   bf16, three equal layers   4096 wide, 256 rows 408 / 344, 600 497 / 464, 1024 576 / 528, 1200 644 / 651, 1400 656 / 660,
+//                              4096 990 / 1004; 6144 wide, 1024 1291 / 1286, 1300 1595 / 1577; 8192 wide, 256 1544 / 1339, 1024
+//                              2152 / 2017, 1280 2660 / 2587, 1400 2680 / 2607, 2048 2394 / 2412, 8192 6624 / 6835; 9216 wide,
+//                              512 2469 / 2377, 1024 3112 / 3215; 10240 wide, 128 2311 / 2164, 512 2822 / 2801, 1024 3653 / 3789,
+//                              1300 3149 / 3256; 12288 wide, 512 3893 / 4061, 1024 4915 / 5270; 16384 wide, 64 5359 / 5397,
+//                              256 5755 / 5869, 512 6518 / 6821, 1024 7388 / 7541, 1300 8641 / 9013
+//   two                        8192 wide, 512 1137 / 973, 1024 1425 / 1271; 12288 wide, 128 2111 / 2036, 512 2639 / 2598, 1024
+//                              3337 / 3340; 16384 wide, 512 4387 / 4411, 1024 4737 / 4808, 1400 5655 / 5780
+//   others at 1024 rows        2048-8192-8192-2048 1282 / 1129; 784-8192-12288-4096 1904 / 1946; 16384-8192-8192-16384 3351 /
+//                              3476; 16384-16384-1000 2414 / 2440
+//   float32, three equal ones  2048 wide, 256 331 / 317, 400 361 / 350, 512 378 / 369, 600 536 / 536, 1024 609 / 622; 3072 wide,
+//                              384 825 / 856, 512 888 / 923; 4096 wide, 128 727 / 683, 200 756 / 753, 256 781 / 778, 320 1101 /
+//                              1118, 512 1242 / 1262, 1024 2188 / 2240; 6144 wide, 256 1908 / 2018, 512 2948 / 3089; 8192 wide,
+//                              64 1816 / 1813, 128 2028 / 2001, 256 2870 / 2953, 512 4674 / 4834
+//   two                        4096 wide, 384 742 / 725, 512 806 / 789; 8192 wide, 256 1906 / 1854, 512 3067 / 3045; 12288 wide,
+//                              256 4297 / 4366, 512 7830 / 7999; 16384 wide, 512 11795 / 12248
+//   four and five              4096 wide, 256 1047 / 1065, 512 1669 / 1725; 2048 wide, 256 564 / 554, 400 615 / 608, 512 646 / 642
+//   others at 512 rows         784-4096-4096-47 592 / 579; 784-2048-2048-2048 330 / 319; 4096-1024-4096-4096 761 / 766;
+//                              784-3072-3072-3072-47 776 / 782; 1024-4096-4096-2048 815 / 816
+// So beside pays from a length of the batch on; below it where a gradient is larger than the memory-side cache's 256 MB (2^26
+// float32 values), in bf16 up to twice that only with enough rows; and in float32, whose products take ten times as long, where
+// those still to come behind the topmost such update are three and long enough.
+bool updates_beside(const slp_segment* s, int batch) {
+  if (batch >= (s->dtype == SLP_BF16 ? 1400 : 640)) return true;
+  long largest = 0;
+  int top = 0;                           // the topmost layer with a separate update
+  for (int l = 1; l <= s->L; ++l) {
+    const Layer& ly = s->layers[l - 1];
+    largest = std::max(largest, (long)ly.N * ly.K);
+    if (!update_is_fused(s, ly) && !product_is_small(s->dtype, EPI_WGRAD_UPDATE, ly.N, ly.K)) top = l;
+  }
+  if (s->dtype == SLP_BF16) return largest > (1L << 27) || (largest > (1L << 26) && batch >= 768);
+  double to_come = 0.0;
+  for (int l = 1; l < top; ++l) to_come += (l > 1 ? 4.0 : 2.0) * batch * (double)s->layers[l - 1].N * s->layers[l - 1].K;
+  return largest > (1L << 26) || (top > 2 && to_come >= 20e9);
+}
+
 // backward + update, last layer first; the data gradient of layer l reads W_l before it is updated
 // Makes `st` wait for updates a previous step left running on the side stream (deferred join).  The flag stays set
 // until the next step replaces the event (or the host has waited): every stream that touches the handle in between
@@ -348,12 +391,7 @@ int backward_and_update(slp_segment* seg, int batch, const SumJob* sum, hipStrea
   // wide configuration (1024) 18 % slower with any pause.
   const int pause = defer ? std::min(14, std::max(0, (batch - 2048) / 256)) : 0;
   if (pause > 0) HIP_TRY(launch_hurry(seg->hurry, 0, st));
-  // Without a deferred join an update beside the next layers' products has to pay for the fork and the join, some 35 us, and for
-  // what the two cost each other: it does where the products are long.  Microseconds a step of three equal layers, beside / in
-  // the caller's stream: bf16 4096 wide, batch 256 408 / 344, 1024 578 / 523, 1400 670 / 682, 4096 990 / 1004, 8192 1768 / 1795;
-  // 8192 wide, 1024 2163 / 1999, 2048 2418 / 2430, 8192 6624 / 6835; float32 2048 wide, 256 329 / 317, 512 378 / 369, 1024
-  // 611 / 621; 4096 wide, 256 780 / 778, 1024 2194 / 2242.
-  const bool beside = batch >= (seg->dtype == SLP_BF16 ? 1400 : 640);
+  const bool beside = updates_beside(seg, batch);
   SmallGroup pending{};                  // weight-gradient products waiting for company
   auto ride_along = [&](SmallGroup& gr) {
     if (!sum) return;
@@ -384,7 +422,7 @@ int backward_and_update(slp_segment* seg, int batch, const SumJob* sum, hipStrea
     g.B = seg->AT[l - 1]; g.ldb = seg->ldb;
     g.M = ly.N; g.N = ly.K; g.K = batch;
     g.Cf = ly.dW; g.ldc = ly.ldk;
-    const bool fused = seg->fused_update && (long)ly.N * ly.K <= seg->fused_max_params;
+    const bool fused = update_is_fused(seg, ly);
     const bool small = product_is_small(seg->dtype, EPI_WGRAD_UPDATE, g.M, g.N);
     if (small) {
       if (fused) g.Cf = nullptr;
@@ -481,7 +519,7 @@ int exchange(slp_segment* s, int layer, float* W, float* b, int which, bool set,
   Layer& ly = s->layers[layer];
   float* mats[3] = {ly.W32, ly.dW, ly.vW};
   float* vecs[3] = {ly.b, ly.db, ly.vb};
-  if (W && which == 1 && s->fused_update && (long)ly.N * ly.K <= s->fused_max_params)
+  if (W && which == 1 && update_is_fused(s, ly))
     return fail(SLP_ERR_STATE, "the weight gradient of layer %d is not stored: its update is fused into the product (slp_segment_set_fused_update)", layer);
   // between device buffers: both in one launch of a kernel; very large layers are left to the runtime's copies (6 TB/s)
   const bool small = on_device && (long)ly.N * ly.K <= kSmallCopy;
