@@ -229,10 +229,11 @@ int slp_segment_set_graph(slp_segment* seg, int on);
 int slp_segment_set_fused_update(slp_segment* seg, int on);
 
 /* ---- several segments trained side by side (end of Sec. 2: partitions are independent jobs) ----
- * The last thing a step does is stream every parameter once (the SGD update); it runs on a stream of the handle
- * beside the matrix products that are still to come, and the step normally ends by making `stream` wait for it.
+ * The last thing a step does is stream every parameter once (the SGD update); where that is faster it runs on a stream of
+ * the handle beside the matrix products that are still to come, and the step normally ends by making `stream` wait for it.
  * With overlap on, slp_segment_step (and slp_segment_step_external) returns without that wait, and the update of
- * the first layer moves to the side stream too: whatever the caller enqueues next on `stream` -- typically the
+ * the first layer moves to the side stream too (but for layers whose update is part of their weight-gradient product, see
+ * slp_segment_set_fused_update: nothing of them is left pending): whatever the caller enqueues next on `stream` -- typically the
  * step of another segment -- runs beside the tail of this one.  Until the handle's next step, every call on the
  * handle that takes a stream first makes that stream wait for the pending updates (whichever stream it is), so calls
  * through this interface see the same values as without overlap (bit for bit).  A caller that reads or frees the

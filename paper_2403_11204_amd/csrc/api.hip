@@ -433,16 +433,9 @@ int backward_and_update(slp_segment* seg, int batch, const SumJob* sum, hipStrea
       pending.bias[pending.n_bias++] = BiasJob{seg->dZT[l], seg->ldb, ly.N, batch, ly.db, ly.b, ly.vb, seg->lr, seg->mu};
       if (l > 1) continue;
     }
-    if (l == 1 && pending.n) {           // the last products: with a deferred join they run beside the caller's next work
-      hipStream_t us = defer ? seg->side : st;
-      if (us != st) {
-        HIP_TRY(hipEventRecord(seg->ev_fork[0], st));
-        HIP_TRY(hipStreamWaitEvent(us, seg->ev_fork[0], 0));
-        forked = true;
-      } else {
-        ride_along(pending);             // (the loss belongs to `st`)
-      }
-      int rc = run_group(seg, pending, us);
+    if (l == 1 && pending.n) {           // the last products; a fork and a join would cost more than they take
+      ride_along(pending);
+      int rc = run_group(seg, pending, st);
       pending = SmallGroup{};
       if (rc) return rc;
       if (small) continue;

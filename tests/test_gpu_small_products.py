@@ -241,3 +241,33 @@ def test_paced_updates_leave_the_same_bits():
     torch.cuda.synchronize()
     for a, b in zip(*finals):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("fused", [0, 2])
+def test_overlap_leaves_nothing_of_small_layers_pending(fused):
+    """The updates of small layers are part of launches in the caller's stream, with overlap on as well: a stream that is being
+    captured right behind a step has nothing to wait for, and the graph gives what an eager call gives."""
+    B, widths = 64, [96, 128, 64]
+    g = torch.Generator().manual_seed(8)
+    seg = api.Segment(widths, api.RELU_ALL, api.MSE_SIL, max_batch=B, dtype=api.F32, lr=0.05, momentum=0.9)
+    seg.init(9)
+    seg.set_labels(torch.rand(10, widths[-1], generator=g).cuda())
+    seg.set_fused_update(fused)
+    seg.set_overlap(True)
+    X = torch.rand(B, widths[0], generator=g).cuda()
+    y = torch.randint(0, 10, (B,), generator=g, dtype=torch.int32).cuda()
+    out = torch.zeros(B, widths[-1], device="cuda")
+    stream = torch.cuda.Stream()
+    stream.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(stream):
+        for _ in range(2):
+            seg.step(X, y)
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream, capture_error_mode="thread_local"):
+            seg.forward(X, out=out)
+        for _ in range(3):
+            out.zero_()
+            graph.replay()
+            stream.synchronize()
+            assert torch.equal(out, seg.forward(X))
+            seg.step(X, y)
