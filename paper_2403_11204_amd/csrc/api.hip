@@ -204,7 +204,7 @@ int direct_launches(const slp_segment* s, const void* X, int batch) {
         (l > 1 && !product_is_small(s->dtype, EPI_DGRAD, batch, s->widths[l - 1])))
       return 0;
   // ingest unless it rides along, forward, cross-entropy, data gradients (weight gradients ride along), the last weight gradients
-  return (reads_input(s, X, batch) ? 0 : 1) + s->L + (s->loss == SLP_MSE_SIL ? 0 : 1) + (s->L - 1) + 1;
+  return (reads_input(s, X, batch) ? 0 : 1) + s->L + (s->loss == SLP_MSE_SIL ? 0 : xent_launch_count(s->dtype, s->widths[s->L])) + (s->L - 1) + 1;
 }
 
 struct Forward {

@@ -114,14 +114,13 @@ __global__ __launch_bounds__(256) void mse_loss_grad_kernel(const T* __restrict_
 }
 
 // ---------------------------------------------------------------------------------
-// softmax cross-entropy, four rows per wavefront
+// softmax cross-entropy
 // ---------------------------------------------------------------------------------
-// A lane holds column c of four consecutive rows, so that it can store them into the transposed gradient as one vector (8 or
-// 16 bytes; neighbouring wavefronts fill the rest of the line in L2) and the four rows' reductions run side by side: what
-// bounds this kernel at the sizes in use is their latency, not its bytes.  256 x 47 float32, loss and transposed copy: 4.0 + 2.9
-// us in two launches (one row per wavefront) and what lies between two launches, another 4 -> one of 4.5-5.  The order of each
-// row's sum is that of one row per wavefront.
-// NC > 0: C <= 64 NC, the logits are read once and stay in registers; NC = 0: any C, read three times.
+// C <= 64 NC: four rows per wavefront, the logits read once and kept in registers.  A lane holds column c of four consecutive
+// rows, so that it can store them into the transposed gradient as one vector of 8 or 16 bytes (a workgroup covers 16 rows, 32
+// or 64 bytes of a line; the rest of it comes from other workgroups) and the four rows' reductions run side by side: what
+// bounds this kernel at the sizes in use is their latency, not its bytes.  The order of each row's sum is that of one row per
+// wavefront.  See launch_xent for where it is used.
 template <typename T, int NC>
 __global__ __launch_bounds__(256) void xent_loss_grad_kernel(const T* __restrict__ ZL, int ld, const int32_t* __restrict__ y,
                                                              int B, int C, int relu_last, float inv_b,
@@ -139,32 +138,25 @@ __global__ __launch_bounds__(256) void xent_loss_grad_kernel(const T* __restrict
     z[r] = ZL + (size_t)m * ld;
     cls[r] = y[m];
   }
-  constexpr int KEEP = NC > 0 ? NC : 1;
-  float zv[KEEP][4];
-  auto value = [&](int i, int r, int c) { return NC > 0 ? zv[i][r] : to_f32<T>(z[r][c]); };
-  if (NC > 0) {
+  float zv[NC][4];
 #pragma unroll
-    for (int i = 0; i < KEEP; ++i)
+  for (int i = 0; i < NC; ++i)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) zv[i][r] = lane + 64 * i < C ? to_f32<T>(z[r][lane + 64 * i]) : -INFINITY;
-  }
+    for (int r = 0; r < 4; ++r) zv[i][r] = lane + 64 * i < C ? to_f32<T>(z[r][lane + 64 * i]) : -INFINITY;
   float mx[4] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY}, sum[4] = {0.0f, 0.0f, 0.0f, 0.0f}, lse[4];
-  const int trips = NC > 0 ? KEEP : (C + 63) / 64;
 #pragma unroll
-  for (int i = 0; i < trips; ++i) {
-    const int c = lane + 64 * i;
-    if (c < C)
+  for (int i = 0; i < NC; ++i) {
+    if (lane + 64 * i < C)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) mx[r] = fmaxf(mx[r], value(i, r, c));
+      for (int r = 0; r < 4; ++r) mx[r] = fmaxf(mx[r], zv[i][r]);
   }
 #pragma unroll
   for (int r = 0; r < 4; ++r) mx[r] = wave_max(mx[r]);
 #pragma unroll
-  for (int i = 0; i < trips; ++i) {
-    const int c = lane + 64 * i;
-    if (c < C)
+  for (int i = 0; i < NC; ++i) {
+    if (lane + 64 * i < C)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) sum[r] += expf(value(i, r, c) - mx[r]);
+      for (int r = 0; r < 4; ++r) sum[r] += expf(zv[i][r] - mx[r]);
   }
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
@@ -178,13 +170,13 @@ __global__ __launch_bounds__(256) void xent_loss_grad_kernel(const T* __restrict
     cls[r] = id;
   }
 #pragma unroll
-  for (int i = 0; i < trips; ++i) {
+  for (int i = 0; i < NC; ++i) {
     const int c = lane + 64 * i;
     if (c < C) {
       vec4 g;
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const float zc = value(i, r, c);
+        const float zc = zv[i][r];
         const float p = expf(zc - lse[r]);
         const float d = (p - (c == cls[r] ? 1.0f : 0.0f)) * inv_b;
         g[r] = from_f32<T>((m0 + r >= B || (relu_last && !(zc > 0.0f))) ? 0.0f : d);
@@ -192,6 +184,39 @@ __global__ __launch_bounds__(256) void xent_loss_grad_kernel(const T* __restrict
       }
       if (dZT) *(vec4*)(dZT + (size_t)c * ldt + m0) = g;
     }
+  }
+}
+
+// Any number of classes: one row per wavefront, the logits read three times, and the transposed gradient by a launch of its own.
+// Four rows per wavefront with three reads were a quarter of the wavefronts, each four times as long, and stored 16 rows' worth
+// of a line at a time.  Microseconds, this kernel + transpose / four rows: float32 256 x 1000 13.6 + 4.2 / 30.3, 8192 x 1000
+// 24.0 + 11.4 / 48.3, 8192 x 4096 106 + 43 / 249; bf16 8192 x 1000 22.0 + 6.8 / 44.5, 8192 x 4096 75.5 + 22.3 / 166.
+template <typename T>
+__global__ __launch_bounds__(256) void xent_loss_grad_wide_kernel(const T* __restrict__ ZL, int ld, const int32_t* __restrict__ y,
+                                                                  int B, int C, int relu_last, float inv_b, T* __restrict__ dZ,
+                                                                  float* __restrict__ row_loss, unsigned* __restrict__ bad_ids) {
+  const int lane = threadIdx.x & 63;
+  const int m = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (m >= B) return;
+  const T* z = ZL + (size_t)m * ld;
+  float mx = -INFINITY;
+  for (int c = lane; c < C; c += 64) mx = fmaxf(mx, to_f32<T>(z[c]));
+  mx = wave_max(mx);
+  float sum = 0.0f;
+  for (int c = lane; c < C; c += 64) sum += expf(to_f32<T>(z[c]) - mx);
+  sum = wave_sum(sum);
+  const float lse = mx + logf(sum);
+  const int cls = min(max(y[m], 0), C - 1);
+  if (lane == 0) {
+    if (cls != y[m]) atomicAdd(bad_ids, 1u);
+    row_loss[m] = lse - to_f32<T>(z[cls]);
+  }
+  T* g = dZ + (size_t)m * ld;
+  for (int c = lane; c < C; c += 64) {
+    const float zc = to_f32<T>(z[c]);
+    const float p = expf(zc - lse);
+    const float d = (p - (c == cls ? 1.0f : 0.0f)) * inv_b;
+    g[c] = from_f32<T>((relu_last && !(zc > 0.0f)) ? 0.0f : d);
   }
 }
 
@@ -409,24 +434,34 @@ hipError_t launch_mse_loss_grad(int dtype, const void* AL, int ld, const int32_t
   return hipGetLastError();
 }
 
+// Four rows per wavefront in one launch as long as the logits fit into registers and the transposed stores are whole enough.
+// A step of 64-C, microseconds, one launch / one row per wavefront and a transpose: float32 256 x 47 15.6 / 18.0, 1024 x 200
+// 18.6 / 19.3, 1024 x 256 18.5 / 19.9, 8192 x 47 40.5 / 43.2, 8192 x 256 49.6 / 53.1; bf16 256 x 47 15.5 / 18.0, 1024 x 128 16.4 /
+// 18.1, 2048 x 128 17.5 / 17.9, 8192 x 128 26.1 / 26.6, but 256 x 200 18.6 / 18.0, 2048 x 200 22.0 / 18.6, 2048 x 256 21.9 / 18.5.
+int xent_launch_count(int dtype, int C) { return C <= (dtype == 1 ? 128 : 256) ? 1 : 2; }
+
 template <typename T>
-static void launch_xent(const void* ZL, int ld, const int32_t* y, int B, int C, int relu_last, void* dZ, void* dZT, int ldt, float* partials,
-                        unsigned* bad_ids, hipStream_t s) {
-  const int grid = (((B + 7) & ~7) / 4 + 3) / 4;
+static hipError_t launch_xent(int dtype, const void* ZL, int ld, const int32_t* y, int B, int C, int relu_last, void* dZ, void* dZT, int ldt,
+                              float* partials, unsigned* bad_ids, hipStream_t s) {
   const float inv_b = (float)(1.0 / (double)B);
-  if (C <= 64)
-    xent_loss_grad_kernel<T, 1><<<grid, 256, 0, s>>>((const T*)ZL, ld, y, B, C, relu_last, inv_b, (T*)dZ, (T*)dZT, ldt, partials, bad_ids);
-  else if (C <= 256)
-    xent_loss_grad_kernel<T, 4><<<grid, 256, 0, s>>>((const T*)ZL, ld, y, B, C, relu_last, inv_b, (T*)dZ, (T*)dZT, ldt, partials, bad_ids);
-  else
-    xent_loss_grad_kernel<T, 0><<<grid, 256, 0, s>>>((const T*)ZL, ld, y, B, C, relu_last, inv_b, (T*)dZ, (T*)dZT, ldt, partials, bad_ids);
+  constexpr int NC = sizeof(T) == 2 ? 2 : 4;
+  if (xent_launch_count(dtype, C) == 1) {
+    const int grid = (((B + 7) & ~7) / 4 + 3) / 4;
+    if (C <= 64)
+      xent_loss_grad_kernel<T, 1><<<grid, 256, 0, s>>>((const T*)ZL, ld, y, B, C, relu_last, inv_b, (T*)dZ, (T*)dZT, ldt, partials, bad_ids);
+    else
+      xent_loss_grad_kernel<T, NC><<<grid, 256, 0, s>>>((const T*)ZL, ld, y, B, C, relu_last, inv_b, (T*)dZ, (T*)dZT, ldt, partials, bad_ids);
+    return hipGetLastError();
+  }
+  xent_loss_grad_wide_kernel<T><<<(B + 3) / 4, 256, 0, s>>>((const T*)ZL, ld, y, B, C, relu_last, inv_b, (T*)dZ, partials, bad_ids);
+  const hipError_t e = hipGetLastError();
+  return e != hipSuccess || !dZT ? e : launch_copy_transpose(dtype, dZ, ld, B, C, nullptr, 0, dZT, ldt, 1, nullptr, 0, s);
 }
 
 hipError_t launch_xent_loss_grad(int dtype, const void* ZL, int ld, const int32_t* y, int B, int C, int relu_last,
                                  void* dZ, void* dZT, int ldt, float* partials, unsigned* bad_ids, hipStream_t s) {
-  if (dtype == 1) launch_xent<bf16>(ZL, ld, y, B, C, relu_last, dZ, dZT, ldt, partials, bad_ids, s);
-  else launch_xent<float>(ZL, ld, y, B, C, relu_last, dZ, dZT, ldt, partials, bad_ids, s);
-  return hipGetLastError();
+  return dtype == 1 ? launch_xent<bf16>(dtype, ZL, ld, y, B, C, relu_last, dZ, dZT, ldt, partials, bad_ids, s)
+                    : launch_xent<float>(dtype, ZL, ld, y, B, C, relu_last, dZ, dZT, ldt, partials, bad_ids, s);
 }
 
 hipError_t launch_hurry(unsigned* hurry, unsigned value, hipStream_t s) {

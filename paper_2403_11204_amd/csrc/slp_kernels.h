@@ -129,6 +129,7 @@ int mse_partial_count(int B, int D);
 // relu_last), and transposed to dZT ([C][ldt], zero-filled pads; may be null); per-row loss to partials[m].
 hipError_t launch_xent_loss_grad(int dtype, const void* ZL, int ld, const int32_t* y, int B, int C, int relu_last,
                                  void* dZ, void* dZT, int ldt, float* partials, unsigned* bad_ids, hipStream_t s);
+int xent_launch_count(int dtype, int C);     // of a call with dZT
 
 // Wd[n][0..K) = W[n][0..K) (rows lds and ldd floats apart; W may be null) and bd[0..N) = b[0..N) (b may be null).
 hipError_t launch_copy_layer(const float* W, int lds, float* Wd, int ldd, int N, int K, const float* b, float* bd, hipStream_t s);

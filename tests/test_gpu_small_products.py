@@ -160,9 +160,9 @@ def test_products_on_the_tiles_between_small_and_large(B, K, N, dtype):
 
 
 @pytest.mark.parametrize("dtype", [api.F32, api.BF16])
-@pytest.mark.parametrize("B,C", [(1, 1), (3, 2), (5, 63), (8, 64), (13, 65), (66, 256), (31, 257), (129, 1000)])
+@pytest.mark.parametrize("B,C", [(1, 1), (3, 2), (5, 63), (8, 64), (13, 65), (40, 128), (21, 129), (66, 256), (31, 257), (129, 1000)])
 def test_cross_entropy_gradient_and_its_transpose(B, C, dtype):
-    """Classes on and beside the sizes that stay in registers (64, 256), batches that leave a wavefront's four rows and the
+    """Classes on and beside the sizes that stay in registers (64, 128 in bf16, 256 in float32), batches that leave a wavefront's four rows and the
     padded columns of the transposed gradient partly filled: dZ, its column sums (read from the transpose) and the loss."""
     g = torch.Generator().manual_seed(B * 1000 + C)
     tdt = torch.float32 if dtype == api.F32 else torch.bfloat16
