@@ -451,7 +451,7 @@ int backward_and_update(slp_segment* seg, int batch, const SumJob* sum, hipStrea
       // The data gradient of layer l read W_l^T before this product was queued (same stream).  What is left of the
       // layer is its bias: one small launch, on the caller's stream (nothing worth a second stream).
       HIP_TRY(launch_layer_update(seg->dtype, nullptr, nullptr, nullptr, ly.N, 0, ly.ldk, nullptr, nullptr, ly.ldn, seg->dZT[l],
-                                  seg->ldb, batch, ly.db, ly.b, ly.vb, seg->lr, seg->mu, 0, 0, 0, nullptr, st));
+                                  seg->ldb, batch, ly.db, ly.b, ly.vb, seg->lr, seg->mu, st));
       continue;
     }
     // everything layer l still needs (bias gradient, both updates) reads dZ_l^T / dW_l, which are complete here, and writes
@@ -467,12 +467,12 @@ int backward_and_update(slp_segment* seg, int batch, const SumJob* sum, hipStrea
     // inside one launch its long reads of dZ^T slowed the products (measured 1 %)
     if ((size_t)ly.N * ly.K <= ((size_t)1 << 22) || us == st) {
       HIP_TRY(launch_layer_update(seg->dtype, ly.W32, ly.vW, ly.dW, ly.N, ly.K, ly.ldk, ly.W16, ly.WT, ly.ldn, seg->dZT[l],
-                                  seg->ldb, batch, ly.db, ly.b, ly.vb, seg->lr, seg->mu, 0, 0, 0, nullptr, us));
+                                  seg->ldb, batch, ly.db, ly.b, ly.vb, seg->lr, seg->mu, us));
     } else {
       HIP_TRY(launch_layer_update(seg->dtype, nullptr, nullptr, nullptr, ly.N, 0, ly.ldk, nullptr, nullptr, ly.ldn, seg->dZT[l],
-                                  seg->ldb, batch, ly.db, ly.b, ly.vb, seg->lr, seg->mu, 0, 0, 0, nullptr, us));
-      HIP_TRY(launch_layer_update(seg->dtype, ly.W32, ly.vW, ly.dW, ly.N, ly.K, ly.ldk, ly.W16, ly.WT, ly.ldn, nullptr, 0, 0,
-                                  nullptr, nullptr, nullptr, seg->lr, seg->mu, 0, us != st ? kSideUpdateWorkgroups : 0, us != st ? pause : 0, seg->hurry, us));
+                                  seg->ldb, batch, ly.db, ly.b, ly.vb, seg->lr, seg->mu, us));
+      HIP_TRY(launch_update_beside(seg->dtype, ly.W32, ly.vW, ly.dW, ly.N, ly.K, ly.ldk, ly.W16, ly.WT, ly.ldn, seg->lr, seg->mu,
+                                   kSideUpdateWorkgroups, pause, seg->hurry, us));
     }
   }
   if (sum) HIP_TRY(launch_reduce_loss(sum->partials, sum->n, sum->scale, sum->out0, sum->out1, st));   // found no company
@@ -488,8 +488,7 @@ int backward_and_update(slp_segment* seg, int batch, const SumJob* sum, hipStrea
 int refresh_copies(slp_segment* s, int layer, hipStream_t st) {
   Layer& ly = s->layers[layer];
   if (!ly.W16 && !ly.WT) return SLP_OK;
-  HIP_TRY(launch_layer_update(s->dtype, ly.W32, ly.vW, ly.dW, ly.N, ly.K, ly.ldk, ly.W16, ly.WT, ly.ldn, nullptr, 0, 0, nullptr,
-                              nullptr, nullptr, 0.0f, 0.0f, 1, 0, 0, nullptr, st));
+  HIP_TRY(launch_refresh_copies(s->dtype, ly.W32, ly.N, ly.K, ly.ldk, ly.W16, ly.WT, ly.ldn, st));
   return SLP_OK;
 }
 

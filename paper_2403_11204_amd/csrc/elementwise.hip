@@ -238,11 +238,11 @@ __global__ __launch_bounds__(256) void reduce_loss_kernel(const float* __restric
 // which goes through an LDS tile.  Pad columns (in >= K, up to the leading dimension) hold
 // zeros in all three streams and stay zero under the update, so the row direction needs
 // no tail handling.
-template <typename T>
+template <typename T, bool REFRESH = false>      // REFRESH: no arithmetic, the copies are rebuilt from W32
 __device__ __forceinline__ void sgd_update_block(int bx, int by, float* __restrict__ W32, float* __restrict__ vW,
                                                  const float* __restrict__ dW, int N, int K, int ldk,
                                                  bf16* __restrict__ W16, T* __restrict__ WT, int ldn, float lr,
-                                                 float mu, int refresh_only) {
+                                                 float mu) {
   typedef float f32x4 __attribute__((ext_vector_type(4)));
   typedef T tx4 __attribute__((ext_vector_type(4)));
   typedef bf16 bf16x4 __attribute__((ext_vector_type(4)));
@@ -253,14 +253,14 @@ __device__ __forceinline__ void sgd_update_block(int bx, int by, float* __restri
   // all loads of the thread's four rows are issued before the first store, so that 9 to 12
   // 16-byte requests per thread are in flight
   f32x4 w[4], gr[4], vo[4];
-  const bool with_v = !refresh_only && mu != 0.0f;
+  const bool with_v = !REFRESH && mu != 0.0f;
 #pragma unroll
   for (int p = 0; p < 4; ++p) {
     const int n = n0 + r + 16 * p;
     const bool in = n < N && k < K;
     const size_t idx = (size_t)n * ldk + k;
     w[p] = in ? __builtin_nontemporal_load((const f32x4*)(W32 + idx)) : f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-    gr[p] = (in && !refresh_only) ? __builtin_nontemporal_load((const f32x4*)(dW + idx)) : f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    gr[p] = (in && !REFRESH) ? __builtin_nontemporal_load((const f32x4*)(dW + idx)) : f32x4{0.0f, 0.0f, 0.0f, 0.0f};
     vo[p] = (in && with_v) ? __builtin_nontemporal_load((const f32x4*)(vW + idx)) : f32x4{0.0f, 0.0f, 0.0f, 0.0f};
   }
 #pragma unroll
@@ -268,7 +268,7 @@ __device__ __forceinline__ void sgd_update_block(int bx, int by, float* __restri
     const int rr = r + 16 * p, n = n0 + rr;
     if (n < N && k < K) {
       const size_t idx = (size_t)n * ldk + k;
-      if (!refresh_only) {
+      if (!REFRESH) {
         f32x4 v = gr[p];
         if (with_v) {
           v = mu * vo[p] + v;
@@ -306,19 +306,17 @@ __device__ __forceinline__ void sgd_update_block(int bx, int by, float* __restri
 struct LayerUpdate {
   float *W32, *vW; const float* dW; int N, K, ldk; void* W16; void* WT; int ldn;     // weights [N][ldk]
   const void* dZT; int ldt, B; float *db, *b, *vb;                                     // bias: dZT [N][ldt]; null = weights only
-  float lr, mu; int refresh_only;
+  float lr, mu;
 };
 
-// the weight matrix alone, one block per 64x64 tile on a 2-D grid (large layers)
+// the copies alone, one block per 64x64 tile on a 2-D grid
 template <typename T>
-__global__ __launch_bounds__(256) void sgd_update_kernel(float* __restrict__ W32, float* __restrict__ vW,
-                                                         const float* __restrict__ dW, int N, int K, int ldk,
-                                                         bf16* __restrict__ W16, T* __restrict__ WT, int ldn, float lr,
-                                                         float mu, int refresh_only) {
-  sgd_update_block<T>(blockIdx.x, blockIdx.y, W32, vW, dW, N, K, ldk, W16, WT, ldn, lr, mu, refresh_only);
+__global__ __launch_bounds__(256) void refresh_copies_kernel(float* __restrict__ W32, int N, int K, int ldk, bf16* __restrict__ W16,
+                                                             T* __restrict__ WT, int ldn) {
+  sgd_update_block<T, true>(blockIdx.x, blockIdx.y, W32, nullptr, nullptr, N, K, ldk, W16, WT, ldn, 0.0f, 0.0f);
 }
 
-// The same on a fixed number of workgroups that walk the tiles with the grid's stride: for updates that run beside
+// The update of the weight matrix alone on a fixed number of workgroups that walk the tiles with the grid's stride: for updates that run beside
 // matrix products.  At full width the update saturates HBM and the product next to it, which waits on every load,
 // all but stops (measured: a 1.3 ms update stretched the product beside it from 3.15 to 4.29 ms); one workgroup per
 // compute unit takes longer over the same bytes and costs the product less.
@@ -339,11 +337,11 @@ template <typename T>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8))) void sgd_update_strided_kernel(float* __restrict__ W32, float* __restrict__ vW,
                                                                  const float* __restrict__ dW, int N, int K, int ldk,
                                                                  bf16* __restrict__ W16, T* __restrict__ WT, int ldn, float lr,
-                                                                 float mu, int refresh_only, int pause, const unsigned* hurry) {
+                                                                 float mu, int pause, const unsigned* hurry) {
   const int kb = (K + 63) / 64, tiles = kb * ((N + 63) / 64);
   for (int id = blockIdx.x; id < tiles; id += gridDim.x) {
     const unsigned h = pause > 0 ? __hip_atomic_load(hurry, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
-    sgd_update_block<T>(id % kb, id / kb, W32, vW, dW, N, K, ldk, W16, WT, ldn, lr, mu, refresh_only);
+    sgd_update_block<T>(id % kb, id / kb, W32, vW, dW, N, K, ldk, W16, WT, ldn, lr, mu);
     if (h) pause = 0;
     for (int i = 0; i < pause; ++i) __builtin_amdgcn_s_sleep(16);
     __syncthreads();   // the LDS tile is reused
@@ -359,7 +357,7 @@ __global__ __launch_bounds__(256) void layer_update_kernel(const LayerUpdate u) 
   const int kb = (u.K + 63) / 64, nb = (u.N + 63) / 64;
   const int id = blockIdx.x;
   if (id < kb * nb)
-    sgd_update_block<T>(id % kb, id / kb, u.W32, u.vW, u.dW, u.N, u.K, u.ldk, (bf16*)u.W16, (T*)u.WT, u.ldn, u.lr, u.mu, u.refresh_only);
+    sgd_update_block<T>(id % kb, id / kb, u.W32, u.vW, u.dW, u.N, u.K, u.ldk, (bf16*)u.W16, (T*)u.WT, u.ldn, u.lr, u.mu);
   else
     bias_grad_update_block<T>(id - kb * nb, (const T*)u.dZT, u.ldt, u.N, u.B, u.db, u.b, u.vb, u.lr, u.mu);
 }
@@ -481,29 +479,28 @@ hipError_t launch_reduce_loss(const float* partials, int n, double scale, float*
 }
 
 hipError_t launch_layer_update(int dtype, float* W32, float* vW, const float* dW, int N, int K, int ldk, void* W16, void* WT,
-                               int ldn, const void* dZT, int ldt, int B, float* db, float* b, float* vb, float lr, float mu,
-                               int refresh_only, int max_workgroups, int pause, const unsigned* hurry, hipStream_t s) {
-  if (pause > 0 && !hurry) return hipErrorInvalidValue;
-  if (!dZT) {       // weights only
-    const int wgs = max_workgroups;
-    if (wgs > 0 && (long)((K + 63) / 64) * ((N + 63) / 64) > wgs) {
-      if (dtype == 1)
-        sgd_update_strided_kernel<bf16><<<wgs, 256, 0, s>>>(W32, vW, dW, N, K, ldk, (bf16*)W16, (bf16*)WT, ldn, lr, mu, refresh_only, pause, hurry);
-      else
-        sgd_update_strided_kernel<float><<<wgs, 256, 0, s>>>(W32, vW, dW, N, K, ldk, nullptr, (float*)WT, ldn, lr, mu, refresh_only, pause, hurry);
-      return hipGetLastError();
-    }
-    dim3 grid2((K + 63) / 64, (N + 63) / 64);
-    if (dtype == 1)
-      sgd_update_kernel<bf16><<<grid2, 256, 0, s>>>(W32, vW, dW, N, K, ldk, (bf16*)W16, (bf16*)WT, ldn, lr, mu, refresh_only);
-    else
-      sgd_update_kernel<float><<<grid2, 256, 0, s>>>(W32, vW, dW, N, K, ldk, nullptr, (float*)WT, ldn, lr, mu, refresh_only);
-    return hipGetLastError();
-  }
-  const LayerUpdate u{W32, vW, dW, N, K, ldk, dtype == 1 ? W16 : nullptr, WT, ldn, dZT, ldt, B, db, b, vb, lr, mu, refresh_only};
-  const int grid = ((K + 63) / 64) * ((N + 63) / 64) + (dZT ? (N + 3) / 4 : 0);
+                               int ldn, const void* dZT, int ldt, int B, float* db, float* b, float* vb, float lr, float mu, hipStream_t s) {
+  const LayerUpdate u{W32, vW, dW, N, K, ldk, dtype == 1 ? W16 : nullptr, WT, ldn, dZT, ldt, B, db, b, vb, lr, mu};
+  const int grid = ((K + 63) / 64) * ((N + 63) / 64) + (N + 3) / 4;
   if (dtype == 1) layer_update_kernel<bf16><<<grid, 256, 0, s>>>(u);
   else layer_update_kernel<float><<<grid, 256, 0, s>>>(u);
+  return hipGetLastError();
+}
+
+hipError_t launch_update_beside(int dtype, float* W32, float* vW, const float* dW, int N, int K, int ldk, void* W16, void* WT, int ldn,
+                                float lr, float mu, int workgroups, int pause, const unsigned* hurry, hipStream_t s) {
+  if (workgroups <= 0 || (pause > 0 && !hurry)) return hipErrorInvalidValue;
+  if (dtype == 1)
+    sgd_update_strided_kernel<bf16><<<workgroups, 256, 0, s>>>(W32, vW, dW, N, K, ldk, (bf16*)W16, (bf16*)WT, ldn, lr, mu, pause, hurry);
+  else
+    sgd_update_strided_kernel<float><<<workgroups, 256, 0, s>>>(W32, vW, dW, N, K, ldk, nullptr, (float*)WT, ldn, lr, mu, pause, hurry);
+  return hipGetLastError();
+}
+
+hipError_t launch_refresh_copies(int dtype, float* W32, int N, int K, int ldk, void* W16, void* WT, int ldn, hipStream_t s) {
+  dim3 grid((K + 63) / 64, (N + 63) / 64);
+  if (dtype == 1) refresh_copies_kernel<bf16><<<grid, 256, 0, s>>>(W32, N, K, ldk, (bf16*)W16, (bf16*)WT, ldn);
+  else refresh_copies_kernel<float><<<grid, 256, 0, s>>>(W32, N, K, ldk, nullptr, (float*)WT, ldn);
   return hipGetLastError();
 }
 

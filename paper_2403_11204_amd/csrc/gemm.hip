@@ -94,7 +94,6 @@ __device__ __forceinline__ void update_quad(const GemmArgs& g, int n, int mb, fl
   if (row < g.M && nb < g.N) {
     const size_t idx = (size_t)row * g.ldc + nb;
     f32x4 vel = f32x4{v[0], v[1], v[2], v[3]};
-    if (g.Cf) *(f32x4*)(g.Cf + idx) = vel;
     if (g.mu != 0.0f) {
       vel = g.mu * vo + vel;
       *(f32x4*)(g.uV + idx) = vel;

@@ -62,7 +62,7 @@ struct GemmArgs {
   float* uW; float* uV; void* uW16; void* uWT;
   int ldwt;
   float lr, mu;
-  // EPI_WGRAD_UPDATE: Cf may be given to store the gradient as well.  Small layers only: a second copy of C for EPI_FWD and
+  // Small layers only: EPI_WGRAD_UPDATE may be given Cf to store the gradient as well; C2 is a second copy of C for EPI_FWD and
   // EPI_DGRAD, e.g. the caller's dense matrix ([M][ldc2], any alignment; columns >= N are not written).
   void* C2;
   int ldc2;
@@ -138,15 +138,16 @@ hipError_t launch_copy_layer(const float* W, int lds, float* Wd, int ldd, int N,
 hipError_t launch_reduce_loss(const float* partials, int n, double scale, float* out0, float* out1, hipStream_t s);
 
 // One launch per layer: SGD with momentum on the weight matrix (v = mu v + g; w -= lr v), its derived copies
-// W16 (bf16 [N][ldk], bf16 mode only) and WT ([K][ldn], element type T, optional), and -- unless dZT is null --
-// the bias: db[n] = sum_{m < B} dZT[n][m], then the same update on b, vb.
-// refresh_only: skip the arithmetic and only rebuild the copies from W32 (dZT must be null).
-// max_workgroups > 0 (weights-only launches): run on at most that many workgroups, for updates issued beside matrix products;
-// pause: units of ~0.5 us each of those workgroups sleeps between two tiles (paces the update's memory traffic) until *hurry
-// (device) is not zero; launch_hurry sets it.
+// W16 (bf16 [N][ldk], bf16 mode only) and WT ([K][ldn], element type T, optional), and the bias: db[n] =
+// sum_{m < B} dZT[n][m], then the same update on b, vb.  K = 0: the bias alone.
 hipError_t launch_layer_update(int dtype, float* W32, float* vW, const float* dW, int N, int K, int ldk, void* W16, void* WT,
-                               int ldn, const void* dZT, int ldt, int B, float* db, float* b, float* vb, float lr, float mu,
-                               int refresh_only, int max_workgroups, int pause, const unsigned* hurry, hipStream_t s);
+                               int ldn, const void* dZT, int ldt, int B, float* db, float* b, float* vb, float lr, float mu, hipStream_t s);
+// The weights alone on `workgroups` workgroups, for updates issued beside matrix products.  pause: units of ~0.5 us each of
+// them sleeps between two tiles (paces the update's memory traffic) until *hurry (device) is not zero; launch_hurry sets it.
+hipError_t launch_update_beside(int dtype, float* W32, float* vW, const float* dW, int N, int K, int ldk, void* W16, void* WT, int ldn,
+                                float lr, float mu, int workgroups, int pause, const unsigned* hurry, hipStream_t s);
+// W16 and WT rebuilt from W32.
+hipError_t launch_refresh_copies(int dtype, float* W32, int N, int K, int ldk, void* W16, void* WT, int ldn, hipStream_t s);
 hipError_t launch_hurry(unsigned* hurry, unsigned value, hipStream_t s);
 
 // Counter-based generators (Philox4x32-10).
