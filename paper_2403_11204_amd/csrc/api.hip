@@ -63,8 +63,11 @@ struct StepGraph {
 };
 constexpr size_t kMaxStepGraphs = 16;
 // Steps of at most this many launches are launched one by one even where graphs are on: starting a graph costs the host more
-// than that many launches, and the device as much between its kernels.  Replayed / one by one, microseconds a step:
-// 784-128-64 batch 64 (4 launches) 25.8 / 18.5, 784-80-60 batch 1410 (4) 31.7 / 26.7, 512-1024-1024-47 batch 256 (7) 65 / 60.
+// than that many launches, and the device as much between its kernels.  Replayed / one by one, microseconds a step: 784-128-64
+// batch 64 (4 launches) 25.8 / 18.5, 784-80-60 batch 1410 (4) 31.7 / 26.7, 512-1024-1024-47 batch 256 (7) 65 / 60; layers of 64,
+// batch 64, 5 launches 26.8 / 19.0, 6 28.0 / 21.6, 7 30.5 / 24.0, 8 31.4 / 26.7, 9 35.0 / 30.6, 10 37.2 / 33.1, 13 47.0 / 43.4.
+// One by one keeps its 4 us beyond the line on an idle host; on a busy one (the same in another run) 11 launches took 41.1 /
+// 52.5 and 12 43.1 / 55.8, and up to 10 nothing, so the line leaves the host some room.
 constexpr int kDirectLaunches = 8;
 
 }  // namespace
@@ -344,7 +347,6 @@ bool updates_beside(const slp_segment* s, int batch) {
   return largest > (1L << 26) || (top > 2 && to_come >= 20e9);
 }
 
-// backward + update, last layer first; the data gradient of layer l reads W_l before it is updated
 // Makes `st` wait for updates a previous step left running on the side stream (deferred join).  The flag stays set
 // until the next step replaces the event (or the host has waited): every stream that touches the handle in between
 // gets the wait, not only the first one.
@@ -357,11 +359,20 @@ int settle(slp_segment* seg, hipStream_t st) {
       return fail(SLP_ERR_STATE, "updates of an overlapped step are still pending and a stream that is being captured cannot "
                                  "wait for them: call slp_segment_set_overlap(seg, 0) before the capture");
   }
-  if (seg->paced) {     // when `st` gets here nothing of it runs beside the updates any more: no reason to pace them
+  if (seg->paced) {     // when `st` gets here nothing of it runs beside the updates any more: no reason to pace them for it
     HIP_TRY(launch_hurry(seg->hurry, 1, st));
     seg->paced = false;
   }
   HIP_TRY(hipStreamWaitEvent(st, seg->ev_join, 0));
+  return SLP_OK;
+}
+
+// The same on the host.  The pauses of paced updates are sat through: there is no stream at hand here to raise the flag on that
+// is not behind work of the caller's.
+int settle_on_host(slp_segment* seg) {
+  if (!seg->join_pending) return SLP_OK;
+  HIP_TRY(hipStreamSynchronize(seg->side));
+  seg->join_pending = seg->paced = false;
   return SLP_OK;
 }
 
@@ -373,7 +384,8 @@ constexpr int kSideUpdateWorkgroups = 256;
 // or 4 M weights is 1-2 % faster than fusing none, fusing the 8 M and 16 M layers as well 2 % and 9 % slower (their
 // epilogues wait on weight and momentum loads that the separate, massively parallel update kernel streams).
 constexpr long kFusedAutoMaxWeights = 1L << 22;
-//
+
+// Backward and update, last layer first; the data gradient of layer l reads W_l before it is updated.
 // Small layers: the weight gradient's product always applies the update in its epilogue (and stores the gradient as well, unless
 // the fused update is on), and it waits for company: the product of layer l + 1 goes into one launch with the data gradient of
 // layer l, which does not read what it writes, or with the weight gradient of layer l at the end; the bias gradients ride
@@ -501,7 +513,10 @@ int copy_matrix(float* dense, float* padded, int rows, int cols, int ld, bool to
   return SLP_OK;
 }
 
-constexpr long kSmallCopy = 1L << 25;      // floats
+// Parameters up to this many floats go between device buffers in one launch of a kernel instead of a rectangle copy and a plain
+// one of the runtime's, beyond it the two are equal.  Weights and bias, microseconds, runtime / kernel: 128 x 784 10.0 / 7.8, 2048 x 2048
+// 9.9 / 7.7, 2048 x 2047 14.0 / 7.9, 4096 x 4096 21.8 / 20.9, 4096 x 4095 44.1 / 22.1, 8192 x 4096 42.8 / 43.3, 5792 x 5793 87.9 / 49.7.
+constexpr long kSmallCopy = 1L << 25;
 int exchange(slp_segment* s, int layer, float* W, float* b, int which, bool set, int on_device, hipStream_t st) {
   int rc = check_seg(s, true, !set);
   if (rc) return rc;
@@ -513,7 +528,6 @@ int exchange(slp_segment* s, int layer, float* W, float* b, int which, bool set,
   float* vecs[3] = {ly.b, ly.db, ly.vb};
   if (W && which == 1 && update_is_fused(s, ly))
     return fail(SLP_ERR_STATE, "the weight gradient of layer %d is not stored: its update is fused into the product (slp_segment_set_fused_update)", layer);
-  // between device buffers: both in one launch of a kernel; very large layers are left to the runtime's copies (6 TB/s)
   const bool small = on_device && (long)ly.N * ly.K <= kSmallCopy;
   if (small && (W || b)) {
     if (set) HIP_TRY(launch_copy_layer(W, ly.K, W ? mats[which] : nullptr, ly.ldk, ly.N, ly.K, b, vecs[which], st));
@@ -667,10 +681,8 @@ int slp_segment_bind(slp_segment* seg, void* params, size_t params_bytes, void* 
                      slp_stream stream) {
   int rc = check_seg(seg, false, false);
   if (rc) return rc;
-  if (seg->join_pending) {     // the old buffers are still being written
-    HIP_TRY(hipStreamSynchronize(seg->side));
-    seg->join_pending = false;
-  }
+  rc = settle_on_host(seg);    // the old buffers are still being written
+  if (rc) return rc;
   if (!params || !workspace) return fail(SLP_ERR_ARG, "params and workspace must not be NULL");
   if (((uintptr_t)params | (uintptr_t)workspace) & (kAlign - 1)) return fail(SLP_ERR_ALLOC, "buffers must be 256-byte aligned");
   if (params_bytes < seg->param_bytes) return fail(SLP_ERR_ALLOC, "params buffer has %zu bytes, %zu needed", params_bytes, seg->param_bytes);
@@ -910,21 +922,15 @@ int slp_segment_set_overlap(slp_segment* seg, int on) {
   int rc = check_seg(seg, false, false);
   if (rc) return rc;
   seg->defer_join = on != 0;
-  if (!on && seg->join_pending) {      // back to ordinary stream order: nothing is left running
-    HIP_TRY(hipStreamSynchronize(seg->side));
-    seg->join_pending = false;
-  }
-  return SLP_OK;
+  return on ? SLP_OK : settle_on_host(seg);      // off: back to ordinary stream order, nothing is left running
 }
 
 int slp_segment_set_fused_update(slp_segment* seg, int on) {
   int rc = check_seg(seg, false, false);
   if (rc) return rc;
   if (on < 0) return fail(SLP_ERR_ARG, "slp_segment_set_fused_update: on must be >= 0 (got %d)", on);
-  if (seg->join_pending) {             // updates of the other kind may still be running on the side stream
-    HIP_TRY(hipStreamSynchronize(seg->side));
-    seg->join_pending = false;
-  }
+  rc = settle_on_host(seg);            // updates of the other kind may still be running on the side stream
+  if (rc) return rc;
   seg->fused_update = on != 0;
   seg->fused_max_params = on == 1 ? (1L << 62) : (on == 2 ? kFusedAutoMaxWeights : (long)on);
   drop_graphs(seg);                    // captured steps hold the other launch sequence

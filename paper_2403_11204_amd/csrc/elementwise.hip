@@ -329,8 +329,9 @@ __global__ __launch_bounds__(256) void refresh_copies_kernel(float* __restrict__
 // them, so the update's loads queue in front of the product's; spread over twice the time they fit into the headroom
 // (comparison configuration 37.1 -> 36.7 ms per step, deep configuration run serially 13.2 -> 12.9 at 8-14 units; the
 // update's tail must still find products to hide behind, which is why the caller sizes the pause by the batch).
-// hurry: a flag that the host has raised on the stream of whoever comes to wait for the update (hurry_kernel): from the next
-// tile on nothing sleeps any more, whatever was to run beside the update is over.  The flag's load is issued before the tile
+// hurry: a flag that is raised on a stream that comes to wait for the update (hurry_kernel): from the next tile on nothing sleeps
+// any more, what that stream ran beside the update is over.  (A second stream of the caller's may still have products in
+// flight; they then share the chip with an update that does not pause.)  The flag's load is issued before the tile
 // and read after it.  A segment of 784-16384-16384-16384 stepped on its own waited 2.4 ms for the paced update of its second
 // layer, 1.3 without the pauses.
 template <typename T>

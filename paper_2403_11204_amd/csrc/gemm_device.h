@@ -1,4 +1,4 @@
-// Device helpers shared by the matrix-product kernels (gemm.hip, gemm_group.hip).
+// Device helpers shared by the matrix-product kernels (gemm.hip, gemm_small.hip).
 #pragma once
 
 #include "slp_kernels.h"
