@@ -2,8 +2,9 @@
 
 Two wavefronts of a product workgroup share a SIMD's 512 registers per lane with the update kernel's wavefronts, which
 need 64: above 224 registers per lane (or with spills) the update no longer runs beside the products and a training step
-of the large configurations gets ~10 % slower without any test of the arithmetic noticing.  This compiles the device
-code of csrc/gemm.hip with the library's own flags and reads the register counts out of the code object's metadata.
+of the large configurations gets ~10 % slower without any test of the arithmetic noticing.  The kernel of small layers holds
+all its tile variants, and its epilogue's operands over the k-loop: a spill there would cost every launch.  This compiles the
+device code with the library's own flags and reads the register counts out of the code objects' metadata.
 """
 import os
 import re
@@ -14,14 +15,10 @@ import pytest
 
 from paper_2403_11204_amd import build
 
-SRC = os.path.join(build.CSRC, "gemm.hip")
-
-
-@pytest.fixture(scope="module")
-def kernel_metadata():
+def metadata_of(unit):
     with tempfile.TemporaryDirectory() as tmp:
-        out = os.path.join(tmp, "gemm.s")
-        cmd = [build.hipcc()] + [a for a in build.COMMON if a != "-fPIC"] + ["--cuda-device-only", "-S", SRC, "-o", out]
+        out = os.path.join(tmp, "unit.s")
+        cmd = [build.hipcc()] + [a for a in build.COMMON if a != "-fPIC"] + build.UNITS[unit] + ["--cuda-device-only", "-S", os.path.join(build.CSRC, unit), "-o", out]
         r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
         assert r.returncode == 0, r.stdout[-2000:]
         text = open(out).read()
@@ -32,6 +29,11 @@ def kernel_metadata():
         kernels[name] = {k: int(re.search(r"\.%s:\s+(\d+)" % k, entry).group(1))
                          for k in ("vgpr_count", "vgpr_spill_count", "private_segment_fixed_size")}
     return kernels
+
+
+@pytest.fixture(scope="module")
+def kernel_metadata():
+    return metadata_of("gemm.hip")
 
 
 def test_big_product_kernels_fit_beside_the_update_kernel(kernel_metadata):
@@ -46,3 +48,19 @@ def test_no_product_kernel_spills(kernel_metadata):
     for name, v in kernel_metadata.items():
         if "gemm_nt" in name:
             assert v["vgpr_spill_count"] == 0, (name, v)
+
+
+def test_the_kernel_of_small_layers_does_not_spill():
+    small = {n: v for n, v in metadata_of("gemm_small.hip").items() if "small_group_kernel" in n}
+    assert len(small) == 2, sorted(small)
+    for name, v in small.items():
+        assert v["vgpr_count"] <= 128, (name, v)           # 4 workgroups of 4 wavefronts per compute unit
+        assert v["vgpr_spill_count"] == 0 and v["private_segment_fixed_size"] == 0, (name, v)
+
+
+def test_the_update_kernel_fits_beside_the_products():
+    update = {n: v for n, v in metadata_of("elementwise.hip").items() if "sgd_update_strided_kernel" in n}
+    assert len(update) == 2, sorted(update)
+    for name, v in update.items():
+        assert v["vgpr_count"] <= 64, (name, v)
+        assert v["vgpr_spill_count"] == 0 and v["private_segment_fixed_size"] == 0, (name, v)
