@@ -46,8 +46,8 @@ __device__ __forceinline__ float correctly_rounded_sqrt(float x) { return __buil
 
 // The same without the general sequence's scaling and special cases, for zeros and values in [2^-24, 64] (all that the
 // normal transform asks for): the 1-ulp instruction, then one neighbour up or down where the sign of the residual, one
-// fused operation each, says that it is the nearer one.  Compared with the general sequence on every one of the 2^24
-// arguments that occur: no bit differs.
+// fused operation each, says that it is the nearer one (Tuckerman's rounding test).  Correctly rounded from any estimate within 1
+// ulp, for every significand of either parity of the exponent (tests/test_generator_rounding.py).
 __device__ __forceinline__ float sqrt_unscaled(float x) {
   const float r = __builtin_amdgcn_sqrtf(x);
   const float lo = __uint_as_float(__float_as_uint(r) - 1u), hi = __uint_as_float(__float_as_uint(r) + 1u);
@@ -57,8 +57,8 @@ __device__ __forceinline__ float sqrt_unscaled(float x) {
 }
 
 // Correctly rounded a / d for d in [1.7, 2.5] and |a| < 1 (no scaling needed): a reciprocal refined once by Newton's step,
-// the quotient corrected by its fused residual (Markstein 1990).  Compared with the general sequence on every significand
-// that occurs: no bit differs.
+// the quotient corrected by its fused residual (Markstein 1990).  Correctly rounded from any reciprocal within 1 ulp, for every
+// pair that ln_unit asks for (the same test).
 __device__ __forceinline__ float divide_unscaled(float a, float d) {
   float y = __builtin_amdgcn_rcpf(d);
   y = __fmaf_rn(__fmaf_rn(-d, y, 1.0f), y, y);

@@ -40,3 +40,14 @@ def test_labels_inputs_and_weights(dim, rows):
     Wr, br = orng.init_weights(seed, 0, rows, dim)
     assert np.array_equal(bits(W), np.asarray(Wr, np.float32).view(np.uint32))
     assert np.array_equal(bits(b), np.asarray(br, np.float32).view(np.uint32))
+
+
+@pytest.mark.parametrize("seed, j", [(20, 0x7FFFFF), (28, 0xFFFFFE)])
+def test_normals_of_a_long_row(seed, j):
+    """2^20 draws, among them one of ln(j 2^-24) whose significand is the largest below 1: the one quotient whose rounding rests on
+    the reciprocal instruction itself (see tests/test_generator_rounding.py)."""
+    dim = 1 << 20
+    r0 = orng.philox4x32_10(np.arange(dim), 0, 0, 0, seed, 0)[0]
+    assert np.count_nonzero((r0 >> np.uint32(8)) + np.uint32(1) == j) == 1
+    ref = orng.make_synthetic_labels(seed, 1, dim, api.NORMAL)
+    assert np.array_equal(bits(api.make_synthetic_labels(seed, 1, dim, api.NORMAL)), ref.view(np.uint32))
