@@ -213,6 +213,9 @@ int slp_segment_step_external(slp_segment* seg, const void* X /*device*/, const 
  * eager launches until this function is called again (copy each batch into one fixed buffer
  * and step on that to have a single combination).  Off by default. */
 int slp_segment_set_graph(slp_segment* seg, int on);
+/* What became of it: *captured = graphs the handle holds now, *replayed = steps it has taken by starting one, the step that
+ * captured it included (either pointer, host, may be NULL).  Errors: SLP_ERR_ARG (null handle). */
+int slp_segment_graph_stats(const slp_segment* seg, int* captured /*host*/, int64_t* replayed /*host*/);
 
 /* ---- optimiser step inside the weight-gradient product (Sec. 3: SGD with momentum) ----------------------
  * With the fused update on, the matrix product that forms dW_l applies v = mu v + dW; w = w - lr v to the tile of the

@@ -64,6 +64,7 @@ def lib():
         "slp_segment_step_external": (i32, [vp, vp, vp, i32, vp]),
         "slp_segment_profile_enable": (i32, [vp, i32]),
         "slp_segment_set_graph": (i32, [vp, i32]),
+        "slp_segment_graph_stats": (i32, [vp, ctypes.POINTER(i32), ctypes.POINTER(i64)]),
         "slp_segment_set_overlap": (i32, [vp, i32]),
         "slp_segment_set_fused_update": (i32, [vp, i32]),
         "slp_segment_target_errors": (i32, [vp, ctypes.POINTER(i64), vp]),
@@ -88,7 +89,8 @@ EXPORTS = ["slp_last_error", "slp_make_synthetic_labels", "slp_make_segment_inpu
            "slp_segment_step", "slp_segment_forward", "slp_segment_input_grad", "slp_segment_step_external",
            "slp_segment_profile_enable", "slp_segment_profile_read", "slp_probe_mfma_rate",
            "slp_segment_set_graph", "slp_segment_set_overlap", "slp_segment_join", "slp_count_correct", "slp_mean_loss",
-           "slp_count_correct_static", "slp_segment_set_fused_update", "slp_segment_target_errors"]
+           "slp_count_correct_static", "slp_segment_set_fused_update", "slp_segment_target_errors",
+           "slp_segment_graph_stats"]
 
 
 def _check(code):
@@ -277,6 +279,12 @@ class Segment:
     def set_graph(self, on=True):
         """slp_segment_set_graph: replay captured launch sequences of step() (for launch-bound segments)."""
         _check(lib().slp_segment_set_graph(self._h, int(bool(on))))
+
+    def graph_stats(self):
+        """slp_segment_graph_stats: (graphs held now, steps taken by starting one)."""
+        captured, replayed = ctypes.c_int(), ctypes.c_int64()
+        _check(lib().slp_segment_graph_stats(self._h, ctypes.byref(captured), ctypes.byref(replayed)))
+        return captured.value, replayed.value
 
     def set_overlap(self, on=True):
         """slp_segment_set_overlap: step() returns with the parameter updates still running beside the caller's next work."""

@@ -118,6 +118,7 @@ struct slp_segment {
   int graph_misses;                          // consecutive steps that found no captured graph
   std::vector<StepGraph> graphs;
   uint64_t graph_tick;
+  int64_t graph_steps;                       // steps taken by starting a graph
 };
 
 namespace {
@@ -653,7 +654,7 @@ int slp_segment_create(const int* widths, int n_widths, int act, int loss, const
   s->side = nullptr; s->ev_join = nullptr;
   s->defer_join = false; s->join_pending = false; s->fused_update = false; s->fused_max_params = 0;
   s->bound = false; s->have_params = false; s->table = nullptr; s->classes = 0; s->last_batch = 0; s->prof = false;
-  s->use_graph = false; s->graph_warm = false; s->graph_tick = 0; s->graph_misses = 0;
+  s->use_graph = false; s->graph_warm = false; s->graph_tick = 0; s->graph_misses = 0; s->graph_steps = 0;
   s->partials = nullptr; s->loss_dev = nullptr; s->bad_ids = nullptr;
   s->hurry = nullptr; s->paced = false;
   *out = s;
@@ -867,6 +868,7 @@ int slp_segment_step(slp_segment* seg, const void* X, const int32_t* targets, in
       g.used = seg->graph_tick;
       seg->graph_misses = 0;
       HIP_TRY(hipGraphLaunch(g.exec, st));
+      ++seg->graph_steps;
       return SLP_OK;
     }
   ++seg->graph_misses;
@@ -893,6 +895,7 @@ int slp_segment_step(slp_segment* seg, const void* X, const int32_t* targets, in
     seg->graphs.push_back(sg);
   }
   HIP_TRY(hipGraphLaunch(sg.exec, st));
+  ++seg->graph_steps;
   return SLP_OK;
 }
 
@@ -915,6 +918,14 @@ int slp_segment_set_graph(slp_segment* seg, int on) {
   seg->use_graph = on != 0;
   seg->graph_misses = 0;
   if (!seg->use_graph) drop_graphs(seg);
+  return SLP_OK;
+}
+
+int slp_segment_graph_stats(const slp_segment* seg, int* captured, int64_t* replayed) {
+  int rc = check_seg(seg, false, false);
+  if (rc) return rc;
+  if (captured) *captured = (int)seg->graphs.size();
+  if (replayed) *replayed = seg->graph_steps;
   return SLP_OK;
 }
 

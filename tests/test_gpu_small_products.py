@@ -211,6 +211,7 @@ def test_replayed_steps_of_more_launches_than_go_one_by_one(dtype, loss):
             seen = []
             for it in range(7):
                 seen.append(seg.step(Xs[it % 2], ys[it % 2]).clone())
+                assert seg.graph_stats()[1] == (it if graph else 0)          # all but the first
                 if it in (3, 6):                      # reads between replays
                     seen += [t.clone() for l in range(seg.L) for t in seg.get_params(l) + seg.get_momentum(l)]
             stream.synchronize()
