@@ -41,19 +41,21 @@ def _batches(n, batch):
 def train_epochs(seg, X, y, epochs, batch, staged=False):
     """Consecutive, unshuffled batches for `epochs` passes.  Returns the mean loss of each epoch.
 
-    staged: copy every batch into one fixed pair of buffers and step on those, so that a handle with graph
-    replay on (Segment.set_graph) sees a single argument combination per batch size and replays one graph."""
+    staged: copy every batch into one fixed pair of buffers and step on those, with one fixed scalar for the loss, so that a
+    handle with graph replay on (Segment.set_graph) sees a single argument combination per batch size and replays one graph."""
     n = X.shape[0]
     losses = torch.zeros((epochs, (n + batch - 1) // batch), dtype=torch.float32, device=X.device)
     if staged:
         Xs = torch.empty((batch, X.shape[1]), dtype=X.dtype, device=X.device)
         ys = torch.empty(batch, dtype=y.dtype, device=y.device)
+        slot = torch.empty(1, dtype=torch.float32, device=X.device)
     for ep in range(epochs):
         for i, (a, b) in enumerate(_batches(n, batch)):
             if staged:
                 Xs[:b - a].copy_(X[a:b])
                 ys[:b - a].copy_(y[a:b])
-                seg.step(Xs[:b - a], ys[:b - a], loss_out=losses[ep, i:i + 1])
+                seg.step(Xs[:b - a], ys[:b - a], loss_out=slot)
+                losses[ep, i:i + 1].copy_(slot)
             else:
                 seg.step(X[a:b], y[a:b], loss_out=losses[ep, i:i + 1])
     return _epoch_means(losses)

@@ -153,11 +153,14 @@ def test_staged_epochs_replay_one_graph_and_match_eager_epochs(hidden):
         lg = pipeline.train_epochs(graph, Xd, yd, epochs=2, batch=B, staged=True)
         assert le == lg
         assert same_state(eager, graph)
+        staged = graph.graph_stats()                       # one graph for the full batches, one for the ragged one
+        assert staged == ((2, 2 * 41 - 1) if len(hidden) > 1 else (0, 0))
         # unstaged with graphs on: every batch is a new combination; the handle must fall back to eager launches
         le = pipeline.train_epochs(eager, Xd, yd, epochs=1, batch=B)
         lg = pipeline.train_epochs(graph, Xd, yd, epochs=1, batch=B)
         assert le == lg
         assert same_state(eager, graph)
+        assert graph.graph_stats() == ((16, staged[1] + 33) if len(hidden) > 1 else (0, 0))
     torch.cuda.synchronize()
 
 
