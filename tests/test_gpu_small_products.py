@@ -187,6 +187,53 @@ def test_cross_entropy_gradient_and_its_transpose(B, C, dtype):
     assert float((seg.get_grads(0)[0].cpu().double() - P.t() @ X.double()).abs().max()) <= TOL[dtype] * scale * math.sqrt(B) + 1e-6
 
 
+@pytest.mark.parametrize("relu", [api.RELU_ALL, api.RELU_HIDDEN_IDENTITY_LAST])
+@pytest.mark.parametrize("external", [False, True])
+@pytest.mark.parametrize("dtype", [api.F32, api.BF16])
+@pytest.mark.parametrize("B,N", [(5, 3), (37, 61), (64, 64), (333, 513), (330, 512), (1000, 777), (1001, 776)])
+def test_gradient_of_the_output_formed_by_the_last_product(B, N, dtype, external, relu):
+    """Squared error against the label table or the caller's gradient, in the epilogue of a small last layer: tile 16 (up to 64 x
+    64), 32 (333 x 513) and 64 (1000 x 777), widths that divide into quads of columns and that do not, batches that leave padded
+    columns in the transpose; then a shorter batch on the same buffers.  The gradient is checked against the stored
+    activations, and its transpose by what reads it: the bias gradient and the weight gradient."""
+    g = torch.Generator().manual_seed(B * 1000 + N)
+    tdt = torch.float32 if dtype == api.F32 else torch.bfloat16
+    K, classes = 24, 7
+    seg = api.Segment([K, N], relu, api.MSE_SIL, max_batch=B + 2, dtype=dtype, lr=0.0, momentum=0.0)
+    seg.set_params(0, (torch.randn(N, K, generator=g) / math.sqrt(K)).cuda(), torch.randn(N, generator=g).cuda())
+    table = torch.rand(classes, N, generator=g).cuda()
+    seg.set_labels(table)
+    bad = 0
+    for rows in (B, max(1, B - 6)):
+        X = torch.rand(rows, K, generator=g).to(tdt).cuda()
+        if external:
+            dA = torch.randn(rows, N, generator=g).to(tdt).cuda()
+            seg.step_external(X, dA)
+        else:
+            y = torch.randint(0, classes, (rows,), generator=g, dtype=torch.int32)
+            y[0], y[rows // 2], y[-1] = classes, -3, 1 << 30             # clamped, and their rows counted once each
+            bad += len({0, rows // 2, rows - 1})
+            loss = float(seg.step(X, y.cuda()))
+            assert seg.target_errors() == bad
+        A, dZ = seg.get_activation(1, rows), seg.get_activation(1, rows, kind=1)
+        live = (A > 0) if relu == api.RELU_ALL else torch.ones_like(A, dtype=torch.bool)
+        if external:
+            assert torch.equal(dZ, torch.where(live, dA, torch.zeros_like(dA)))
+        else:
+            diff = A.double() - table.double()[y.clamp(0, classes - 1).long().cuda()]
+            mse = float(diff.square().mean())
+            assert abs(loss - mse) <= 1e-5 * mse
+            ref = torch.where(live, diff * (2.0 / (rows * N)), torch.zeros_like(diff))
+            # three float32 roundings, the difference's relative to its terms; bf16 storage: 2^-9 of each element
+            err, step = (dZ.double() - ref).abs(), 2.0 ** -22 * 2.0 / (rows * N) * (A.double().abs() + 1.0)
+            assert bool((err <= step + (2.0 ** -8 * ref.abs() if dtype == api.BF16 else 0.0)).all())
+        # float32 sums of at most 1000 terms: within 1000 2^-24 = 6e-5 of the sum of absolute values, 1e-5 as they are added here
+        d = dZ.double()
+        assert bool(((seg.get_bias_grad(0).double() - d.sum(0)).abs() <= 1e-5 * d.abs().sum(0) + 1e-30).all())
+        dW, bound = d.t() @ X.double(), d.abs().t() @ X.double().abs()
+        assert bool(((seg.get_grads(0)[0].double() - dW).abs() <= 1e-5 * bound + 1e-30).all())
+
+
 @pytest.mark.parametrize("loss", [api.MSE_SIL, api.SOFTMAX_XENT])
 @pytest.mark.parametrize("dtype", [api.F32, api.BF16])
 def test_replayed_steps_of_more_launches_than_go_one_by_one(dtype, loss):
