@@ -93,7 +93,7 @@ def build_segments(cfg, n_batches, only=None):
             continue
         seg = api.Segment(widths, act, loss, max_batch=B, dtype=dt, lr=cfg["lr"], momentum=cfg["mom"])
         seg.init(100 + si)
-        if cfg.get("graph"):        # launch-bound sizes: replay the captured launch sequence of a step
+        if cfg.get("graph"):        # launch-bound sizes: replay the captured launch sequence of a step where it is long
             seg.set_graph(True)
         if cfg.get("fused"):        # optimiser step inside the weight-gradient products (pays on short products)
             seg.set_fused_update(cfg["fused"])
@@ -274,6 +274,14 @@ def pipeline_phases(cfg, reps=5):
     return out
 
 
+def launch_mode(segs):
+    """How the steps timed so far were launched: a handle with graphs on replays a step, or launches its few kernels one by one."""
+    replayed = [seg.graph_stats()[1] > 0 for seg in segs]
+    if all(replayed):
+        return "hip graph replay"
+    return "hip graph replay (%d of %d segments), one by one" % (sum(replayed), len(segs)) if any(replayed) else "eager"
+
+
 def quick_config(cid, steps, warmup):
     """ms per step, TFLOP/s and fractions of another configuration, measured the same way as the main workload."""
     cfg = dict(CONFIGS[cid])
@@ -297,7 +305,7 @@ def quick_config(cid, steps, warmup):
            "step_tflops": flops_step / (ms * 1e-3) / 1e12, "step_frac_of_mfma_peak": flops_step / (ms * 1e-3) / 1e12 / peak,
            # launch-by-launch events overlap when the segments run concurrently: no per-kernel rate then
            "gemm_tflops": gemm_fl / (gemm_ms * 1e-3) / 1e12 if gemm_ms > 0 and (cfg.get("graph") or not cfg["streams"]) else None,
-           "launch": "hip graph replay" if cfg.get("graph") else "eager", "fused_update": cfg.get("fused", 0),
+           "launch": launch_mode(segs), "fused_update": cfg.get("fused", 0),
            "concurrent_streams": len(segs) if cfg["streams"] else 1,
            # the other roof: every parameter streams through the step once per product that reads it and through the
            # update (24 B with momentum in bf16 mode: g, v, w read; v, w, bf16 copy, transposed copy written)
@@ -403,7 +411,7 @@ def main():
         "config": {"workload": cfg["name"], "global_batch": B, "classes": cfg["classes"],
                    "segments": [s[0] for s in cfg["segs"]], "optimizer": "sgd lr %g momentum %g" % (cfg["lr"], cfg["mom"]),
                    "concurrent_streams": len(segs) if cfg["streams"] else 1,
-                   "launch": "hip graph replay" if cfg.get("graph") and not args.eager else "eager",
+                   "launch": launch_mode(segs),
                    "update_overlap": bool(cfg["overlap"]), "fused_update": cfg.get("fused", 0)},
         "step_tflops": flops_step / (ms * 1e-3) / 1e12,
         "step_frac_of_mfma_peak": flops_step / (ms * 1e-3) / 1e12 / peak,
