@@ -331,8 +331,8 @@ __global__ __launch_bounds__(256) void refresh_copies_kernel(float* __restrict__
 // update's tail must still find products to hide behind, which is why the caller sizes the pause by the batch).
 // hurry: a flag that is raised on a stream that comes to wait for the update (hurry_kernel): from the next tile on nothing sleeps
 // any more, what that stream ran beside the update is over.  (A second stream of the caller's may still have products in
-// flight; they then share the chip with an update that does not pause.)  The flag's load is issued before the tile
-// and read after it.  A segment of 784-16384-16384-16384 stepped on its own waited 2.4 ms for the paced update of its second
+// flight; they then share the chip with an update that does not pause.)  Only a
+// launch that pauses reads the flag, once a tile.  A segment of 784-16384-16384-16384 stepped on its own waited 2.4 ms for the paced update of its second
 // layer, 1.3 without the pauses.
 template <typename T>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8))) void sgd_update_strided_kernel(float* __restrict__ W32, float* __restrict__ vW,

@@ -439,7 +439,7 @@ hipError_t configure() {
 
 }  // namespace
 
-// Tile for a product: 64 from 128 64x64 tiles on (fewer leave half of the compute units idle; also where float32's order of
+// Tile for a product: 64 from 128 64x64 tiles on (fewer leave half of the compute units idle; also where the order of
 // summation changes from four partial sums to one, so the line stays); else 16 while there are few of them, 32 otherwise.
 // Microseconds per launch behind another, tiles 16 / 32, in brackets the kernels this one replaced (32x32 with the contraction
 // split and operands loaded by the quad in the epilogue; 64x64):
