@@ -234,6 +234,36 @@ def test_gradient_of_the_output_formed_by_the_last_product(B, N, dtype, external
         assert bool(((seg.get_grads(0)[0].double() - dW).abs() <= 1e-5 * bound + 1e-30).all())
 
 
+@pytest.mark.parametrize("dtype", [api.F32, api.BF16])
+@pytest.mark.parametrize("B,w", [(3, 5), (37, 61), (64, 64), (333, 513), (1000, 777), (1001, 776)])
+def test_data_gradients_that_nothing_rides_along_with(B, w, dtype):
+    """The last layer's in a step from a given gradient (masked, both layouts) and the first layer's of an input gradient (the caller's
+    dense matrix), on tiles 16, 32 and 64, against float64 products of the stored factors."""
+    g = torch.Generator().manual_seed(B + w)
+    tdt = torch.float32 if dtype == api.F32 else torch.bfloat16
+    N = 50
+    X, dA = torch.rand(B, w, generator=g).to(tdt).cuda(), torch.randn(B, N, generator=g).to(tdt).cuda()
+    y = torch.randint(0, N, (B,), generator=g, dtype=torch.int32).cuda()
+    seg = api.Segment([w, w, N], api.RELU_HIDDEN_IDENTITY_LAST, api.SOFTMAX_XENT, max_batch=B, dtype=dtype, lr=0.0, momentum=0.0, input_grad=True)
+    for l, (n, k) in enumerate(((w, w), (N, w))):
+        seg.set_params(l, (torch.randn(n, k, generator=g) / math.sqrt(k)).cuda(), torch.randn(n, generator=g).cuda())
+    Wop = [seg.get_params(l)[0].to(tdt).double() for l in (0, 1)]
+
+    def check(got, left, right, live):
+        # float32 sums of up to 777 terms, 1e-5 of the absolute values as they are added; bf16 storage: 2^-9 of each element
+        ref, bound = torch.where(live, left @ right, torch.zeros_like(got, dtype=torch.float64)), left.abs() @ right.abs()
+        err = (got.double() - ref).abs()
+        assert bool((err <= 1e-5 * bound + (2.0 ** -8 * ref.abs() if dtype == api.BF16 else 0.0)).all())
+
+    seg.step_external(X, dA)
+    A1, dZ1 = seg.get_activation(1, B), seg.get_activation(1, B, kind=1)
+    check(dZ1, dA.double(), Wop[1], A1 > 0)
+    d = dZ1.double()                                  # the transpose, by what reads it
+    assert bool(((seg.get_bias_grad(0).double() - d.sum(0)).abs() <= 1e-5 * d.abs().sum(0) + 1e-30).all())
+    dX, _ = seg.input_grad(X, y)
+    check(dX, seg.get_activation(1, B, kind=1).double(), Wop[0], torch.ones_like(dX, dtype=torch.bool))
+
+
 @pytest.mark.parametrize("loss", [api.MSE_SIL, api.SOFTMAX_XENT])
 @pytest.mark.parametrize("dtype", [api.F32, api.BF16])
 def test_replayed_steps_of_more_launches_than_go_one_by_one(dtype, loss):

@@ -50,9 +50,9 @@ def test_no_product_kernel_spills(kernel_metadata):
             assert v["vgpr_spill_count"] == 0, (name, v)
 
 
-def test_the_kernel_of_small_layers_does_not_spill():
-    small = {n: v for n, v in metadata_of("gemm_small.hip").items() if "small_group_kernel" in n}
-    assert len(small) == 2, sorted(small)
+def test_the_kernels_of_small_layers_do_not_spill():
+    small = metadata_of("gemm_small.hip")
+    assert sum("small_group_kernel" in n for n in small) == 2 and sum("small_product_kernel" in n for n in small) == 12, sorted(small)
     for name, v in small.items():
         assert v["vgpr_count"] <= 128, (name, v)           # 4 workgroups of 4 wavefronts per compute unit
         assert v["vgpr_spill_count"] == 0 and v["private_segment_fixed_size"] == 0, (name, v)
