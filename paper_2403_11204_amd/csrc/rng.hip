@@ -130,23 +130,34 @@ __device__ __forceinline__ void store_value(__bf16* out, size_t idx, float v) { 
 // not by the bytes it writes.  A wavefront therefore takes a run of kRun columns of ONE row, column by column across its
 // lanes: the row's index is uniform over the wavefront, so the division that finds it and every part of the counter
 // arithmetic that depends on the row and the key only is done once per run on the scalar unit, and the stores are
-// coalesced whatever the alignment of a row.  Rows of up to 32 columns share a wavefront (2^lanes_log2 lanes each).
-// fn(row, column) is called for every element, whole runs without a test per column.
+// coalesced whatever the alignment of a row.  fn(row, column) is called for every element, whole runs without a test per column.
 // 8192 x 16384 bf16 inputs and their 1000 x 16384 table, both calls: one element per lane with a 64-bit division each, the
 // general division and square root and separate halves of the products 564 us -> 330 us; the inputs' ~90 instructions an
 // element are issued at the rate of the vector units.  Unrolled by 4: by 2 +5 %, by 8 the same.
-constexpr int kRun = 512;
+// Rows of up to kFlat columns leave too many lanes without one and pay for the row too often: there a wavefront takes kFlat elements
+// as they lie, over the rows' ends; one division on the scalar unit for the first, by 2^32 / cols for the others.  200000 rows of
+// float32 inputs, microseconds, one element per lane as before / a run per row (up to 32 columns several rows per wavefront) / this:
+// 17 columns 19.5 / 23.9 / 14.9, 33 33.3 / 50.2 / 25.0, 47 45.6 / 51.5 / 32.9, 60 57 / 51 / 40, 65 61 / 72 / 43, 72 67 / 73 / 47;
+// 300 232 / 157 / 178.
+constexpr int kRun = 512, kFlat = 256;
 template <typename F>
-__device__ __forceinline__ void for_each_element(uint32_t rows, uint32_t cols, int lanes_log2, F fn) {
-  const int lane = threadIdx.x & 63;
+__device__ __forceinline__ void for_each_element(uint32_t rows, uint32_t cols, uint32_t reciprocal, F fn) {
+  const uint32_t lane = threadIdx.x & 63;
   const uint64_t waves = (uint64_t)gridDim.x * 4;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  if (lanes_log2 < 6) {
-    const uint32_t per = 64u >> lanes_log2;
-    for (uint64_t u = (uint64_t)blockIdx.x * 4 + wave; u * per < rows; u += waves) {
-      const uint64_t r = u * per + (lane >> lanes_log2);
-      const uint32_t c = lane & ((1 << lanes_log2) - 1);
-      if (r < rows && c < cols) fn((uint32_t)r, c);
+  if (reciprocal) {
+    const uint64_t total = (uint64_t)rows * cols;
+    for (uint64_t u = (uint64_t)blockIdx.x * 4 + wave; u * kFlat < total; u += waves) {
+      const uint64_t first = u * kFlat, left = total - first;
+      const uint32_t r0 = total >> 32 ? (uint32_t)(first / cols) : (uint32_t)first / cols, c0 = (uint32_t)(first - (uint64_t)r0 * cols);
+#pragma unroll
+      for (uint32_t j = 0; j < kFlat; j += 64)
+        if (j + lane < left) {
+          const uint32_t e = c0 + j + lane;                     // below cols + kFlat: the quotient is at most one too small
+          uint32_t q = __umulhi(e, reciprocal), c = e - q * cols;
+          if (c >= cols) { ++q; c -= cols; }
+          fn(r0 + q, c);
+        }
     }
     return;
   }
@@ -165,8 +176,8 @@ __device__ __forceinline__ void for_each_element(uint32_t rows, uint32_t cols, i
 
 template <typename T, int DIST>
 __global__ __launch_bounds__(256) void labels_kernel(uint32_t k0, uint32_t k1, int classes, int dim, float kappa, T* __restrict__ out,
-                                                     int lanes_log2) {
-  for_each_element(classes, dim, lanes_log2, [&](uint32_t j, uint32_t i) {
+                                                     uint32_t reciprocal) {
+  for_each_element(classes, dim, reciprocal, [&](uint32_t j, uint32_t i) {
     store_value(out, (size_t)j * dim + i, draw<DIST>(kappa, philox4x32_10(i, j, 0u, 0u, k0, k1)));
   });
 }
@@ -174,8 +185,8 @@ __global__ __launch_bounds__(256) void labels_kernel(uint32_t k0, uint32_t k1, i
 template <typename T>
 __global__ __launch_bounds__(256) void inputs_kernel(uint32_t k0, uint32_t k1, const float* __restrict__ table, int classes,
                                                      const int32_t* __restrict__ y, uint64_t first, int batch, int dim, float sigma,
-                                                     T* __restrict__ out, int lanes_log2) {
-  for_each_element(batch, dim, lanes_log2, [&](uint32_t row, uint32_t i) {
+                                                     T* __restrict__ out, uint32_t reciprocal) {
+  for_each_element(batch, dim, reciprocal, [&](uint32_t row, uint32_t i) {
     const uint64_t n = first + row;
     const Words w = philox4x32_10(i, (uint32_t)n, 2u, (uint32_t)(n >> 32), k0, k1);
     const float z = standard_normal(w.r0, w.r1);
@@ -186,9 +197,9 @@ __global__ __launch_bounds__(256) void inputs_kernel(uint32_t k0, uint32_t k1, c
 }
 
 __global__ __launch_bounds__(256) void init_kernel(uint32_t k0, uint32_t k1, uint32_t layer, float* __restrict__ W, int N, int K,
-                                                   int ldk, float* __restrict__ b, int lanes_log2) {
+                                                   int ldk, float* __restrict__ b, uint32_t reciprocal) {
   const float bound = __fdiv_rn(1.0f, correctly_rounded_sqrt((float)K));
-  for_each_element(N, (uint32_t)K + 1, lanes_log2, [&](uint32_t o, uint32_t k) {
+  for_each_element(N, (uint32_t)K + 1, reciprocal, [&](uint32_t o, uint32_t k) {
     const Words w = philox4x32_10(k, o, 1u, layer, k0, k1);
     const float v = __fmul_rn(__fsub_rn(__fmul_rn(2.0f, unit_uniform(w.r0)), 1.0f), bound);
     if ((int)k < K) W[(size_t)o * ldk + k] = v;
@@ -196,28 +207,25 @@ __global__ __launch_bounds__(256) void init_kernel(uint32_t k0, uint32_t k1, uin
   });
 }
 
-// lanes of a wavefront that one row of `cols` elements gets, as a power of two
-inline int lanes_log2_for(size_t cols) {
-  int l = 0;
-  while (l < 6 && ((size_t)1 << l) < cols) ++l;
-  return l;
-}
+// 2^32 / cols, rounded down, for rows of up to kFlat columns; 0 for others
+inline uint32_t reciprocal_for(size_t cols) { return cols <= (size_t)kFlat ? (uint32_t)(0xFFFFFFFFu / cols) : 0u; }
 // blocks of 4 wavefronts; above 2^18 of them the kernels loop
-inline int grid_for(size_t rows, size_t cols, int lanes_log2) {
-  const size_t units = lanes_log2 < 6 ? (rows + (64u >> lanes_log2) - 1) / (64u >> lanes_log2) : rows * ((cols + kRun - 1) / kRun);
+inline int grid_for(size_t rows, size_t cols, uint32_t reciprocal) {
+  const size_t units = reciprocal ? (rows * cols + kFlat - 1) / kFlat : rows * ((cols + kRun - 1) / kRun);
   const size_t blocks = (units + 3) / 4;
   return (int)(blocks < 1 ? 1 : (blocks > (1u << 18) ? (1u << 18) : blocks));
 }
 
 template <typename T>
 void launch_labels(uint64_t seed, int classes, int dim, int dist, float kappa, T* out, hipStream_t s) {
-  const int ll = lanes_log2_for(dim), grid = grid_for(classes, dim, ll);
+  const uint32_t rc = reciprocal_for(dim);
+  const int grid = grid_for(classes, dim, rc);
   const uint32_t k0 = (uint32_t)seed, k1 = (uint32_t)(seed >> 32);
   switch (dist) {
-    case 0: labels_kernel<T, 0><<<grid, 256, 0, s>>>(k0, k1, classes, dim, kappa, out, ll); break;
-    case 1: labels_kernel<T, 1><<<grid, 256, 0, s>>>(k0, k1, classes, dim, kappa, out, ll); break;
-    case 2: labels_kernel<T, 2><<<grid, 256, 0, s>>>(k0, k1, classes, dim, kappa, out, ll); break;
-    default: labels_kernel<T, 3><<<grid, 256, 0, s>>>(k0, k1, classes, dim, kappa, out, ll); break;
+    case 0: labels_kernel<T, 0><<<grid, 256, 0, s>>>(k0, k1, classes, dim, kappa, out, rc); break;
+    case 1: labels_kernel<T, 1><<<grid, 256, 0, s>>>(k0, k1, classes, dim, kappa, out, rc); break;
+    case 2: labels_kernel<T, 2><<<grid, 256, 0, s>>>(k0, k1, classes, dim, kappa, out, rc); break;
+    default: labels_kernel<T, 3><<<grid, 256, 0, s>>>(k0, k1, classes, dim, kappa, out, rc); break;
   }
 }
 
@@ -232,19 +240,20 @@ hipError_t launch_make_labels(uint64_t seed, int classes, int dim, int dist, flo
 
 hipError_t launch_make_inputs(uint64_t seed, const float* table, int classes, const int32_t* y, int64_t first_sample,
                               int batch, int dim, float sigma, void* out, int dt, hipStream_t s) {
-  const int ll = lanes_log2_for(dim), grid = grid_for(batch, dim, ll);
+  const uint32_t rc = reciprocal_for(dim);
+  const int grid = grid_for(batch, dim, rc);
   const uint32_t k0 = (uint32_t)seed, k1 = (uint32_t)(seed >> 32);
   if (dt == 1)
-    inputs_kernel<<<grid, 256, 0, s>>>(k0, k1, table, classes, y, (uint64_t)first_sample, batch, dim, sigma, (__bf16*)out, ll);
+    inputs_kernel<<<grid, 256, 0, s>>>(k0, k1, table, classes, y, (uint64_t)first_sample, batch, dim, sigma, (__bf16*)out, rc);
   else
-    inputs_kernel<<<grid, 256, 0, s>>>(k0, k1, table, classes, y, (uint64_t)first_sample, batch, dim, sigma, (float*)out, ll);
+    inputs_kernel<<<grid, 256, 0, s>>>(k0, k1, table, classes, y, (uint64_t)first_sample, batch, dim, sigma, (float*)out, rc);
   return hipGetLastError();
 }
 
 hipError_t launch_init_weights(uint64_t seed, int layer, float* W32, int N, int K, int ldk, float* b, hipStream_t s) {
-  const int ll = lanes_log2_for((size_t)K + 1);
-  init_kernel<<<grid_for(N, (size_t)K + 1, ll), 256, 0, s>>>((uint32_t)seed, (uint32_t)(seed >> 32), (uint32_t)layer, W32, N, K, ldk,
-                                                             b, ll);
+  const uint32_t rc = reciprocal_for((size_t)K + 1);
+  init_kernel<<<grid_for(N, (size_t)K + 1, rc), 256, 0, s>>>((uint32_t)seed, (uint32_t)(seed >> 32), (uint32_t)layer, W32, N, K, ldk,
+                                                             b, rc);
   return hipGetLastError();
 }
 

@@ -1,7 +1,7 @@
 """Generator kernels at the widths where their split into wavefront runs can go wrong, bit for bit against the oracle.
 
-A wavefront takes runs of 512 columns of one row, rows of at most 32 columns share one: the widths sit on and beside
-those edges, the row counts beside a wavefront's share of short rows."""
+A wavefront takes runs of 512 columns of one row, or 256 elements over the rows' ends where rows have at most 256 columns: the
+widths sit on and beside those edges, the row counts leave a last wavefront partly filled."""
 
 import numpy as np
 import pytest
@@ -17,7 +17,7 @@ def bits(t):
     return t.to(torch.float32).cpu().numpy().view(np.uint32)
 
 
-@pytest.mark.parametrize("dim", [1, 2, 31, 32, 33, 63, 65, 511, 512, 513, 1100])
+@pytest.mark.parametrize("dim", [1, 2, 31, 32, 33, 63, 65, 255, 256, 257, 511, 512, 513, 1100])
 @pytest.mark.parametrize("rows", [1, 5, 67])
 def test_labels_inputs_and_weights(dim, rows):
     seed = (9 << 32) | (dim * 1000 + rows)
