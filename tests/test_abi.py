@@ -62,6 +62,17 @@ def test_create_rejects_bad_arguments():
     assert _create([64, 64], max_batch=1 << 24)[0] == -2              # an activation matrix of 4 GiB
 
 
+def test_graph_stats_of_a_new_handle():
+    L = api.lib()
+    n, steps = ctypes.c_int(-1), ctypes.c_int64(-1)
+    assert L.slp_segment_graph_stats(None, ctypes.byref(n), ctypes.byref(steps)) == -1
+    rc, h = _create([8, 4])
+    assert rc == 0
+    assert L.slp_segment_graph_stats(h, ctypes.byref(n), ctypes.byref(steps)) == 0 and (n.value, steps.value) == (0, 0)
+    assert L.slp_segment_graph_stats(h, None, None) == 0
+    L.slp_segment_destroy(h)
+
+
 def test_sizes_and_state_errors_without_device():
     L = api.lib()
     rc, h = _create([784, 80, 60], max_batch=1410)
