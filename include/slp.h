@@ -224,8 +224,8 @@ int slp_segment_graph_stats(const slp_segment* seg, int* captured /*host*/, int6
  * segment ends with its last product instead of a tail of update launches.  It pays where a layer's products are short; for very wide layers the separate
  * update, which streams beside the next products, is faster.  on = 0: off (default); 1: every layer; 2: the layers
  * where it measured faster, those with at most 4,194,304 weights; on > 2: the layers with at most `on` weights.
- * Layers with fewer than 224 tiles of 128x128 weights take the update inside the product in any case, off or on; off, the
- * gradient is stored beside it.
+ * Layers with fewer than 224 tiles of 128x128 weights take the update inside the product in any case, off or on, and so do
+ * larger ones at batches up to 2048 (float32 4096; with overlap on below 1400, float32 640); off, the gradient is stored beside it.
  * Results equal the separate update's to float32 rounding (the same expressions on the same values).  For a layer
  * that is fused, slp_segment_get_grads returns the bias gradient only (a request for dW fails with SLP_ERR_STATE).
  * Drops captured graphs.  Errors: SLP_ERR_ARG (null handle, on < 0). */
@@ -235,8 +235,8 @@ int slp_segment_set_fused_update(slp_segment* seg, int on);
  * The last thing a step does is stream every parameter once (the SGD update); where that is faster it runs on a stream of
  * the handle beside the matrix products that are still to come, and the step normally ends by making `stream` wait for it.
  * With overlap on, slp_segment_step (and slp_segment_step_external) returns without that wait, and the update of
- * the first layer moves to the side stream too (but for layers whose update is part of their weight-gradient product, see
- * slp_segment_set_fused_update: nothing of them is left pending): whatever the caller enqueues next on `stream` -- typically the
+ * the first layer moves to the side stream too, at short batches with the product it is part of (but not for layers of fewer than 224
+ * tiles of 128x128 weights and those that slp_segment_set_fused_update names: nothing of them is left pending): whatever the caller enqueues next on `stream` -- typically the
  * step of another segment -- runs beside the tail of this one.  Until the handle's next step, every call on the
  * handle that takes a stream first makes that stream wait for the pending updates (whichever stream it is), so calls
  * through this interface see the same values as without overlap (bit for bit).  A caller that reads or frees the

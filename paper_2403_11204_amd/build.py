@@ -32,6 +32,7 @@ UNITS = {
     "elementwise.hip": [],
     "gemm.hip": [],
     "gemm_small.hip": [],
+    "gemm_pair.hip": [],
     "probe.hip": [],
     "accuracy.hip": [],
 }
@@ -74,7 +75,7 @@ def build_tools(verbose=True):
     """Development tools beside the library: the stand-alone matrix-product timer (csrc/gemm_bench.hip)."""
     os.makedirs(BUILD, exist_ok=True)
     out = os.path.join(BUILD, "gemm_bench")
-    cmd = [hipcc()] + [a for a in COMMON if a != "-fPIC"] + [os.path.join(CSRC, f) for f in ("gemm_bench.hip", "gemm_small.hip")] + ["-o", out]
+    cmd = [hipcc()] + [a for a in COMMON if a != "-fPIC"] + [os.path.join(CSRC, f) for f in ("gemm_bench.hip", "gemm_small.hip", "gemm_pair.hip")] + ["-o", out]
     if verbose:
         print(" ".join(cmd), flush=True)
     r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)

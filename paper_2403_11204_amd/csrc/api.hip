@@ -98,7 +98,7 @@ struct slp_segment {
   std::vector<ProfRec> prof_log;
   std::vector<hipEvent_t> ev_pool;
   // The parameter update of layer l is memory-bound and independent of the matrix products of the
-  // layers below it, so where that pays (see updates_beside) it runs on a side stream next to
+  // layers below it, so where it is not part of its own product's launch (see update_in_product) it runs on a side stream next to
   // them (fork after the weight gradient of layer l, join at the end of the step: the caller's stream still orders
   // everything).
   hipStream_t side;
@@ -161,7 +161,7 @@ int run_gemm(slp_segment* s, int epi, const GemmArgs& g, hipStream_t st) {
 }
 
 // The same for a launch of small layers; the time of what rides along in it counts as the products'.
-int run_group(slp_segment* s, const SmallGroup& gr, hipStream_t st) {
+int run_group(slp_segment* s, const SmallGroup& gr, hipStream_t st, bool small = true) {
   ProfRec rec{nullptr, nullptr, 0.0};
   for (int p = 0; p < gr.n; ++p) rec.flops += 2.0 * gr.g[p].M * (double)gr.g[p].N * gr.g[p].K;
   if (s->prof) {
@@ -170,7 +170,7 @@ int run_group(slp_segment* s, const SmallGroup& gr, hipStream_t st) {
     if (!rec.a || !rec.b) return fail(SLP_ERR_DEVICE, "hipEventCreate failed");
     HIP_TRY(hipEventRecord(rec.a, st));
   }
-  HIP_TRY(launch_small_group(s->dtype, gr, st));
+  HIP_TRY(small ? launch_small_group(s->dtype, gr, st) : launch_pair(s->dtype, gr, st));
   if (s->prof) {
     HIP_TRY(hipEventRecord(rec.b, st));
     s->prof_log.push_back(rec);
@@ -308,44 +308,22 @@ GemmArgs data_gradient(slp_segment* seg, int l, int batch) {
 // Whether the caller asked for the optimiser step of this layer inside its weight-gradient product.
 bool update_is_fused(const slp_segment* s, const Layer& ly) { return s->fused_update && (long)ly.N * ly.K <= s->fused_max_params; }
 
-// Whether the separate updates of a step without a deferred join run on the side stream, beside the products still to come.
-// There they pay for the fork and the join, some 35 us, and for what the two cost each other; in the caller's stream they follow
-// their product at full width.  Microseconds a step, beside / in the caller's stream:
-//   bf16, three equal layers   4096 wide, 256 rows 408 / 344, 600 497 / 464, 1024 576 / 528, 1200 644 / 651, 1400 656 / 660,
-//                              4096 990 / 1004; 6144 wide, 1024 1291 / 1286, 1300 1595 / 1577; 8192 wide, 256 1544 / 1339, 1024
-//                              2152 / 2017, 1280 2660 / 2587, 1400 2680 / 2607, 2048 2394 / 2412, 8192 6624 / 6835; 9216 wide,
-//                              512 2469 / 2377, 1024 3112 / 3215; 10240 wide, 128 2311 / 2164, 512 2822 / 2801, 1024 3653 / 3789,
-//                              1300 3149 / 3256; 12288 wide, 512 3893 / 4061, 1024 4915 / 5270; 16384 wide, 64 5359 / 5397,
-//                              256 5755 / 5869, 512 6518 / 6821, 1024 7388 / 7541, 1300 8641 / 9013
-//   two                        8192 wide, 512 1137 / 973, 1024 1425 / 1271; 12288 wide, 128 2111 / 2036, 512 2639 / 2598, 1024
-//                              3337 / 3340; 16384 wide, 512 4387 / 4411, 1024 4737 / 4808, 1400 5655 / 5780
-//   others at 1024 rows        2048-8192-8192-2048 1282 / 1129; 784-8192-12288-4096 1904 / 1946; 16384-8192-8192-16384 3351 /
-//                              3476; 16384-16384-1000 2414 / 2440
-//   float32, three equal ones  2048 wide, 256 331 / 317, 400 361 / 350, 512 378 / 369, 600 536 / 536, 1024 609 / 622; 3072 wide,
-//                              384 825 / 856, 512 888 / 923; 4096 wide, 128 727 / 683, 200 756 / 753, 256 781 / 778, 320 1101 /
-//                              1118, 512 1242 / 1262, 1024 2188 / 2240; 6144 wide, 256 1908 / 2018, 512 2948 / 3089; 8192 wide,
-//                              64 1816 / 1813, 128 2028 / 2001, 256 2870 / 2953, 512 4674 / 4834
-//   two                        4096 wide, 384 742 / 725, 512 806 / 789; 8192 wide, 256 1906 / 1854, 512 3067 / 3045; 12288 wide,
-//                              256 4297 / 4366, 512 7830 / 7999; 16384 wide, 512 11795 / 12248
-//   four and five              4096 wide, 256 1047 / 1065, 512 1669 / 1725; 2048 wide, 256 564 / 554, 400 615 / 608, 512 646 / 642
-//   others at 512 rows         784-4096-4096-47 592 / 579; 784-2048-2048-2048 330 / 319; 4096-1024-4096-4096 761 / 766;
-//                              784-3072-3072-3072-47 776 / 782; 1024-4096-4096-2048 815 / 816
-// So beside pays from a length of the batch on; below it where a gradient is larger than the memory-side cache's 256 MB (2^26
-// float32 values), in bf16 up to twice that only with enough rows; and in float32, whose products take ten times as long, where
-// those still to come behind the topmost such update are three and long enough.
-bool updates_beside(const slp_segment* s, int batch) {
-  if (batch >= (s->dtype == SLP_BF16 ? 1400 : 640)) return true;
-  long largest = 0;
-  int top = 0;                           // the topmost layer with a separate update
-  for (int l = 1; l <= s->L; ++l) {
-    const Layer& ly = s->layers[l - 1];
-    largest = std::max(largest, (long)ly.N * ly.K);
-    if (!update_is_fused(s, ly) && !product_is_small(s->dtype, EPI_WGRAD_UPDATE, ly.N, ly.K)) top = l;
-  }
-  if (s->dtype == SLP_BF16) return largest > (1L << 27) || (largest > (1L << 26) && batch >= 768);
-  double to_come = 0.0;
-  for (int l = 1; l < top; ++l) to_come += (l > 1 ? 4.0 : 2.0) * batch * (double)s->layers[l - 1].N * s->layers[l - 1].K;
-  return largest > (1L << 26) || (top > 2 && to_come >= 20e9);
+// Whether the update of a large layer goes into the launch of its weight-gradient product (launch_pair).  There the gradient is not read
+// back and the update's streams run beside other tiles' products; but a product on 256x256 tiles is faster from some length of the batch
+// on, and with it an update that runs beside the next products.  Microseconds a step, update apart / in the product's launch:
+//   bf16      784-2048-2048-2048, 256 rows 114 / 103, 1400 217 / 186; 4096 wide, three layers, 256 346 / 296, 1400 683 / 639, 2048
+//             790 / 786, 3000 1099 / 1128, 4096 1048 / 1150; 8192 wide, three, 1400 2758 / 2510, 2048 2503 / 2533, 3000 3497 / 3610;
+//             16384 wide, two, 512 3076 / 2081, 2048 4504 / 3694, 4096 9917 / 10842
+//   float32   784-2048-2048-2048, 256 275 / 253, 1024 532 / 517; 4096 wide, 512 1248 / 1202, 2048 4076 / 4037, two layers, 4096 4985 / 4910
+// With the join left to a later call a product in its own stream, beside the others (two such segments in turns, a step of both):
+//   bf16      784-2048-2048-2048, 256 254 / 202, 1024 355 / 306; 8192 wide, two layers, 512 1895 / 1671, 2048 2812 / 3100; 4096 wide, 2048
+//             1505 / 1651;   float32 784-2048-2048-2048, 512 635 / 598; 4096 wide, 1024 2719 / 2727; 2048 wide, 2048 2267 / 2292
+// Where the caller asked for it in any case (slp_segment_set_fused_update), the product alone, its own tiles / this one: batch 4096,
+// 4096x784 64.0 / 65.1, 8192x8192 854 / 686; batch 8192 100.8 / 114.6, 16384x16384 4650 / 4981.
+bool update_in_product(const slp_segment* s, const Layer& ly, int batch, bool defer) {
+  const bool b16 = s->dtype == SLP_BF16;
+  if (update_is_fused(s, ly)) return batch <= 4096;
+  return defer ? batch < (b16 ? 1400 : 640) : batch <= (b16 ? 2048 : 4096);
 }
 
 // Makes `st` wait for updates a previous step left running on the side stream (deferred join).  The flag stays set
@@ -380,17 +358,20 @@ int settle_on_host(slp_segment* seg) {
 // Weight updates of large layers that run on the side stream, beside the next matrix products, are held to one workgroup
 // per compute unit (256, 512 and 128 were tried: 256 is best, -2 % per step on the comparison and deep configurations).
 constexpr int kSideUpdateWorkgroups = 256;
-// slp_segment_set_fused_update(seg, 2): layers up to this many weights take the update inside their weight-gradient product.
-// Measured on the wide configuration (784-4096-4096-2048 | 2048-4096-4096-47, batch 1024): fusing the layers up to 1 M
-// or 4 M weights is 1-2 % faster than fusing none, fusing the 8 M and 16 M layers as well 2 % and 9 % slower (their
-// epilogues wait on weight and momentum loads that the separate, massively parallel update kernel streams).
+// slp_segment_set_fused_update(seg, 2): layers up to this many weights take the update inside their weight-gradient product at any batch
+// and do without a stored gradient.  Part of the interface: it says which gradients can be read back.
 constexpr long kFusedAutoMaxWeights = 1L << 22;
+
+constexpr size_t kMemoryCache = (size_t)256 << 20;
 
 // Backward and update, last layer first; the data gradient of layer l reads W_l before it is updated.
 // Small layers: the weight gradient's product always applies the update in its epilogue (and stores the gradient as well, unless
 // the fused update is on), and it waits for company: the product of layer l + 1 goes into one launch with the data gradient of
 // layer l, which does not read what it writes, or with the weight gradient of layer l at the end; the bias gradients ride
 // along, and `sum` with the first such launch.  A step of 784-128-64 is 4 launches instead of 10 that way.
+// Larger layers whose update is in their product's launch (update_in_product) do the same in launch_pair, also with one layer small
+// and the other not; but a small float32 data gradient stays by itself: on 128 columns a tile it has too few tiles for its products
+// (784-2048-2048-2048, 256 rows: 336 us a step with it, 275 without).
 int backward_and_update(slp_segment* seg, int batch, const SumJob* sum, hipStream_t st) {
   // a join cannot be left to a later call while the launches are being captured into a graph
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
@@ -404,30 +385,58 @@ int backward_and_update(slp_segment* seg, int batch, const SumJob* sum, hipStrea
   // wide configuration (1024) 18 % slower with any pause.
   const int pause = defer ? std::min(14, std::max(0, (batch - 2048) / 256)) : 0;
   if (pause > 0) HIP_TRY(launch_hurry(seg->hurry, 0, st));
-  const bool beside = updates_beside(seg, batch);
-  SmallGroup pending{};                  // weight-gradient products waiting for company
-  auto ride_along = [&](SmallGroup& gr) {
-    if (!sum) return;
-    gr.has_sum = true;
-    gr.sum = *sum;
-    sum = nullptr;
+  auto fork = [&](int l) -> int {        // what goes to the side stream from here on follows what layer l has queued
+    HIP_TRY(hipEventRecord(seg->ev_fork[l - 1], st));
+    HIP_TRY(hipStreamWaitEvent(seg->side, seg->ev_fork[l - 1], 0));
+    forked = true;
+    return SLP_OK;
+  };
+  // What a step touches comes round again with the next one: from the memory-side cache if all of it fits, else past the caches, so
+  // that the weights' copies and the activations, which this step reads again, stay there.  Microseconds a step, kept / streamed:
+  // bf16, three layers 2048 wide (0.2 GB) 111 / 121, 2304 (0.26 GB) 170 / 166, 2560 (0.32 GB) 211 / 191, 3072 295 / 235, two layers 2560
+  // wide (0.22 GB) 116 / 127; float32, three layers 2048 wide 279 / 292, 2560 400 / 395.
+  const bool resident = seg->param_bytes + seg->work_bytes <= kMemoryCache;
+  SmallGroup pending{};                  // products waiting for company
+  bool pending_small = true;             // whether they are for launch_small_group or for launch_pair ...
+  bool pending_pairs = false;            // ... or could be for either
+  auto flush = [&]() -> int {
+    if (!pending.n) return SLP_OK;
+    if (sum) {
+      pending.has_sum = true;
+      pending.sum = *sum;
+      sum = nullptr;
+    }
+    pending.resident = resident;
+    const int rc = run_group(seg, pending, st, pending_small);
+    pending = SmallGroup{};
+    return rc;
   };
   for (int l = seg->L; l >= 1; --l) {
     Layer& ly = seg->layers[l - 1];
     if (l > 1) {
-      const GemmArgs d = data_gradient(seg, l, batch);
+      GemmArgs d = data_gradient(seg, l, batch);
       const bool small = product_is_small(seg->dtype, EPI_DGRAD, d.M, d.N);
-      if (small) {
+      const bool pairs = pending.n && pending_pairs && !(small && (pending_small || seg->dtype == SLP_F32)) && product_can_pair(seg->dtype, EPI_DGRAD, d.M, d.N);
+      int rc = SLP_OK;
+      if (pending.n && !pairs && (!small || !pending_small)) rc = flush();
+      if (rc) return rc;
+      if (pairs) {                       // the data gradient first: its tiles are the longer ones
+        d.maskT = seg->A[l - 1]; d.ldmask = seg->ldw[l - 1];
+        pending.g[1] = pending.g[0];
+        pending.epi[1] = pending.epi[0];
+        pending.g[0] = d;
+        pending.epi[0] = EPI_DGRAD;
+        pending.n = 2;
+        pending_small = false;
+        rc = flush();
+      } else if (small) {
         pending.g[pending.n] = d;
         pending.epi[pending.n++] = EPI_DGRAD;
+        pending_small = true;
+        rc = flush();
+      } else {
+        rc = run_gemm(seg, EPI_DGRAD, d, st);
       }
-      int rc = SLP_OK;
-      if (pending.n) {
-        ride_along(pending);
-        rc = run_group(seg, pending, st);
-      }
-      pending = SmallGroup{};
-      if (!rc && !small) rc = run_gemm(seg, EPI_DGRAD, d, st);
       if (rc) return rc;
     }
     GemmArgs g{};
@@ -437,32 +446,42 @@ int backward_and_update(slp_segment* seg, int batch, const SumJob* sum, hipStrea
     g.Cf = ly.dW; g.ldc = ly.ldk;
     const bool fused = update_is_fused(seg, ly);
     const bool small = product_is_small(seg->dtype, EPI_WGRAD_UPDATE, g.M, g.N);
-    if (small) {
-      if (fused) g.Cf = nullptr;
+    if (fused) g.Cf = nullptr;
+    if (small || fused || update_in_product(seg, ly, batch, defer)) {
+      // The data gradient of layer l read W_l^T before this product is queued.
       g.uW = ly.W32; g.uV = ly.vW; g.uW16 = ly.W16; g.uWT = ly.WT; g.ldwt = ly.ldn;
       g.lr = seg->lr; g.mu = seg->mu;
+    }
+    const BiasJob bias{seg->dZT[l], seg->ldb, ly.N, batch, ly.db, ly.b, ly.vb, seg->lr, seg->mu};
+    const bool in_product = !small && update_in_product(seg, ly, batch, defer);
+    if (small || (in_product && (fused || !defer))) {      // waits for company
+      const bool pairs = product_can_pair(seg->dtype, EPI_WGRAD_UPDATE, g.M, g.N) || !small;
+      if (pending.n && pending_small != small && !(pending_pairs && pairs)) {
+        int rc = flush();
+        if (rc) return rc;
+      }
+      pending_small = small && (!pending.n || pending_small);
+      pending_pairs = pairs;
       pending.g[pending.n] = g;
       pending.epi[pending.n++] = EPI_WGRAD_UPDATE;
-      pending.bias[pending.n_bias++] = BiasJob{seg->dZT[l], seg->ldb, ly.N, batch, ly.db, ly.b, ly.vb, seg->lr, seg->mu};
-      if (l > 1) continue;
+      pending.bias[pending.n_bias++] = bias;
+      continue;
     }
-    if (l == 1 && pending.n) {           // the last products; a fork and a join would cost more than they take
-      ride_along(pending);
-      int rc = run_group(seg, pending, st);
-      pending = SmallGroup{};
+    int rc = flush();
+    if (rc) return rc;
+    if (in_product) {                      // left to a later call: beside what is still to come
+      SmallGroup gr{};
+      gr.n = gr.n_bias = 1;
+      gr.g[0] = g; gr.epi[0] = EPI_WGRAD_UPDATE; gr.bias[0] = bias; gr.resident = resident;
+      rc = fork(l);
+      if (!rc) rc = run_group(seg, gr, seg->side, false);
       if (rc) return rc;
-      if (small) continue;
+      continue;
     }
-    if (fused) {     // weights, momentum and the derived copies are rewritten by the product's epilogue
-      g.uW = ly.W32; g.uV = ly.vW; g.uW16 = ly.W16; g.uWT = ly.WT; g.ldwt = ly.ldn;
-      g.lr = seg->lr; g.mu = seg->mu;
-      g.Cf = nullptr;
-    }
-    int rc = run_gemm(seg, fused ? EPI_WGRAD_UPDATE : EPI_WGRAD, g, st);
+    rc = run_gemm(seg, fused ? EPI_WGRAD_UPDATE : EPI_WGRAD, g, st);
     if (rc) return rc;
     if (fused) {
-      // The data gradient of layer l read W_l^T before this product was queued (same stream).  What is left of the
-      // layer is its bias: one small launch, on the caller's stream (nothing worth a second stream).
+      // What is left of the layer is its bias: one small launch, on the caller's stream (nothing worth a second stream).
       HIP_TRY(launch_layer_update(seg->dtype, nullptr, nullptr, nullptr, ly.N, 0, ly.ldk, nullptr, nullptr, ly.ldn, seg->dZT[l],
                                   seg->ldb, batch, ly.db, ly.b, ly.vb, seg->lr, seg->mu, st));
       continue;
@@ -470,11 +489,10 @@ int backward_and_update(slp_segment* seg, int batch, const SumJob* sum, hipStrea
     // everything layer l still needs (bias gradient, both updates) reads dZ_l^T / dW_l, which are complete here, and writes
     // only layer l's parameters, which nothing below reads in this step; without a deferred join the first layer has nothing
     // left in this step to overlap with
-    hipStream_t us = (defer || (l > 1 && beside)) ? seg->side : st;
+    hipStream_t us = (defer || l > 1) ? seg->side : st;
     if (us != st) {
-      HIP_TRY(hipEventRecord(seg->ev_fork[l - 1], st));
-      HIP_TRY(hipStreamWaitEvent(us, seg->ev_fork[l - 1], 0));
-      forked = true;
+      rc = fork(l);
+      if (rc) return rc;
     }
     // weights and bias in one launch, but for large layers beside products: there the bias part is a launch of its own first,
     // inside one launch its long reads of dZ^T slowed the products (measured 1 %)
@@ -488,6 +506,8 @@ int backward_and_update(slp_segment* seg, int batch, const SumJob* sum, hipStrea
                                    kSideUpdateWorkgroups, pause, seg->hurry, us));
     }
   }
+  const int rc = flush();                // the last products; a fork and a join would cost more than they take
+  if (rc) return rc;
   if (sum) HIP_TRY(launch_reduce_loss(sum->partials, sum->n, sum->scale, sum->out0, sum->out1, st));   // found no company
   if (forked) {     // join: later work on the caller's stream sees every update
     HIP_TRY(hipEventRecord(seg->ev_join, seg->side));

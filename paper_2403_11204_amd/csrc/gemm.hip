@@ -53,27 +53,6 @@ namespace {
 constexpr int kGroupM = 8;
 constexpr int kRegionWalk = -1;   // GemmArgs::group_m value: walk 16 x 16 regions of tiles (big kernel only)
 
-// MFMA geometry per element type.  bf16: v_mfma_f32_16x16x32_bf16 (a 16x16 block over 32 k = 4 chunks per row; the
-// block's 4 accumulator registers hold rows 4*(lane/16)..+3 of column lane%16); float32: v_mfma_f32_32x32x2_f32, four
-// per chunk pair.  MB = block edge, AH = parts the A fragments of one k-sub-step are read in (pipeline units).
-template <typename T> struct Mma;
-template <> struct Mma<bf16> {
-  static constexpr int MB = 16, AH = 2, ACC = 4;
-  typedef f32x4 acc_t;
-  static __device__ __forceinline__ void mma(acc_t& acc, const u32x4& a, const u32x4& b) {
-    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), acc, 0, 0, 0);
-  }
-};
-template <> struct Mma<float> {
-  static constexpr int MB = 32, AH = 1, ACC = 16;
-  typedef f32x16 acc_t;
-  static __device__ __forceinline__ void mma(acc_t& acc, const u32x4& a, const u32x4& b) {
-    const f32x4 af = __builtin_bit_cast(f32x4, a), bfv = __builtin_bit_cast(f32x4, b);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(af[q], bfv[q], acc, 0, 0, 0);
-  }
-};
-
 // The optimiser step in the epilogue of the weight gradient (EPI_WGRAD_UPDATE), one accumulator register quad: the float32
 // weights and momenta of 4 consecutive columns of the output row the lane holds after the transpose ...
 __device__ __forceinline__ void request_update(const GemmArgs& g, int n, int mb, int lane, f32x4& w, f32x4& vel) {
@@ -842,7 +821,15 @@ hipError_t gemm_configure_all() {
   if (e == hipSuccess) e = configure_epi<float, EPI_WGRAD>();
   if (e == hipSuccess) e = configure_epi<float, EPI_WGRAD_UPDATE>();
   if (e == hipSuccess) e = small_configure_all();
+  if (e == hipSuccess) e = pair_configure_all();
   return e;
+}
+
+// Whether launch_pair may take the product: the sums of its 128x128 tiles are in the order of every tile but the 16 and 32 ones, whose
+// products are better off in a group of their kind; 256x256 tiles are faster where there are enough of them.
+bool product_can_pair(int dtype, int epi, int M, int N) {
+  const int c = pick_cfg(dtype, epi, M, N);
+  return c != 0 && !(c == 2 && small_tile(dtype, M, N) < 64);
 }
 
 bool product_is_small(int dtype, int epi, int M, int N) { return pick_cfg(dtype, epi, M, N) == 2; }

@@ -30,6 +30,27 @@ __device__ __forceinline__ void mma_chunk(f32x16& acc, const u32x4& a, const u32
   for (int q = 0; q < 4; ++q) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(af[q], bfv[q], acc, 0, 0, 0);
 }
 
+// MFMA geometry per element type.  bf16: v_mfma_f32_16x16x32_bf16 (a 16x16 block over 32 k = 4 chunks per row; the
+// block's 4 accumulator registers hold rows 4*(lane/16)..+3 of column lane%16); float32: v_mfma_f32_32x32x2_f32, four
+// per chunk pair.  MB = block edge, AH = parts the A fragments of one k-sub-step are read in (pipeline units).
+template <typename T> struct Mma;
+template <> struct Mma<bf16> {
+  static constexpr int MB = 16, AH = 2, ACC = 4;
+  typedef f32x4 acc_t;
+  static __device__ __forceinline__ void mma(acc_t& acc, const u32x4& a, const u32x4& b) {
+    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), acc, 0, 0, 0);
+  }
+};
+template <> struct Mma<float> {
+  static constexpr int MB = 32, AH = 1, ACC = 16;
+  typedef f32x16 acc_t;
+  static __device__ __forceinline__ void mma(acc_t& acc, const u32x4& a, const u32x4& b) {
+    const f32x4 af = __builtin_bit_cast(f32x4, a), bfv = __builtin_bit_cast(f32x4, b);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(af[q], bfv[q], acc, 0, 0, 0);
+  }
+};
+
 template <typename T> struct Vec4;
 template <> struct Vec4<bf16> { typedef bf16x4 type; };
 template <> struct Vec4<float> { typedef f32x4 type; };

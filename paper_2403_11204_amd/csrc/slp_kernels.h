@@ -44,7 +44,7 @@ struct GemmArgs {
   int ldc, ldct;
   const float* bias;
   int relu;
-  const void* maskT;  // [N][ldmask], element type T
+  const void* maskT;  // [N][ldmask], element type T; launch_pair takes the mask row-major, [M][ldmask]
   int ldmask;
   // The same mask as one bit per element, for products that run on the 256x256 bf16 tile (every other tile configuration
   // ignores both pointers): EPI_FWD writes bits_out, EPI_DGRAD reads bits instead of maskT when it is not null.
@@ -104,9 +104,15 @@ struct SmallGroup {
   SumJob sum;
   CopyJob copy;
   OutJob out;
+  bool resident;             // launch_pair: weights, momenta and gradients are still in the memory-side cache when they are next used
 };
 hipError_t launch_small_group(int dtype, const SmallGroup& group, hipStream_t s);
 hipError_t small_configure_all();
+// Up to two products of larger layers on 128x128 tiles, weight gradients with their update (EPI_WGRAD_UPDATE, Cf set to store the
+// gradient as well) and data gradients (EPI_DGRAD with its mask row-major), and what hangs on them (no copy, no EPI_FWD_OUT).
+hipError_t launch_pair(int dtype, const SmallGroup& group, hipStream_t s);
+hipError_t pair_configure_all();
+bool product_can_pair(int dtype, int epi, int M, int N);
 // Name of the tile configuration launch_gemm would pick (for logs and profiles).
 const char* gemm_config_name(int dtype, int M, int N, int K);
 

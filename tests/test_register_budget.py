@@ -58,6 +58,14 @@ def test_the_kernels_of_small_layers_do_not_spill():
         assert v["vgpr_spill_count"] == 0 and v["private_segment_fixed_size"] == 0, (name, v)
 
 
+def test_the_kernels_of_product_pairs_fit_their_workgroups():
+    pair = metadata_of("gemm_pair.hip")
+    assert len(pair) == 8, sorted(pair)
+    for name, v in pair.items():
+        assert v["vgpr_count"] <= (168 if "Li64E" in name else 256), (name, v)      # 3 and 2 workgroups of 4 wavefronts per compute unit
+        assert v["vgpr_spill_count"] == 0 and v["private_segment_fixed_size"] == 0, (name, v)
+
+
 def test_the_update_kernel_fits_beside_the_products():
     update = {n: v for n, v in metadata_of("elementwise.hip").items() if "sgd_update_strided_kernel" in n}
     assert len(update) == 2, sorted(update)
