@@ -33,6 +33,7 @@ UNITS = {
     "gemm.hip": [],
     "gemm_small.hip": [],
     "gemm_pair.hip": [],
+    "chain.hip": [],
     "probe.hip": [],
     "accuracy.hip": [],
 }
@@ -75,7 +76,7 @@ def build_tools(verbose=True):
     """Development tools beside the library: the stand-alone matrix-product timer (csrc/gemm_bench.hip)."""
     os.makedirs(BUILD, exist_ok=True)
     out = os.path.join(BUILD, "gemm_bench")
-    cmd = [hipcc()] + [a for a in COMMON if a != "-fPIC"] + [os.path.join(CSRC, f) for f in ("gemm_bench.hip", "gemm_small.hip", "gemm_pair.hip")] + ["-o", out]
+    cmd = [hipcc()] + [a for a in COMMON if a != "-fPIC"] + [os.path.join(CSRC, f) for f in ("gemm_bench.hip", "gemm_small.hip", "gemm_pair.hip", "chain.hip")] + ["-o", out]
     if verbose:
         print(" ".join(cmd), flush=True)
     r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)

@@ -822,6 +822,7 @@ hipError_t gemm_configure_all() {
   if (e == hipSuccess) e = configure_epi<float, EPI_WGRAD_UPDATE>();
   if (e == hipSuccess) e = small_configure_all();
   if (e == hipSuccess) e = pair_configure_all();
+  if (e == hipSuccess) e = chain_configure_all();
   return e;
 }
 

@@ -113,6 +113,23 @@ hipError_t small_configure_all();
 hipError_t launch_pair(int dtype, const SmallGroup& group, hipStream_t s);
 hipError_t pair_configure_all();
 bool product_can_pair(int dtype, int epi, int M, int N);
+// The forward pass through consecutive layers of at most kChainWidth inputs and outputs in one launch, a strip of 16 rows of the batch per workgroup.
+constexpr int kChainLayers = 4, kChainWidth = 64;
+struct ChainLayer {
+  const void* W;            // [N][ldk], element type T
+  const float* b;
+  void* A;                  // [M][lda], may be null
+  int N, ldk, lda;
+};
+struct ChainLaunch {
+  const void* X; int ldx, K0, M;     // input rows of the first layer, each on a 16-byte boundary
+  int layers, relu_last;
+  ChainLayer layer[kChainLayers];
+  void* out;                // the last layer's output, dense: [M][its N], any alignment; must not overlap X
+  void* copy; int ldcopy;   // a copy of the input, may be null
+};
+hipError_t launch_chain(int dtype, const ChainLaunch& a, hipStream_t s);
+hipError_t chain_configure_all();
 // Name of the tile configuration launch_gemm would pick (for logs and profiles).
 const char* gemm_config_name(int dtype, int M, int N, int K);
 
