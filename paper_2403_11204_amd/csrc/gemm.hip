@@ -38,8 +38,8 @@
 //     is one vector store into the transposed output; for the row-major output the quad of lanes holding
 //     4 adjacent columns transposes its 4x4 block with DPP moves, after which a lane holds 4 consecutive
 //     columns of one row: one vector store as well (2 stores per quad instead of 5).
-//     The big kernel's bf16 outputs go through LDS instead and leave as whole 128- and 256-byte row segments
-//     (see its epilogue).
+//     The bf16 outputs of the forward product and the data gradient go through LDS instead and leave as whole 128- and
+//     256-byte row segments (see the epilogues).
 //   * workgroup -> tile: consecutive workgroup ids go round-robin over the 8 XCDs, so
 //     ids are first regrouped per XCD (each XCD gets a contiguous range of tiles and
 //     its own 4 MB L2 sees a compact set of operand rows), then walked in column-major groups of 8 tile-rows.
@@ -109,6 +109,25 @@ __device__ __forceinline__ void update_quad(const GemmArgs& g, int n, int mb, fl
 //   stores 4 consecutive columns of one row as one vector (pad columns up to the leading dimension receive
 //   zeros);  EPI_WGRAD: float32 row-major, same transposed vector store.
 template <typename T, int EPI>
+__device__ __forceinline__ void finish_values(const GemmArgs& g, int n, int mb, float bias, float (&v)[4]) {
+  if (EPI == EPI_FWD) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      v[e] += bias;
+      if (g.relu) v[e] = fmaxf(v[e], 0.0f);
+    }
+  } else if (g.maskT && n < g.N && mb < ((g.M + 7) & ~7)) {     // no mask: the gradient w.r.t. the segment input
+    typedef typename Vec4<T>::type mvec_t;
+    const mvec_t mk = *(const mvec_t*)((const T*)g.maskT + (size_t)n * g.ldmask + mb);
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (!((float)mk[e] > 0.0f)) v[e] = 0.0f;
+  }
+#pragma unroll
+  for (int e = 0; e < 4; ++e)
+    if (mb + e >= g.M || n >= g.N) v[e] = 0.0f;
+}
+template <typename T, int EPI>
 __device__ __forceinline__ void store_quad(const GemmArgs& g, int n, int mb, float bias, float (&v)[4], int lane) {
   typedef __attribute__((ext_vector_type(4))) float f32x4_t;
   const bool col_ok = n < g.N;
@@ -125,22 +144,7 @@ __device__ __forceinline__ void store_quad(const GemmArgs& g, int n, int mb, flo
     return;
   }
   if (mb >= ((g.M + 7) & ~7)) return;       // the same for the whole quad
-  if (EPI == EPI_FWD) {
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      v[e] += bias;
-      if (g.relu) v[e] = fmaxf(v[e], 0.0f);
-    }
-  } else if (g.maskT && col_ok) {   // no mask: the gradient w.r.t. the segment input
-    typedef typename Vec4<T>::type mvec_t;
-    const mvec_t mk = *(const mvec_t*)((const T*)g.maskT + (size_t)n * g.ldmask + mb);
-#pragma unroll
-    for (int e = 0; e < 4; ++e)
-      if (!((float)mk[e] > 0.0f)) v[e] = 0.0f;
-  }
-#pragma unroll
-  for (int e = 0; e < 4; ++e)
-    if (mb + e >= g.M || !col_ok) v[e] = 0.0f;
+  finish_values<T, EPI>(g, n, mb, bias, v);
   if (g.CT && col_ok) {
     typename Vec4<T>::type o;
 #pragma unroll
@@ -270,6 +274,23 @@ __global__ __launch_bounds__(NW * 64) void gemm_nt_kernel(const GemmArgs g) {
   for (int st = 0; st < NS; ++st)
 #pragma unroll
     for (int i = 0; i < NLD; ++i) gload_one(st, st, i);
+  SLP_FENCE();
+  // what the epilogue of bf16 outputs reads, behind the first operands
+  constexpr bool kStaged = ES == 2 && (EPI == EPI_FWD || EPI == EPI_DGRAD);
+  float bias[NI];
+  uint32_t bits[NI];                     // data gradient: this lane's rows of the mask, bit 4 i + e (GemmArgs::bits)
+  if constexpr (kStaged) {
+#pragma unroll
+    for (int j = 0; j < NI; ++j) {
+      const int n = n0 + wn * WTN + j * MB + lrow;
+      bias[j] = 0.0f;
+      bits[j] = 0;
+      if (EPI == EPI_FWD && n < g.N) bias[j] = g.bias[n];
+      if (EPI == EPI_DGRAD && g.bits && n < g.N && m0 + wm * WTM < g.M)
+        bits[j] = ((const uint16_t*)(g.bits + (size_t)n * g.ldbits + (m0 >> 5) + lgrp))[wm];
+    }
+    SLP_FENCE();
+  }
   __builtin_amdgcn_s_waitcnt(VMCNT((NS - 1) * NLD));
   __syncthreads();
 #pragma unroll
@@ -349,6 +370,68 @@ __global__ __launch_bounds__(NW * 64) void gemm_nt_kernel(const GemmArgs g) {
             update_quad<T>(g, n0 + wn * WTN + j * MB + lrow, m0 + wm * WTM + (i0 + i) * MB + (256 / MB) * q + 4 * lgrp, x, lane, w[i][j][q], v[i][j][q]);
             __builtin_amdgcn_sched_barrier(0);
           }
+    }
+    return;
+  }
+  typedef typename Vec4<T>::type vec4;
+  if constexpr (kStaged) {
+    // bf16: straight from the accumulators a store covers 32 bytes of each of 16 rows.  The tile goes through LDS in both layouts, rows
+    // of 256 bytes transposed and 2 BN row-major (no bank conflicts on either side), and leaves in 16-byte pieces of whole row segments.
+    // Forward, microseconds before / after: 1024x4096, K = 64 9.2 / 8.3, 784 15.7 / 14.7, 4096 36.8 / 35.5, 2048x4096x1024 26.2 / 23.3,
+    // 1024x2048x4096 26.7 / 25.0, 1280x1664x1024 13.8 / 12.7.  (float32 blocks are 32 columns: whole lines already.)
+    // The mask of the data gradient comes as bits; as 8-byte pieces of the activation behind the stores it cost 5 us on 2048x4096, all of
+    // them requested before the k-loop 1 us more than that at K = 4096.
+    constexpr int CROW = BN * 2, CCH = CROW / 16, TCH = BM / 8;
+    static_assert(BM == 128 && WTM == 64 && BN * 256 + BM * CROW <= NS * STAGE, "half a word of mask bits per lane; both layouts fit into the stages");
+    unsigned char *const ct = smem, *const cm = smem + BN * 256;
+    auto at_t = [&](int r, int c) { return ct + r * 256 + ((c ^ (r & 15)) << 4); };
+    auto at_m = [&](int r, int c) { return cm + r * CROW + ((c ^ (CCH == 16 ? (r << 1) & 14 : r & 6)) << 4); };
+    __syncthreads();                     // nobody reads the stages any more and every load into them has landed
+#pragma unroll
+    for (int j = 0; j < NI; ++j) {
+      const int nl = wn * WTN + j * MB + lrow, n = n0 + nl;
+      uint32_t word = 0;
+#pragma unroll
+      for (int i = 0; i < MI; ++i) {
+        const int ml = wm * WTM + i * MB + 4 * lgrp;
+        float v[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = acc[i][j][e];
+        if (EPI == EPI_DGRAD && g.bits) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (!((bits[j] >> (4 * i + e)) & 1u) || n >= g.N || m0 + ml + e >= g.M) v[e] = 0.0f;
+        } else {
+          finish_values<T, EPI>(g, n, m0 + ml, bias[j], v);
+        }
+        if (EPI == EPI_FWD) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) word |= (uint32_t)((float)(T)v[e] > 0.0f) << (4 * i + e);
+        }
+        if (g.CT) *(vec4*)(at_t(nl, ml >> 3) + (ml & 4) * 2) = vec4{(T)v[0], (T)v[1], (T)v[2], (T)v[3]};
+        if (g.C) {
+          quad_transpose(v, lane);
+          const int nb = nl - (lane & 3);
+          *(vec4*)(at_m(ml + (lane & 3), nb >> 3) + (nb & 4) * 2) = vec4{(T)v[0], (T)v[1], (T)v[2], (T)v[3]};
+        }
+      }
+      if (EPI == EPI_FWD && g.bits_out && n < g.N && m0 + wm * WTM < g.M)
+        ((uint16_t*)(g.bits_out + (size_t)n * g.ldbits + (m0 >> 5) + lgrp))[wm] = (uint16_t)word;
+    }
+    __syncthreads();
+    if (g.CT) {
+#pragma unroll
+      for (int x = t; x < BN * TCH; x += NW * 64) {
+        const int r = x / TCH, c = x % TCH;
+        if (n0 + r < g.N && m0 + c * 8 < g.M) *(u32x4*)((T*)g.CT + (size_t)(n0 + r) * g.ldct + m0 + c * 8) = *(const u32x4*)at_t(r, c);
+      }
+    }
+    if (g.C) {
+#pragma unroll
+      for (int x = t; x < BM * CCH; x += NW * 64) {
+        const int r = x / CCH, c = x % CCH;
+        if (m0 + r < g.M && n0 + c * 8 < g.N) *(u32x4*)((T*)g.C + (size_t)(m0 + r) * g.ldc + n0 + c * 8) = *(const u32x4*)at_m(r, c);
+      }
     }
     return;
   }

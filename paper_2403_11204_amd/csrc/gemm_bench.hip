@@ -5,7 +5,7 @@
 //
 //   hipcc --offload-arch=gfx950 -O3 -std=c++17 -Xclang -target-feature -Xclang -packed-fp32-ops -I include \
 //         -I paper_2403_11204_amd/csrc paper_2403_11204_amd/csrc/gemm_bench.hip \
-//         paper_2403_11204_amd/csrc/gemm_small.hip -o _build/gemm_bench
+//         paper_2403_11204_amd/csrc/gemm_small.hip paper_2403_11204_amd/csrc/gemm_pair.hip paper_2403_11204_amd/csrc/chain.hip -o _build/gemm_bench
 //   _build/gemm_bench M N K epilogue iters pad data outputs
 //     epilogue: 0 forward (+bias), 1 data gradient (masked), 2 weight gradient (float32 output)
 //     pad     : elements added to every leading dimension (192 = what the library's own buffers use at these widths)

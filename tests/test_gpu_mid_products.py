@@ -1,0 +1,50 @@
+"""Forward products and data gradients on 128x128 and 128x64 bf16 tiles: both layouts of the output and the mask that goes from one to the
+other as bits, against float64 on the activations as the library stored them.
+
+Tolerances against max|ref| of each tensor: bf16 rounds every stored tensor to 2^-9 of itself, a handful of them in a row: 2e-2.  The mask
+is exact: a data gradient is zero wherever the stored activation is."""
+
+import math
+
+import pytest
+import torch
+
+from paper_2403_11204_amd import api
+
+pytestmark = pytest.mark.gpu
+TOL = 2e-2
+
+
+def close(got, ref):
+    got, ref = got.double(), ref.double()
+    return float((got - ref).abs().max()) <= TOL * max(float(ref.abs().max()), 1e-30)
+
+
+# batch, hidden width: tiles of 128x128 each with a compute unit (one row, rows and columns on and beside their edges), two workgroups of
+# them a unit, and tiles of 128x64; contractions of less than one k-tile, of several and a remainder
+@pytest.mark.parametrize("ends", [(40, 72), (321, 517)])
+@pytest.mark.parametrize("act", [api.RELU_ALL, api.RELU_HIDDEN_IDENTITY_LAST])
+@pytest.mark.parametrize("B,N", [(1, 16513), (130, 8321), (1000, 2055), (1024, 2048), (1089, 1930), (1030, 3700), (65, 11501), (1000, 1500), (1024, 1408)])
+def test_step_against_float64(B, N, act, ends):
+    widths = [ends[0], N, ends[1]]
+    g = torch.Generator(device="cuda").manual_seed(B + sum(widths))
+    rand = lambda *s: torch.rand(*s, generator=g, device="cuda") * 2 - 1
+    seg = api.Segment(widths, act, api.MSE_SIL, max_batch=B + 200, dtype=api.BF16, lr=0.0, momentum=0.0)
+    params = [(rand(n, k) / math.sqrt(k), rand(n) / math.sqrt(k)) for k, n in zip(widths, widths[1:])]
+    for l, (W, b) in enumerate(params):
+        seg.set_params(l, W, b)
+    for rows in (B + 200, B):              # the second batch is shorter: what the first one left behind it is not read
+        X, dA = rand(rows, widths[0]).bfloat16(), rand(rows, widths[-1]).bfloat16()
+        seg.step_external(X, dA)
+        acts = [X] + [seg.get_activation(l, rows) for l in (1, 2)]
+        W16 = [W.bfloat16().double() for W, _ in params]
+        assert close(acts[1], torch.relu(X.double() @ W16[0].t() + params[0][1].double()))
+        dZ2 = seg.get_activation(2, rows, kind=1).double()
+        dZ1 = seg.get_activation(1, rows, kind=1)
+        assert torch.all(dZ1[acts[1] <= 0] == 0)
+        ref = (dZ2 @ W16[1]) * (acts[1] > 0)
+        assert close(dZ1, ref)
+        # the transposed copies, as the weight gradients read them
+        assert close(seg.get_grads(1)[0], dZ2.t() @ acts[1].double())
+        assert close(seg.get_grads(0)[0], dZ1.double().t() @ X.double())
+        assert torch.equal(seg.forward(X), acts[2])
