@@ -239,7 +239,8 @@ int slp_segment_set_fused_update(slp_segment* seg, int on);
  * tiles of 128x128 weights and those that slp_segment_set_fused_update names: nothing of them is left pending): whatever the caller enqueues next on `stream` -- typically the
  * step of another segment -- runs beside the tail of this one.  Until the handle's next step, every call on the
  * handle that takes a stream first makes that stream wait for the pending updates (whichever stream it is), so calls
- * through this interface see the same values as without overlap (bit for bit).  A caller that reads or frees the
+ * through this interface see the same values as without overlap (bit for bit); that step waits
+ * for each layer's where it needs it.  A caller that reads or frees the
  * parameter or workspace buffers directly must call slp_segment_join first (slp_segment_destroy and slp_segment_bind
  * wait on the host).  No effect on steps that are captured into a graph; a stream that is being captured cannot wait
  * for updates left pending outside the capture: such a call fails with SLP_ERR_STATE.  With overlap on, the weight updates of

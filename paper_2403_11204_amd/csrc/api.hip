@@ -108,6 +108,9 @@ struct slp_segment {
   // handle's next call that takes a stream (settle), so that the optimiser tail of one segment runs beside whatever
   // the caller enqueues next -- typically the step of another segment.
   bool defer_join, join_pending;
+  // Whether the pending updates came in the order of the layers, an event behind each (ev_update): the next step waits layer by layer.
+  bool pending_by_layer;
+  std::vector<hipEvent_t> ev_update;
   // slp_segment_set_fused_update: the weight-gradient product applies the optimiser step in its epilogue; the weight
   // gradient itself is never stored.
   bool fused_update;
@@ -252,7 +255,18 @@ struct Forward {
   bool keeps_input;         // whether nothing is written to X before the last launch that could read it has ended, of one launch a layer
   bool apart;               // forward-only: the same of any number of layers a launch
   const OutJob* last;       // training: the gradient of the output rides along with a small last layer
+  bool wait_by_layer;       // training: each layer's launches follow its update of the step before (see settle_step)
 };
+
+// What a layer's forward product waits for where settle_step left the wait to it.
+int settle_layer(slp_segment* seg, int l, hipStream_t st) {
+  if (l == seg->L && seg->paced) {       // (the last of them: see settle)
+    HIP_TRY(launch_hurry(seg->hurry, 1, st));
+    seg->paced = false;
+  }
+  HIP_TRY(hipStreamWaitEvent(st, seg->ev_update[l - 1], 0));
+  return SLP_OK;
+}
 
 // Ingest and all layers.  *out_done: the last layer wrote f.out itself; *last_done: it formed the output's gradient.
 int forward_layers(slp_segment* s, int batch, const Forward& f, hipStream_t st, bool* out_done, bool* last_done) {
@@ -275,7 +289,8 @@ int forward_layers(slp_segment* s, int batch, const Forward& f, hipStream_t st, 
     g.CT = (f.training && l < s->L) ? s->AT[l] : nullptr; g.ldct = s->ldb;
     g.bits_out = (f.training && l < s->L) ? s->bits[l] : nullptr; g.ldbits = s->ldbits;
     g.bias = ly.b; g.relu = relu_on(s, l) ? 1 : 0;
-    int rc;
+    int rc = f.wait_by_layer ? settle_layer(s, l, st) : SLP_OK;
+    if (rc) return rc;
     if (product_is_small(s->dtype, EPI_FWD, g.M, g.N)) {
       SmallGroup gr{};
       gr.n = 1; gr.epi[0] = EPI_FWD;
@@ -313,7 +328,7 @@ int forward_layers(slp_segment* s, int batch, const Forward& f, hipStream_t st, 
 // Forward pass of a training step with the loss and dZ_L (row-major for the data gradient, transposed -- with_transpose --
 // for the weight gradient).  *sum: the loss's partial sums, still to be added up.
 int forward_and_loss(slp_segment* seg, const void* X, const int32_t* targets, int batch, bool with_transpose, float* loss_out,
-                     SumJob* sum, hipStream_t st) {
+                     bool wait_by_layer, SumJob* sum, hipStream_t st) {
   const int L = seg->L, D = seg->widths[L];
   bool out_done = false, last_done = false;
   OutJob oj{};
@@ -322,7 +337,7 @@ int forward_and_loss(slp_segment* seg, const void* X, const int32_t* targets, in
   oj.scale = (float)(2.0 / ((double)batch * (double)D));
   oj.partials = seg->partials; oj.bad_ids = seg->bad_ids;
   oj.dZ = seg->dZ[L]; oj.lddz = seg->ldw[L]; oj.dZT = seg->dZT[L]; oj.lddzt = seg->ldb;
-  int rc = forward_layers(seg, batch, Forward{true, X, nullptr, nullptr, nullptr, true, true, mse ? &oj : nullptr}, st, &out_done, &last_done);
+  int rc = forward_layers(seg, batch, Forward{true, X, nullptr, nullptr, nullptr, true, true, mse ? &oj : nullptr, wait_by_layer}, st, &out_done, &last_done);
   if (rc) return rc;
   *sum = SumJob{seg->partials, 0, 0.0, seg->loss_dev, loss_out};
   if (mse) {
@@ -395,6 +410,20 @@ int settle(slp_segment* seg, hipStream_t st) {
   return SLP_OK;
 }
 
+// The same for a step.  Where the updates came in the order of the layers, the step only needs each layer's when its forward pass gets
+// there (*by_layer), and the tail of them runs beside the first products; what it needs at once, in whichever stream it is, is that the
+// products of the step before have ended.  With graphs on, whose steps hold no such waits, it is the whole wait.
+int settle_step(slp_segment* seg, hipStream_t st, bool* by_layer) {
+  if (seg->join_pending && seg->pending_by_layer && !seg->use_graph) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (st) HIP_TRY(hipStreamIsCapturing(st, &cap));
+    *by_layer = cap == hipStreamCaptureStatusNone;
+  }
+  if (!*by_layer) return settle(seg, st);
+  HIP_TRY(hipStreamWaitEvent(st, seg->ev_fork[seg->L - 1], 0));      // (recorded behind the last of them)
+  return SLP_OK;
+}
+
 // The same on the host.  The pauses of paced updates are sat through: there is no stream at hand here to raise the flag on that
 // is not behind work of the caller's.
 int settle_on_host(slp_segment* seg) {
@@ -412,6 +441,7 @@ constexpr int kSideUpdateWorkgroups = 256;
 constexpr long kFusedAutoMaxWeights = 1L << 22;
 
 constexpr size_t kMemoryCache = (size_t)256 << 20;
+constexpr long kByLayerWeights = 1L << 26;       // (see backward_and_update)
 
 // Backward and update, last layer first; the data gradient of layer l reads W_l before it is updated.
 // Small layers: the weight gradient's product always applies the update in its epilogue (and stores the gradient as well, unless
@@ -427,13 +457,6 @@ int backward_and_update(slp_segment* seg, int batch, const SumJob* sum, hipStrea
   if (seg->defer_join && st) HIP_TRY(hipStreamIsCapturing(st, &cap));
   const bool defer = seg->defer_join && cap == hipStreamCaptureStatusNone;
   bool forked = false;           // whether anything of this step went to the side stream
-  // With the join left to a later call the update's tail has the caller's next work to hide behind, and the update can
-  // be paced so that its loads fit beside the products' (see sgd_update_strided_kernel).  How long it may take scales
-  // with the batch (the products beside it do): nothing up to 2048 rows, 8 units at 4096, capped at 14 from 5632 on --
-  // measured: comparison configuration (8192 rows) best at 10-16 units, deep configuration run serially (4096) at 8-14,
-  // wide configuration (1024) 18 % slower with any pause.
-  const int pause = defer ? std::min(14, std::max(0, (batch - 2048) / 256)) : 0;
-  if (pause > 0) HIP_TRY(launch_hurry(seg->hurry, 0, st));
   auto fork = [&](int l) -> int {        // what goes to the side stream from here on follows what layer l has queued
     HIP_TRY(hipEventRecord(seg->ev_fork[l - 1], st));
     HIP_TRY(hipStreamWaitEvent(seg->side, seg->ev_fork[l - 1], 0));
@@ -445,6 +468,39 @@ int backward_and_update(slp_segment* seg, int batch, const SumJob* sum, hipStrea
   // bf16, three layers 2048 wide (0.2 GB) 111 / 121, 2304 (0.26 GB) 170 / 166, 2560 (0.32 GB) 211 / 191, 3072 295 / 235, two layers 2560
   // wide (0.22 GB) 116 / 127; float32, three layers 2048 wide 279 / 292, 2560 400 / 395.
   const bool resident = seg->param_bytes + seg->work_bytes <= kMemoryCache;
+  // With the join left to a later call and every layer's update apart, the data gradients come first and the weight gradients in the order
+  // of the layers, so that the updates end in the order in which the next step needs them and the tail runs beside its first products
+  // (settle_step), where the first layer's was waited for with nothing beside it.  From a layer of 8192x8192 on: smaller ones' updates are
+  // as long as the products beside them, and spread over all of the backward pass they cost other segments less.  bf16, microseconds,
+  // that order / this one, a step of one handle and of two in turns: 784-16384-16384-16384 8192 rows 19953 / 19432 and 37996 / 37972,
+  // 784-16384-16384 4096 rows 6722 / 6026 and 11046 / 10952, 8192 wide, three layers, 4096 rows 4337 / 4024 and 7281 / 7244, 2048 rows
+  // 2407 / 2309 and 4440 / 4435; 4096 wide, three layers, 4096 rows 926 / 908 and 1797 / 1809, 3000 rows 1019 / 1010 and 2011 / 2046.
+  bool by_layer = defer && seg->dtype == SLP_BF16;
+  long largest = 0;
+  for (int l = 1; l <= seg->L && by_layer; ++l) {
+    const Layer& ly = seg->layers[l - 1];
+    largest = std::max(largest, (long)ly.N * ly.K);
+    by_layer = !product_is_small(seg->dtype, EPI_WGRAD_UPDATE, ly.N, ly.K) && !update_is_fused(seg, ly) && !update_in_product(seg, ly, batch, defer);
+  }
+  by_layer = by_layer && largest >= kByLayerWeights;
+  // With the join left to a later call the update's tail has the caller's next work to hide behind, and the update can
+  // be paced so that its loads fit beside the products' (see sgd_update_strided_kernel).  How long it may take scales
+  // with the batch (the products beside it do): nothing up to 2048 rows, 8 units at 4096, capped at 14 from 5632 on --
+  // measured: comparison configuration (8192 rows) best at 10-16 units, deep configuration run serially (4096) at 8-14,
+  // wide configuration (1024) 18 % slower with any pause.  In the order of the layers an update has about one product's time until the
+  // next step needs it, and less of a pause is best: 8192 wide, three layers, 4096 rows 4260 us a step with 8 units, 4144 with 2 and
+  // with none; 16384 wide, 8192 rows 20515 with 13, 20585 with 14.
+  const int pause = !defer ? 0 : std::min(14, std::max(0, by_layer ? (batch - 3072) / 384 : (batch - 2048) / 256));
+  if (pause > 0) HIP_TRY(launch_hurry(seg->hurry, 0, st));
+  while (by_layer && (int)seg->ev_update.size() < seg->L) {      // (the first such step of a handle)
+    hipEvent_t e = nullptr;
+    HIP_TRY(hipEventCreateWithFlags(&e, hipEventDisableTiming));
+    seg->ev_update.push_back(e);
+  }
+  for (int l = seg->L; by_layer && l > 1; --l) {
+    const int rc = run_gemm(seg, EPI_DGRAD, data_gradient(seg, l, batch), st);
+    if (rc) return rc;
+  }
   SmallGroup pending{};                  // products waiting for company
   bool pending_small = true;             // whether they are for launch_small_group or for launch_pair ...
   bool pending_pairs = false;            // ... or could be for either
@@ -460,9 +516,10 @@ int backward_and_update(slp_segment* seg, int batch, const SumJob* sum, hipStrea
     pending = SmallGroup{};
     return rc;
   };
-  for (int l = seg->L; l >= 1; --l) {
+  for (int i = 0; i < seg->L; ++i) {
+    const int l = by_layer ? i + 1 : seg->L - i;
     Layer& ly = seg->layers[l - 1];
-    if (l > 1) {
+    if (l > 1 && !by_layer) {
       GemmArgs d = data_gradient(seg, l, batch);
       const bool small = product_is_small(seg->dtype, EPI_DGRAD, d.M, d.N);
       const bool pairs = pending.n && pending_pairs && !(small && (pending_small || seg->dtype == SLP_F32)) && product_can_pair(seg->dtype, EPI_DGRAD, d.M, d.N);
@@ -554,6 +611,7 @@ int backward_and_update(slp_segment* seg, int batch, const SumJob* sum, hipStrea
       HIP_TRY(launch_update_beside(seg->dtype, ly.W32, ly.vW, ly.dW, ly.N, ly.K, ly.ldk, ly.W16, ly.WT, ly.ldn, seg->lr, seg->mu,
                                    kSideUpdateWorkgroups, pause, seg->hurry, us));
     }
+    if (by_layer) HIP_TRY(hipEventRecord(seg->ev_update[l - 1], seg->side));
   }
   const int rc = flush();                // the last products; a fork and a join would cost more than they take
   if (rc) return rc;
@@ -563,6 +621,7 @@ int backward_and_update(slp_segment* seg, int batch, const SumJob* sum, hipStrea
     if (!defer) HIP_TRY(hipStreamWaitEvent(st, seg->ev_join, 0));
   }
   seg->join_pending = defer && forked;
+  seg->pending_by_layer = by_layer;
   seg->paced = seg->join_pending && pause > 0;
   return SLP_OK;
 }
@@ -721,7 +780,7 @@ int slp_segment_create(const int* widths, int n_widths, int act, int loss, const
   s->work_bytes = off;
 
   s->side = nullptr; s->ev_join = nullptr;
-  s->defer_join = false; s->join_pending = false; s->fused_update = false; s->fused_max_params = 0;
+  s->defer_join = false; s->join_pending = false; s->pending_by_layer = false; s->fused_update = false; s->fused_max_params = 0;
   s->bound = false; s->have_params = false; s->table = nullptr; s->classes = 0; s->last_batch = 0; s->prof = false;
   s->use_graph = false; s->graph_warm = false; s->graph_tick = 0; s->graph_misses = 0; s->graph_steps = 0;
   s->partials = nullptr; s->loss_dev = nullptr; s->bad_ids = nullptr;
@@ -735,6 +794,7 @@ void slp_segment_destroy(slp_segment* seg) {
   for (auto& r : seg->prof_log) { (void)hipEventDestroy(r.a); (void)hipEventDestroy(r.b); }
   for (auto e : seg->ev_pool) (void)hipEventDestroy(e);
   for (auto e : seg->ev_fork) (void)hipEventDestroy(e);
+  for (auto e : seg->ev_update) (void)hipEventDestroy(e);
   if (seg->ev_join) (void)hipEventDestroy(seg->ev_join);
   drop_graphs(seg);
   if (seg->side) {
@@ -891,7 +951,7 @@ int slp_segment_forward(slp_segment* seg, const void* X, int batch, void* out, s
   const bool x_direct = keeps_input && w0 % kLdRows == 0 && (xa & 127) == 0;      // rows on cache-line boundaries, else the copy pays
   const bool out_direct = w % kLdAlign == 0 && ((uintptr_t)out & 15) == 0;
   bool out_done = false, last_done = false;
-  rc = forward_layers(seg, batch, Forward{false, X, x_direct ? X : nullptr, out_direct ? out : nullptr, out, keeps_input, apart, nullptr}, st, &out_done,
+  rc = forward_layers(seg, batch, Forward{false, X, x_direct ? X : nullptr, out_direct ? out : nullptr, out, keeps_input, apart, nullptr, false}, st, &out_done,
                       &last_done);
   if (rc) return rc;
   if (!out_direct && !out_done)
@@ -908,12 +968,13 @@ int slp_segment_step(slp_segment* seg, const void* X, const int32_t* targets, in
   if (seg->loss == SLP_MSE_SIL && !seg->table) return fail(SLP_ERR_STATE, "no label table bound: call slp_segment_set_labels first");
   hipStream_t st = (hipStream_t)stream;
   seg->last_batch = batch;
-  rc = settle(seg, st);
+  bool by_layer = false;
+  rc = settle_step(seg, st, &by_layer);
   if (rc) return rc;
 
   auto launch_all = [&]() -> int {
     SumJob sum{};
-    int r = forward_and_loss(seg, X, targets, batch, true, loss_out, &sum, st);
+    int r = forward_and_loss(seg, X, targets, batch, true, loss_out, by_layer, &sum, st);
     if (!r) r = backward_and_update(seg, batch, &sum, st);
     return r;
   };
@@ -1036,7 +1097,7 @@ int slp_segment_input_grad(slp_segment* seg, const void* X, const int32_t* targe
   rc = settle(seg, st);
   if (rc) return rc;
   SumJob sum{};
-  rc = forward_and_loss(seg, X, targets, batch, false, loss_out, &sum, st);
+  rc = forward_and_loss(seg, X, targets, batch, false, loss_out, false, &sum, st);
   if (rc) return rc;
   const int w0 = seg->widths[0];
   bool summed = false, dx_done = false;
@@ -1074,7 +1135,7 @@ int slp_segment_step_external(slp_segment* seg, const void* X, const void* dA_ou
   oj.ext = dA_out;
   oj.dZ = seg->dZ[L]; oj.lddz = seg->ldw[L]; oj.dZT = seg->dZT[L]; oj.lddzt = seg->ldb;
   bool out_done = false, last_done = false;
-  rc = forward_layers(seg, batch, Forward{true, X, nullptr, nullptr, nullptr, true, true, &oj}, st, &out_done, &last_done);
+  rc = forward_layers(seg, batch, Forward{true, X, nullptr, nullptr, nullptr, true, true, &oj, false}, st, &out_done, &last_done);
   if (rc) return rc;
   if (!last_done)
     HIP_TRY(launch_copy_transpose(seg->dtype, dA_out, D, batch, D, seg->dZ[L], seg->ldw[L], seg->dZT[L], seg->ldb, 1,

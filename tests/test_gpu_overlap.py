@@ -171,3 +171,47 @@ def test_capturing_stream_with_pending_updates_is_refused():
         graph2.replay()
         stream.synchronize()
         assert torch.equal(out, ref)
+
+
+@pytest.mark.parametrize("B", [1500, 3500])        # without pauses of the updates and with them
+@pytest.mark.parametrize("widths,loss", [([500, 8200, 8191, 601], api.MSE_SIL), ([8193, 8192], api.MSE_SIL), ([784, 4100, 16400, 600], api.SOFTMAX_XENT)])
+def test_consecutive_steps_that_wait_layer_by_layer(widths, loss, B):
+    # a layer of 2^26 weights or more, every layer's update apart: one handle stepped again and again, with short batches, another stream,
+    # reads and calls that change the parameters in between
+    classes = widths[-1] if loss == api.SOFTMAX_XENT else 12
+    act = api.RELU_ALL if loss == api.MSE_SIL else api.RELU_HIDDEN_IDENTITY_LAST
+    g = torch.Generator(device=DEV).manual_seed(B)
+    rand = lambda *s: torch.rand(s, generator=g, device=DEV) * 2 - 1
+    table = rand(classes, widths[-1])
+    params = [(rand(n, k) / k ** 0.5, rand(n)) for k, n in zip(widths, widths[1:])]
+    Xs = [rand(B, widths[0]).to(torch.bfloat16) for _ in range(3)]
+    ys = [torch.randint(0, classes, (B,), generator=g, device=DEV, dtype=torch.int32) for _ in range(3)]
+    runs = []
+    for overlap in (False, True):
+        seg = api.Segment(widths, act, loss, max_batch=B, dtype=api.BF16, lr=0.05, momentum=0.9)
+        for l, (W, b) in enumerate(params):
+            seg.set_params(l, W, b)
+        seg.set_overlap(overlap)
+        if loss == api.MSE_SIL:
+            seg.set_labels(table)
+        sa, sb = torch.cuda.Stream(), torch.cuda.Stream()
+        sa.wait_stream(torch.cuda.current_stream())
+        seen = []
+        with torch.cuda.stream(sa):
+            for it, rows in enumerate([B, B, B, 40, B, B - 100, B]):
+                seen.append(seg.step(Xs[it % 3][:rows], ys[it % 3][:rows]).clone())
+                if it == 1:
+                    seen.append(seg.forward(Xs[0]))
+                if it == 4:
+                    W, b = seg.get_params(0)
+                    seg.set_params(0, W * 0.5, b)
+        sb.wait_stream(sa)
+        with torch.cuda.stream(sb):
+            for it in range(2):
+                seen.append(seg.step(Xs[it], ys[it]).clone())
+            seen += [t for l in range(seg.L) for t in (*seg.get_params(l), *seg.get_momentum(l), *seg.get_grads(l))]
+        sb.synchronize()
+        runs.append(seen)
+        del seg
+    for a, b in zip(*runs):
+        assert torch.equal(a, b)
