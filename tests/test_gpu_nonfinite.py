@@ -1,0 +1,50 @@
+"""A batch that overflows leaves nothing behind: after slp_segment_init a handle steps to the bits of a new one.
+
+The pads of the weights and of their copies are multiplied with the zeros that pad the other operand, so an infinity or a NaN that an
+update let into them would turn every later step to NaN, also behind new weights."""
+
+import pytest
+import torch
+
+from paper_2403_11204_amd import api
+
+pytestmark = pytest.mark.gpu
+
+# batch, widths, fused update: every place an update is written from.  Widths beside the pads of a transposed copy's rows (8).
+CASES = [(200, [784, 2048, 2052], 0), (64, [784, 2048, 2052], 1), (200, [784, 2052, 2049], 0),      # the update in a launch of larger products
+         (50, [64, 60, 52], 0), (64, [1000, 1028, 1028], 0),                                        # small products
+         (4100, [784, 2052, 2049], 0), (4100, [784, 2052, 2049], 1),                                # 128x128 tiles, gradient stored and not
+         (4100, [784, 4092, 3588], 0), (4100, [784, 4092, 3588], 1)]                                # 256x256
+
+
+def outcome(seg, X, y):
+    seen = [seg.step(X, y).clone(), seg.forward(X)]
+    seen.append(seg.step(X, y).clone())                # reads what the first step wrote
+    return seen + [t for l in range(seg.L) for t in (*seg.get_params(l), *seg.get_momentum(l))]
+
+
+@pytest.mark.parametrize("dtype", [api.F32, api.BF16])
+@pytest.mark.parametrize("bad", [float("inf"), float("nan")])
+@pytest.mark.parametrize("B,widths,fused", CASES)
+def test_init_after_an_overflowed_batch(B, widths, fused, bad, dtype):
+    g = torch.Generator(device="cuda").manual_seed(B + sum(widths))
+    tdt = torch.float32 if dtype == api.F32 else torch.bfloat16
+    X = torch.rand((B, widths[0]), generator=g, device="cuda").to(tdt)
+    y = torch.randint(0, 12, (B,), generator=g, device="cuda", dtype=torch.int32)
+    table = torch.rand((12, widths[-1]), generator=g, device="cuda")
+    runs = []
+    for overflow in (False, True):
+        seg = api.Segment(widths, api.RELU_HIDDEN_IDENTITY_LAST, api.MSE_SIL, max_batch=B, dtype=dtype, lr=0.05, momentum=0.9)
+        seg.set_labels(table)
+        seg.set_fused_update(fused)
+        seg.init(3)
+        if overflow:
+            Xbad = X.clone()
+            Xbad[B // 2, widths[0] // 2] = bad
+            seg.step(Xbad, y)
+            assert not all(torch.isfinite(seg.get_params(l)[0]).all() for l in range(2))
+            seg.init(3)
+        runs.append(outcome(seg, X, y))
+    assert all(torch.isfinite(t.float()).all() for t in runs[0])
+    for a, b in zip(*runs):
+        assert torch.equal(a, b)
