@@ -63,10 +63,18 @@ __device__ __forceinline__ void request_update(const GemmArgs& g, int n, int mb,
     if (g.mu != 0.0f) vel = *(const f32x4*)(g.uV + idx);
   }
 }
+// A lane whose column is past N has a zero row of one operand times the other, which is NaN where that one holds an infinity: the pads of
+// gradients, weights and momenta stay zero, whatever a batch holds.
+__device__ __forceinline__ void clear_past(const GemmArgs& g, int n, float (&v)[4]) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e)
+    if (n >= g.N) v[e] = 0.0f;
+}
 // ... and the step itself (pad columns hold zeros in every stream and stay zero); then back through the transpose, so that the
 // lane holds 4 consecutive output rows of one input column: one vector store into the transposed copy.
 template <typename T>
 __device__ __forceinline__ void update_quad(const GemmArgs& g, int n, int mb, float (&v)[4], int lane, const f32x4& wo, const f32x4& vo) {
+  clear_past(g, n, v);
   quad_transpose(v, lane);
   const int row = mb + (lane & 3), nb = n - (lane & 3);
   float w[4] = {0.0f, 0.0f, 0.0f, 0.0f};
@@ -133,6 +141,7 @@ __device__ __forceinline__ void store_quad(const GemmArgs& g, int n, int mb, flo
   const bool col_ok = n < g.N;
   const int row = mb + (lane & 3), nb = n - (lane & 3);      // after the transpose: this lane's row, first of its 4 columns
   if (EPI == EPI_WGRAD) {
+    clear_past(g, n, v);
     quad_transpose(v, lane);
     if (row < g.M && nb < g.N) *(f32x4_t*)(g.Cf + (size_t)row * g.ldc + nb) = f32x4_t{v[0], v[1], v[2], v[3]};
     return;

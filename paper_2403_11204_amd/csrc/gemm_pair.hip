@@ -228,8 +228,10 @@ __device__ __forceinline__ void update_tile(const GemmArgs& g, int m0, int n0, u
     for (int e = 0; e < 4; ++e) {
       const uint32_t o = uo + (uint32_t)((32 * s + e) * g.ldc) * 4u;
       f32x4 d = tile_row(smem, s, e);
-      // rows past M: a zero row of one operand times an infinity of the other is NaN, and the pads of the transposed copy stay zero
-      if (m0 + 32 * s + 4 * g8 + e >= g.M) d = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+      // past M and N a zero row of one operand times an infinity of the other is NaN: the pads of every stream and copy stay zero
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+        if (m0 + 32 * s + 4 * g8 + e >= g.M || n0 + 4 * q + c >= g.N) d[c] = 0.0f;
       __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, d), rsrcG, o, 0, STREAM);
       const f32x4 vel = g.mu * __builtin_bit_cast(f32x4, vv[s >> 1][4 * (s & 1) + e]) + d;
       __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, vel), rsrcV, o, 0, STREAM);

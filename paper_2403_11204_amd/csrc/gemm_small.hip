@@ -85,6 +85,9 @@ __device__ __forceinline__ void finish_quad(const GemmArgs& g, const OutJob& out
   const int row = mb + (lane & 3), nb = n - (lane & 3);
   const bool in = row < g.M && nb < g.N;
   if (EPI == EPI_WGRAD_UPDATE) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (!col_ok) v[e] = 0.0f;              // (an infinity times the zeros past the operand is NaN)
     quad_transpose(v, lane);
     const size_t idx = (size_t)row * g.ldc + nb;
     if (g.Cf && in) *(f32x4*)(g.Cf + idx) = f32x4{v[0], v[1], v[2], v[3]};

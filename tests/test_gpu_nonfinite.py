@@ -10,11 +10,16 @@ from paper_2403_11204_amd import api
 
 pytestmark = pytest.mark.gpu
 
-# batch, widths, fused update: every place an update is written from.  Widths beside the pads of a transposed copy's rows (8).
+# batch, widths, fused update: every place an update is written from.  Widths beside the pads of a transposed copy's rows (8) and of the
+# columns of weights and momenta (4).
 CASES = [(200, [784, 2048, 2052], 0), (64, [784, 2048, 2052], 1), (200, [784, 2052, 2049], 0),      # the update in a launch of larger products
+         (200, [783, 2047, 2050], 0), (64, [130, 2050, 2047], 1),
          (50, [64, 60, 52], 0), (64, [1000, 1028, 1028], 0),                                        # small products
+         (50, [45, 61, 50], 0), (33, [201, 330, 27], 1), (64, [1001, 1031, 1025], 0),
          (4100, [784, 2052, 2049], 0), (4100, [784, 2052, 2049], 1),                                # 128x128 tiles, gradient stored and not
-         (4100, [784, 4092, 3588], 0), (4100, [784, 4092, 3588], 1)]                                # 256x256
+         (4100, [785, 2050, 2047], 0), (4100, [785, 2050, 2047], 1),
+         (4100, [784, 4092, 3588], 0), (4100, [784, 4092, 3588], 1),                                # 256x256
+         (4100, [785, 4090, 3590], 0), (4100, [785, 4090, 3590], 1)]
 
 
 def outcome(seg, X, y):
