@@ -488,9 +488,14 @@ int backward_and_update(slp_segment* seg, int batch, const SumJob* sum, hipStrea
   // with the batch (the products beside it do): nothing up to 2048 rows, 8 units at 4096, capped at 14 from 5632 on --
   // measured: comparison configuration (8192 rows) best at 10-16 units, deep configuration run serially (4096) at 8-14,
   // wide configuration (1024) 18 % slower with any pause.  In the order of the layers an update has about one product's time until the
-  // next step needs it, and less of a pause is best: 8192 wide, three layers, 4096 rows 4260 us a step with 8 units, 4144 with 2 and
-  // with none; 16384 wide, 8192 rows 20515 with 13, 20585 with 14.
-  const int pause = !defer ? 0 : std::min(14, std::max(0, by_layer ? (batch - 3072) / 384 : (batch - 2048) / 256));
+  // next step needs it, and less of a pause is best for one handle: 8192 wide, three layers, 4096 rows 4260 us a step with 8 units, 4144 with
+  // 2 and with none; 16384 wide, 8192 rows 20515 with 13, 20585 with 14; 8192 wide, two layers, 5632 rows 3971 with 14, 3482 with 6.  Two
+  // handles in turns want some of it from shorter batches on.  A step of both, updates in the old order / in this one without a pause / as here:
+  // 8192 wide, two layers, 2304 rows 3844 / 3910 / 3858, 2700 4007 / 4058 / 3989, 3000 4068 / 4125 / 4050; 784-16384-16384, 2048 rows 6767 / 6787
+  // / 6658, 2700 8517 / 8666 / 8539, 3000 8777 / 8972 / 8788; 784-8192-8192-8192-8192, 2048 rows 5125 / 5086 / 5009, 3300 7527 / 7576 / 7526.
+  // What is still slower in this order: 8192 wide, three layers, 1500 rows 2764 / 2804, 1800 2480 / 2506, two handles 3000 rows 6360 / 6432.
+  const int by_layer_pause = batch < 1792 ? 0 : batch < 2560 ? 1 : std::max(2, (batch - 3072) / 384);
+  const int pause = !defer ? 0 : std::min(14, by_layer ? by_layer_pause : std::max(0, (batch - 2048) / 256));
   if (pause > 0) HIP_TRY(launch_hurry(seg->hurry, 0, st));
   while (by_layer && (int)seg->ev_update.size() < seg->L) {      // (the first such step of a handle)
     hipEvent_t e = nullptr;
