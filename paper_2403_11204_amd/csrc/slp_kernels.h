@@ -101,10 +101,10 @@ struct SmallGroup {
   int n, n_bias;             // products (1 or 2; the second is never EPI_FWD_OUT), bias jobs (0 to 2)
   BiasJob bias[2];
   bool has_sum, has_copy;
+  bool resident;             // launch_pair: weights, momenta and gradients are still in the memory-side cache when they are next used
   SumJob sum;
   CopyJob copy;
   OutJob out;
-  bool resident;             // launch_pair: weights, momenta and gradients are still in the memory-side cache when they are next used
 };
 hipError_t launch_small_group(int dtype, const SmallGroup& group, hipStream_t s);
 hipError_t small_configure_all();
