@@ -48,3 +48,22 @@ def test_step_against_float64(B, N, act, ends):
         assert close(seg.get_grads(1)[0], dZ2.t() @ acts[1].double())
         assert close(seg.get_grads(0)[0], dZ1.double().t() @ X.double())
         assert torch.equal(seg.forward(X), acts[2])
+
+
+# the gradient of the input has no mask: the input's signs are not looked at
+@pytest.mark.parametrize("B,N", [(1, 16513), (1000, 2055), (1089, 4100), (1000, 1500), (1024, 1408), (2100, 6150)])
+def test_gradient_of_the_input(B, N):
+    widths = [N, 72, 40]
+    g = torch.Generator(device="cuda").manual_seed(B + N)
+    rand = lambda *s: torch.rand(*s, generator=g, device="cuda") * 2 - 1
+    seg = api.Segment(widths, api.RELU_HIDDEN_IDENTITY_LAST, api.SOFTMAX_XENT, max_batch=B + 200, dtype=api.BF16, input_grad=True)
+    params = [(rand(n, k) / math.sqrt(k), rand(n) / math.sqrt(k)) for k, n in zip(widths, widths[1:])]
+    for l, (W, b) in enumerate(params):
+        seg.set_params(l, W, b)
+    for rows in (B + 200, B):
+        X, y = rand(rows, N).bfloat16(), torch.randint(0, 40, (rows,), generator=g, device="cuda", dtype=torch.int32)
+        X[:, ::7] = 0.0
+        dX, _ = seg.input_grad(X, y)
+        dZ1 = seg.get_activation(1, rows, kind=1).double()
+        assert float(dZ1.abs().max()) > 0.0
+        assert close(dX, dZ1 @ params[0][0].bfloat16().double())

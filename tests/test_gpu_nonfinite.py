@@ -53,3 +53,22 @@ def test_init_after_an_overflowed_batch(B, widths, fused, bad, dtype):
     assert all(torch.isfinite(t.float()).all() for t in runs[0])
     for a, b in zip(*runs):
         assert torch.equal(a, b)
+
+
+# chains of narrow layers, and products on 128x64, 128x128 and 256x256 tiles
+@pytest.mark.parametrize("dtype", [api.F32, api.BF16])
+@pytest.mark.parametrize("bad", [float("inf"), float("nan")])
+@pytest.mark.parametrize("B,widths", [(50, [61, 20, 30]), (100, [15, 16, 17, 63, 62]), (1000, [70, 1500]), (1000, [70, 2055, 37]), (2100, [70, 6150])])
+def test_rows_of_a_batch_do_not_meet(B, widths, bad, dtype):
+    g = torch.Generator(device="cuda").manual_seed(B + sum(widths))
+    X = torch.rand((B, widths[0]), generator=g, device="cuda").to(torch.float32 if dtype == api.F32 else torch.bfloat16)
+    seg = api.Segment(widths, api.RELU_HIDDEN_IDENTITY_LAST, api.MSE_SIL, max_batch=B, dtype=dtype)
+    seg.init(3)
+    ref = seg.forward(X)
+    row = B // 2
+    X[row, -1] = bad
+    got = seg.forward(X)
+    if len(widths) == 2:               # (a unit that is not a number counts as zero behind a hidden layer)
+        assert not torch.isfinite(got[row].float()).any()
+    keep = torch.arange(B, device="cuda") != row
+    assert torch.isfinite(got[keep].float()).all() and torch.equal(got[keep], ref[keep])

@@ -64,6 +64,8 @@ def run(B, widths, dtype, fused, mu, overlap):
             # the difference of two float32 numbers up to 2^-24 of the weights off
             slack = 2.0 ** -23 / (lr * float(vW.abs().max())) * float(W.abs().max())
             assert close(W2.double() - W.double(), -lr * vW, TOL[dtype] + slack), ("W", l)
+            slack = 2.0 ** -23 / (lr * float(vb.abs().max())) * float(b.abs().max())
+            assert close(b2.double() - b.double(), -lr * vb, TOL[dtype] + slack), ("b", l)
             vel[l - 1] = (vW, vb)
             if l > 1:
                 dZ = (dZ @ W.to(tdt).double()) * (acts[l - 1] > 0)
@@ -86,6 +88,7 @@ def test_past_the_caches(B, widths, dtype):
 
 
 @pytest.mark.parametrize("dtype", [api.F32, api.BF16])
-def test_beside_the_stream_and_in_it_leave_the_same_bits(dtype):
-    for a, b in zip(run(300, [130, 2050, 2047], dtype, 0, 0.9, False), run(300, [130, 2050, 2047], dtype, 0, 0.9, True)):
+@pytest.mark.parametrize("B", [300, 1500])         # with overlap on in the product's launch as well, and apart: the two kernels' sums
+def test_beside_the_stream_and_in_it_leave_the_same_bits(B, dtype):
+    for a, b in zip(run(B, [130, 2050, 2047], dtype, 0, 0.9, False), run(B, [130, 2050, 2047], dtype, 0, 0.9, True)):
         assert torch.equal(a, b)
