@@ -376,19 +376,36 @@ bool update_is_fused(const slp_segment* s, const Layer& ly) { return s->fused_up
 // Whether the update of a large layer goes into the launch of its weight-gradient product (launch_pair).  There the gradient is not read
 // back and the update's streams run beside other tiles' products; but a product on 256x256 tiles is faster from some length of the batch
 // on, and with it an update that runs beside the next products.  Microseconds a step, update apart / in the product's launch:
-//   bf16      784-2048-2048-2048, 256 rows 114 / 103, 1400 217 / 186; 4096 wide, three layers, 256 346 / 296, 1400 683 / 639, 2048
-//             790 / 786, 3000 1099 / 1128, 4096 1048 / 1150; 8192 wide, three, 1400 2758 / 2510, 2048 2503 / 2533, 3000 3497 / 3610;
-//             16384 wide, two, 512 3076 / 2081, 2048 4504 / 3694, 4096 9917 / 10842
-//   float32   784-2048-2048-2048, 256 275 / 253, 1024 532 / 517; 4096 wide, 512 1248 / 1202, 2048 4076 / 4037, two layers, 4096 4985 / 4910
+//   bf16      784-2048-2048-2048, 256 rows 114 / 103, 1600 206 / 173, 2048 219 / 197; 4096 wide, two layers, 1700 447 / 409, 2048 460 / 445, three,
+//             256 346 / 296; 5000 wide, three, 1800 1210 / 1137, 2048 1424 / 1278; 6144 wide, three, 1536 1637 / 1464, 2048 1814 / 1718; 8192 wide,
+//             two, 1700 1542 / 1435, 2048 1632 / 1575; 16384 wide, two, 512 3076 / 2081, 1700 6117 / 5598, 2048 6498 / 6138
+//   beyond    784-2048-2048-2048, 2300 279 / 250, 4096 338 / 321; 4096 wide, three, 2300 993 / 943, 2600 1003 / 1026, 4096 1042 / 1123; 8192
+//             wide, three, 2300 3234 / 3196, 2600 3265 / 3321, 4096 3891 / 4136; 16384 wide, two, 2300 7624 / 7156, 3000 8097 / 8234, 4096 9775 /
+//             10591
+//   float32   784-2048-2048-2048, 300 rows 298 / 258, 1024 531 / 515, 4096 1887 / 1808, 6000 2841 / 3003; 3000 wide, two layers, 1024 936 / 818,
+//             4096 3409 / 3119, 6000 6495 / 6129; 4096 wide, two, 300 722 / 640, 4096 5029 / 4937, 6000 8727 / 8731; 6144 wide, two, 4096 14527 / 13068
+// A weight gradient that is whole rounds of 256x256 tiles wastes nothing on them, and from seven rows of such tiles on the data gradients of wide
+// layers take them too and have no launch in common with an update: there the update is faster apart as long as the products of two
+// layers are still to come, for it to run beside.  All apart / all in the product / the third layer and those above it apart:
+//   4096 wide three layers, 1100 rows - / 574 / 611, 1600 - / 651 / 664, 2048 744 / 767 / 762, four, 1600 - / 923 / 898, 2048 1014 / 1059 / 1035, six, 2048
+//             1537 / 1623 / 1558; 8192 wide, three, 1500 - / 2457 / 2510, 1600 - / 2160 / 2134, 2048 2465 / 2463 / 2445, five, 1700 3819 / 3859 / 3750, 2048
+//             4102 / 4246 / 4074; 784-8192-8192-8192-8192, 1700 2502 / 2519 / 2448; 12288 wide, three, 1600 - / 5099 / 5116, 1900 5660 / 5561 / 5462;
+//             16384 wide, four, 2048 12882 / 13018 / 12753; the second layer apart as well: 784-8192-8192-8192, 2048 1924 for 1830
 // With the join left to a later call a product in its own stream, beside the others (two such segments in turns, a step of both):
-//   bf16      784-2048-2048-2048, 256 254 / 202, 1024 355 / 306; 8192 wide, two layers, 512 1895 / 1671, 2048 2812 / 3100; 4096 wide, 2048
+//   bf16      784-2048-2048-2048, 256 rows 254 / 202, 1024 355 / 306; 8192 wide, two layers, 512 1895 / 1671, 2048 2812 / 3100; 4096 wide, 2048
 //             1505 / 1651;   float32 784-2048-2048-2048, 512 635 / 598; 4096 wide, 1024 2719 / 2727; 2048 wide, 2048 2267 / 2292
-// Where the caller asked for it in any case (slp_segment_set_fused_update), the product alone, its own tiles / this one: batch 4096,
-// 4096x784 64.0 / 65.1, 8192x8192 854 / 686; batch 8192 100.8 / 114.6, 16384x16384 4650 / 4981.
-bool update_in_product(const slp_segment* s, const Layer& ly, int batch, bool defer) {
+// Where the caller asked for it in any case (slp_segment_set_fused_update), a step with every product on its own tiles / in launch_pair:
+//   bf16      784-4096, 512 rows 41 / 32, 4096 97.6 / 94.9, 8192 186.2 / 187.1; 784-2048-2048-2048, 4096 358 / 307, 6000 526 / 489;
+//             1024-4096-1024-4096, 4096 419 / 393, 6000 615 / 621, 8192 760 / 797; 8192-8192, 512 579 / 311, 4096 1217 / 1115, 8192 1970 / 2050
+//   float32   784-4096, 512 rows 85.5 / 75.8, 4096 510 / 499, 6000 859 / 845; 784-2048-2048-2048, 4096 1848 / 1798, 6000 2961 / 2985;
+//             1024-4096-1024, 4096 1362 / 1323, 6000 2358 / 2319
+bool update_in_product(const slp_segment* s, int l, int batch, bool defer) {
+  const Layer& ly = s->layers[l - 1];
   const bool b16 = s->dtype == SLP_BF16;
   if (update_is_fused(s, ly)) return batch <= 4096;
-  return defer ? batch < (b16 ? 1400 : 640) : batch <= (b16 ? 2048 : 4096);
+  if (defer) return batch < (b16 ? 1400 : 640);
+  if (b16 && batch > 1536 && l > 2 && product_fills_rounds(ly.N, ly.K)) return false;
+  return batch <= (b16 ? 2048 : 4096);
 }
 
 // Makes `st` wait for updates a previous step left running on the side stream (deferred join).  The flag stays set
@@ -488,7 +505,7 @@ int backward_and_update(slp_segment* seg, int batch, const SumJob* sum, hipStrea
   for (int l = 1; l <= seg->L && by_layer; ++l) {
     const Layer& ly = seg->layers[l - 1];
     largest = std::max(largest, (long)ly.N * ly.K);
-    by_layer = !product_is_small(seg->dtype, EPI_WGRAD_UPDATE, ly.N, ly.K) && !update_is_fused(seg, ly) && !update_in_product(seg, ly, batch, defer);
+    by_layer = !product_is_small(seg->dtype, EPI_WGRAD_UPDATE, ly.N, ly.K) && !update_is_fused(seg, ly) && !update_in_product(seg, l, batch, defer);
   }
   by_layer = by_layer && largest >= kByLayerWeights;
   // With the join left to a later call the update's tail has the caller's next work to hide behind, and the update can
@@ -566,13 +583,13 @@ int backward_and_update(slp_segment* seg, int batch, const SumJob* sum, hipStrea
     const bool fused = update_is_fused(seg, ly);
     const bool small = product_is_small(seg->dtype, EPI_WGRAD_UPDATE, g.M, g.N);
     if (fused) g.Cf = nullptr;
-    if (small || fused || update_in_product(seg, ly, batch, defer)) {
+    if (small || fused || update_in_product(seg, l, batch, defer)) {
       // The data gradient of layer l read W_l^T before this product is queued.
       g.uW = ly.W32; g.uV = ly.vW; g.uW16 = ly.W16; g.uWT = ly.WT; g.ldwt = ly.ldn;
       g.lr = seg->lr; g.mu = seg->mu;
     }
     const BiasJob bias{seg->dZT[l], seg->ldb, ly.N, batch, ly.db, ly.b, ly.vb, seg->lr, seg->mu};
-    const bool in_product = !small && update_in_product(seg, ly, batch, defer);
+    const bool in_product = !small && update_in_product(seg, l, batch, defer);
     if (small || (in_product && (fused || !defer))) {      // waits for company
       const bool pairs = product_can_pair(seg->dtype, EPI_WGRAD_UPDATE, g.M, g.N) || !small;
       if (pending.n && pending_small != small && !(pending_pairs && pairs)) {

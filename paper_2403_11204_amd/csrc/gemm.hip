@@ -925,6 +925,9 @@ bool product_can_pair(int dtype, int epi, int M, int N) {
   return c != 0 && !(c == 2 && small_tile(dtype, M, N) < 64);
 }
 
+// Whether the 256x256 tiles of an output are whole rounds of the 256 compute units.
+bool product_fills_rounds(int M, int N) { return tiles_of(M, N, 0) % 256 == 0; }
+
 bool product_is_small(int dtype, int epi, int M, int N) { return pick_cfg(dtype, epi, M, N) == 2; }
 
 const char* gemm_config_name(int dtype, int M, int N, int K) {

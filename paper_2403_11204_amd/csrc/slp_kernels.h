@@ -113,6 +113,7 @@ hipError_t small_configure_all();
 hipError_t launch_pair(int dtype, const SmallGroup& group, hipStream_t s);
 hipError_t pair_configure_all();
 bool product_can_pair(int dtype, int epi, int M, int N);
+bool product_fills_rounds(int M, int N);
 // The forward pass through consecutive layers of at most kChainWidth inputs and outputs in one launch, a strip of 16 rows of the batch per workgroup.
 constexpr int kChainLayers = 4, kChainWidth = 64;
 struct ChainLayer {

@@ -92,3 +92,10 @@ def test_past_the_caches(B, widths, dtype):
 def test_beside_the_stream_and_in_it_leave_the_same_bits(B, dtype):
     for a, b in zip(run(B, [130, 2050, 2047], dtype, 0, 0.9, False), run(B, [130, 2050, 2047], dtype, 0, 0.9, True)):
         assert torch.equal(a, b)
+
+
+# a layer above the second of whole rounds of 256x256 tiles has its update apart, those below share launches; against all of them apart
+def test_upper_layer_apart():
+    widths = [130, 2050, 2047, 4090, 4093]
+    for a, b in zip(run(1600, widths, api.BF16, 0, 0.9, False), run(1600, widths, api.BF16, 0, 0.9, True)):
+        assert torch.equal(a, b)
