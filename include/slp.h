@@ -221,11 +221,13 @@ int slp_segment_graph_stats(const slp_segment* seg, int* captured /*host*/, int6
  * With the fused update on, the matrix product that forms dW_l applies v = mu v + dW; w = w - lr v to the tile of the
  * weight matrix it holds and rewrites the bf16 and transposed copies from there: the gradient is never written to
  * memory and never read back (20 instead of 28 bytes per parameter and step in bf16 mode), and a step of a mid-size
- * segment ends with its last product instead of a tail of update launches.  It pays where a layer's products are short; for very wide layers the separate
- * update, which streams beside the next products, is faster.  on = 0: off (default); 1: every layer; 2: the layers
- * where it measured faster, those with at most 4,194,304 weights; on > 2: the layers with at most `on` weights.
- * Layers with fewer than 224 tiles of 128x128 weights take the update inside the product in any case, off or on, and so do
- * larger ones at batches up to 2048 (float32 4096; with overlap on below 1400, float32 640); off, the gradient is stored beside it.
+ * segment ends with its last product instead of a tail of update launches.  It pays while the batch is short, whatever the
+ * width: at long ones (bf16: from 2300 to 4000 rows on, by the shape) the separate update, which streams beside the next products,
+ * is faster.  on = 0: off (default); 1: every layer; 2: the layers with at most 4,194,304 weights; on > 2: the layers with at
+ * most `on` weights.  What the switch decides is which gradients are stored.
+ * Off or on, layers with fewer than 224 tiles of 128x128 weights take the update inside the product in any case, and so do
+ * larger ones at batches up to 2048 (float32 4096; with overlap on below 1400, float32 640) where that is the faster place; off, the
+ * gradient is stored beside it.
  * Results equal the separate update's to float32 rounding (the same expressions on the same values).  For a layer
  * that is fused, slp_segment_get_grads returns the bias gradient only (a request for dW fails with SLP_ERR_STATE).
  * Drops captured graphs.  Errors: SLP_ERR_ARG (null handle, on < 0). */

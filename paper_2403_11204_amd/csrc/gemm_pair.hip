@@ -12,9 +12,11 @@
 //     beside it 73 us, one after the other 41 + 23 + 33 with the update apart.
 //   * The tile goes through LDS and every stream through memory in whole row segments (512 bytes of the float32 streams, 256 of
 //     the bf16 copies); the first half of the weights and momenta is requested before the last k-tile's products, the second
-//     behind the accumulators' way into LDS.  With 64-byte segments straight from the accumulators (the epilogue of gemm.hip)
-//     4096x4096x1024 bf16 took 160 us, now 86; product and update apart 104.  2048x2048x512 36, 21, 32; 16384x16384x1024 2493,
-//     1167, 1949; float32 2048x2048x256 45, 31, 43.  With K = 64, next to nothing to multiply, 4096x4096 takes 70 us: 4.8 TB/s.
+//     behind the accumulators' way into LDS.  Alone, nothing in the caches: with 64-byte segments straight from the accumulators (the epilogue
+//     of gemm.hip) on 128x128 tiles 4096x4096x1024 bf16 took 160 us, now 86; product and update apart 104.  2048x2048x512 36, 21, 32;
+//     16384x16384x1024 2493, 1167, 1949; float32 2048x2048x256 45, 31, 43.  With K = 64, next to nothing to multiply, 4096x4096 takes 70 us:
+//     4.8 TB/s.  In a step of a segment 4096-4096, 1024 rows: 83 us, 94 with the gradient stored as well, apart 41 + 58, on 256x256 tiles with the
+//     update in the epilogue of gemm.hip 96 + 5 for the bias.
 //   * Weights, momenta and gradients pass the caches by where a step's data do not fit into them (see the caller).
 // The order of every sum is that of gemm.hip's tiles and of the 64x64 ones (float32: the same bits).
 #include <stddef.h>
@@ -356,8 +358,16 @@ hipError_t configure_type() {
   return e == hipSuccess ? configure<T, 128, 2>() : e;
 }
 
-constexpr long kSlots = 512;      // workgroups of 128-row tiles that the chip holds at once (a line of 800 takes 784-4096-4096-2048
-                                  // from 1374 to 1443 us a pass, whose launches have 768 and 1248)
+// Workgroups of 128-row tiles that the chip holds at once; a launch that has no more of them is split into 64-row ones.  784-N-N-N,
+// microseconds a step with a line of 0 / 256 / 512 / 768 / 1024:
+//   bf16      256 rows: N = 2048 97.6 / 97.6 / 94.0 / 93.8 / 93.8, 2816 154 / 154 / 154 / 145 / 145, 3584 199 / 199 / 197 / 199 / 192, 4096 236 / 236 /
+//             235 / 236 / 236; 1024 rows: N = 2048 130 / 130 / 134 / 134 / 134, 2304 163 / 163 / 171 / 171 / 173, 3072 250 / 251 / 250 / 245 / 244, 3584
+//             303 / 302 / 303 / 304 / 302, 5120 673 / 673 / 673 / 673 / 675
+//   float32   256 rows: N = 2304 291 / 291 / 282 / 282 / 282, 3072 427 / 427 / 426 / 404 / 403; 1024 rows: N = 2048 541 / 541 / 511 / 510 / 511, 2560 928
+//             / 927 / 925 / 888 / 889, 3584 1465 / 1471 / 1449 / 1472 / 1456, 4096 1727 / 1725 / 1718 / 1720 / 1721
+// So the split pays up to some 800 tiles, but for bf16 launches of 256 to 512 of them with long contractions, 3-5 % faster on 128 rows.  784-4096-4096-2048,
+// 1024 rows, four steps: 1374 us with 512, 1443 with 800.
+constexpr long kSlots = 512;
 
 }  // namespace
 
