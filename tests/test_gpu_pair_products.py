@@ -99,3 +99,29 @@ def test_upper_layer_apart():
     widths = [130, 2050, 2047, 4090, 4093]
     for a, b in zip(run(1600, widths, api.BF16, 0, 0.9, False), run(1600, widths, api.BF16, 0, 0.9, True)):
         assert torch.equal(a, b)
+
+
+def test_upper_layer_apart_in_replayed_steps():
+    widths, B = [130, 2050, 2047, 4090, 4093], 1600
+    g = torch.Generator(device="cuda").manual_seed(B)
+    X = torch.rand((B, widths[0]), generator=g, device="cuda").bfloat16()
+    y = torch.randint(0, 20, (B,), generator=g, device="cuda", dtype=torch.int32)
+    table = torch.rand((20, widths[-1]), generator=g, device="cuda")
+    stream, runs = torch.cuda.Stream(), []
+    stream.wait_stream(torch.cuda.current_stream())
+    for graph in (False, True):
+        with torch.cuda.stream(stream):
+            seg = api.Segment(widths, api.RELU_ALL, api.MSE_SIL, max_batch=B, dtype=api.BF16, lr=0.05, momentum=0.9)
+            seg.init(5)
+            seg.set_labels(table)
+            seg.set_graph(graph)
+            seen = []
+            for _ in range(4):                 # eager work between the replays
+                seen.append(seg.step(X, y).clone())
+                seen.append(seg.forward(X))
+            seen += [t for l in range(seg.L) for t in (*seg.get_params(l), *seg.get_momentum(l), *seg.get_grads(l))]
+        stream.synchronize()
+        assert (seg.graph_stats()[1] > 0) == graph
+        runs.append(seen)
+    for a, b in zip(*runs):
+        assert torch.equal(a, b)
