@@ -24,7 +24,8 @@
 //     over all 64 banks (no conflicts counted).  The hardware writes lane l of an LDS-direct load at
 //     base + 16 l, so the swizzle is applied on the global side: each lane fetches the chunk that belongs at its
 //     physical position.
-//   * big products (256x256 tile, bf16): gemm_nt_big_kernel, 8 wavefronts of 128x64, two LDS stages of 64 KB,
+//   * big products (256x256 tile, bf16) of long contractions: gemm_nt_long_kernel, 4 wavefronts of 128x128, two LDS stages of 64 KB;
+//   * of shorter ones: gemm_nt_big_kernel, 8 wavefronts of 128x64, two LDS stages of 64 KB,
 //     the loads of a k-tile issued evenly over the whole k-tile (two barriers per k-tile free the stage piecewise);
 //     see the comment on that kernel.
 //   * small layers have a kernel of their own (gemm_small.hip);
@@ -46,6 +47,9 @@
 //     Big products whose tile grid divides into 16 x 16 regions are walked region by region instead, all 8 XCDs
 //     inside one region at a time (see the kernel).
 #include "gemm_device.h"
+
+#include <type_traits>
+#include <utility>
 
 namespace slp {
 namespace {
@@ -466,8 +470,30 @@ __global__ __launch_bounds__(NW * 64) void gemm_nt_kernel(const GemmArgs g) {
 #endif
 }
 
-// Big bf16 products: 256x256 tile, NW = 8 wavefronts in a 2 x 4 grid (128 x 64 each; NW = 4, 128 x 128 each with the
-// accumulators in AGPRs, is kept compilable: measured equal, but its data-gradient epilogue spills),
+// workgroup -> 256x256 tile
+__device__ __forceinline__ void big_tile(const GemmArgs& g, int& tm, int& tn) {
+  const int tilesM = (g.M + 255) / 256, tilesN = (g.N + 255) / 256;
+  const int pid = blockIdx.x, xcd = pid % kXcds, q = pid / kXcds;
+  if (g.group_m == kRegionWalk) {
+    // All 8 XCDs work on one 16 x 16 region of tiles at a time, as 2 x 4 blocks of 8 x 4 tiles (one block per XCD,
+    // one tile per compute unit): 32 operand strips feed 256 concurrent tiles, and what one XCD fetched is in the
+    // memory-side cache for the XCDs that share its strips.  Regions are walked down the rows first.
+    const int r = q / 32, sl = q % 32, regM = tilesM / 16;
+    tm = (r % regM) * 16 + (xcd % 2) * 8 + sl % 8;
+    tn = (r / regM) * 16 + (xcd / 2) * 4 + sl / 8;
+    return;
+  }
+  const int total = tilesM * tilesN, base = total / kXcds, rem = total % kXcds;
+  const int tid = xcd * base + (xcd < rem ? xcd : rem) + q;
+  const int group_m = g.group_m > 0 ? g.group_m : kGroupM;
+  const int width = group_m * tilesN;
+  const int group = tid / width, first_m = group * group_m;
+  const int gsz = (tilesM - first_m) < group_m ? (tilesM - first_m) : group_m;
+  tm = first_m + (tid % width) % gsz;
+  tn = (tid % width) / gsz;
+}
+
+// Big bf16 products of shorter contractions: 256x256 tile, 8 wavefronts in a 2 x 4 grid, 128 x 64 each,
 // v_mfma_f32_16x16x32_bf16, two LDS stages of 64 KB.
 // A k-tile (64 k) is 4 units: (row half h, k-sub-step kk) in the order (0,0) (0,1) (1,0) (1,1), each 4 A fragments
 // against the NB B fragments of the sub-step.  The B fragments of a k-tile stay in registers for the whole tile, the A
@@ -489,37 +515,18 @@ __global__ __launch_bounds__(NW * 64) void gemm_nt_big_kernel(const GemmArgs g) 
   __builtin_amdgcn_s_setprio(3);
   constexpr int BM = 256, BN = 256, ES = 2, CH = 8, BK = 64;
   constexpr int A_BYTES = BM * 128, STAGE = (BM + BN) * 128;
+  static_assert(NW == 8, "loads, schedule and epilogue are laid out for 8 wavefronts of 128 x 64");
   constexpr int WN = NW / 2;             // wavefront columns
-  constexpr int WTN = BN / WN;           // columns per wavefront (128 or 64)
-  constexpr int NB = WTN / 16;           // B fragments per sub-step (8 or 4)
-  constexpr int RPL = 8 * NW;            // rows one load instruction of the workgroup covers (32 or 64)
-  constexpr int NBLK = 256 / RPL;        // row blocks (= loads per lane) per operand per k-tile (8 or 4)
-  constexpr int NL = 2 * NBLK;           // loads per lane per k-tile (16 or 8)
-  constexpr int LPU = NL / 4;            // loads per unit (4 or 2)
-  constexpr int NSLOT = 2 * NB;          // slots of 2 MFMAs per unit (16 or 8)
+  constexpr int WTN = BN / WN;           // columns per wavefront
+  constexpr int NB = WTN / 16;           // B fragments per sub-step
+  constexpr int RPL = 8 * NW;            // rows one load instruction of the workgroup covers
+  constexpr int NBLK = 256 / RPL;        // row blocks (= loads per lane) per operand per k-tile
+  constexpr int NL = 2 * NBLK;           // loads per lane per k-tile
+  constexpr int LPU = NL / 4;            // loads per unit
+  constexpr int NSLOT = 2 * NB;          // slots of 2 MFMAs per unit
 
-  const int tilesM = (g.M + BM - 1) / BM, tilesN = (g.N + BN - 1) / BN;
-  const int total = tilesM * tilesN;
-  int tid;
-  {
-    const int pid = blockIdx.x, xcd = pid % kXcds, q = pid / kXcds;
-    const int base = total / kXcds, rem = total % kXcds;
-    tid = xcd * base + (xcd < rem ? xcd : rem) + q;
-  }
-  const int group_m = g.group_m > 0 ? g.group_m : kGroupM;
-  const int width = group_m * tilesN;
-  const int group = tid / width, first_m = group * group_m;
-  const int gsz = (tilesM - first_m) < group_m ? (tilesM - first_m) : group_m;
-  int tm = first_m + (tid % width) % gsz, tn = (tid % width) / gsz;
-  if (g.group_m == kRegionWalk) {
-    // All 8 XCDs work on one 16 x 16 region of tiles at a time, as 2 x 4 blocks of 8 x 4 tiles (one block per XCD,
-    // one tile per compute unit): 32 operand strips feed 256 concurrent tiles, and what one XCD fetched is in the
-    // memory-side cache for the XCDs that share its strips.  Regions are walked down the rows first.
-    const int pid = blockIdx.x, xcd = pid % kXcds, q = pid / kXcds;
-    const int r = q / 32, sl = q % 32, regM = tilesM / 16;
-    tm = (r % regM) * 16 + (xcd % 2) * 8 + sl % 8;
-    tn = (r / regM) * 16 + (xcd / 2) * 4 + sl / 8;
-  }
+  int tm, tn;
+  big_tile(g, tm, tn);
   const int m0 = tm * BM, n0 = tn * BN;
 
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
@@ -563,9 +570,8 @@ __global__ __launch_bounds__(NW * 64) void gemm_nt_big_kernel(const GemmArgs g) 
   auto gload = [&](int kt, int stage, int idx) {
     const bool in_k = kt * BK + kc * CH < Kr;
     const uint32_t koff = (uint32_t)kt * 128u;
-    constexpr int order4[16] = {0, 8, 1, 9, 4, 10, 5, 11, 12, 13, 14, 15, 2, 3, 6, 7};
-    constexpr int order8[8] = {0, 4, 2, 5, 6, 7, 1, 3};
-    const int o = NW == 4 ? order4[idx] : order8[idx % 8];
+    constexpr int order[8] = {0, 4, 2, 5, 6, 7, 1, 3};
+    const int o = order[idx];
     if (o < NBLK)
       __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrcA, (lds_ptr_t)(smem + stage * STAGE + lds_wave + o * RPL * 128), 16,
                                                in_k ? voffA[o] + koff : kOutOfRange, 0, 0, 0);
@@ -602,20 +608,16 @@ __global__ __launch_bounds__(NW * 64) void gemm_nt_big_kernel(const GemmArgs g) 
   // A slot = up to two memory operations followed by 2 MFMAs.  Operation codes: 0 none, 1 + r: read A fragment r,
   // 5 + c: read B fragment c, 13 + i: the unit's load i.  Reads are ordered by first use in the next unit (A0, B0.., A1..).
   struct Slot { int a, b; };
-  constexpr Slot kWide4[16] = {{1, 0}, {5, 0}, {6, 0}, {13, 0}, {7, 0}, {8, 0}, {9, 0}, {14, 0},
-                               {10, 0}, {11, 0}, {12, 0}, {15, 0}, {2, 0}, {3, 0}, {4, 0}, {16, 0}};
-  constexpr Slot kNarrow4[16] = {{1, 0}, {0, 0}, {13, 0}, {0, 0}, {2, 0}, {0, 0}, {14, 0}, {0, 0},
-                                 {3, 0}, {0, 0}, {15, 0}, {0, 0}, {4, 0}, {0, 0}, {16, 0}, {0, 0}};
-  // 8 wavefronts: the reads go first (they have then returned when the unit ends in a barrier: +1 % over reads
+  // the reads go first (they have then returned when the unit ends in a barrier: +1 % over reads
   // spread through the unit), the loads after them
-  constexpr Slot kWide8[8] = {{1, 5}, {6, 7}, {8, 2}, {3, 4}, {13, 0}, {0, 0}, {14, 0}, {0, 0}};
-  constexpr Slot kNarrow8[8] = {{1, 2}, {3, 4}, {13, 0}, {0, 0}, {0, 0}, {14, 0}, {0, 0}, {0, 0}};
+  constexpr Slot kWide[8] = {{1, 5}, {6, 7}, {8, 2}, {3, 4}, {13, 0}, {0, 0}, {14, 0}, {0, 0}};
+  constexpr Slot kNarrow[8] = {{1, 2}, {3, 4}, {13, 0}, {0, 0}, {0, 0}, {14, 0}, {0, 0}, {0, 0}};
   // one unit: fragments of (h, kk) from af[buf], bfr[kk]; reads for the next unit (A fragments of (rh, rk) into
   // af[buf ^ 1], and, in a wide unit, the B fragments of sub-step rk) from stage rs; loads lbase.. of tile lkt into stage ls
   auto unit = [&](bool wide, int h, int kk, int buf, int rs, int rh, int rk, int lkt, int ls, int lbase) {
 #pragma unroll
     for (int sl = 0; sl < NSLOT; ++sl) {
-      const Slot so = NW == 4 ? (wide ? kWide4[sl % 16] : kNarrow4[sl % 16]) : (wide ? kWide8[sl % 8] : kNarrow8[sl % 8]);
+      const Slot so = wide ? kWide[sl] : kNarrow[sl];
 #pragma unroll
       for (int q = 0; q < 2; ++q) {
         const int op = q == 0 ? so.a : so.b;
@@ -679,7 +681,6 @@ __global__ __launch_bounds__(NW * 64) void gemm_nt_big_kernel(const GemmArgs g) 
     // before the staging.  (Applying the bf16 mask on the way out instead, from coalesced 16-byte loads of both layouts
     // of the activation, measured 2-3 % slower on short contractions.)  Against one shared 256 x 512-byte staging area
     // with a workgroup barrier around each pass: 8192 x 16384 products -4 % at K = 1024, -0.5 % at K = 16384.
-    static_assert(NW == 8, "the staged epilogue is laid out for 8 wavefronts of 128 x 64");
     typedef __attribute__((ext_vector_type(2))) unsigned int u32x2;
     const int rowW = m0 + wm * 128, colW = n0 + wn * WTN;     // origin of this wavefront's sub-tile
     // data gradient with the mask as bits: the 32 bits a lane needs per accumulator column are one dword
@@ -783,6 +784,291 @@ __global__ __launch_bounds__(NW * 64) void gemm_nt_big_kernel(const GemmArgs g) 
 #endif
 }
 
+// f(0), f(1), ... f(N - 1) with the index as a constant.
+template <typename F, int... I>
+__device__ __forceinline__ void static_for_impl(F f, std::integer_sequence<int, I...>) { (f(std::integral_constant<int, I>{}), ...); }
+template <int N, typename F>
+__device__ __forceinline__ void static_for(F f) { static_for_impl(f, std::make_integer_sequence<int, N>{}); }
+
+// The same 256x256 tile for long contractions (see big_is_long): 4 wavefronts of 128 x 128, one per SIMD, accumulators in 256 AGPRs.  Per
+// k-tile they read 128 KB of fragments from LDS where 8 wavefronts of 128 x 64 read 192, in a third fewer instructions, and what the chip saves
+// there it spends on a higher clock.  With one wavefront on a SIMD nothing else fills its issue slots: an MFMA takes the matrix pipe 16 cycles, so
+// between two of them there is room for about three other instructions, and any place with more of them is lost time.  So the k-loop has at
+// most two: fragment reads at every second or third MFMA, and loads whose LDS address (m0) is set in front of an MFMA and whose offset
+// holds nothing but one register and one scalar, every sixth (builtins with their address arithmetic in one place cost 160 cycles a k-tile).
+// The MFMAs are written as assembly so that the accumulators stay where they are: the register allocator otherwise moves a quarter of
+// them between VGPRs and AGPRs in every k-tile.
+// A k-tile is 128 MFMAs, m = 0 .. 63 of k-sub-step 0, then of 1; all 16 fragments of a sub-step are in registers before it starts:
+//   MFMA   0 ..  30   reads of sub-step 1
+//         40          barrier X: nobody reads this k-tile's stage any more
+//         42 .. 132   the 16 loads of k-tile kt + 2 into that stage (the last one in the next k-tile's time)
+//         79          barrier Y: k-tile kt + 1 has landed
+//         80 .. 125   reads of its sub-step 0
+// Cycles per k-tile, 8192 x 16384 x 16384 (2048 of them MFMAs): 2170 with no loads, 2260 with loads past the operands, 2310 with loads that all hit
+// the L2, 2430-2460 as it is; the kernel above 2360-2390 at a clock 5-8 % lower.
+template <int EPI>
+__global__ __launch_bounds__(256) void gemm_nt_long_kernel(const GemmArgs g) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  typedef bf16 T;
+  typedef __attribute__((ext_vector_type(4))) int i32x4;
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  __builtin_amdgcn_s_setprio(3);
+  constexpr int BM = 256, BN = 256, ES = 2, CH = 8, BK = 64;
+  constexpr int A_BYTES = BM * 128, STAGE = (BM + BN) * 128;
+  constexpr int RD1 = 0, X = 40, LD = 42, LD_STEP = 6, Y = 79, RD0 = 80;      // MFMA index of what the comment above lists
+  constexpr int kOwn = (128 - LD + LD_STEP - 1) / LD_STEP;                    // loads of a k-tile that do not go out in the next one's time
+  constexpr int kBeforeY = (Y - LD + LD_STEP - 1) / LD_STEP;                  // loads of k-tile kt + 2 that are out at barrier Y
+  static_assert(kOwn <= 16 && LD > X && LD + 15 * LD_STEP - 128 < X && RD1 + 2 * 15 < X && RD0 + 3 * 15 < 128, "order of the events of a k-tile");
+  int tm, tn;
+  big_tile(g, tm, tn);
+  const int m0 = tm * BM, n0 = tn * BN;
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+  const int wm = w & 1, wn = w >> 1;
+  const int lgrp = lane >> 4, lrow = lane & 15;
+
+  const int Kr = (g.K + CH - 1) / CH * CH;
+  const int nk = (Kr + BK - 1) / BK;
+  // the buffer resource by words: as an operand of assembly it has to be a vector
+  auto rsrc_of = [](const void* p, size_t bytes) {
+    const uint64_t a = (uint64_t)(uintptr_t)p;
+    return i32x4{(int)(uint32_t)a, (int)(uint32_t)(a >> 32), (int)bytes, 0x00020000};
+  };
+  const i32x4 rsrcA = rsrc_of(g.A, (size_t)g.M * g.lda * ES), rsrcB = rsrc_of(g.B, (size_t)g.N * g.ldb * ES);
+  // load i < 8 fills rows [32 i, 32 i + 32) of A's tile, i >= 8 of B's; wavefront w rows 8w .. 8w + 7 of those
+  const int prow = w * 8 + (lane >> 3);
+  const int pchunk = (lane & 7) ^ ((prow >> 1) & 7);
+  uint32_t voff[16];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) voff[i] = (uint32_t)(((size_t)(m0 + prow + 32 * i) * g.lda + pchunk * CH) * ES);
+#pragma unroll
+  for (int i = 0; i < 8; ++i) voff[8 + i] = (uint32_t)(((size_t)(n0 + prow + 32 * i) * g.ldb + pchunk * CH) * ES);
+  typedef __attribute__((address_space(3))) void* lds_ptr_t;
+  const uint32_t lds_wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)((uint32_t)(uintptr_t)(lds_ptr_t)smem + w * 8 * 128));
+
+  f32x4 acc[8][8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i)
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.0f;
+
+  // Chunks past K become zero fills: one that is past it in a k-tile is past it in all that follow.
+  auto clip = [&](int kt) {
+    if (kt * BK + BK > Kr) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i)
+        if (kt * BK + pchunk * CH >= Kr) voff[i] = kOutOfRange;
+    }
+  };
+  // The k offset is a scalar; k-tiles past the end, whose offsets are out of range already, take 0, so that no sum of the two wraps.
+  auto koff_of = [&](int kt) { return (uint32_t)(kt < nk ? kt : 0) * 128u; };
+#define SLP_LOAD "s_add_u32 m0, %[base], %[row]\n\t"
+#define SLP_LOAD_ARGS(i, base_, koff_)                                                                                             \
+  [base] "s"(base_), [row] "i"((i) < 8 ? (i) * 4096 : A_BYTES + ((i) - 8) * 4096), [off] "v"(voff[i]), [rsrc] "s"((i) < 8 ? rsrcA : rsrcB), \
+      [koff] "s"(koff_)
+  auto load = [&](int i, uint32_t base, uint32_t koff) {
+    asm volatile(SLP_LOAD "s_nop 1\n\tbuffer_load_dwordx4 %[off], %[rsrc], %[koff] offen lds" : : SLP_LOAD_ARGS(i, base, koff) : "memory", "scc");
+  };
+  u32x4 af[2][8], bfr[2][8];
+  uint32_t fa[2], fb[2];
+#pragma unroll
+  for (int kk = 0; kk < 2; ++kk) {
+    const uint32_t xo = (uint32_t)(((kk * 4 + lgrp) ^ ((lane >> 1) & 7)) << 4);
+    fa[kk] = (uint32_t)((wm * 128 + lrow) * 128) + xo;
+    fb[kk] = (uint32_t)(A_BYTES + (wn * 128 + lrow) * 128) + xo;
+  }
+  // fragment r of a sub-step in the order of their first use: A0, B0 .. B7, A1 .. A7
+  auto read = [&](int stage, int kk, int r) {
+    if (r == 0 || r > 8) {
+      const int i = r == 0 ? 0 : r - 8;
+      af[kk][i] = *(const u32x4*)(smem + stage * STAGE + fa[kk] + i * 2048);
+    } else {
+      bfr[kk][r - 1] = *(const u32x4*)(smem + stage * STAGE + fb[kk] + (r - 1) * 2048);
+    }
+  };
+  // MFMA m of a sub-step: A fragment m / 8 against the B fragments in turn, back and forth (see the kernel above)
+  auto mma = [&](int kk, int m) {
+    const int ia = m / 8, ib = (ia & 1) ? 7 - m % 8 : m % 8;
+    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc[ia][ib]) : "v"(af[kk][ia]), "v"(bfr[kk][ib]));
+  };
+  auto mma_load = [&](int kk, int m, int i, uint32_t base, uint32_t koff) {        // the MFMA is the wait state that m0 needs
+    const int ia = m / 8, ib = (ia & 1) ? 7 - m % 8 : m % 8;
+    asm volatile(SLP_LOAD "v_mfma_f32_16x16x32_bf16 %[acc], %[a], %[b], %[acc]\n\tbuffer_load_dwordx4 %[off], %[rsrc], %[koff] offen lds"
+                 : [acc] "+a"(acc[ia][ib]) : [a] "v"(af[kk][ia]), [b] "v"(bfr[kk][ib]), SLP_LOAD_ARGS(i, base, koff) : "memory", "scc");
+  };
+#define SLP_FENCE() __builtin_amdgcn_sched_barrier(0)
+#define SLP_BARRIER(cnt)                                            \
+  do {                                                              \
+    __builtin_amdgcn_s_waitcnt(cnt);                                \
+    asm volatile("" ::: "memory");                                  \
+    __builtin_amdgcn_s_barrier();                                   \
+    asm volatile("" ::: "memory");                                  \
+  } while (0)
+  constexpr int kLgkm0 = 0xC07F;         // every LDS read has returned
+  clip(0);
+  static_for<16>([&](auto i) { load(i, lds_wave, 0u); });
+  clip(1);
+  static_for<kOwn>([&](auto i) { load(i, lds_wave + STAGE, koff_of(1)); });
+  SLP_BARRIER(SLP_VMCNT(kOwn));
+#pragma unroll
+  for (int r = 0; r < 16; ++r) read(0, 0, r);
+  for (int kt = 0; kt < nk; ++kt) {
+    const int cur = kt & 1, nxt = cur ^ 1;
+    const uint32_t base1 = lds_wave + nxt * STAGE, base2 = lds_wave + cur * STAGE, koff1 = koff_of(kt + 1), koff2 = koff_of(kt + 2);
+    static_for<128>([&](auto pc) {
+      constexpr int p = decltype(pc)::value, late = p + 128 - LD, own = p - LD;
+      if constexpr (p == X) {
+        SLP_BARRIER(kLgkm0);
+        clip(kt + 2);
+      }
+      if constexpr (p == Y) SLP_BARRIER(SLP_VMCNT(kBeforeY));
+      if constexpr (p >= RD1 && (p - RD1) % 2 == 0 && (p - RD1) / 2 < 16) read(cur, 1, (p - RD1) / 2);
+      if constexpr (p >= RD0 && (p - RD0) % 3 == 0 && (p - RD0) / 3 < 16) read(nxt, 0, (p - RD0) / 3);
+      if constexpr (late % LD_STEP == 0 && late / LD_STEP < 16) mma_load(p / 64, p % 64, late / LD_STEP, base1, koff1);
+      else if constexpr (own >= 0 && own % LD_STEP == 0 && own / LD_STEP < 16) mma_load(p / 64, p % 64, own / LD_STEP, base2, koff2);
+      else mma(p / 64, p % 64);
+      SLP_FENCE();
+    });
+  }
+  // the last zero fills have landed, and the matrix pipe is done with the accumulators (the compiler does not see MFMAs in assembly)
+  __builtin_amdgcn_s_waitcnt(SLP_VMCNT(0));
+  asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+#pragma unroll
+  for (int i = 0; i < 64; ++i) asm volatile("" : "+a"(acc[i / 8][i % 8]));
+#undef SLP_FENCE
+#undef SLP_BARRIER
+#undef SLP_LOAD
+#undef SLP_LOAD_ARGS
+
+  if constexpr (EPI == EPI_WGRAD) {
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const int n = n0 + wn * 128 + j * 16 + lrow;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        float v[4];
+        asm volatile("" : "+a"(acc[i][j]));        // one block at a time leaves the AGPRs
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = acc[i][j][e];
+        store_quad<T, EPI>(g, n, m0 + wm * 128 + i * 16 + 4 * lgrp, 0.0f, v, lane);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  } else {
+    // Forward / data gradient: a wavefront stages its 128 x 128 sub-tile in a private 32 KB of the stages, transposed (128 rows n of 256
+    // bytes), and takes both layouts out of it: whole rows, and, through transposing LDS reads (a group of 16 lanes reads 4 rows of 16
+    // columns, lane l gets the 4 values of column l), pieces of 16 bytes of 64-byte row segments of the row-major output.  16-byte chunk c of
+    // staged row n sits at c ^ swz(n): 16 rows in a row lie on 16 chunks, and the 8 rows that half a wavefront reads transposed, 0 .. 3 and 8 .. 11
+    // or 4 .. 7 and 12 .. 15, on disjoint ones.  A row-major copy staged on its own cost 16 more instructions a block for the transpose
+    // inside lane quads: 8192 x 16384 outputs took 56000 cycles outside the k-loop where they now take
+    // 40000.
+    typedef __attribute__((ext_vector_type(2))) unsigned int u32x2;
+    typedef __attribute__((ext_vector_type(4))) short i16x4;
+    typedef __attribute__((address_space(3))) i16x4* lds_i16x4;
+    const int rowW = m0 + wm * 128, colW = n0 + wn * 128;
+    const bool edge = rowW + 128 > g.M || colW + 128 > g.N;      // uniform over the wavefront
+    const int Mr = (g.M + 7) & ~7;
+    float bias[8];
+    uint32_t mbits[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const int n = colW + j * 16 + lrow;
+      bias[j] = 0.0f;
+      mbits[j] = 0u;
+      if (EPI == EPI_FWD && n < g.N) bias[j] = g.bias[n];
+      if (EPI == EPI_DGRAD && g.bits && n < g.N && rowW < g.M) mbits[j] = g.bits[(size_t)n * g.ldbits + (rowW >> 5) + lgrp];
+    }
+    __syncthreads();
+    unsigned char* const st = smem + w * 32768;
+    auto swz = [](int n) { return ((n & 3) << 1) | (n & 8) | ((n >> 2) & 1); };
+    unsigned char* const wbase = st + lrow * 256 + (lgrp & 1) * 8;
+    const int wsw = (lgrp >> 1) ^ swz(lrow);
+    const bool relu = EPI == EPI_FWD && g.relu;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const int n = colW + j * 16 + lrow;
+      const bool col_ok = n < g.N;
+      uint32_t xw[2] = {0, 0};
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const int mb = rowW + i * 16 + 4 * lgrp;
+        float v[4];
+        asm volatile("" : "+a"(acc[i][j]));
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = acc[i][j][e];
+        if (EPI == EPI_FWD) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) v[e] += bias[j];
+          if (relu) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) asm("v_max_f32 %0, 0, %1" : "=v"(v[e]) : "v"(v[e]));
+          }
+        } else if (g.bits) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            v[e] = __builtin_bit_cast(float, __builtin_bit_cast(int, v[e]) & (((int)(mbits[j] << (31 - 4 * i - e))) >> 31));
+        } else if (g.maskT && col_ok && mb < Mr) {
+          const bf16x4 mk = *(const bf16x4*)((const bf16*)g.maskT + (size_t)n * g.ldmask + mb);
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (!((float)mk[e] > 0.0f)) v[e] = 0.0f;
+        }
+        if (edge) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (mb + e >= g.M || !col_ok) v[e] = 0.0f;
+        }
+        const bf16x4 o = {(bf16)v[0], (bf16)v[1], (bf16)v[2], (bf16)v[3]};
+        const u32x2 pk = __builtin_bit_cast(u32x2, o);
+        *(u32x2*)(wbase + j * 4096 + ((wsw ^ (2 * i)) << 4)) = pk;
+        if (EPI == EPI_FWD) {
+          uint32_t lo, hi;                         // 1 in each half that holds a positive value
+          asm("v_pk_max_i16 %0, %1, 0\n\tv_pk_min_i16 %0, %0, %2" : "=&v"(lo) : "v"(pk[0]), "s"(0x00010001));
+          asm("v_pk_max_i16 %0, %1, 0\n\tv_pk_min_i16 %0, %0, %2" : "=&v"(hi) : "v"(pk[1]), "s"(0x00010001));
+          xw[i >> 2] |= (lo | (hi << 2)) << (4 * (i & 3));
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if (EPI == EPI_FWD && g.bits_out && col_ok && rowW < g.M) {
+        uint32_t word = 0;
+#pragma unroll
+        for (int q = 0; q < 2; ++q) word |= ((xw[q] & 0x5555u) | ((xw[q] >> 15) & 0xAAAAu)) << (16 * q);
+        g.bits_out[(size_t)n * g.ldbits + (rowW >> 5) + lgrp] = word;
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    if (g.CT) {
+      const int r0 = lane >> 4, c = lane & 15, m = rowW + c * 8;
+#pragma unroll
+      for (int it = 0; it < 32; ++it) {
+        const int r = it * 4 + r0, n = colW + r;
+        const u32x4 val = *(const u32x4*)(st + r * 256 + ((c ^ swz(r & 15)) << 4));
+        if (n < g.N && m < Mr) *(u32x4*)((bf16*)g.CT + (size_t)n * g.ldct + m) = val;
+      }
+    }
+    if (g.C) {
+      const int gq = lane >> 4, jj = lane & 15;
+      const int r0 = gq * 8 + (jj >> 2);                           // staged row of the first of the two reads
+      const uint32_t base = (uint32_t)(r0 * 256 + ((((jj & 3) >> 1) ^ swz(r0 & 15)) << 4) + (jj & 1) * 8);
+#pragma unroll
+      for (int b = 0; b < 8; ++b) {
+        const int m = rowW + b * 16 + jj;
+#pragma unroll
+        for (int nq = 0; nq < 4; ++nq) {
+          const uint32_t o1 = (base ^ (b << 5)) + nq * 8192;
+          const i16x4 x = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4)(st + o1));
+          const i16x4 y = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4)(st + ((o1 ^ 16) + 1024)));
+          const u32x2 xu = __builtin_bit_cast(u32x2, x), yu = __builtin_bit_cast(u32x2, y);
+          const int n = colW + nq * 32 + gq * 8;
+          if (m < g.M && n < g.N) *(u32x4*)((bf16*)g.C + (size_t)m * g.ldc + n) = u32x4{xu[0], xu[1], yu[0], yu[1]};
+        }
+      }
+    }
+  }
+#endif
+}
+
 // ---- host side -------------------------------------------------------------------------------
 struct TileCfg { int bm, bn; const char* name; };
 const TileCfg kCfgs[3] = {{256, 256, "256x256"}, {128, 128, "128x128"}, {64, 64, "64x64"}};
@@ -849,12 +1135,37 @@ hipError_t configure_big() {
   return result;
 }
 
+// Whether the 256x256 tiles of a product run on 4 wavefronts (gemm_nt_long_kernel) instead of 8: from a length of the contraction on from which
+// the cheaper k-tiles outweigh an epilogue in which one wavefront a SIMD waits for its own LDS reads.  Milliseconds, 8 / 4 wavefronts:
+// forward 8192 x 16384, K = 784 0.290 / 0.300, 1024 0.303 / 0.308, 8192 x 8192, 1536 0.185 / 0.186, 2048 0.228 / 0.225, 4096 0.400 / 0.391, 8192 x
+// 16384 x 16384 2.93 / 2.84; weight gradient 16384 x 16384, 1024 0.668 / 0.674, 8192 x 8192, 2048 0.228 / 0.225, 3072 0.321 / 0.314, 16384 x
+// 16384 x 8192 3.08 / 3.00; data gradient 8192 x 16384, 1024 0.294 / 0.308, 16384 2.93 / 2.84.
+bool big_is_long(int K) { return K >= 2048; }
+
+template <int EPI>
+hipError_t configure_long() {
+  static std::once_flag once;
+  static hipError_t result = hipSuccess;
+  std::call_once(once, [] {
+    result = hipFuncSetAttribute((const void*)gemm_nt_long_kernel<EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, kBigSmem);
+  });
+  return result;
+}
+
 template <int EPI>
 hipError_t launch_big(const GemmArgs& g, hipStream_t s) {
   constexpr int smem = kBigSmem;
+  const int tiles = ((g.M + 255) / 256) * ((g.N + 255) / 256);
+  if constexpr (EPI != EPI_WGRAD_UPDATE) {
+    if (big_is_long(g.K)) {
+      hipError_t e = configure_long<EPI>();
+      if (e != hipSuccess) return e;
+      hipLaunchKernelGGL(gemm_nt_long_kernel<EPI>, dim3(tiles), dim3(256), smem, s, g);
+      return hipGetLastError();
+    }
+  }
   hipError_t e = configure_big<EPI>();
   if (e != hipSuccess) return e;
-  const int tiles = ((g.M + 255) / 256) * ((g.N + 255) / 256);
   hipLaunchKernelGGL((gemm_nt_big_kernel<EPI, kBigWaves>), dim3(tiles), dim3(kBigWaves * 64), smem, s, g);
   return hipGetLastError();
 }
@@ -889,8 +1200,11 @@ hipError_t launch_epi(int epi, int cfg, const GemmArgs& g, hipStream_t s) {
 template <typename T, int EPI>
 hipError_t configure_epi() {
   hipError_t e;
-  if constexpr (sizeof(T) == 2) e = configure_big<EPI>();
-  else e = configure_one<T, 256, 256, EPI, 8, 2>();
+  if constexpr (sizeof(T) == 2) {
+    e = configure_big<EPI>();
+    if constexpr (EPI != EPI_WGRAD_UPDATE)
+      if (e == hipSuccess) e = configure_long<EPI>();
+  } else e = configure_one<T, 256, 256, EPI, 8, 2>();
   if (e == hipSuccess) e = configure_one<T, 128, 128, EPI, 8, 4>();
   if (e == hipSuccess) e = configure_one<T, 128, 128, EPI, 4, 2>();
   if constexpr (sizeof(T) == 2 && (EPI == EPI_FWD || EPI == EPI_DGRAD)) {

@@ -1,0 +1,61 @@
+"""Products on 256x256 bf16 tiles with contractions of 2048 and more (4 wavefronts a tile), against float64 on the tensors as the library
+stored them: forward, data gradient and weight gradient, both layouts of the outputs and the mask bits between them.
+
+Tolerances against max|ref| of each tensor: bf16 rounds every stored tensor to 2^-9 of itself, a handful of them in a row: 2e-2.  The mask
+is exact: a data gradient is zero wherever the stored activation is.  A weight gradient of stored bf16 tensors is a float32 sum of exact
+products: 1e-4 is sqrt(K) 2^-24 of the row norm for K = 4352, times 25."""
+
+import math
+
+import pytest
+import torch
+
+from paper_2403_11204_amd import api
+
+pytestmark = pytest.mark.gpu
+
+
+def close(got, ref, tol):
+    got, ref = got.double(), ref.double()
+    return float((got - ref).abs().max()) <= tol * max(float(ref.abs().max()), 1e-30)
+
+
+# rows and columns on, one beside and half a tile beside an edge of the 256-wide tiles; contractions of whole k-tiles of 64, of one chunk of 8
+# more and of one chunk less, down to the shortest on this path; a batch shorter than what the one before it left in the buffers
+@pytest.mark.parametrize("B,widths", [(4096, (2048, 4096, 4096)), (4090, (2049, 4100, 4103)), (4225, (2056, 3968, 4352)), (3841, (2111, 4097, 4031))])
+def test_step_against_float64(B, widths):
+    g = torch.Generator(device="cuda").manual_seed(B + sum(widths))
+    rand = lambda *s: torch.rand(*s, generator=g, device="cuda") * 2 - 1
+    seg = api.Segment(list(widths), api.RELU_ALL, api.MSE_SIL, max_batch=B + 130, dtype=api.BF16, lr=0.0, momentum=0.0)
+    params = [(rand(n, k) / math.sqrt(k), rand(n) / math.sqrt(k)) for k, n in zip(widths, widths[1:])]
+    for l, (W, b) in enumerate(params):
+        seg.set_params(l, W, b)
+    for rows in (B + 130, B):
+        X, dA = rand(rows, widths[0]).bfloat16(), rand(rows, widths[-1]).bfloat16()
+        seg.step_external(X, dA)
+        a1, a2 = (seg.get_activation(l, rows) for l in (1, 2))
+        W16 = [W.bfloat16().double() for W, _ in params]
+        assert close(a1, torch.relu(X.double() @ W16[0].t() + params[0][1].double()), 2e-2)
+        assert close(a2, torch.relu(a1.double() @ W16[1].t() + params[1][1].double()), 2e-2)
+        dZ2, dZ1 = (seg.get_activation(l, rows, kind=1) for l in (2, 1))
+        assert torch.all(dZ1[a1 <= 0] == 0)
+        assert close(dZ1, (dZ2.double() @ W16[1]) * (a1 > 0), 2e-2)
+        assert close(seg.get_grads(1)[0], dZ2.double().t() @ a1.double(), 1e-4)      # reads both transposed copies
+        assert close(seg.get_grads(0)[0], dZ1.double().t() @ X.double(), 1e-4)
+
+
+# an infinite input: its row is what IEEE arithmetic gives, and nothing of it gets into rows and columns beside the matrix
+def test_an_infinite_input_stays_in_its_row():
+    B, widths = 4090, (2049, 4100, 4103)
+    g = torch.Generator(device="cuda").manual_seed(5)
+    seg = api.Segment(list(widths), api.RELU_ALL, api.MSE_SIL, max_batch=B, dtype=api.BF16, lr=0.0, momentum=0.0)
+    params = [(torch.rand((n, k), generator=g, device="cuda") / k + 1e-3, torch.zeros(n, device="cuda")) for k, n in zip(widths, widths[1:])]
+    for l, (W, b) in enumerate(params):
+        seg.set_params(l, W, b)
+    X = torch.rand((B, widths[0]), generator=g, device="cuda").bfloat16()
+    X[B - 1, 3] = float("inf")
+    out = seg.forward(X)
+    assert torch.all(torch.isinf(out[B - 1]))
+    assert torch.all(torch.isfinite(out[: B - 1]))
+    ref = torch.relu(torch.relu(X[: B - 1].double() @ params[0][0].bfloat16().double().t()) @ params[1][0].bfloat16().double().t())
+    assert close(out[: B - 1], ref, 2e-2)

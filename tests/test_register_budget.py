@@ -44,6 +44,14 @@ def test_big_product_kernels_fit_beside_the_update_kernel(kernel_metadata):
         assert v["vgpr_spill_count"] == 0 and v["private_segment_fixed_size"] == 0, (name, v)
 
 
+def test_long_product_kernels_fit_beside_the_update_kernel(kernel_metadata):
+    long = {n: v for n, v in kernel_metadata.items() if "gemm_nt_long_kernel" in n}
+    assert len(long) == 3, sorted(long)        # forward, data gradient, weight gradient
+    for name, v in long.items():
+        assert v["vgpr_count"] <= 448, (name, v)           # one wavefront of a workgroup on a SIMD, and one of the update's
+        assert v["vgpr_spill_count"] == 0 and v["private_segment_fixed_size"] == 0, (name, v)
+
+
 def test_no_product_kernel_spills(kernel_metadata):
     for name, v in kernel_metadata.items():
         if "gemm_nt" in name:
