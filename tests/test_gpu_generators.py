@@ -1,6 +1,6 @@
 """Generator kernels at the widths where their split into wavefront runs can go wrong, bit for bit against the oracle.
 
-A wavefront takes runs of 512 columns of one row, or 256 elements over the rows' ends where rows have at most 256 columns: the
+A wavefront takes runs of 256 columns of up to 16 rows, or 256 elements over the rows' ends where rows have at most 256 columns: the
 widths sit on and beside those edges, the row counts leave a last wavefront partly filled."""
 
 import numpy as np
@@ -40,6 +40,24 @@ def test_labels_inputs_and_weights(dim, rows):
     Wr, br = orng.init_weights(seed, 0, rows, dim)
     assert np.array_equal(bits(W), np.asarray(Wr, np.float32).view(np.uint32))
     assert np.array_equal(bits(b), np.asarray(br, np.float32).view(np.uint32))
+
+
+# 12288 waves of 256 columns and more take 2 to 16 rows each: a last one with fewer rows, a last run with one column, and the sample counter's low
+# word wrapping inside a wave's rows
+@pytest.mark.parametrize("rows,dim", [(12290, 257), (4099, 1025), (1537, 8192), (1031, 32769)])
+def test_several_rows_per_wavefront(rows, dim):
+    seed = (7 << 32) | dim
+    assert np.array_equal(bits(api.make_synthetic_labels(seed, rows, dim, api.UNIFORM_PM1)),
+                          orng.make_synthetic_labels(seed, rows, dim, api.UNIFORM_PM1).view(np.uint32))
+    table = api.make_synthetic_labels(seed, 3, dim, api.NORMAL)
+    y = datagen.balanced_classes(rows, 3)
+    part = slice(rows - 70, rows)            # the oracle's share, from 35 rows before the wrap on
+    first = (1 << 32) - rows + 35
+    ref = orng.make_segment_inputs(seed, table.cpu().numpy(), y[part], first + part.start, 0.05)
+    got = api.make_segment_inputs(seed, table, torch.from_numpy(y).cuda(), first, 0.05)
+    assert np.array_equal(bits(got[part]), ref.view(np.uint32))
+    again = api.make_segment_inputs(seed, table, torch.from_numpy(y[:64].copy()).cuda(), first, 0.05)      # one row per wavefront
+    assert torch.equal(got[:64], again)
 
 
 @pytest.mark.parametrize("seed, j", [(20, 0x7FFFFF), (28, 0xFFFFFE)])
