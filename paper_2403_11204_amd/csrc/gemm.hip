@@ -790,6 +790,29 @@ __device__ __forceinline__ void static_for_impl(F f, std::integer_sequence<int, 
 template <int N, typename F>
 __device__ __forceinline__ void static_for(F f) { static_for_impl(f, std::make_integer_sequence<int, N>{}); }
 
+// The order in which gemm_nt_long_kernel multiplies the 8 A fragments of a sub-step with its 8 B fragments: strips of two A rows, down the
+// columns and back up, so that from one MFMA to the next one operand changes, A and B in turn, and each is used again within two.  The chip is
+// power-limited here.  Milliseconds with one A fragment against all of B's, back and forth / strips of 4 / of 2: forward 8192 x 16384 x
+// 16384 2.793 / 2.787 / 2.763, data gradient 2.784 / 2.782 / 2.760, weight gradient 16384 x 16384 x 8192 2.937 / 2.912 / 2.902; pairs of columns
+// instead of rows the same.
+struct LongWalk {
+  int a[64], b[64], first[16];     // fragments of MFMA m; all fragments (0 .. 7 A, 8 .. 15 B) in the order of their first use
+  constexpr LongWalk() : a(), b(), first() {
+    for (int m = 0; m < 64; ++m) {
+      const int strip = m / 16, c = m % 16 / 2;
+      a[m] = 2 * strip + (c & 1 ? 1 - m % 2 : m % 2);
+      b[m] = strip & 1 ? 7 - c : c;
+    }
+    bool seen[16] = {};
+    for (int m = 0, n = 0; m < 64; ++m)
+      for (int f : {a[m], 8 + b[m]})
+        if (!seen[f]) {
+          seen[f] = true;
+          first[n++] = f;
+        }
+  }
+};
+
 // The same 256x256 tile for long contractions (see big_is_long): 4 wavefronts of 128 x 128, one per SIMD, accumulators in 256 AGPRs.  Per
 // k-tile they read 128 KB of fragments from LDS where 8 wavefronts of 128 x 64 read 192, in a third fewer instructions, and what the chip saves
 // there it spends on a higher clock.  With one wavefront on a SIMD nothing else fills its issue slots: an MFMA takes the matrix pipe 16 cycles, so
@@ -804,7 +827,7 @@ __device__ __forceinline__ void static_for(F f) { static_for_impl(f, std::make_i
 //         42 .. 132   the 16 loads of k-tile kt + 2 into that stage (the last one in the next k-tile's time)
 //         79          barrier Y: k-tile kt + 1 has landed
 //         80 .. 125   reads of its sub-step 0
-// Cycles per k-tile, 8192 x 16384 x 16384 (2048 of them MFMAs): 2170 with no loads, 2260 with loads past the operands, 2310 with loads that all hit
+// Cycles per k-tile, 8192 x 16384 x 16384 (2048 of them MFMAs), one A fragment against all of B's at a time: 2170 with no loads, 2260 with loads past the operands, 2310 with loads that all hit
 // the L2, 2430-2460 as it is; the kernel above 2360-2390 at a clock 5-8 % lower.
 template <int EPI>
 __global__ __launch_bounds__(256) void gemm_nt_long_kernel(const GemmArgs g) {
@@ -845,6 +868,19 @@ __global__ __launch_bounds__(256) void gemm_nt_long_kernel(const GemmArgs g) {
   typedef __attribute__((address_space(3))) void* lds_ptr_t;
   const uint32_t lds_wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)((uint32_t)(uintptr_t)(lds_ptr_t)smem + w * 8 * 128));
 
+  // what the epilogue reads, ahead of the operands
+  const int rowW = m0 + wm * 128, colW = n0 + wn * 128;
+  float bias[8];
+  uint32_t mbits[8];
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    const int n = colW + j * 16 + lrow;
+    bias[j] = 0.0f;
+    mbits[j] = 0u;
+    if (EPI == EPI_FWD && n < g.N) bias[j] = g.bias[n];
+    if (EPI == EPI_DGRAD && g.bits && n < g.N && rowW < g.M) mbits[j] = g.bits[(size_t)n * g.ldbits + (rowW >> 5) + lgrp];
+  }
+
   f32x4 acc[8][8];
 #pragma unroll
   for (int i = 0; i < 8; ++i)
@@ -878,22 +914,15 @@ __global__ __launch_bounds__(256) void gemm_nt_long_kernel(const GemmArgs g) {
     fa[kk] = (uint32_t)((wm * 128 + lrow) * 128) + xo;
     fb[kk] = (uint32_t)(A_BYTES + (wn * 128 + lrow) * 128) + xo;
   }
-  // fragment r of a sub-step in the order of their first use: A0, B0 .. B7, A1 .. A7
-  auto read = [&](int stage, int kk, int r) {
-    if (r == 0 || r > 8) {
-      const int i = r == 0 ? 0 : r - 8;
-      af[kk][i] = *(const u32x4*)(smem + stage * STAGE + fa[kk] + i * 2048);
-    } else {
-      bfr[kk][r - 1] = *(const u32x4*)(smem + stage * STAGE + fb[kk] + (r - 1) * 2048);
-    }
+  constexpr LongWalk walk;
+  auto read = [&](int stage, int kk, int f) {
+    if (f < 8) af[kk][f] = *(const u32x4*)(smem + stage * STAGE + fa[kk] + f * 2048);
+    else bfr[kk][f - 8] = *(const u32x4*)(smem + stage * STAGE + fb[kk] + (f - 8) * 2048);
   };
-  // MFMA m of a sub-step: A fragment m / 8 against the B fragments in turn, back and forth (see the kernel above)
-  auto mma = [&](int kk, int m) {
-    const int ia = m / 8, ib = (ia & 1) ? 7 - m % 8 : m % 8;
+  auto mma = [&](int kk, int ia, int ib) {
     asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc[ia][ib]) : "v"(af[kk][ia]), "v"(bfr[kk][ib]));
   };
-  auto mma_load = [&](int kk, int m, int i, uint32_t base, uint32_t koff) {        // the MFMA is the wait state that m0 needs
-    const int ia = m / 8, ib = (ia & 1) ? 7 - m % 8 : m % 8;
+  auto mma_load = [&](int kk, int ia, int ib, int i, uint32_t base, uint32_t koff) {        // the MFMA is the wait state that m0 needs
     asm volatile(SLP_LOAD "v_mfma_f32_16x16x32_bf16 %[acc], %[a], %[b], %[acc]\n\tbuffer_load_dwordx4 %[off], %[rsrc], %[koff] offen lds"
                  : [acc] "+a"(acc[ia][ib]) : [a] "v"(af[kk][ia]), [b] "v"(bfr[kk][ib]), SLP_LOAD_ARGS(i, base, koff) : "memory", "scc");
   };
@@ -912,22 +941,22 @@ __global__ __launch_bounds__(256) void gemm_nt_long_kernel(const GemmArgs g) {
   static_for<kOwn>([&](auto i) { load(i, lds_wave + STAGE, koff_of(1)); });
   SLP_BARRIER(SLP_VMCNT(kOwn));
 #pragma unroll
-  for (int r = 0; r < 16; ++r) read(0, 0, r);
+  for (int f = 0; f < 16; ++f) read(0, 0, f);
   for (int kt = 0; kt < nk; ++kt) {
     const int cur = kt & 1, nxt = cur ^ 1;
     const uint32_t base1 = lds_wave + nxt * STAGE, base2 = lds_wave + cur * STAGE, koff1 = koff_of(kt + 1), koff2 = koff_of(kt + 2);
     static_for<128>([&](auto pc) {
-      constexpr int p = decltype(pc)::value, late = p + 128 - LD, own = p - LD;
+      constexpr int p = decltype(pc)::value, kk = p / 64, ia = walk.a[p % 64], ib = walk.b[p % 64], late = p + 128 - LD, own = p - LD;
       if constexpr (p == X) {
         SLP_BARRIER(kLgkm0);
         clip(kt + 2);
       }
       if constexpr (p == Y) SLP_BARRIER(SLP_VMCNT(kBeforeY));
-      if constexpr (p >= RD1 && (p - RD1) % 2 == 0 && (p - RD1) / 2 < 16) read(cur, 1, (p - RD1) / 2);
-      if constexpr (p >= RD0 && (p - RD0) % 3 == 0 && (p - RD0) / 3 < 16) read(nxt, 0, (p - RD0) / 3);
-      if constexpr (late % LD_STEP == 0 && late / LD_STEP < 16) mma_load(p / 64, p % 64, late / LD_STEP, base1, koff1);
-      else if constexpr (own >= 0 && own % LD_STEP == 0 && own / LD_STEP < 16) mma_load(p / 64, p % 64, own / LD_STEP, base2, koff2);
-      else mma(p / 64, p % 64);
+      if constexpr (p >= RD1 && (p - RD1) % 2 == 0 && (p - RD1) / 2 < 16) read(cur, 1, walk.first[(p - RD1) / 2]);
+      if constexpr (p >= RD0 && (p - RD0) % 3 == 0 && (p - RD0) / 3 < 16) read(nxt, 0, walk.first[(p - RD0) / 3]);
+      if constexpr (late % LD_STEP == 0 && late / LD_STEP < 16) mma_load(kk, ia, ib, late / LD_STEP, base1, koff1);
+      else if constexpr (own >= 0 && own % LD_STEP == 0 && own / LD_STEP < 16) mma_load(kk, ia, ib, own / LD_STEP, base2, koff2);
+      else mma(kk, ia, ib);
       SLP_FENCE();
     });
   }
@@ -966,19 +995,8 @@ __global__ __launch_bounds__(256) void gemm_nt_long_kernel(const GemmArgs g) {
     typedef __attribute__((ext_vector_type(2))) unsigned int u32x2;
     typedef __attribute__((ext_vector_type(4))) short i16x4;
     typedef __attribute__((address_space(3))) i16x4* lds_i16x4;
-    const int rowW = m0 + wm * 128, colW = n0 + wn * 128;
     const bool edge = rowW + 128 > g.M || colW + 128 > g.N;      // uniform over the wavefront
     const int Mr = (g.M + 7) & ~7;
-    float bias[8];
-    uint32_t mbits[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const int n = colW + j * 16 + lrow;
-      bias[j] = 0.0f;
-      mbits[j] = 0u;
-      if (EPI == EPI_FWD && n < g.N) bias[j] = g.bias[n];
-      if (EPI == EPI_DGRAD && g.bits && n < g.N && rowW < g.M) mbits[j] = g.bits[(size_t)n * g.ldbits + (rowW >> 5) + lgrp];
-    }
     __syncthreads();
     unsigned char* const st = smem + w * 32768;
     auto swz = [](int n) { return ((n & 3) << 1) | (n & 8) | ((n >> 2) & 1); };
@@ -1038,30 +1056,45 @@ __global__ __launch_bounds__(256) void gemm_nt_long_kernel(const GemmArgs g) {
       }
       __builtin_amdgcn_sched_barrier(0);
     }
+    // 8 pieces at a time: their LDS reads are under way together
     if (g.CT) {
       const int r0 = lane >> 4, c = lane & 15, m = rowW + c * 8;
+      bf16* const out = (bf16*)g.CT + (size_t)(colW + r0) * g.ldct + m;
 #pragma unroll
-      for (int it = 0; it < 32; ++it) {
-        const int r = it * 4 + r0, n = colW + r;
-        const u32x4 val = *(const u32x4*)(st + r * 256 + ((c ^ swz(r & 15)) << 4));
-        if (n < g.N && m < Mr) *(u32x4*)((bf16*)g.CT + (size_t)n * g.ldct + m) = val;
+      for (int b = 0; b < 4; ++b) {
+        u32x4 val[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+          const int r = (8 * b + q) * 4 + r0;
+          val[q] = *(const u32x4*)(st + r * 256 + ((c ^ swz(r & 15)) << 4));
+        }
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+          const int r = (8 * b + q) * 4;
+          if (!edge || (colW + r + r0 < g.N && m < Mr)) *(u32x4*)(out + (size_t)r * g.ldct) = val[q];
+        }
       }
     }
     if (g.C) {
       const int gq = lane >> 4, jj = lane & 15;
       const int r0 = gq * 8 + (jj >> 2);                           // staged row of the first of the two reads
       const uint32_t base = (uint32_t)(r0 * 256 + ((((jj & 3) >> 1) ^ swz(r0 & 15)) << 4) + (jj & 1) * 8);
+      const int n = colW + gq * 8;
+      bf16* const out = (bf16*)g.C + (size_t)(rowW + jj) * g.ldc + n;
 #pragma unroll
-      for (int b = 0; b < 8; ++b) {
-        const int m = rowW + b * 16 + jj;
+      for (int b = 0; b < 8; b += 2) {
+        u32x2 val[8][2];
 #pragma unroll
-        for (int nq = 0; nq < 4; ++nq) {
-          const uint32_t o1 = (base ^ (b << 5)) + nq * 8192;
-          const i16x4 x = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4)(st + o1));
-          const i16x4 y = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4)(st + ((o1 ^ 16) + 1024)));
-          const u32x2 xu = __builtin_bit_cast(u32x2, x), yu = __builtin_bit_cast(u32x2, y);
-          const int n = colW + nq * 32 + gq * 8;
-          if (m < g.M && n < g.N) *(u32x4*)((bf16*)g.C + (size_t)m * g.ldc + n) = u32x4{xu[0], xu[1], yu[0], yu[1]};
+        for (int q = 0; q < 8; ++q) {
+          const uint32_t o1 = (base ^ ((b + q / 4) << 5)) + q % 4 * 8192;
+          val[q][0] = __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4)(st + o1)));
+          val[q][1] = __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4)(st + ((o1 ^ 16) + 1024))));
+        }
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+          const int r = (b + q / 4) * 16, c = q % 4 * 32;
+          if (!edge || (rowW + jj + r < g.M && n + c < g.N))
+            *(u32x4*)(out + (size_t)r * g.ldc + c) = u32x4{val[q][0][0], val[q][0][1], val[q][1][0], val[q][1][1]};
         }
       }
     }
@@ -1136,11 +1169,10 @@ hipError_t configure_big() {
 }
 
 // Whether the 256x256 tiles of a product run on 4 wavefronts (gemm_nt_long_kernel) instead of 8: from a length of the contraction on from which
-// the cheaper k-tiles outweigh an epilogue in which one wavefront a SIMD waits for its own LDS reads.  Milliseconds, 8 / 4 wavefronts:
-// forward 8192 x 16384, K = 784 0.290 / 0.300, 1024 0.303 / 0.308, 8192 x 8192, 1536 0.185 / 0.186, 2048 0.228 / 0.225, 4096 0.400 / 0.391, 8192 x
-// 16384 x 16384 2.93 / 2.84; weight gradient 16384 x 16384, 1024 0.668 / 0.674, 8192 x 8192, 2048 0.228 / 0.225, 3072 0.321 / 0.314, 16384 x
-// 16384 x 8192 3.08 / 3.00; data gradient 8192 x 16384, 1024 0.294 / 0.308, 16384 2.93 / 2.84.
-bool big_is_long(int K) { return K >= 2048; }
+// the cheaper k-tiles outweigh an epilogue in which one wavefront a SIMD waits for its own LDS reads, on ragged outputs too.  Microseconds, 8 / 4
+// wavefronts: forward 8192 x 8192, K = 1024 146 / 149, 2048 225 / 221, 8192 x 16384, 2048 461 / 449, 16384 2890 / 2770; data gradient 4100 x 4104,
+// 2050 103 / 106, 3072 129 / 130, 8192 x 16384, 2048 455 / 456; weight gradient 8192 x 8192, 3072 321 / 314, 16384 x 16384 x 8192 3075 / 2945.
+bool big_is_long(int K) { return K >= 3072; }
 
 template <int EPI>
 hipError_t configure_long() {
