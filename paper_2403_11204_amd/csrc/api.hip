@@ -182,6 +182,23 @@ int run_group(slp_segment* s, const SmallGroup& gr, hipStream_t st, bool small =
   return SLP_OK;
 }
 
+// The same for a last layer with its cross-entropy.
+int run_logits(slp_segment* s, const GemmArgs& g, const OutJob& out, hipStream_t st) {
+  ProfRec rec{nullptr, nullptr, 2.0 * g.M * (double)g.N * g.K};
+  if (s->prof) {
+    rec.a = get_event(s);
+    rec.b = get_event(s);
+    if (!rec.a || !rec.b) return fail(SLP_ERR_DEVICE, "hipEventCreate failed");
+    HIP_TRY(hipEventRecord(rec.a, st));
+  }
+  HIP_TRY(launch_logits(s->dtype, g, out, st));
+  if (s->prof) {
+    HIP_TRY(hipEventRecord(rec.b, st));
+    s->prof_log.push_back(rec);
+  }
+  return SLP_OK;
+}
+
 // The same for a chain of narrow layers.
 int run_chain(slp_segment* s, const ChainLaunch& c, hipStream_t st) {
   ProfRec rec{nullptr, nullptr, 0.0};
@@ -215,6 +232,12 @@ int ingest(slp_segment* s, const void* X, int batch, bool with_transpose, hipStr
   return SLP_OK;
 }
 
+// Whether the cross-entropy is formed in the launch of the last layer's forward product.  (With one layer that launch would have the input's
+// copies to make.)
+bool xent_in_product(const slp_segment* s, int batch) {
+  return s->loss == SLP_SOFTMAX_XENT && s->L > 1 && logits_fit(s->dtype, batch, s->widths[s->L], s->widths[s->L - 1]);
+}
+
 // Launches of a training step whose products are all small (one stream, no events); 0 for any other step.
 int direct_launches(const slp_segment* s, const void* X, int batch);
 
@@ -230,7 +253,7 @@ int direct_launches(const slp_segment* s, const void* X, int batch) {
         (l > 1 && !product_is_small(s->dtype, EPI_DGRAD, batch, s->widths[l - 1])))
       return 0;
   // ingest unless it rides along, forward, cross-entropy, data gradients (weight gradients ride along), the last weight gradients
-  return (reads_input(s, X, batch) ? 0 : 1) + s->L + (s->loss == SLP_MSE_SIL ? 0 : xent_launch_count(s->dtype, s->widths[s->L])) + (s->L - 1) + 1;
+  return (reads_input(s, X, batch) ? 0 : 1) + s->L + (s->loss == SLP_MSE_SIL || xent_in_product(s, batch) ? 0 : xent_launch_count(s->dtype, s->widths[s->L])) + (s->L - 1) + 1;
 }
 
 // The layers s + 1 .. L of a forward-only pass that go through one launch_chain, as s; L where there is no such run of two or more.  All of
@@ -255,7 +278,7 @@ struct Forward {
   void* out;                // forward-only: the caller's output buffer
   bool keeps_input;         // whether nothing is written to X before the last launch that could read it has ended, of one launch a layer
   bool apart;               // forward-only: the same of any number of layers a launch
-  const OutJob* last;       // training: the gradient of the output rides along with a small last layer
+  const OutJob* last;       // training: the gradient of the output rides along with a small last layer (neither table nor ext: cross-entropy)
   bool wait_by_layer;       // training: each layer's launches follow its update of the step before (see settle_step)
 };
 
@@ -292,7 +315,10 @@ int forward_layers(slp_segment* s, int batch, const Forward& f, hipStream_t st, 
     g.bias = ly.b; g.relu = relu_on(s, l) ? 1 : 0;
     int rc = f.wait_by_layer ? settle_layer(s, l, st) : SLP_OK;
     if (rc) return rc;
-    if (product_is_small(s->dtype, EPI_FWD, g.M, g.N)) {
+    if (l == s->L && f.last && !f.last->table && !f.last->ext && xent_in_product(s, batch)) {
+      rc = run_logits(s, g, *f.last, st);
+      *last_done = true;
+    } else if (product_is_small(s->dtype, EPI_FWD, g.M, g.N)) {
       SmallGroup gr{};
       gr.n = 1; gr.epi[0] = EPI_FWD;
       if (l == 1 && direct) {
@@ -301,7 +327,7 @@ int forward_layers(slp_segment* s, int batch, const Forward& f, hipStream_t st, 
         gr.copy = CopyJob{f.X, s->widths[0], batch, s->widths[0], s->A[0], s->ldw[0], f.training ? s->AT[0] : nullptr, s->ldb, rows_t};
       }
       if (l == s->L && f.out && f.out != g.C) { g.C2 = f.out; g.ldc2 = s->widths[l]; *out_done = true; }
-      if (l == s->L && f.last) { gr.epi[0] = EPI_FWD_OUT; gr.out = *f.last; *last_done = true; }
+      if (l == s->L && f.last && (f.last->table || f.last->ext)) { gr.epi[0] = EPI_FWD_OUT; gr.out = *f.last; *last_done = true; }
       gr.g[0] = g;
       rc = run_group(s, gr, st);
     } else {
@@ -335,10 +361,10 @@ int forward_and_loss(slp_segment* seg, const void* X, const int32_t* targets, in
   OutJob oj{};
   const bool mse = seg->loss == SLP_MSE_SIL;
   oj.y = targets; oj.table = seg->table; oj.classes = seg->classes;
-  oj.scale = (float)(2.0 / ((double)batch * (double)D));
+  oj.scale = mse ? (float)(2.0 / ((double)batch * (double)D)) : (float)(1.0 / (double)batch);
   oj.partials = seg->partials; oj.bad_ids = seg->bad_ids;
-  oj.dZ = seg->dZ[L]; oj.lddz = seg->ldw[L]; oj.dZT = seg->dZT[L]; oj.lddzt = seg->ldb;
-  int rc = forward_layers(seg, batch, Forward{true, X, nullptr, nullptr, nullptr, true, true, mse ? &oj : nullptr, wait_by_layer}, st, &out_done, &last_done);
+  oj.dZ = seg->dZ[L]; oj.lddz = seg->ldw[L]; oj.dZT = mse || with_transpose ? seg->dZT[L] : nullptr; oj.lddzt = seg->ldb;
+  int rc = forward_layers(seg, batch, Forward{true, X, nullptr, nullptr, nullptr, true, true, &oj, wait_by_layer}, st, &out_done, &last_done);
   if (rc) return rc;
   *sum = SumJob{seg->partials, 0, 0.0, seg->loss_dev, loss_out};
   if (mse) {
@@ -350,8 +376,9 @@ int forward_and_loss(slp_segment* seg, const void* X, const int32_t* targets, in
   } else {
     sum->scale = 1.0 / (double)batch;
     sum->n = batch;
-    HIP_TRY(launch_xent_loss_grad(seg->dtype, seg->A[L], seg->ldw[L], targets, batch, D, relu_on(seg, L) ? 1 : 0,
-                                  seg->dZ[L], with_transpose ? seg->dZT[L] : nullptr, seg->ldb, seg->partials, seg->bad_ids, st));
+    if (!last_done)
+      HIP_TRY(launch_xent_loss_grad(seg->dtype, seg->A[L], seg->ldw[L], targets, batch, D, relu_on(seg, L) ? 1 : 0,
+                                    seg->dZ[L], with_transpose ? seg->dZT[L] : nullptr, seg->ldb, seg->partials, seg->bad_ids, st));
   }
   return SLP_OK;
 }

@@ -143,48 +143,7 @@ __global__ __launch_bounds__(256) void xent_loss_grad_kernel(const T* __restrict
   for (int i = 0; i < NC; ++i)
 #pragma unroll
     for (int r = 0; r < 4; ++r) zv[i][r] = lane + 64 * i < C ? to_f32<T>(z[r][lane + 64 * i]) : -INFINITY;
-  float mx[4] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY}, sum[4] = {0.0f, 0.0f, 0.0f, 0.0f}, lse[4];
-#pragma unroll
-  for (int i = 0; i < NC; ++i) {
-    if (lane + 64 * i < C)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) mx[r] = fmaxf(mx[r], zv[i][r]);
-  }
-#pragma unroll
-  for (int r = 0; r < 4; ++r) mx[r] = wave_max(mx[r]);
-#pragma unroll
-  for (int i = 0; i < NC; ++i) {
-    if (lane + 64 * i < C)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) sum[r] += expf(zv[i][r] - mx[r]);
-  }
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    sum[r] = wave_sum(sum[r]);
-    lse[r] = mx[r] + logf(sum[r]);
-    const int id = min(max(cls[r], 0), C - 1);
-    if (lane == 0 && m0 + r < B) {
-      if (id != cls[r]) atomicAdd(bad_ids, 1u);
-      row_loss[m0 + r] = lse[r] - to_f32<T>(z[r][id]);
-    }
-    cls[r] = id;
-  }
-#pragma unroll
-  for (int i = 0; i < NC; ++i) {
-    const int c = lane + 64 * i;
-    if (c < C) {
-      vec4 g;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const float zc = zv[i][r];
-        const float p = expf(zc - lse[r]);
-        const float d = (p - (c == cls[r] ? 1.0f : 0.0f)) * inv_b;
-        g[r] = from_f32<T>((m0 + r >= B || (relu_last && !(zc > 0.0f))) ? 0.0f : d);
-        if (m0 + r < B) dZ[(size_t)(m0 + r) * ld + c] = g[r];
-      }
-      if (dZT) *(vec4*)(dZT + (size_t)c * ldt + m0) = g;
-    }
-  }
+  xent_rows<T, NC>(zv, cls, [&](int r, int id) { return to_f32<T>(z[r][id]); }, m0, B, C, relu_last, inv_b, dZ, ld, dZT, ldt, row_loss, bad_ids);
 }
 
 // Any number of classes: one row per wavefront, the logits read three times, and the transposed gradient by a launch of its own.

@@ -173,5 +173,57 @@ __device__ __forceinline__ void reduce_loss_block(double* red, const float* __re
   }
 }
 
+// Cross-entropy of four rows m0 .. m0 + 3 by one wavefront, whose lane holds logits zv[i][r] of columns lane + 64 i (past C: anything): losses,
+// gradient row-major and, one vector of the four rows per column, transposed (dZT may be null).  at(r, id): logit id of row r.
+template <typename T, int NC, typename At>
+__device__ __forceinline__ void xent_rows(const float (&zv)[NC][4], int (&cls)[4], At at, int m0, int B, int C, int relu_last, float inv_b,
+                                          T* __restrict__ dZ, int ld, T* __restrict__ dZT, int ldt, float* __restrict__ row_loss,
+                                          unsigned* __restrict__ bad_ids) {
+  typedef T vec4 __attribute__((ext_vector_type(4)));
+  const int lane = threadIdx.x & 63;
+  float mx[4] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY}, sum[4] = {0.0f, 0.0f, 0.0f, 0.0f}, lse[4];
+#pragma unroll
+  for (int i = 0; i < NC; ++i) {
+    if (lane + 64 * i < C)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) mx[r] = fmaxf(mx[r], zv[i][r]);
+  }
+#pragma unroll
+  for (int r = 0; r < 4; ++r) mx[r] = wave_max(mx[r]);
+#pragma unroll
+  for (int i = 0; i < NC; ++i) {
+    if (lane + 64 * i < C)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) sum[r] += expf(zv[i][r] - mx[r]);
+  }
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    sum[r] = wave_sum(sum[r]);
+    lse[r] = mx[r] + logf(sum[r]);
+    const int id = min(max(cls[r], 0), C - 1);
+    if (lane == 0 && m0 + r < B) {
+      if (id != cls[r]) atomicAdd(bad_ids, 1u);
+      row_loss[m0 + r] = lse[r] - at(r, id);
+    }
+    cls[r] = id;
+  }
+#pragma unroll
+  for (int i = 0; i < NC; ++i) {
+    const int c = lane + 64 * i;
+    if (c < C) {
+      vec4 g;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const float zc = zv[i][r];
+        const float p = expf(zc - lse[r]);
+        const float d = (p - (c == cls[r] ? 1.0f : 0.0f)) * inv_b;
+        g[r] = from_f32<T>((m0 + r >= B || (relu_last && !(zc > 0.0f))) ? 0.0f : d);
+        if (m0 + r < B) dZ[(size_t)(m0 + r) * ld + c] = g[r];
+      }
+      if (dZT) *(vec4*)(dZT + (size_t)c * ldt + m0) = g;
+    }
+  }
+}
+
 }  // namespace
 }  // namespace slp

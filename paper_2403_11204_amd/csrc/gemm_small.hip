@@ -466,6 +466,149 @@ hipError_t launch_product(const GemmArgs& g, int tile, int tiles, hipStream_t s)
   return hipGetLastError();
 }
 
+// The last layer's forward product and the cross-entropy behind it, for up to 64 classes: a workgroup owns 16 rows with all their columns (NT
+// tiles of 16), so that their logits need not be in memory before the loss is formed from them.  The products are those of TILE 16 above,
+// column tile by column tile, the rows' arithmetic that of the cross-entropy kernel: the same bits.  What bounds it is one
+// compute unit's stream of 16 rows of activations and all rows of the weights, where the product by itself spreads the columns over NT units;
+// six stages keep 80 KB of it in flight.  See logits_fit for where it is used.
+constexpr int kLogitStages = 6;
+constexpr int logit_lds(int nt) { return kLogitStages * 2 * 16 * (1 + nt) * 128; }
+template <typename T, int NT>
+__global__ __launch_bounds__(256) void logits_xent_kernel(const GemmArgs g, const OutJob out) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  constexpr int ES = sizeof(T), CH = Chunk<T>::elems, BK = 128 / ES;
+  constexpr int ROWS = 16 * (1 + NT), TSZ = ROWS * 128, STAGE = 2 * TSZ, NLD = 1 + NT;      // a stage: two k-tiles; loads of a wavefront per stage
+  constexpr bool kBoth = ES == 2;
+  constexpr int NJ = kBoth ? 1 : 2;
+  const int m0 = blockIdx.x * 16;
+  const int t = threadIdx.x, lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int l16 = lane & 15, g16 = lane >> 4;
+  // what the end needs, ahead of the operands: the bias of this wavefront's column tile, the class ids of its four rows
+  const int n = w * 16 + l16, mr = m0 + 4 * w;
+  const float bias = w < NT && n < g.N ? g.bias[n] : 0.0f;
+  int cls[4];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) cls[r] = out.y[min(mr + r, g.M - 1)];
+
+  const int Kr = (g.K + CH - 1) / CH * CH, nk = (Kr + BK - 1) / BK, nit = (nk + 1) / 2;
+  const __amdgpu_buffer_rsrc_t rsrcA =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(g.A), 0, (int)((size_t)g.M * g.lda * ES), 0x00020000);
+  const __amdgpu_buffer_rsrc_t rsrcB =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(g.B), 0, (int)((size_t)g.N * g.ldb * ES), 0x00020000);
+  // load i of wavefront w is number q = w + 4 i of a stage's: rows 8 (q mod ROWS / 8) .. + 7 of its k-tile q / (ROWS / 8)
+  const int lr = lane >> 3, lc = lane & 7;
+  uint32_t off[NLD];
+  int chunk[NLD];
+#pragma unroll
+  for (int i = 0; i < NLD; ++i) {
+    const int q = w + 4 * i, j = q / (ROWS / 8), row = q % (ROWS / 8) * 8 + lr;
+    const int pc = lc ^ (((row & 15) >> 1) & 7);
+    chunk[i] = j * BK + pc * CH;
+    off[i] = (uint32_t)((row < 16 ? (size_t)(m0 + row) * g.lda : (size_t)(row - 16) * g.ldb) * ES) + (uint32_t)chunk[i] * ES;
+  }
+  auto load = [&](int it, int stage) {         // past the end of K every load becomes a zero fill
+#pragma unroll
+    for (int i = 0; i < NLD; ++i) {
+      const int q = w + 4 * i;
+      const uint32_t o = it * 2 * BK + chunk[i] < Kr ? off[i] + (uint32_t)it * 256u : kOutOfRange;
+      const lds_ptr_t d = (lds_ptr_t)(smem + stage * STAGE + q * 1024);
+      if (q % (ROWS / 8) < 2) __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrcA, d, 16, o, 0, 0, 0);
+      else __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrcB, d, 16, o, 0, 0, 0);
+    }
+  };
+  const uint32_t fo = (uint32_t)((kBoth ? (g16 >> 1) * TSZ : 0) + l16 * 128 + (((2 * w + (g16 & 1)) ^ ((l16 >> 1) & 7)) << 4));
+  f32x4 acc[NT];
+#pragma unroll
+  for (int c = 0; c < NT; ++c) acc[c] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+  for (int s = 0; s < kLogitStages - 1; ++s) load(s, s);
+  int stage = 0, next = kLogitStages - 1;
+  for (int it = 0; it < nit; ++it) {
+    SLP_WAIT_BARRIER((kLogitStages - 2) * NLD);        // stage `it` has landed; nobody reads the one before any more
+    const unsigned char* d = smem + stage * STAGE + fo;
+    u32x4 af[NJ], bf[NJ][NT];
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+      af[j] = *(const u32x4*)(d + j * TSZ);
+#pragma unroll
+      for (int c = 0; c < NT; ++c) bf[j][c] = *(const u32x4*)(d + j * TSZ + (1 + c) * 2048);
+    }
+    load(it + kLogitStages - 1, next);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+#pragma unroll
+      for (int c = 0; c < NT; ++c) mma16(acc[c], af[j], bf[j][c], g16 >= 2, (T*)nullptr);
+    stage = stage + 1 == kLogitStages ? 0 : stage + 1;
+    next = next + 1 == kLogitStages ? 0 : next + 1;
+  }
+  __builtin_amdgcn_s_waitcnt(SLP_VMCNT(0));
+  __syncthreads();                 // the stages become the reduction buffer, [4 wavefronts][NT tiles][4 registers][64 lanes] ...
+  float* red = (float*)smem;
+  float* logits = red + 4 * NT * 256;        // ... and behind it the logits, [16 rows][64 columns]
+#pragma unroll
+  for (int c = 0; c < NT; ++c)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) red[((w * NT + c) * 4 + e) * 64 + lane] = acc[c][e];
+  __syncthreads();
+  if (w < NT) {                    // wavefront w finishes column tile w: rows 4 g16 .. + 3 of column n
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      float v = red[(w * 4 + e) * 64 + lane];
+#pragma unroll
+      for (int p = 1; p < 4; ++p) v += red[((p * NT + w) * 4 + e) * 64 + lane];
+      v += bias;
+      if (g.relu) v = fmaxf(v, 0.0f);
+      logits[(4 * g16 + e) * 64 + n] = (float)(T)v;
+    }
+  }
+  __syncthreads();
+  if (mr >= ((g.M + 7) & ~7)) return;
+  float zv[1][4];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int row = min(4 * w + r, g.M - 1 - m0);          // rows past the batch take its last one and store zeros
+    zv[0][r] = lane < g.N ? logits[row * 64 + lane] : -INFINITY;
+    if (mr + r < g.M && lane < g.N) ((T*)g.C)[(size_t)(mr + r) * g.ldc + lane] = (T)zv[0][r];
+  }
+  xent_rows<T, 1>(zv, cls, [&](int r, int id) { return logits[min(4 * w + r, g.M - 1 - m0) * 64 + id]; }, mr, g.M, g.N, g.relu, out.scale, (T*)out.dZ,
+                  out.lddz, (T*)out.dZT, out.lddzt, out.partials, out.bad_ids);
+#endif
+}
+
+template <typename T, int NT>
+hipError_t configure_logits() {
+  static std::once_flag once;
+  static hipError_t result = hipSuccess;
+  std::call_once(once, [] { result = hipFuncSetAttribute((const void*)logits_xent_kernel<T, NT>, hipFuncAttributeMaxDynamicSharedMemorySize, logit_lds(NT)); });
+  return result;
+}
+template <typename T, int NT>
+hipError_t launch_logits_nt(const GemmArgs& g, const OutJob& out, hipStream_t s) {
+  const hipError_t e = configure_logits<T, NT>();
+  if (e != hipSuccess) return e;
+  logits_xent_kernel<T, NT><<<(((g.M + 7) & ~7) + 15) / 16, 256, logit_lds(NT), s>>>(g, out);
+  return hipGetLastError();
+}
+template <typename T>
+hipError_t launch_logits_t(const GemmArgs& g, const OutJob& out, hipStream_t s) {
+  switch ((g.N + 15) / 16) {
+    case 1: return launch_logits_nt<T, 1>(g, out, s);
+    case 2: return launch_logits_nt<T, 2>(g, out, s);
+    case 3: return launch_logits_nt<T, 3>(g, out, s);
+    case 4: return launch_logits_nt<T, 4>(g, out, s);
+    default: return hipErrorInvalidValue;
+  }
+}
+template <typename T>
+hipError_t configure_logits_all() {
+  hipError_t e = configure_logits<T, 1>();
+  if (e == hipSuccess) e = configure_logits<T, 2>();
+  if (e == hipSuccess) e = configure_logits<T, 3>();
+  return e == hipSuccess ? configure_logits<T, 4>() : e;
+}
+
 template <typename T>
 hipError_t configure() {
   static std::once_flag once;
@@ -502,7 +645,28 @@ int small_tile_count(int dtype, int M, int N) {
 
 hipError_t small_configure_all() {
   hipError_t e = configure<bf16>();
-  return e == hipSuccess ? configure<float>() : e;
+  if (e == hipSuccess) e = configure<float>();
+  if (e == hipSuccess) e = configure_logits_all<bf16>();
+  return e == hipSuccess ? configure_logits_all<float>() : e;
+}
+
+// One launch less against columns that share a compute unit, whose float32 matrix rate is then the limit.  A step of 256-K-C, microseconds, product
+// and cross-entropy apart / in one launch: float32 64 rows, 64-47 19.7 / 15.7, 1024-10 21.6 / 19.5, 1410 rows, 60-47 24.3 / 22.5, 256 rows, 256-47
+// 20.2 / 18.5, 512-47 22.3 / 21.8, 1024-47 25.5 / 26.5, 2048-47 39.4 / 43.8, 1024-64 25.4 / 29.1; bf16 256 rows, 512-47 19.7 / 17.2, 4096-47 35.4 /
+// 34.1, 1024 rows, 1024-47 26.9 / 24.8, 4096-47 50.2 / 49.0, 2000 rows, 4096-47 64.1 / 62.0.
+bool logits_fit(int dtype, int M, int N, int K) {
+  if (N > 64 || !product_is_small(dtype, EPI_FWD, M, N) || small_tile(dtype, M, N) != 16) return false;
+  return dtype == 1 ? K <= 4096 : (N + 15) / 16 * K <= 1536;
+}
+
+hipError_t launch_logits(int dtype, const GemmArgs& g, const OutJob& out, hipStream_t s) {
+  const int es = dtype == 1 ? 2 : 4, ch = 16 / es;
+  auto off = [](const void* p) { return ((uintptr_t)p & 15) != 0; };
+  if (g.M <= 0 || g.N <= 0 || g.N > 64 || g.K <= 0 || !g.A || !g.B || off(g.A) || off(g.B) || g.lda % ch || g.ldb % ch) return hipErrorInvalidValue;
+  if ((size_t)g.M * g.lda * es >= 0x80000000ull || (size_t)g.N * g.ldb * es >= 0x80000000ull) return hipErrorInvalidValue;
+  if (!g.bias || !g.C || g.ldc < g.N || !out.y || !out.partials || !out.bad_ids || !out.dZ || out.lddz < g.N) return hipErrorInvalidValue;
+  if (out.dZT && (off(out.dZT) || out.lddzt % kLdAlign)) return hipErrorInvalidValue;
+  return dtype == 1 ? launch_logits_t<bf16>(g, out, s) : launch_logits_t<float>(g, out, s);
 }
 
 hipError_t launch_small_group(int dtype, const SmallGroup& group, hipStream_t s) {

@@ -108,6 +108,10 @@ struct SmallGroup {
 };
 hipError_t launch_small_group(int dtype, const SmallGroup& group, hipStream_t s);
 hipError_t small_configure_all();
+// The forward product of a last layer of few classes with the cross-entropy behind it, where that is the faster one (logits_fit): A = act(acc + bias)
+// to C, the gradient to out.dZ and, if not null, out.dZT, each row's loss to out.partials[m]; out.scale is 1 / batch.
+bool logits_fit(int dtype, int M, int N, int K);
+hipError_t launch_logits(int dtype, const GemmArgs& g, const OutJob& out, hipStream_t s);
 // Up to two products of larger layers on 128x128 tiles, weight gradients with their update (EPI_WGRAD_UPDATE, Cf set to store the
 // gradient as well) and data gradients (EPI_DGRAD with its mask row-major), and what hangs on them (no copy, no EPI_FWD_OUT).
 hipError_t launch_pair(int dtype, const SmallGroup& group, hipStream_t s);
