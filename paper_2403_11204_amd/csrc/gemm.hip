@@ -989,9 +989,8 @@ __global__ __launch_bounds__(256) void gemm_nt_long_kernel(const GemmArgs g) {
     // bytes), and takes both layouts out of it: whole rows, and, through transposing LDS reads (a group of 16 lanes reads 4 rows of 16
     // columns, lane l gets the 4 values of column l), pieces of 16 bytes of 64-byte row segments of the row-major output.  16-byte chunk c of
     // staged row n sits at c ^ swz(n): 16 rows in a row lie on 16 chunks, and the 8 rows that half a wavefront reads transposed, 0 .. 3 and 8 .. 11
-    // or 4 .. 7 and 12 .. 15, on disjoint ones.  A row-major copy staged on its own cost 16 more instructions a block for the transpose
-    // inside lane quads: 8192 x 16384 outputs took 56000 cycles outside the k-loop where they now take
-    // 40000.
+    // or 4 .. 7 and 12 .. 15, on disjoint ones.  A row-major copy staged on its own took 16 more instructions a block for the transpose
+    // inside lane quads and half of the staging's LDS writes.
     typedef __attribute__((ext_vector_type(2))) unsigned int u32x2;
     typedef __attribute__((ext_vector_type(4))) short i16x4;
     typedef __attribute__((address_space(3))) i16x4* lds_i16x4;
