@@ -899,12 +899,16 @@ __global__ __launch_bounds__(256) void gemm_nt_long_kernel(const GemmArgs g) {
   };
   // The k offset is a scalar; k-tiles past the end, whose offsets are out of range already, take 0, so that no sum of the two wraps.
   auto koff_of = [&](int kt) { return (uint32_t)(kt < nk ? kt : 0) * 128u; };
+  // The statements name the m0 they set, so that one set by the compiler for an access of its own does not pass for still set behind them; it
+  // warns of every register it reserves.
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
 #define SLP_LOAD "s_add_u32 m0, %[base], %[row]\n\t"
 #define SLP_LOAD_ARGS(i, base_, koff_)                                                                                             \
   [base] "s"(base_), [row] "i"((i) < 8 ? (i) * 4096 : A_BYTES + ((i) - 8) * 4096), [off] "v"(voff[i]), [rsrc] "s"((i) < 8 ? rsrcA : rsrcB), \
       [koff] "s"(koff_)
   auto load = [&](int i, uint32_t base, uint32_t koff) {
-    asm volatile(SLP_LOAD "s_nop 1\n\tbuffer_load_dwordx4 %[off], %[rsrc], %[koff] offen lds" : : SLP_LOAD_ARGS(i, base, koff) : "memory", "scc");
+    asm volatile(SLP_LOAD "s_nop 1\n\tbuffer_load_dwordx4 %[off], %[rsrc], %[koff] offen lds" : : SLP_LOAD_ARGS(i, base, koff) : "memory", "scc", "m0");
   };
   u32x4 af[2][8], bfr[2][8];
   uint32_t fa[2], fb[2];
@@ -924,7 +928,7 @@ __global__ __launch_bounds__(256) void gemm_nt_long_kernel(const GemmArgs g) {
   };
   auto mma_load = [&](int kk, int ia, int ib, int i, uint32_t base, uint32_t koff) {        // the MFMA is the wait state that m0 needs
     asm volatile(SLP_LOAD "v_mfma_f32_16x16x32_bf16 %[acc], %[a], %[b], %[acc]\n\tbuffer_load_dwordx4 %[off], %[rsrc], %[koff] offen lds"
-                 : [acc] "+a"(acc[ia][ib]) : [a] "v"(af[kk][ia]), [b] "v"(bfr[kk][ib]), SLP_LOAD_ARGS(i, base, koff) : "memory", "scc");
+                 : [acc] "+a"(acc[ia][ib]) : [a] "v"(af[kk][ia]), [b] "v"(bfr[kk][ib]), SLP_LOAD_ARGS(i, base, koff) : "memory", "scc", "m0");
   };
 #define SLP_FENCE() __builtin_amdgcn_sched_barrier(0)
 #define SLP_BARRIER(cnt)                                            \
@@ -969,6 +973,7 @@ __global__ __launch_bounds__(256) void gemm_nt_long_kernel(const GemmArgs g) {
 #undef SLP_BARRIER
 #undef SLP_LOAD
 #undef SLP_LOAD_ARGS
+#pragma clang diagnostic pop
 
   if constexpr (EPI == EPI_WGRAD) {
 #pragma unroll

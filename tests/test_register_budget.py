@@ -4,7 +4,8 @@ Two wavefronts of a product workgroup share a SIMD's 512 registers per lane with
 need 64: above 224 registers per lane (or with spills) the update no longer runs beside the products and a training step
 of the large configurations gets ~10 % slower without any test of the arithmetic noticing.  The kernel of small layers holds
 all its tile variants, and its epilogue's operands over the k-loop: a spill there would cost every launch.  This compiles the
-device code with the library's own flags and reads the register counts out of the code objects' metadata.
+device code with the library's own flags and reads the register counts out of the code objects' metadata.  What the
+kernels' assembly writes beside its operands has to be known to the compiler; that is read out of the intermediate code.
 """
 import os
 import re
@@ -80,3 +81,22 @@ def test_the_update_kernel_fits_beside_the_products():
     for name, v in update.items():
         assert v["vgpr_count"] <= 64, (name, v)
         assert v["vgpr_spill_count"] == 0 and v["private_segment_fixed_size"] == 0, (name, v)
+
+
+@pytest.mark.parametrize("unit", sorted(build.UNITS))
+def test_assembly_names_what_it_writes(unit):
+    with tempfile.TemporaryDirectory() as tmp:
+        out = os.path.join(tmp, "unit.ll")
+        cmd = [build.hipcc()] + [a for a in build.COMMON if a != "-fPIC"] + build.UNITS[unit] + ["--cuda-device-only", "-S", "-emit-llvm", "-Xclang", "-disable-llvm-passes", os.path.join(build.CSRC, unit), "-o", out]
+        r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+        assert r.returncode == 0, r.stdout[-2000:]
+        statements = re.findall(r'asm (?:sideeffect )?"([^"]*)", "([^"]*)"', open(out).read())
+    assert len(statements) > 0 or unit != "gemm.hip"
+    for text, constraints in statements:
+        for line in re.split(r"\\0A(?:\\09)?", text):
+            op, _, operands = line.strip().partition(" ")
+            written = operands.split(",")[0].strip()
+            if re.fullmatch(r"m0|vcc|exec|[sva]\d+", written):
+                assert "~{%s}" % written in constraints, (line, constraints)
+            if re.match(r"s_(add|sub|and|or|xor|lsh[lr]|cmp)", op):
+                assert "~{scc}" in constraints, (line, constraints)
