@@ -39,9 +39,9 @@ __device__ __forceinline__ Words philox4x32_10(uint32_t c0, uint32_t c1, uint32_
   return Words{c0, c1};
 }
 
-// The counter is (column, row, stream, high word), and three rounds pass before column and row have met in every word.  What of those rounds
-// depends on the column alone is computed once for all rows that a lane takes of it (three of the seven products of an element's first
-// three rounds that are left on the vector units), what depends on the row alone once per row on the scalar unit.
+// The counter is (column, row, stream, high word), and three rounds pass before column and row have met in every word.  Of their six products
+// three depend on the column alone and are computed once for all rows that a lane takes of it, two on what a wavefront shares (stream, row) and
+// are on the scalar unit, and one is left for every element.
 struct ColumnPart { uint32_t x2, x0, y2, c3; };
 __device__ __forceinline__ ColumnPart column_part(uint32_t column, uint32_t stream, uint32_t high, uint32_t k0, uint32_t k1) {
   const uint64_t a = (uint64_t)kM0 * column;                                                    // round 1, word 0
@@ -147,55 +147,75 @@ __device__ __forceinline__ void store_value(float* out, size_t idx, float v) { o
 __device__ __forceinline__ void store_value(__bf16* out, size_t idx, float v) { out[idx] = (__bf16)v; }
 
 // Every kernel here is bound by its integer and float instructions (10 rounds of two 64-bit products, then the transform),
-// not by the bytes it writes.  A wavefront therefore takes kRun columns of `deep` rows, column by column across its lanes: a row's
-// index is uniform over the wavefront, so that what depends on it is done once per run on the scalar unit, the columns' share of the
-// counter arithmetic stays in registers from row to row, and the stores are coalesced whatever the alignment of a row.
-// fn(row, column, words of the counter) is called for every element, whole runs without a test per column; low(row), high(row) give the row's
-// words of the counter.
+// not by the bytes it writes.  A wavefront therefore takes a run of kRun columns of ONE row, column by column across its
+// lanes: the row's index is uniform over the wavefront, so the division that finds it and every part of the counter
+// arithmetic that depends on the row and the key only is done once per run on the scalar unit, and the stores are
+// coalesced whatever the alignment of a row.  fn(row, column) is called for every element, whole runs without a test per column.
 // 8192 x 16384 bf16 inputs and their 1000 x 16384 table, both calls: one element per lane with a 64-bit division each, the
-// general division and square root and separate halves of the products 564 us, 512 columns of one row at a time 323, 256 of 16 rows
-// 293 (the inputs 3 of 17 products and 5 of 18 three-way xors an element fewer); what is left is issued at the rate of the vector units.
+// general division and square root and separate halves of the products 564 us -> 323 us (with several rows per wavefront, below, 293); what is
+// left is issued at the rate of the vector units.  Unrolled by 4: by 2 +5 %, by 8 the same.
 // Rows of up to kFlat columns leave too many lanes without one and pay for the row too often: there a wavefront takes kFlat elements
 // as they lie, over the rows' ends; one division on the scalar unit for the first, by 2^32 / cols for the others.  200000 rows of
-// float32 inputs, microseconds, one element per lane as before / 512 columns of a row (up to 32 columns several rows per wavefront) / this:
+// float32 inputs, microseconds, one element per lane as before / a run per row (up to 32 columns several rows per wavefront) / this:
 // 17 columns 19.5 / 23.9 / 14.9, 33 33.3 / 50.2 / 25.0, 47 45.6 / 51.5 / 32.9, 60 57 / 51 / 40, 65 61 / 72 / 43, 72 67 / 73 / 47;
 // 300 232 / 157 / 178.
-constexpr int kRun = 256, kFlat = 256, kDeepest = 16;
-struct Grid { uint32_t rows, cols, reciprocal, deep; };
-template <typename L, typename H, typename F>
-__device__ __forceinline__ void for_each_element(const Grid& g, uint32_t stream, uint32_t k0, uint32_t k1, L low, H high, F fn) {
+constexpr int kRun = 512, kFlat = 256;
+template <typename F>
+__device__ __forceinline__ void for_each_element(uint32_t rows, uint32_t cols, uint32_t reciprocal, F fn) {
   const uint32_t lane = threadIdx.x & 63;
   const uint64_t waves = (uint64_t)gridDim.x * 4;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  if (g.reciprocal) {
-    const uint64_t total = (uint64_t)g.rows * g.cols;
+  if (reciprocal) {
+    const uint64_t total = (uint64_t)rows * cols;
     for (uint64_t u = (uint64_t)blockIdx.x * 4 + wave; u * kFlat < total; u += waves) {
       const uint64_t first = u * kFlat, left = total - first;
-      const uint32_t r0 = total >> 32 ? (uint32_t)(first / g.cols) : (uint32_t)first / g.cols, c0 = (uint32_t)(first - (uint64_t)r0 * g.cols);
+      const uint32_t r0 = total >> 32 ? (uint32_t)(first / cols) : (uint32_t)first / cols, c0 = (uint32_t)(first - (uint64_t)r0 * cols);
 #pragma unroll
       for (uint32_t j = 0; j < kFlat; j += 64)
         if (j + lane < left) {
           const uint32_t e = c0 + j + lane;                     // below cols + kFlat: the quotient is at most one too small
-          uint32_t q = __umulhi(e, g.reciprocal), c = e - q * g.cols;
-          if (c >= g.cols) { ++q; c -= g.cols; }
-          fn(r0 + q, c, philox4x32_10(c, low(r0 + q), stream, high(r0 + q), k0, k1));
+          uint32_t q = __umulhi(e, reciprocal), c = e - q * cols;
+          if (c >= cols) { ++q; c -= cols; }
+          fn(r0 + q, c);
         }
     }
     return;
   }
-  const uint32_t runs = (g.cols + kRun - 1) / kRun;
-  const uint64_t units = (uint64_t)((g.rows + g.deep - 1) / g.deep) * runs;
+  const uint32_t runs = (cols + kRun - 1) / kRun;
+  const uint64_t units = (uint64_t)rows * runs;
   for (uint64_t u = (uint64_t)blockIdx.x * 4 + wave; u < units; u += waves) {
-    const uint32_t r0 = (uint32_t)(u / runs) * g.deep, c0 = (uint32_t)(u % runs) * kRun;
-    const uint32_t r1 = g.rows - r0 < g.deep ? g.rows : r0 + g.deep;
-    ColumnPart cp[kRun / 64];
+    const uint32_t r = (uint32_t)(u / runs), c0 = (uint32_t)(u % runs) * kRun;
+    if (cols - c0 >= kRun) {
+#pragma unroll 4
+      for (int j = 0; j < kRun / 64; ++j) fn(r, c0 + 64 * j + lane);
+    } else {
+      for (uint32_t c = c0 + lane; c < cols; c += 64) fn(r, c);
+    }
+  }
+}
+
+// Large matrices (see rows_per_wave): a wavefront takes kDeepRun columns of `deep` rows, and the columns' share of the counter arithmetic stays in
+// registers from row to row: for inputs 14 products and 13 three-way xors an element instead of 17 and 18.
+// fn(row, column, words of the counter); low(row), high(row) give the row's words of the counter.
+constexpr int kDeepRun = 256;
+template <typename L, typename H, typename F>
+__device__ __forceinline__ void for_each_of_rows(uint32_t rows, uint32_t cols, uint32_t deep, uint32_t stream, uint32_t k0, uint32_t k1, L low, H high, F fn) {
+  const uint32_t lane = threadIdx.x & 63;
+  const uint64_t waves = (uint64_t)gridDim.x * 4;
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t runs = (cols + kDeepRun - 1) / kDeepRun;
+  const uint64_t units = (uint64_t)((rows + deep - 1) / deep) * runs;
+  for (uint64_t u = (uint64_t)blockIdx.x * 4 + wave; u < units; u += waves) {
+    const uint32_t r0 = (uint32_t)(u / runs) * deep, c0 = (uint32_t)(u % runs) * kDeepRun;
+    const uint32_t r1 = rows - r0 < deep ? rows : r0 + deep;
+    ColumnPart cp[kDeepRun / 64];
     uint32_t h = high(r0);
     auto columns = [&]() {
 #pragma unroll
-      for (int j = 0; j < kRun / 64; ++j) cp[j] = column_part(c0 + 64 * j + lane, stream, h, k0, k1);
+      for (int j = 0; j < kDeepRun / 64; ++j) cp[j] = column_part(c0 + 64 * j + lane, stream, h, k0, k1);
     };
     columns();
-    const bool whole = g.cols - c0 >= kRun;
+    const bool whole = cols - c0 >= kDeepRun;
     for (uint32_t r = r0; r < r1; ++r) {
       if (high(r) != h) {          // the row's index went past 2^32
         h = high(r);
@@ -204,72 +224,121 @@ __device__ __forceinline__ void for_each_element(const Grid& g, uint32_t stream,
       const RowPart rp = row_part(low(r), stream, k0, k1);
       if (whole) {
 #pragma unroll
-        for (int j = 0; j < kRun / 64; ++j) fn(r, c0 + 64 * j + lane, philox_of(cp[j], rp, k0, k1));
+        for (int j = 0; j < kDeepRun / 64; ++j) fn(r, c0 + 64 * j + lane, philox_of(cp[j], rp, k0, k1));
       } else {
 #pragma unroll
-        for (int j = 0; j < kRun / 64; ++j)
-          if (c0 + 64 * j + lane < g.cols) fn(r, c0 + 64 * j + lane, philox_of(cp[j], rp, k0, k1));
+        for (int j = 0; j < kDeepRun / 64; ++j)
+          if (c0 + 64 * j + lane < cols) fn(r, c0 + 64 * j + lane, philox_of(cp[j], rp, k0, k1));
       }
     }
   }
 }
 
 template <typename T, int DIST>
-__global__ __launch_bounds__(256) void labels_kernel(uint32_t k0, uint32_t k1, Grid g, float kappa, T* __restrict__ out) {
-  for_each_element(g, 0u, k0, k1, [](uint32_t j) { return j; }, [](uint32_t) { return 0u; },
-                   [&](uint32_t j, uint32_t i, const Words& w) { store_value(out, (size_t)j * g.cols + i, draw<DIST>(kappa, w)); });
+__global__ __launch_bounds__(256) void labels_kernel(uint32_t k0, uint32_t k1, int classes, int dim, float kappa, T* __restrict__ out,
+                                                     uint32_t reciprocal) {
+  for_each_element(classes, dim, reciprocal, [&](uint32_t j, uint32_t i) {
+    store_value(out, (size_t)j * dim + i, draw<DIST>(kappa, philox4x32_10(i, j, 0u, 0u, k0, k1)));
+  });
+}
+template <typename T, int DIST>
+__global__ __launch_bounds__(256) void labels_rows_kernel(uint32_t k0, uint32_t k1, int classes, int dim, float kappa, T* __restrict__ out,
+                                                          uint32_t deep) {
+  for_each_of_rows(classes, dim, deep, 0u, k0, k1, [](uint32_t j) { return j; }, [](uint32_t) { return 0u; },
+                   [&](uint32_t j, uint32_t i, const Words& w) { store_value(out, (size_t)j * dim + i, draw<DIST>(kappa, w)); });
 }
 
 template <typename T>
+__device__ __forceinline__ void store_input(const float* __restrict__ table, int classes, const int32_t* __restrict__ y, uint32_t row, int dim, uint32_t i,
+                                            float sigma, const Words& w, T* __restrict__ out) {
+  const float z = standard_normal(w.r0, w.r1);
+  const int cls = min(max(y[row], 0), classes - 1);
+  const float v = __fadd_rn(table[(size_t)cls * dim + i], __fmul_rn(sigma, z));
+  store_value(out, (size_t)row * dim + i, v);
+}
+template <typename T>
 __global__ __launch_bounds__(256) void inputs_kernel(uint32_t k0, uint32_t k1, const float* __restrict__ table, int classes,
-                                                     const int32_t* __restrict__ y, uint64_t first, Grid g, float sigma,
-                                                     T* __restrict__ out) {
-  for_each_element(g, 2u, k0, k1, [&](uint32_t row) { return (uint32_t)(first + row); }, [&](uint32_t row) { return (uint32_t)((first + row) >> 32); },
-                   [&](uint32_t row, uint32_t i, const Words& w) {
-    const float z = standard_normal(w.r0, w.r1);
-    const int cls = min(max(y[row], 0), classes - 1);
-    const float v = __fadd_rn(table[(size_t)cls * g.cols + i], __fmul_rn(sigma, z));
-    store_value(out, (size_t)row * g.cols + i, v);
+                                                     const int32_t* __restrict__ y, uint64_t first, int batch, int dim, float sigma,
+                                                     T* __restrict__ out, uint32_t reciprocal) {
+  for_each_element(batch, dim, reciprocal, [&](uint32_t row, uint32_t i) {
+    const uint64_t n = first + row;
+    store_input(table, classes, y, row, dim, i, sigma, philox4x32_10(i, (uint32_t)n, 2u, (uint32_t)(n >> 32), k0, k1), out);
   });
 }
+template <typename T>
+__global__ __launch_bounds__(256) void inputs_rows_kernel(uint32_t k0, uint32_t k1, const float* __restrict__ table, int classes,
+                                                          const int32_t* __restrict__ y, uint64_t first, int batch, int dim, float sigma,
+                                                          T* __restrict__ out, uint32_t deep) {
+  for_each_of_rows(batch, dim, deep, 2u, k0, k1, [&](uint32_t row) { return (uint32_t)(first + row); }, [&](uint32_t row) { return (uint32_t)((first + row) >> 32); },
+                   [&](uint32_t row, uint32_t i, const Words& w) { store_input(table, classes, y, row, dim, i, sigma, w, out); });
+}
 
-__global__ __launch_bounds__(256) void init_kernel(uint32_t k0, uint32_t k1, uint32_t layer, float* __restrict__ W, Grid g, int K,
-                                                   int ldk, float* __restrict__ b) {
+__device__ __forceinline__ void store_weight(float* __restrict__ W, int K, int ldk, float* __restrict__ b, uint32_t o, uint32_t k, float bound, const Words& w) {
+  const float v = __fmul_rn(__fsub_rn(__fmul_rn(2.0f, unit_uniform(w.r0)), 1.0f), bound);
+  if ((int)k < K) W[(size_t)o * ldk + k] = v;
+  else b[o] = v;
+}
+__global__ __launch_bounds__(256) void init_kernel(uint32_t k0, uint32_t k1, uint32_t layer, float* __restrict__ W, int N, int K,
+                                                   int ldk, float* __restrict__ b, uint32_t reciprocal) {
   const float bound = __fdiv_rn(1.0f, correctly_rounded_sqrt((float)K));
-  for_each_element(g, 1u, k0, k1, [](uint32_t o) { return o; }, [&](uint32_t) { return layer; }, [&](uint32_t o, uint32_t k, const Words& w) {
-    const float v = __fmul_rn(__fsub_rn(__fmul_rn(2.0f, unit_uniform(w.r0)), 1.0f), bound);
-    if ((int)k < K) W[(size_t)o * ldk + k] = v;
-    else b[o] = v;
-  });
+  for_each_element(N, (uint32_t)K + 1, reciprocal,
+                   [&](uint32_t o, uint32_t k) { store_weight(W, K, ldk, b, o, k, bound, philox4x32_10(k, o, 1u, layer, k0, k1)); });
+}
+__global__ __launch_bounds__(256) void init_rows_kernel(uint32_t k0, uint32_t k1, uint32_t layer, float* __restrict__ W, int N, int K,
+                                                        int ldk, float* __restrict__ b, uint32_t deep) {
+  const float bound = __fdiv_rn(1.0f, correctly_rounded_sqrt((float)K));
+  for_each_of_rows(N, (uint32_t)K + 1, deep, 1u, k0, k1, [](uint32_t o) { return o; }, [&](uint32_t) { return layer; },
+                   [&](uint32_t o, uint32_t k, const Words& w) { store_weight(W, K, ldk, b, o, k, bound, w); });
 }
 
-// 2^32 / cols, rounded down, for rows of up to kFlat columns; 0 for others.  As many rows per wavefront as leave
-// every SIMD eight of them: with four, 1000 x 16384 uniform labels take 24.7 us instead of 22.0 (25.1 with one row per wavefront), 1000 x 4096
-// normal ones 15.7 instead of 14.8 (15.0; with 16, 16.3).
-inline Grid grid_of(size_t rows, size_t cols) {
-  const size_t waves = rows * ((cols + kRun - 1) / kRun);
-  const size_t deep = (waves + 4096) / (256 * 4 * 8);
-  return Grid{(uint32_t)rows, (uint32_t)cols, cols <= (size_t)kFlat ? (uint32_t)(0xFFFFFFFFu / cols) : 0u,
-              (uint32_t)(deep < 1 ? 1 : (deep > kDeepest ? kDeepest : deep))};
-}
-// blocks of 4 wavefronts; above 2^18 of them the kernels loop
-inline int blocks_for(const Grid& g) {
-  const size_t units = g.reciprocal ? ((size_t)g.rows * g.cols + kFlat - 1) / kFlat : (size_t)((g.rows + g.deep - 1) / g.deep) * ((g.cols + kRun - 1) / kRun);
+// 2^32 / cols, rounded down, for rows of up to kFlat columns; 0 for others
+inline uint32_t reciprocal_for(size_t cols) { return cols <= (size_t)kFlat ? (uint32_t)(0xFFFFFFFFu / cols) : 0u; }
+inline int blocks_of(size_t units) {            // of 4 wavefronts; above 2^18 of them the kernels loop
   const size_t blocks = (units + 3) / 4;
   return (int)(blocks < 1 ? 1 : (blocks > (1u << 18) ? (1u << 18) : blocks));
 }
+inline int grid_for(size_t rows, size_t cols) {
+  return blocks_of(cols <= (size_t)kFlat ? (rows * cols + kFlat - 1) / kFlat : rows * ((cols + kRun - 1) / kRun));
+}
+inline int grid_of_rows(size_t rows, size_t cols, uint32_t deep) { return blocks_of((rows + deep - 1) / deep * ((cols + kDeepRun - 1) / kDeepRun)); }
 
+// Rows per wavefront of for_each_of_rows; 0: for_each_element.  So many that every SIMD still has eight wavefronts or more, and only where the last
+// run of a row has most of its columns: a lane past them idles for all rows.  Microseconds, one row / 2 / 4 / 8, bf16 normal labels (bf16
+// inputs): 1000 x 2048 (8000 runs of kDeepRun columns) 7.0 / 7.3 / 7.5 / 9.3, 4096 x 1000 (16384) 12.7 / 12.5 / 12.4 / 13.2 (13.3 / 12.8 / 12.9 / 14.5),
+// 8192 x 768 (24576) 18.1 / 17.4 / 16.8 / 17.6, 2000 x 16384 (128000) 74.8 / 75.8 / 72.7 / 71.6 (77.1 / 74.5 / 73.0 / 72.0), 8192 x 16384 (524288)
+// 292 / 298 / 287 / 285 (310 / 309 / 297 / 294); a last run of 1 column of 256 in 5 runs, 8192 x 1025, 28.2 / 26.2 / 25.7 / 26.0, of 88 in 3, 8192 x 600,
+// 16.2 / 16.9 / 16.6 / 17.4, of 1 in 3, 8192 x 513, 14.7 / 17.0 / 16.6 / 17.5.
+inline uint32_t rows_per_wave(size_t rows, size_t cols) {
+  const size_t runs = (cols + kDeepRun - 1) / kDeepRun, total = rows * runs;
+  if (cols <= (size_t)kFlat || 4 * runs * kDeepRun > 5 * cols || total < 16384) return 0;
+  return total < 24576 ? 2 : (total < 131072 ? 4 : 8);
+}
+
+template <typename T, int DIST>
+void launch_labels_of(uint32_t k0, uint32_t k1, int classes, int dim, float kappa, T* out, hipStream_t s) {
+  if (const uint32_t deep = rows_per_wave(classes, dim))
+    labels_rows_kernel<T, DIST><<<grid_of_rows(classes, dim, deep), 256, 0, s>>>(k0, k1, classes, dim, kappa, out, deep);
+  else
+    labels_kernel<T, DIST><<<grid_for(classes, dim), 256, 0, s>>>(k0, k1, classes, dim, kappa, out, reciprocal_for(dim));
+}
 template <typename T>
 void launch_labels(uint64_t seed, int classes, int dim, int dist, float kappa, T* out, hipStream_t s) {
-  const Grid g = grid_of(classes, dim);
-  const int grid = blocks_for(g);
   const uint32_t k0 = (uint32_t)seed, k1 = (uint32_t)(seed >> 32);
   switch (dist) {
-    case 0: labels_kernel<T, 0><<<grid, 256, 0, s>>>(k0, k1, g, kappa, out); break;
-    case 1: labels_kernel<T, 1><<<grid, 256, 0, s>>>(k0, k1, g, kappa, out); break;
-    case 2: labels_kernel<T, 2><<<grid, 256, 0, s>>>(k0, k1, g, kappa, out); break;
-    default: labels_kernel<T, 3><<<grid, 256, 0, s>>>(k0, k1, g, kappa, out); break;
+    case 0: launch_labels_of<T, 0>(k0, k1, classes, dim, kappa, out, s); break;
+    case 1: launch_labels_of<T, 1>(k0, k1, classes, dim, kappa, out, s); break;
+    case 2: launch_labels_of<T, 2>(k0, k1, classes, dim, kappa, out, s); break;
+    default: launch_labels_of<T, 3>(k0, k1, classes, dim, kappa, out, s); break;
   }
+}
+template <typename T>
+void launch_inputs(uint64_t seed, const float* table, int classes, const int32_t* y, int64_t first_sample, int batch, int dim, float sigma, T* out,
+                   hipStream_t s) {
+  const uint32_t k0 = (uint32_t)seed, k1 = (uint32_t)(seed >> 32);
+  if (const uint32_t deep = rows_per_wave(batch, dim))
+    inputs_rows_kernel<<<grid_of_rows(batch, dim, deep), 256, 0, s>>>(k0, k1, table, classes, y, (uint64_t)first_sample, batch, dim, sigma, out, deep);
+  else
+    inputs_kernel<<<grid_for(batch, dim), 256, 0, s>>>(k0, k1, table, classes, y, (uint64_t)first_sample, batch, dim, sigma, out, reciprocal_for(dim));
 }
 
 }  // namespace
@@ -283,19 +352,18 @@ hipError_t launch_make_labels(uint64_t seed, int classes, int dim, int dist, flo
 
 hipError_t launch_make_inputs(uint64_t seed, const float* table, int classes, const int32_t* y, int64_t first_sample,
                               int batch, int dim, float sigma, void* out, int dt, hipStream_t s) {
-  const Grid g = grid_of(batch, dim);
-  const int grid = blocks_for(g);
-  const uint32_t k0 = (uint32_t)seed, k1 = (uint32_t)(seed >> 32);
-  if (dt == 1)
-    inputs_kernel<<<grid, 256, 0, s>>>(k0, k1, table, classes, y, (uint64_t)first_sample, g, sigma, (__bf16*)out);
-  else
-    inputs_kernel<<<grid, 256, 0, s>>>(k0, k1, table, classes, y, (uint64_t)first_sample, g, sigma, (float*)out);
+  if (dt == 1) launch_inputs(seed, table, classes, y, first_sample, batch, dim, sigma, (__bf16*)out, s);
+  else launch_inputs(seed, table, classes, y, first_sample, batch, dim, sigma, (float*)out, s);
   return hipGetLastError();
 }
 
 hipError_t launch_init_weights(uint64_t seed, int layer, float* W32, int N, int K, int ldk, float* b, hipStream_t s) {
-  const Grid g = grid_of(N, (size_t)K + 1);
-  init_kernel<<<blocks_for(g), 256, 0, s>>>((uint32_t)seed, (uint32_t)(seed >> 32), (uint32_t)layer, W32, g, K, ldk, b);
+  const uint32_t k0 = (uint32_t)seed, k1 = (uint32_t)(seed >> 32);
+  const size_t cols = (size_t)K + 1;
+  if (const uint32_t deep = rows_per_wave(N, cols))
+    init_rows_kernel<<<grid_of_rows(N, cols, deep), 256, 0, s>>>(k0, k1, (uint32_t)layer, W32, N, K, ldk, b, deep);
+  else
+    init_kernel<<<grid_for(N, cols), 256, 0, s>>>(k0, k1, (uint32_t)layer, W32, N, K, ldk, b, reciprocal_for(cols));
   return hipGetLastError();
 }
 

@@ -1,7 +1,7 @@
 """Generator kernels at the widths where their split into wavefront runs can go wrong, bit for bit against the oracle.
 
-A wavefront takes runs of 256 columns of up to 16 rows, or 256 elements over the rows' ends where rows have at most 256 columns: the
-widths sit on and beside those edges, the row counts leave a last wavefront partly filled."""
+A wavefront takes runs of 512 columns of one row, of 256 columns of up to 8 rows in large matrices, or 256 elements over the rows' ends where
+rows have at most 256 columns: the widths sit on and beside those edges, the row counts leave a last wavefront partly filled."""
 
 import numpy as np
 import pytest
@@ -42,8 +42,8 @@ def test_labels_inputs_and_weights(dim, rows):
     assert np.array_equal(bits(b), np.asarray(br, np.float32).view(np.uint32))
 
 
-# 12288 waves of 256 columns and more take 2 to 16 rows each: a last one with fewer rows, a last run with one column, and the sample counter's low
-# word wrapping inside a wave's rows
+# 16384 runs of 256 columns and more go 2, 4 or 8 rows to a wavefront: a last one with fewer rows, a last run with one column, and the sample
+# counter's low word wrapping inside a wavefront's rows.  Rows whose last run is mostly empty (257 columns) stay single
 @pytest.mark.parametrize("rows,dim", [(12290, 257), (4099, 1025), (1537, 8192), (1031, 32769)])
 def test_several_rows_per_wavefront(rows, dim):
     seed = (7 << 32) | dim
@@ -58,6 +58,11 @@ def test_several_rows_per_wavefront(rows, dim):
     assert np.array_equal(bits(got[part]), ref.view(np.uint32))
     again = api.make_segment_inputs(seed, table, torch.from_numpy(y[:64].copy()).cuda(), first, 0.05)      # one row per wavefront
     assert torch.equal(got[:64], again)
+    if dim <= 8192:
+        seg = api.Segment([dim - 1, rows], api.RELU_ALL, api.MSE_SIL, max_batch=4)      # a row of weights and its bias
+        seg.init(seed)
+        for tensor, ref in zip(seg.get_params(0), orng.init_weights(seed, 0, rows, dim - 1)):
+            assert np.array_equal(bits(tensor), np.asarray(ref, np.float32).view(np.uint32))
 
 
 @pytest.mark.parametrize("seed, j", [(20, 0x7FFFFF), (28, 0xFFFFFE)])
