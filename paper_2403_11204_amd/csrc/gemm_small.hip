@@ -650,13 +650,18 @@ hipError_t small_configure_all() {
   return e == hipSuccess ? configure_logits_all<float>() : e;
 }
 
-// One launch less against columns that share a compute unit, whose float32 matrix rate is then the limit.  A step of 256-K-C, microseconds, product
-// and cross-entropy apart / in one launch: float32 64 rows, 64-47 19.7 / 15.7, 1024-10 21.6 / 19.5, 1410 rows, 60-47 24.3 / 22.5, 256 rows, 256-47
-// 20.2 / 18.5, 512-47 22.3 / 21.8, 1024-47 25.5 / 26.5, 2048-47 39.4 / 43.8, 1024-64 25.4 / 29.1; bf16 256 rows, 512-47 19.7 / 17.2, 4096-47 35.4 /
-// 34.1, 1024 rows, 1024-47 26.9 / 24.8, 4096-47 50.2 / 49.0, 2000 rows, 4096-47 64.1 / 62.0.
+// One launch less against columns that share a compute unit, whose float32 matrix rate is then the limit.  A step of 64-K-C on the device alone, rows
+// 1 / 64 / 1000, microseconds, product and cross-entropy apart -> in one launch:
+//   float32 1536-16 18.9 / 21.4 / 36.2 -> 18.0 / 19.8 / 34.2, 512-32 15.7 / 17.2 / 26.3 -> 15.3 / 16.1 / 26.2, 768-32 16.4 / 17.8 / 29.5 -> 16.4 / 17.6 /
+//   30.0, 256-48 15.0 / 16.1 / 21.4 -> 14.5 / 15.8 / 21.3, 384-48 15.4 / 16.8 / 23.4 -> 15.7 / 16.7 / 24.0, 128-64 14.7 / 15.8 / 20.7 -> 14.4 / 15.5 /
+//   20.2, 256-64 15.2 / 16.2 / 21.7 -> 15.4 / 16.6 / 22.3;
+//   bf16 4096-16 20.2 / 22.8 / 39.7 -> 18.8 / 20.4 / 36.6, 4096-47 22.0 / 24.4 / 41.0 -> 22.1 / 23.7 / 40.4, 6144-47 26.6 / 29.6 / 53.1 -> 27.5 / 29.8 /
+//   52.2, 1024-64 15.8 / 17.7 / 23.4 -> 15.7 / 16.8 / 22.3, 2048-64 17.3 / 19.6 / 31.5 -> 17.7 / 19.2 / 31.1, 4096-64 22.2 / 24.6 / 41.5 -> 23.2 / 25.1 /
+//   41.8.
 bool logits_fit(int dtype, int M, int N, int K) {
   if (N > 64 || !product_is_small(dtype, EPI_FWD, M, N) || small_tile(dtype, M, N) != 16) return false;
-  return dtype == 1 ? K <= 4096 : (N + 15) / 16 * K <= 1536;
+  const int nt = (N + 15) / 16;
+  return dtype == 1 ? K <= (nt == 4 ? 1024 : 4096) : K <= 1536 && nt * nt * K <= 2304;
 }
 
 hipError_t launch_logits(int dtype, const GemmArgs& g, const OutJob& out, hipStream_t s) {

@@ -22,7 +22,9 @@ def close(got, ref, tol):
 @pytest.mark.parametrize("act", [api.RELU_HIDDEN_IDENTITY_LAST, api.RELU_ALL])
 @pytest.mark.parametrize("dtype,K,C", [(api.F32, 8, 1), (api.F32, 60, 47), (api.F32, 513, 17), (api.F32, 512, 48), (api.F32, 1536, 16), (api.F32, 384, 64),
                                        (api.F32, 385, 64), (api.BF16, 8, 1), (api.BF16, 60, 47), (api.BF16, 1001, 16), (api.BF16, 257, 33),
-                                       (api.BF16, 4096, 64), (api.BF16, 4097, 47), (api.BF16, 300, 65)])
+                                       (api.BF16, 4096, 64), (api.BF16, 4097, 47), (api.BF16, 300, 65),
+                                       (api.F32, 1537, 16), (api.F32, 576, 32), (api.F32, 256, 33), (api.F32, 144, 49), (api.F32, 145, 64),
+                                       (api.BF16, 1024, 64), (api.BF16, 1025, 49), (api.BF16, 4096, 47)])
 @pytest.mark.parametrize("B", [1, 9, 16, 250])
 def test_step_against_float64(dtype, K, C, act, B):
     tdt, tol = (torch.float32, 1e-5) if dtype == api.F32 else (torch.bfloat16, 2e-2)
@@ -73,3 +75,28 @@ def test_external_gradient_on_a_classifier():
     seg.step_external(rand(rows, 24), dA)
     assert torch.equal(seg.get_activation(2, rows, kind=1), dA)
     assert seg.target_errors() == 0
+
+
+# the launch gives the bits of the two it takes the place of: hidden units that are always zero change no sum, but take a layer over the line to them;
+# and the logits are those of the forward-only pass
+@pytest.mark.parametrize("dtype,K,beyond,C", [(api.F32, 1536, 1544, 16), (api.F32, 570, 584, 30), (api.F32, 255, 272, 47), (api.F32, 144, 160, 64),
+                                              (api.BF16, 1000, 1032, 64), (api.BF16, 4096, 4104, 47)])
+@pytest.mark.parametrize("act", [api.RELU_HIDDEN_IDENTITY_LAST, api.RELU_ALL])
+@pytest.mark.parametrize("B", [3, 130])
+def test_same_bits_as_product_and_cross_entropy_apart(dtype, K, beyond, C, act, B):
+    g = torch.Generator(device="cuda").manual_seed(K + C + B)
+    rand = lambda *s: torch.rand(*s, generator=g, device="cuda") * 2 - 1
+    W1, b1, W2, b2 = rand(K, 24), rand(K), rand(C, K) / math.sqrt(K), rand(C)
+    X, y = rand(B, 24).to(torch.float32 if dtype == api.F32 else torch.bfloat16), torch.randint(0, C, (B,), generator=g, device="cuda", dtype=torch.int32)
+    outs = []
+    for k in (K, beyond):
+        seg = api.Segment([24, k, C], act, api.SOFTMAX_XENT, max_batch=B, dtype=dtype, lr=0.0, momentum=0.0)
+        seg.set_params(0, torch.cat([W1, W1.new_zeros(k - K, 24)]), torch.cat([b1, b1.new_zeros(k - K)]))
+        seg.set_params(1, torch.cat([W2, W2.new_zeros(C, k - K)], 1), b2)
+        loss = seg.step(X, y).clone()
+        z = seg.get_activation(2, B)
+        assert torch.equal(z, seg.forward(X))
+        dW, db = seg.get_grads(1)
+        outs.append((loss, z, seg.get_activation(2, B, kind=1), dW[:, :K].clone(), db))
+    for one, two in zip(*outs):
+        assert torch.equal(one, two)
