@@ -1173,10 +1173,19 @@ hipError_t configure_big() {
 }
 
 // Whether the 256x256 tiles of a product run on 4 wavefronts (gemm_nt_long_kernel) instead of 8: from a length of the contraction on from which
-// the cheaper k-tiles outweigh an epilogue in which one wavefront a SIMD waits for its own LDS reads, on ragged outputs too.  Microseconds, 8 / 4
-// wavefronts: forward 8192 x 8192, K = 1024 146 / 149, 2048 225 / 221, 8192 x 16384, 2048 461 / 449, 16384 2890 / 2770; data gradient 4100 x 4104,
-// 2050 103 / 106, 3072 129 / 130, 8192 x 16384, 2048 455 / 456; weight gradient 8192 x 8192, 3072 321 / 314, 16384 x 16384 x 8192 3075 / 2945.
-bool big_is_long(int K) { return K >= 3072; }
+// the cheaper k-tiles outweigh an epilogue in which one wavefront a SIMD waits for its own LDS reads.  What they save is power: on a chip that the last
+// round of tiles leaves mostly empty the clock is not the limit and the 8 wavefronts are faster for longer.  Microseconds, 8 / 4 wavefronts:
+//   full rounds: forward 8192 x 8192, K = 1024 146 / 149, 2048 225 / 221, 8192 x 16384, 2048 461 / 449, 16384 2890 / 2770, 7680 x 8192 (960 tiles),
+//   3072 288 / 275; data gradient 8192 x 16384, 2048 455 / 456, 7680 x 8192, 3072 288 / 275, 4096 x 12000 (752), 3072 214 / 208; weight gradient 8192 x
+//   8192, 3072 321 / 314, 16384 x 16384 x 8192 3075 / 2945;
+//   others: forward 4352 x 4352 (289), 3072 128 / 130, 4096 163 / 163, 6144 231 / 229, 12000 x 4100 (799), 3072 261 / 263, 4096 334 / 332; data gradient
+//   4352 x 4352, 3072 126 / 129, 4096 160 / 162, 6144 229 / 229, 8192 298 / 295, 12000 x 4100, 3072 257 / 265, 4096 332 / 335, 6144 480 / 472; weight
+//   gradient 4352 x 4352, 3072 126 / 125, 4096 160 / 158.
+bool big_is_long(int epi, int M, int N, int K) {
+  const long tiles = tiles_of(M, N, 0), rounds = (tiles + 255) / 256;
+  if (epi == EPI_WGRAD || 8 * tiles >= 7 * 256 * rounds) return K >= 3072;
+  return K >= (epi == EPI_FWD ? 4096 : 6144);
+}
 
 template <int EPI>
 hipError_t configure_long() {
@@ -1193,7 +1202,7 @@ hipError_t launch_big(const GemmArgs& g, hipStream_t s) {
   constexpr int smem = kBigSmem;
   const int tiles = ((g.M + 255) / 256) * ((g.N + 255) / 256);
   if constexpr (EPI != EPI_WGRAD_UPDATE) {
-    if (big_is_long(g.K)) {
+    if (big_is_long(EPI, g.M, g.N, g.K)) {
       hipError_t e = configure_long<EPI>();
       if (e != hipSuccess) return e;
       hipLaunchKernelGGL(gemm_nt_long_kernel<EPI>, dim3(tiles), dim3(256), smem, s, g);

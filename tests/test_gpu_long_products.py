@@ -1,5 +1,6 @@
-"""Products on 256x256 bf16 tiles with contractions of 3072 and more (4 wavefronts a tile), against float64 on the tensors as the library
-stored them: forward, data gradient and weight gradient, both layouts of the outputs and the mask bits between them.
+"""Products on 256x256 bf16 tiles with long contractions, against float64 on the tensors as the library stored them: forward, data gradient
+and weight gradient, both layouts of the outputs and the mask bits between them.  They run on 4 wavefronts a tile from K = 3072 on where the tiles fill their last
+round of 256 compute units (240 and 256 tiles here), from 4096 (forward) and 6144 (data gradient) on where they do not (272 to 425), on 8 below.
 
 Tolerances against max|ref| of each tensor: bf16 rounds every stored tensor to 2^-9 of itself, a handful of them in a row: 2e-2.  The mask
 is exact: a data gradient is zero wherever the stored activation is.  A weight gradient of stored bf16 tensors is a float32 sum of exact
@@ -22,7 +23,8 @@ def close(got, ref, tol):
 
 # rows and columns on, one beside and half a tile beside an edge of the 256-wide tiles; contractions of whole k-tiles of 64, of one chunk of 8
 # more and of one chunk less, down to the shortest on this path; a batch shorter than what the one before it left in the buffers
-@pytest.mark.parametrize("B,widths", [(4096, (3072, 4096, 4096)), (4090, (3073, 4100, 4103)), (4225, (3080, 3968, 4352)), (3841, (3135, 4097, 4031))])
+@pytest.mark.parametrize("B,widths", [(4096, (3072, 4096, 4096)), (4090, (3073, 4100, 4103)), (4225, (3080, 3968, 4352)), (3841, (3135, 4097, 4031)),
+                                      (4090, (3585, 4090, 4095)), (3970, (3591, 4031, 4094)), (4100, (4104, 4100, 6150))])
 def test_step_against_float64(B, widths):
     g = torch.Generator(device="cuda").manual_seed(B + sum(widths))
     rand = lambda *s: torch.rand(*s, generator=g, device="cuda") * 2 - 1
@@ -45,8 +47,8 @@ def test_step_against_float64(B, widths):
 
 
 # an infinite input: its row is what IEEE arithmetic gives, and nothing of it gets into rows and columns beside the matrix
-def test_an_infinite_input_stays_in_its_row():
-    B, widths = 4090, (3073, 4100, 4103)
+@pytest.mark.parametrize("B,widths", [(4090, (3073, 4100, 4103)), (4090, (3073, 4090, 4095))])
+def test_an_infinite_input_stays_in_its_row(B, widths):
     g = torch.Generator(device="cuda").manual_seed(5)
     seg = api.Segment(list(widths), api.RELU_ALL, api.MSE_SIL, max_batch=B, dtype=api.BF16, lr=0.0, momentum=0.0)
     params = [(torch.rand((n, k), generator=g, device="cuda") / k + 1e-3, torch.zeros(n, device="cuda")) for k, n in zip(widths, widths[1:])]
