@@ -46,6 +46,46 @@ def test_step_against_float64(B, widths):
         assert close(seg.get_grads(0)[0], dZ1.double().t() @ X.double(), 1e-4)
 
 
+# the input gradient has no mask, the last layer of a regression no ReLU
+def test_input_gradient_and_identity_output():
+    B, widths = 4090, (3585, 4090, 4095)
+    g = torch.Generator(device="cuda").manual_seed(11)
+    rand = lambda *s: torch.rand(*s, generator=g, device="cuda") * 2 - 1
+    seg = api.Segment(list(widths), api.RELU_HIDDEN_IDENTITY_LAST, api.MSE_SIL, max_batch=B, dtype=api.BF16, lr=0.0, momentum=0.0, input_grad=True)
+    params = [(rand(n, k) / math.sqrt(k), rand(n) / math.sqrt(k)) for k, n in zip(widths, widths[1:])]
+    for l, (W, b) in enumerate(params):
+        seg.set_params(l, W, b)
+    seg.set_labels(rand(3, widths[-1]))
+    X, y = rand(B, widths[0]).bfloat16(), torch.randint(0, 3, (B,), generator=g, device="cuda", dtype=torch.int32)
+    dX, _ = seg.input_grad(X, y)
+    W16 = [W.bfloat16().double() for W, _ in params]
+    a1, a2 = (seg.get_activation(l, B) for l in (1, 2))
+    dZ2, dZ1 = (seg.get_activation(l, B, kind=1).double() for l in (2, 1))
+    assert close(a2, a1.double() @ W16[1].t() + params[1][1].double(), 2e-2) and float(a2.min()) < 0
+    assert close(dZ1, (dZ2 @ W16[1]) * (a1 > 0), 2e-2)
+    assert close(dX, dZ1 @ W16[0], 2e-2) and torch.any(dX[X < 0] != 0)
+    assert torch.equal(seg.forward(X), a2)
+
+
+# the caller's own dense rows as operand and output, with rows behind them that stay as they are
+@pytest.mark.parametrize("B,widths", [(4090, (3080, 4088, 3976)), (4100, (4104, 4104, 4120))])
+def test_forward_into_dense_rows(B, widths):
+    g = torch.Generator(device="cuda").manual_seed(12)
+    rand = lambda *s: torch.rand(*s, generator=g, device="cuda") * 2 - 1
+    seg = api.Segment(list(widths), api.RELU_HIDDEN_IDENTITY_LAST, api.MSE_SIL, max_batch=B, dtype=api.BF16, lr=0.0, momentum=0.0)
+    params = [(rand(n, k) / math.sqrt(k), rand(n) / math.sqrt(k)) for k, n in zip(widths, widths[1:])]
+    for l, (W, b) in enumerate(params):
+        seg.set_params(l, W, b)
+    X = torch.full((B + 9, widths[0]), float("nan"), device="cuda", dtype=torch.bfloat16)
+    X[:B] = rand(B, widths[0])
+    out = torch.full((B + 9, widths[-1]), 7.0, device="cuda", dtype=torch.bfloat16)
+    seg.forward(X[:B], out=out[:B])
+    W16 = [W.bfloat16().double() for W, _ in params]
+    a1 = torch.relu(X[:B].double() @ W16[0].t() + params[0][1].double()).bfloat16().double()
+    assert close(out[:B], a1 @ W16[1].t() + params[1][1].double(), 2e-2)
+    assert torch.all(out[B:] == 7.0)
+
+
 # an infinite input: its row is what IEEE arithmetic gives, and nothing of it gets into rows and columns beside the matrix
 @pytest.mark.parametrize("B,widths", [(4090, (3073, 4100, 4103)), (4090, (3073, 4090, 4095))])
 def test_an_infinite_input_stays_in_its_row(B, widths):
