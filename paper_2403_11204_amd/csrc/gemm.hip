@@ -675,12 +675,11 @@ __global__ __launch_bounds__(NW * 64) void gemm_nt_big_kernel(const GemmArgs g) 
     // workgroup barrier after the first one (LDS operations of one wavefront execute in order).  16-byte chunk c of
     // a staged row r sits at chunk c ^ (r & 15) (transposed) / c ^ ((r >> 1) & 7) (row-major), which keeps the
     // 8-byte writes and the 16-byte reads of a wavefront free of bank conflicts.
-    // The data gradient's ReLU mask comes as bits when the forward product of the layer below ran on this tile too
-    // (GemmArgs::bits: one dword per lane and 16-column block, 4 loads instead of 32 gathered 8-byte pieces of the
-    // transposed activation; the gather was 10 of the epilogue's 17 us per tile), else it is gathered from maskT
-    // before the staging.  (Applying the bf16 mask on the way out instead, from coalesced 16-byte loads of both layouts
-    // of the activation, measured 2-3 % slower on short contractions.)  Against one shared 256 x 512-byte staging area
-    // with a workgroup barrier around each pass: 8192 x 16384 products -4 % at K = 1024, -0.5 % at K = 16384.
+    // The data gradient's ReLU mask comes as bits (GemmArgs::bits, from the forward product of the layer below, which ran on this tile
+    // too): one dword per lane and 16-column block, 4 loads instead of 32 gathered 8-byte pieces of the
+    // transposed activation (the gather was 10 of the epilogue's 17 us per tile).  Applying the bf16 mask on the way out instead, from
+    // coalesced 16-byte loads of both layouts of the activation, measured 2-3 % slower on short contractions.  Against one shared 256 x 512-byte
+    // staging area with a workgroup barrier around each pass: 8192 x 16384 products -4 % at K = 1024, -0.5 % at K = 16384.
     typedef __attribute__((ext_vector_type(2))) unsigned int u32x2;
     const int rowW = m0 + wm * 128, colW = n0 + wn * WTN;     // origin of this wavefront's sub-tile
     // data gradient with the mask as bits: the 32 bits a lane needs per accumulator column are one dword
@@ -716,11 +715,6 @@ __global__ __launch_bounds__(NW * 64) void gemm_nt_big_kernel(const GemmArgs g) 
 #pragma unroll
           for (int e = 0; e < 4; ++e)
             if (!((mbits[j] >> (4 * i + e)) & 1u)) acc[i][j][e] = 0.0f;
-        } else if (g.maskT && col_ok && mb < Mr) {
-          const bf16x4 mk = *(const bf16x4*)((const bf16*)g.maskT + (size_t)n * g.ldmask + mb);
-#pragma unroll
-          for (int e = 0; e < 4; ++e)
-            if (!((float)mk[e] > 0.0f)) acc[i][j][e] = 0.0f;
         }
 #pragma unroll
         for (int e = 0; e < 4; ++e)
@@ -876,7 +870,7 @@ __global__ __launch_bounds__(256) void gemm_nt_long_kernel(const GemmArgs g) {
   for (int j = 0; j < 8; ++j) {
     const int n = colW + j * 16 + lrow;
     bias[j] = 0.0f;
-    mbits[j] = 0u;
+    mbits[j] = EPI == EPI_DGRAD && !g.bits ? 0xFFFFFFFFu : 0u;
     if (EPI == EPI_FWD && n < g.N) bias[j] = g.bias[n];
     if (EPI == EPI_DGRAD && g.bits && n < g.N && rowW < g.M) mbits[j] = g.bits[(size_t)n * g.ldbits + (rowW >> 5) + lgrp];
   }
@@ -1026,15 +1020,10 @@ __global__ __launch_bounds__(256) void gemm_nt_long_kernel(const GemmArgs g) {
 #pragma unroll
             for (int e = 0; e < 4; ++e) asm("v_max_f32 %0, 0, %1" : "=v"(v[e]) : "v"(v[e]));
           }
-        } else if (g.bits) {
+        } else {
 #pragma unroll
           for (int e = 0; e < 4; ++e)
             v[e] = __builtin_bit_cast(float, __builtin_bit_cast(int, v[e]) & (((int)(mbits[j] << (31 - 4 * i - e))) >> 31));
-        } else if (g.maskT && col_ok && mb < Mr) {
-          const bf16x4 mk = *(const bf16x4*)((const bf16*)g.maskT + (size_t)n * g.ldmask + mb);
-#pragma unroll
-          for (int e = 0; e < 4; ++e)
-            if (!((float)mk[e] > 0.0f)) v[e] = 0.0f;
         }
         if (edge) {
 #pragma unroll
@@ -1316,6 +1305,7 @@ hipError_t launch_gemm(int dtype, int epi, const GemmArgs& g, hipStream_t s) {
     return hipErrorInvalidValue;
   if (epi == EPI_WGRAD && (g.ldc % 4 || ((uintptr_t)g.Cf & 15))) return hipErrorInvalidValue;
   const int cfg = pick_cfg(dtype, epi, g.M, g.N);
+  if (cfg == 0 && dtype == 1 && epi == EPI_DGRAD && g.maskT && !g.bits) return hipErrorInvalidValue;      // 256x256 bf16 tiles read the mask as bits only
   if (cfg == 2) {
     SmallGroup one{};
     one.g[0] = g; one.epi[0] = epi; one.n = 1;

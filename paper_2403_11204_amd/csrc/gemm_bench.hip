@@ -7,8 +7,8 @@
 //         -I paper_2403_11204_amd/csrc paper_2403_11204_amd/csrc/gemm_bench.hip \
 //         paper_2403_11204_amd/csrc/gemm_small.hip paper_2403_11204_amd/csrc/gemm_pair.hip paper_2403_11204_amd/csrc/chain.hip -o _build/gemm_bench
 //   _build/gemm_bench M N K epilogue iters pad data outputs
-//     epilogue: 0 forward (+bias), 1 data gradient (masked), 2 weight gradient (float32 output)
-//     pad     : elements added to every leading dimension (192 = what the library's own buffers use at these widths)
+//     epilogue: 0 forward (+bias, mask bits written), 1 data gradient (masked: by bits where the tile takes them), 2 weight gradient (float32 output)
+//     pad     : elements added to every leading dimension; below 0 the leading dimensions of the library's own buffers
 //     data    : 0 uniform(-1,1), 1 zeros, 2 half zeros (ReLU-like), 3 quarter steps
 //     outputs : 0 row-major and transposed, 1 row-major only, 2 transposed only (epilogues 0 and 1)
 #include "gemm.hip"
@@ -24,7 +24,9 @@ static float bf2f(uint16_t h) { uint32_t b = (uint32_t)h << 16; float f; memcpy(
 int main(int argc, char** argv) {
   int M = argc > 1 ? atoi(argv[1]) : 8192, N = argc > 2 ? atoi(argv[2]) : 16384, K = argc > 3 ? atoi(argv[3]) : 16384;
   int epi = argc > 4 ? atoi(argv[4]) : 2, iters = argc > 5 ? atoi(argv[5]) : 10;
-  int pad = argc > 6 ? atoi(argv[6]) : 0; int dmode = argc > 7 ? atoi(argv[7]) : 0; int outs = argc > 8 ? atoi(argv[8]) : 0; int lda = (K + 7) / 8 * 8 + pad, ldb = lda, ldc = (N + 7) / 8 * 8 + pad, ldct = (M + 7) / 8 * 8 + pad;
+  int pad = argc > 6 ? atoi(argv[6]) : 0; int dmode = argc > 7 ? atoi(argv[7]) : 0; int outs = argc > 8 ? atoi(argv[8]) : 0;
+  auto ld = [&](int width) { return pad < 0 ? slp::internal_ld(width, 2) : (width + 7) / 8 * 8 + pad; };
+  const int lda = ld(K), ldb = lda, ldc = ld(N), ldct = ld(M);
   std::vector<uint16_t> hA((size_t)M * lda), hB((size_t)N * ldb);
   uint32_t s = 12345;
   auto rnd = [&]() { s = s * 1664525u + 1013904223u; float r = ((s >> 8) & 0xFFFF) / 32768.0f - 1.0f; if (dmode == 1) return 0.0f; if (dmode == 2) return r > 0 ? r : 0.0f; if (dmode == 3) return (float)((int)(r * 4)) * 0.25f; return r; };
@@ -39,8 +41,19 @@ int main(int argc, char** argv) {
   std::vector<uint16_t> hMask((size_t)N * ldct + (size_t)M * ldc);
   for (size_t i = 0; i < hMask.size(); i++) { s = s * 1664525u + 1013904223u; hMask[i] = f2bf((s >> 20) % 3 ? 1.0f : ((s >> 8) & 1 ? 0.0f : -0.5f)); }   // 1/3 masked out
   CK(hipMemcpy(dMask, hMask.data(), hMask.size() * 2, hipMemcpyHostToDevice));
+  // the same mask as bits, laid out as GemmArgs says
+  const int ldbits = (M + 127) / 128 * 4;
+  std::vector<uint32_t> hBits((size_t)N * ldbits, 0u);
+  for (int n = 0; n < N; n++)
+    for (int m = 0; m < M; m++)
+      if (bf2f(hMask[(size_t)n * ldct + m]) > 0.0f) hBits[(size_t)n * ldbits + m / 128 * 4 + m % 16 / 4] |= 1u << (m % 128 / 16 * 4 + m % 4);
+  uint32_t* dBits;
+  CK(hipMalloc(&dBits, hBits.size() * 4)); CK(hipMemcpy(dBits, hBits.data(), hBits.size() * 4, hipMemcpyHostToDevice));
   slp::GemmArgs g{}; g.A = dA; g.B = dB; g.lda = lda; g.ldb = ldb; g.M = M; g.N = N; g.K = K;
   g.C = dC; g.CT = dCT; g.ldc = ldc; g.ldct = ldct; g.bias = dBias; g.relu = 0; g.maskT = dMask; g.ldmask = ldct; g.Cf = dCf;
+  g.ldbits = ldbits;
+  if (epi == 0) g.bits_out = dBits;
+  if (epi == 1) g.bits = dBits;
   if (outs == 1) g.CT = nullptr; if (outs == 2) g.C = nullptr;
   hipEvent_t e0, e1; CK(hipEventCreate(&e0)); CK(hipEventCreate(&e1));
   // warm-up: at least two launches and at least 0.3 s of them -- the chip's clock settles over the first ~0.1 s of a

@@ -47,7 +47,8 @@ struct GemmArgs {
   const void* maskT;  // [N][ldmask], element type T; launch_pair takes the mask row-major, [M][ldmask]
   int ldmask;
   // The same mask as one bit per element, for bf16 products that launch_gemm runs on tiles of 128 or 256 rows (the small ones and
-  // launch_pair ignore both pointers): EPI_FWD writes bits_out, EPI_DGRAD reads bits instead of maskT when it is not null.
+  // launch_pair ignore both pointers): EPI_FWD writes bits_out, EPI_DGRAD reads bits instead of maskT when it is not null; on 256 rows a
+  // mask has to come as bits.
   // Row n holds ldbits dwords; dword 4 * (m / 128) + g carries, at bit 4 i + e, the element m = 128 (m / 128) + 16 i + 4 g + e
   // (g = 0..3, i = 0..7, e = 0..3: the elements one lane of the tile's accumulator layout holds), set where the stored
   // output is > 0.  ldbits >= 4 * ceil(M / 128); both products must have the same M and N.
