@@ -18,6 +18,7 @@ bounded sample of the same workload.
 """
 
 import argparse
+import hashlib
 import json
 import os
 import sys
@@ -35,9 +36,12 @@ PEAK_TFLOPS = {api.BF16: 2516.6, api.F32: 157.3}     # dense MFMA peaks of MI355
 HBM_BYTES_PER_S = 8.0e12                             # published HBM3E rate of MI355X
 # Bytes crossing the L2 boundary per matrix-product launch (read + written), average over the 16 launches of
 # one step of the default workload: rocprofv3 FETCH_SIZE / WRITE_SIZE passes scaled by a 1 GiB copy kernel in
-# the same process (profiles/comparison_config_gemm_hbm_traffic.md).  Valid for the kernel those passes ran;
-# set to None whenever csrc/gemm.hip changes until the passes are repeated.
-GEMM_TRAFFIC_BYTES_PER_LAUNCH = {4: 5.19e9}
+# the same process (profiles/comparison_config_gemm_hbm_traffic.md), with the digest of the kernel sources that those passes ran:
+# with any other code in them the figure is not given (see gemm_traffic) until the passes are repeated.
+GEMM_TRAFFIC_BYTES_PER_LAUNCH = {4: (5.20e9, "002205db29fd33a7")}
+# The kernels that take the matrix products of a configuration's steps, those that take most of their time first.
+PRODUCT_KERNELS = {0: "small_group_kernel, small_product_kernel", 1: "small_group_kernel, small_product_kernel", 2: "gemm_nt_kernel, pair_kernel",
+                   3: "gemm_nt_long_kernel, gemm_nt_big_kernel", 4: "gemm_nt_long_kernel, gemm_nt_big_kernel", 5: "small_group_kernel, small_product_kernel"}
 MSE, CE = api.MSE_SIL, api.SOFTMAX_XENT
 ALL, LAST = api.RELU_ALL, api.RELU_HIDDEN_IDENTITY_LAST
 
@@ -65,6 +69,20 @@ CONFIGS = {
             segs=[([784, 80, 60], ALL, MSE, api.UNIFORM01, 3), ([60, 60, 60, 47], LAST, CE, None, None)]),
 }
 E2E_WIDTHS = [784, 16384, 16384, 16384, 16384, 16384, 1000]
+
+
+def product_source_digest():
+    """Of the sources that decide which bytes the large products move, comments and white space aside."""
+    h = hashlib.sha256()
+    for name in ("gemm.hip", "gemm_device.h"):
+        with open(os.path.join(ROOT, "paper_2403_11204_amd", "csrc", name)) as f:
+            h.update("".join("".join(line.split("//")[0].split()) for line in f).encode())
+    return h.hexdigest()[:16]
+
+
+def gemm_traffic(config):
+    figure, digest = GEMM_TRAFFIC_BYTES_PER_LAUNCH.get(config, (None, None))
+    return figure if digest == product_source_digest() else None
 
 
 def gemm_flops_per_sample(widths):
@@ -416,7 +434,7 @@ def main():
         "step_tflops": flops_step / (ms * 1e-3) / 1e12,
         "step_frac_of_mfma_peak": flops_step / (ms * 1e-3) / 1e12 / peak,
         "roofline": {"bound": "mfma", "achieved": achieved, "peak": peak, "unit": "TFLOP/s", "frac": achieved / peak,
-                     "traffic": GEMM_TRAFFIC_BYTES_PER_LAUNCH.get(args.config), "kernel": "gemm_nt_big_kernel" if args.config in (3, 4) else "gemm_nt_kernel", "launches": gemm_n,
+                     "traffic": gemm_traffic(args.config), "kernel": PRODUCT_KERNELS[args.config], "launches": gemm_n,
                      "avg_launch_ms": gemm_ms / max(gemm_n, 1), "flops_per_launch": gemm_fl / max(gemm_n, 1)},
         "segment_bytes": [{"params": p, "workspace": w} for p, w in seg_bytes],
         "peak_hbm_bytes_torch": int(torch.cuda.max_memory_allocated()),
