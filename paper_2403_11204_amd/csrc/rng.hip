@@ -303,15 +303,16 @@ inline int grid_for(size_t rows, size_t cols) {
 inline int grid_of_rows(size_t rows, size_t cols, uint32_t deep) { return blocks_of((rows + deep - 1) / deep * ((cols + kDeepRun - 1) / kDeepRun)); }
 
 // Rows per wavefront of for_each_of_rows; 0: for_each_element.  So many that every SIMD still has eight wavefronts or more, and only where the last
-// run of a row has most of its columns: a lane past them idles for all rows.  Microseconds, one row / 2 / 4 / 8, bf16 normal labels (bf16
+// run of a row has most of its columns: a lane past them idles for all rows.  Microseconds, one row / 2 / 4 / 8 (/ 16), bf16 normal labels (bf16
 // inputs): 1000 x 2048 (8000 runs of kDeepRun columns) 7.0 / 7.3 / 7.5 / 9.3, 4096 x 1000 (16384) 12.7 / 12.5 / 12.4 / 13.2 (13.3 / 12.8 / 12.9 / 14.5),
-// 8192 x 768 (24576) 18.1 / 17.4 / 16.8 / 17.6, 2000 x 16384 (128000) 74.8 / 75.8 / 72.7 / 71.6 (77.1 / 74.5 / 73.0 / 72.0), 8192 x 16384 (524288)
-// 292 / 298 / 287 / 285 (310 / 309 / 297 / 294); a last run of 1 column of 256 in 5 runs, 8192 x 1025, 28.2 / 26.2 / 25.7 / 26.0, of 88 in 3, 8192 x 600,
+// 8192 x 768 (24576) 18.1 / 17.4 / 16.8 / 17.6, 20000 x 768 (60000) 39.6 / 38.1 / 36.4 / 38.7, float32 uniform ones 1000 x 16384 (64000) 22.2 / 21.6 /
+// 20.0 / 19.3, 2000 x 16384 (128000) 74.8 / 75.8 / 72.7 / 71.6 (77.1 / 74.5 / 73.0 / 72.0), 8192 x 16384 (524288)
+// 292 / 298 / 287 / 285 / 283 (310 / 309 / 297 / 294 / 288); a last run of 1 column of 256 in 5 runs, 8192 x 1025, 28.2 / 26.2 / 25.7 / 26.0, of 88 in 3, 8192 x 600,
 // 16.2 / 16.9 / 16.6 / 17.4, of 1 in 3, 8192 x 513, 14.7 / 17.0 / 16.6 / 17.5.
 inline uint32_t rows_per_wave(size_t rows, size_t cols) {
   const size_t runs = (cols + kDeepRun - 1) / kDeepRun, total = rows * runs;
   if (cols <= (size_t)kFlat || 4 * runs * kDeepRun > 5 * cols || total < 16384) return 0;
-  return total < 24576 ? 2 : (total < 131072 ? 4 : 8);
+  return total < 24576 ? 2 : (total < 62000 ? 4 : (total < 262144 ? 8 : 16));
 }
 
 template <typename T, int DIST>

@@ -1,6 +1,6 @@
 """Generator kernels at the widths where their split into wavefront runs can go wrong, bit for bit against the oracle.
 
-A wavefront takes runs of 512 columns of one row, of 256 columns of up to 8 rows in large matrices, or 256 elements over the rows' ends where
+A wavefront takes runs of 512 columns of one row, of 256 columns of up to 16 rows in large matrices, or 256 elements over the rows' ends where
 rows have at most 256 columns: the widths sit on and beside those edges, the row counts leave a last wavefront partly filled."""
 
 import numpy as np
@@ -42,9 +42,9 @@ def test_labels_inputs_and_weights(dim, rows):
     assert np.array_equal(bits(b), np.asarray(br, np.float32).view(np.uint32))
 
 
-# 16384 runs of 256 columns and more go 2, 4 or 8 rows to a wavefront: a last one with fewer rows, a last run with one column, and the sample
+# 16384 runs of 256 columns and more go 2 to 16 rows to a wavefront: a last one with fewer rows, a last run with one column, and the sample
 # counter's low word wrapping inside a wavefront's rows.  Rows whose last run is mostly empty (257 columns) stay single
-@pytest.mark.parametrize("rows,dim", [(12290, 257), (4099, 1025), (1537, 8192), (1031, 32769)])
+@pytest.mark.parametrize("rows,dim", [(12290, 257), (4099, 1025), (1537, 8192), (1031, 32769), (1029, 65600)])
 def test_several_rows_per_wavefront(rows, dim):
     seed = (7 << 32) | dim
     assert np.array_equal(bits(api.make_synthetic_labels(seed, rows, dim, api.UNIFORM_PM1)),
