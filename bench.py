@@ -40,7 +40,7 @@ HBM_BYTES_PER_S = 8.0e12                             # published HBM3E rate of M
 # with any other code in them the figure is not given (see gemm_traffic) until the passes are repeated.
 GEMM_TRAFFIC_BYTES_PER_LAUNCH = {4: (5.20e9, "002205db29fd33a7")}
 # The kernels that take the matrix products of a configuration's steps, those that take most of their time first.
-PRODUCT_KERNELS = {0: "small_group_kernel, small_product_kernel", 1: "small_group_kernel, small_product_kernel", 2: "gemm_nt_kernel, pair_kernel",
+PRODUCT_KERNELS = {0: "small_group_kernel, small_product_kernel", 1: "small_group_kernel, small_product_kernel", 2: "pair_kernel, gemm_nt_kernel",
                    3: "gemm_nt_long_kernel, gemm_nt_big_kernel", 4: "gemm_nt_long_kernel, gemm_nt_big_kernel", 5: "small_group_kernel, small_product_kernel"}
 MSE, CE = api.MSE_SIL, api.SOFTMAX_XENT
 ALL, LAST = api.RELU_ALL, api.RELU_HIDDEN_IDENTITY_LAST
