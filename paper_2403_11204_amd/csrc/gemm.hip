@@ -823,6 +823,8 @@ struct LongWalk {
 //         80 .. 125   reads of its sub-step 0
 // Cycles per k-tile, 8192 x 16384 x 16384 (2048 of them MFMAs), one A fragment against all of B's at a time: 2170 with no loads, 2260 with loads past the operands, 2310 with loads that all hit
 // the L2, 2430-2460 as it is; the kernel above 2360-2390 at a clock 5-8 % lower.
+// At the loop's head the compiler waits for every LDS read, and the first one of sub-step 1 has just gone out before that wait: one LDS latency a k-tile
+// that nothing on the SIMD covers.
 template <int EPI>
 __global__ __launch_bounds__(256) void gemm_nt_long_kernel(const GemmArgs g) {
 #if defined(__HIP_DEVICE_COMPILE__)
